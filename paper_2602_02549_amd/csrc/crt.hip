@@ -253,7 +253,7 @@ __device__ __forceinline__ void crt_sums_3m(const int8_t* __restrict__ w1,
       const int l = min(l0 + u, cc.N - 1);
       const bool in = l0 + u < cc.N;
       const double s1 = in ? cc.s1[l] : 0.0, s2 = in ? cc.s2[l] : 0.0;
-      const int p = cc.p[l], hi = (p - 1) / 2, lo = hi + 1 - p;
+      const int p = cc.mod[l].p, hi = (p - 1) / 2, lo = hi + 1 - p;
       auto fix = [&](int x) {
         x -= x > hi ? p : 0;
         return x + (x < lo ? p : 0);

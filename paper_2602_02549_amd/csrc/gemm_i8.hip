@@ -276,7 +276,7 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
                             (float)acc[tx][ty][4 * r4 + 2], (float)acc[tx][ty][4 * r4 + 3]);
           }
     } else if constexpr (EPI == 0) {
-      const int p = cc.p[z];
+      const int p = cc.mod[z].p;
       int8_t* Wz = W + (size_t)(sidx * nz + z) * sw;
       // The modulus is uniform: one branch for the whole tile.
       if (p == 256) {
@@ -292,7 +292,7 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
             store_block(Wz, tx, ty, R[0], R[1], R[2], R[3]);
           }
       } else {
-        const double pd = (double)p, pinv = cc.pinv[z];
+        const double pd = (double)p, pinv = cc.mod[z].pinv;
 #pragma unroll
         for (int tx = 0; tx < TX; ++tx)
 #pragma unroll
@@ -377,9 +377,9 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
   constexpr bool kFold = FOLD && (EPI == 0 || EPI == 4);
   const int chunk = kFold ? kFoldGroups : NG - g_lo;
   auto fold = [&]() {
-    const int p = cc.p[z];
+    const int p = cc.mod[z].p;
     if (p == 256) return;
-    const double pd = (double)p, pinv = cc.pinv[z];
+    const double pd = (double)p, pinv = cc.mod[z].pinv;
 #pragma unroll
     for (int tx = 0; tx < TX; ++tx)
 #pragma unroll
@@ -503,8 +503,8 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
     j.xs = d.As + (size_t)z * d.mp * d.kp + (size_t)(j.x0 + wave * IX * RPI + lr) * d.kp;
     j.ys = d.Bs + (size_t)z * d.np * d.kp + (size_t)(j.y0 + wave * IY * RPI + lr) * d.kp;
     j.Wz = d.W + (size_t)z * d.np * d.mp;
-    j.p = ctab[d.N].p[z];
-    j.pinv = ctab[d.N].pinv[z];
+    j.p = ctab[d.N].mod[z].p;
+    j.pinv = ctab[d.N].mod[z].pinv;
     return true;
   };
   auto issue_x = [&](int8_t* buf, const Job& j, int k0) {

@@ -20,6 +20,15 @@ constexpr int kCrtRows = 4;      // CRT: consecutive rows per thread (256 thread
 // Per-(N, b) constants of Section 3.1 and Algorithms 2-3, passed to kernels
 // by value (they land in the kernel-argument segment and are read with
 // scalar loads).
+struct ModConst {   // one modulus, as the kernels use it (uniform, scalar loads)
+  double pinv;             // double(1/p)
+  // Limb weights of the residue paths, symmetric mod p (0 for p = 256): two
+  // limbs: c1 = mod(2^48, p); three: c1 = mod(2^40, p), c2 = mod(2^80, p).
+  double c1, c2;
+  uint32_t c1p, c2p, negp; // c1, c2 and -p in both 16-bit halves
+  int p;
+};
+
 struct CrtConsts {
   int N;
   int b;            // 64 or 32
@@ -30,8 +39,7 @@ struct CrtConsts {
   float c;          // single_down(-0.5 / (1 - 4 u_32))
   double P1, P2;    // double-double P (P2 = 0 for b = 32)
   double Pinv;      // double(1/P)
-  int p[kMaxModuli];
-  double pinv[kMaxModuli];  // double(1/p_l)
+  ModConst mod[kMaxModuli]; // p_l
   double s1[kMaxModuli];    // s_l1
   double s2[kMaxModuli];    // s_l2 (0 for b = 32)
 };

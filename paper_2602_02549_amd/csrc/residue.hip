@@ -57,29 +57,31 @@ __device__ __forceinline__ double round_prod(double x, double y) {
   return fma(x, y, kRound) - kRound;
 }
 
-__device__ __forceinline__ int int_of(double x) { return __double2loint(x + kRound); }
-
-// One exact reduction step r - p * round(r / p) for |r| < 2^50: the rounded
-// product is the nearest integer to r / p itself, because |r| |pinv - 1/p|
-// <= 2^-3 / p is below the distance 1 / (2p) from r / p to a half-integer
-// (odd p), and pinv is exact for p = 256.  The result lies in
-// [-(p-1)/2, (p-1)/2] for odd p and in [-128, 128] for p = 256.
-__device__ __forceinline__ double reduce_last(double r, double p, double pinv) {
-  return fma(-round_prod(r, pinv), p, r);
+// The low 32 bits, in two's complement, of an integer-valued |x| < 2^51.
+__device__ __forceinline__ uint32_t low32(double x) {
+  return (uint32_t)__double2loint(x + kRound);
 }
 
-// nsteps reduction steps (the last from |r| < 2^50); NS = 1..4 for N <= 49.
-// The earlier steps only shrink |r| exactly, for which rint of the rounded
-// product suffices.
-template <int NS>
-__device__ __forceinline__ int residue_i8(double v, int p, double pinv) {
-  double r = v;
-#pragma unroll
-  for (int s = 0; s + 1 < NS; ++s) {
-    const double q = rint(r * pinv);
-    r = fma(-q, (double)p, r);
-  }
-  return int_of(reduce_last(r, (double)p, pinv));
+typedef unsigned short v2u16 __attribute__((ext_vector_type(2)));
+
+// 16-bit pairs: the low halves of a (low half) and b; a * b + c in each half
+// (one packed instruction); a value in both halves.
+__device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b) {
+  return __builtin_amdgcn_perm(b, a, 0x05040100u);
+}
+__device__ __forceinline__ uint32_t pk_mad(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(v2u16, a) * __builtin_bit_cast(v2u16, b) +
+                                          __builtin_bit_cast(v2u16, c));
+}
+__device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(v2u16, a) + __builtin_bit_cast(v2u16, b));
+}
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(v2u16, a),
+                                                                __builtin_bit_cast(v2u16, b)));
+}
+__device__ __forceinline__ uint32_t both16(int x) {
+  return ((uint32_t)x & 0xFFFF) * 0x10001u;
 }
 
 // Low bytes of a, b, c, d as one word (byte 0 = a), three byte permutes:
@@ -91,63 +93,160 @@ __device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
   return __builtin_amdgcn_perm(cd, ab, 0x05040100u);
 }
 
-// The N residue bytes of 16 consecutive k of one row, one 16-byte store per
-// modulus.
-template <int NS>
-__device__ __forceinline__ void store_residues(const double (&v)[16], const CrtConsts& cc,
-                                               int8_t* __restrict__ dst, size_t slice) {
-  for (int l = 0; l < cc.N; ++l) {
-    const int p = cc.p[l];
-    const double pinv = cc.pinv[l];
-    int b[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) b[e] = residue_i8<NS>(v[e], p, pinv);
-    uint4 w;
-    w.x = pack4(b[0], b[1], b[2], b[3]);
-    w.y = pack4(b[4], b[5], b[6], b[7]);
-    w.z = pack4(b[8], b[9], b[10], b[11]);
-    w.w = pack4(b[12], b[13], b[14], b[15]);
-    *reinterpret_cast<uint4*>(dst + (size_t)l * slice) = w;
+// The low bytes of the four halves of two pairs (elements 0, 1 and 2, 3).
+__device__ __forceinline__ uint32_t bytes_of_pairs(uint32_t x01, uint32_t x23) {
+  return __builtin_amdgcn_perm(x23, x01, 0x06040200u);
+}
+
+// Residue paths of mode 1: limbs (2 or 3) or exact reduction steps (1, 3 or
+// 4; the limbs cover every N that would take two steps, and an extra step is
+// exact anyway); kAnyPath chooses at run time from the constants (grouped
+// launches, whose problems differ in N).
+enum ResiduePath { kLimbs2, kLimbs3, kSteps1, kSteps3, kSteps4, kAnyPath };
+
+// The constants of one modulus; 2^-40 (three limbs) or 2^-48 as a scalar that
+// the compiler takes for another value for each modulus, so that the mid limbs
+// computed from it are not kept in registers across the moduli.
+struct Modulus : ModConst {
+  double minv = 0.0;
+  __device__ __forceinline__ explicit Modulus(const ModConst& m) : ModConst(m) {}
+  __device__ __forceinline__ void forget(double mid_inv) {
+    minv = mid_inv;
+    __asm__ volatile("" : "+s"(minv));
+  }
+};
+
+// Calls f(l, modulus l) for this workgroup's moduli; the next modulus'
+// constants are loaded while f works on this one's.  The workgroups of grid
+// row y of Y take moduli [y N / Y, (y + 1) N / Y): when a launch has too few
+// tiles to occupy the GPU, several workgroups share a tile.
+template <typename F>
+__device__ __forceinline__ void for_moduli(const CrtConsts& cc, F&& f) {
+  const int y = (int)blockIdx.y, parts = (int)gridDim.y;
+  const int l0 = y * cc.N / parts, l1 = (y + 1) * cc.N / parts;
+  ModConst next = cc.mod[l0];
+  for (int l = l0; l < l1; ++l) {
+    const Modulus md(next);
+    next = cc.mod[min(l + 1, kMaxModuli - 1)];
+    f(l, md);
   }
 }
 
-// Limb form of the residues: L = 2 limbs split at 2^48, or L = 3 limbs
-// split at 2^80 and 2^40 (bounds in the file header).
-template <int L>
-__device__ __forceinline__ void store_residues_limbs(const double (&v)[16], const CrtConsts& cc,
-                                                     int8_t* __restrict__ dst, size_t slice) {
-  static_assert(L == 2 || L == 3, "limbs");
-  constexpr double kS = L == 2 ? 0x1p48 : 0x1p40, kSinv = L == 2 ? 0x1p-48 : 0x1p-40;
-  double lo[16], mid[16], hi[16];
+// M scaled integers v, |v| < 2^B, prepared for their residues on one path.
+// Only the rounded quotient needs FP64: q = round(r / p) of the limb sum
+// r = hi c2 + mid c1 + lo, |r| < 2^50 (exact), comes out of one fma with
+// kRound (its low bits are q; the rounded product is the nearest integer to
+// r / p itself, because |r| |pinv - 1/p| <= 2^-3 / p is below the distance
+// 1 / (2p) from r / p to a half-integer for odd p, and pinv is exact for
+// p = 256).  The residue r - q p, which lies in [-(p-1)/2, (p-1)/2] for odd p
+// and in [-128, 128] for p = 256, is then formed mod 2^16 from the low 16
+// bits of the limbs and of q, two elements per packed instruction.
+// KEEP: the limbs stay in registers, and an element and modulus cost 2 FP64
+// instructions (3 for three limbs, 1 for one step).  Otherwise (the complex
+// forms, with twice the elements) the mid limbs are formed again for each
+// modulus, through mid c1 + lo = w + mid (c1 - 2^48), w = mid 2^48 + lo: 4
+// FP64 (5).  Either way 1 packed
+// (1.5, 0.5) and 0.75 permute instructions follow.  Forming r - q p in FP64
+// and reading its low word took 5 (6, 4) FP64 with the limbs kept and 8 (12)
+// without.  At 2048^3 (N = 14) a side's residues went from 23.7 to 20.0 us, at
+// 4096^3 (N = 18) from 103 to 91 us, at 8192^3 (N = 14), where the pass runs
+// at the copy rate, from 301 to 289 us.
+template <int PATH, int M, bool KEEP>
+struct Scaled {
+  static constexpr bool kLimbs = PATH == kLimbs2 || PATH == kLimbs3;
+  static constexpr bool k3 = PATH == kLimbs3;
+  static constexpr bool kOne = kLimbs || PATH == kSteps1;   // r needs no earlier step
+  static constexpr double kS = k3 ? 0x1p40 : 0x1p48, kSinv = k3 ? 0x1p-40 : 0x1p-48;
+  // KEEP: lo; otherwise mid kS + lo
+  double lo[M], mid[kLimbs && KEEP ? M : 1], hi[k3 ? M : 1];
+  uint32_t lo16[kOne ? M / 2 : 1], mid16[kLimbs ? M / 2 : 1], hi16[k3 ? M / 2 : 1];
+
+  __device__ __forceinline__ explicit Scaled(const double (&v)[M]) {
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    double rem = v[e];
-    if (L == 3) {
-      hi[e] = round_prod(rem, 0x1p-80);        // |v| < 2^122: |hi| <= 2^42
-      rem = fma(-hi[e], 0x1p80, rem);          // exact, |rem| <= 2^79
-    }
-    mid[e] = round_prod(rem, kSinv);
-    lo[e] = fma(-mid[e], kS, rem);             // exact, |lo| <= 2^47 (L = 2), 2^39 (L = 3)
-  }
-  for (int l = 0; l < cc.N; ++l) {
-    const double p = (double)cc.p[l];
-    const double pinv = cc.pinv[l];
-    const double c1 = reduce_last(kS, p, pinv);                     // mod(2^s, p)
-    const double c2 = L == 3 ? reduce_last(c1 * c1, p, pinv) : 0.0;  // mod(2^80, p)
-    int b[16];
+    for (int e = 0; e < M; e += 2) {
+      uint32_t lw[2], mw[2], hw[2];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      double r = fma(mid[e], c1, lo[e]);
-      if (L == 3) r = fma(hi[e], c2, r);
-      b[e] = int_of(reduce_last(r, p, pinv));
+      for (int u = 0; u < 2; ++u) {
+        double rem = v[e + u];
+        if constexpr (k3) {
+          const double t = fma(rem, 0x1p-80, kRound);   // |v| < 2^122: |hi| <= 2^42
+          hw[u] = (uint32_t)__double2loint(t);
+          hi[e + u] = t - kRound;
+          rem = fma(-hi[e + u], 0x1p80, rem);           // exact, |rem| <= 2^79
+        }
+        if constexpr (kLimbs) {
+          lo[e + u] = rem;
+          const double t = fma(rem, kSinv, kRound);
+          mw[u] = (uint32_t)__double2loint(t);
+          if constexpr (KEEP) mid[e + u] = t - kRound;
+          rem = fma(-(t - kRound), kS, rem);            // exact, <= 2^47 (2), 2^39 (3)
+        }
+        if constexpr (KEEP || !kLimbs) lo[e + u] = rem;
+        if constexpr (kOne) lw[u] = low32(rem);
+      }
+      if constexpr (kOne) lo16[e / 2] = pair16(lw[0], lw[1]);
+      if constexpr (kLimbs) mid16[e / 2] = pair16(mw[0], mw[1]);
+      if constexpr (k3) hi16[e / 2] = pair16(hw[0], hw[1]);
     }
-    uint4 w;
-    w.x = pack4(b[0], b[1], b[2], b[3]);
-    w.y = pack4(b[4], b[5], b[6], b[7]);
-    w.z = pack4(b[8], b[9], b[10], b[11]);
-    w.w = pack4(b[12], b[13], b[14], b[15]);
-    *reinterpret_cast<uint4*>(dst + (size_t)l * slice) = w;
   }
+
+  // Residues of elements 2e and 2e + 1 as signed 16-bit halves.
+  __device__ __forceinline__ uint32_t pair(int e, const Modulus& md) const {
+    if constexpr (kOne) {
+      double q[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        double r = lo[2 * e + u];
+        if constexpr (KEEP) {
+          if constexpr (kLimbs) r = fma(mid[2 * e + u], md.c1, r);
+          if constexpr (k3) r = fma(hi[2 * e + u], md.c2, r);
+        } else {
+          if constexpr (kLimbs) r = fma(round_prod(r, md.minv), md.c1 - kS, r);
+          if constexpr (k3) r = fma(hi[2 * e + u], md.c2, r);
+        }
+        q[u] = fma(r, md.pinv, kRound);
+      }
+      uint32_t x = lo16[e];
+      if constexpr (kLimbs) x = pk_mad(mid16[e], md.c1p, x);
+      if constexpr (k3) x = pk_mad(hi16[e], md.c2p, x);
+      return pk_mad(pair16(__double2loint(q[0]), __double2loint(q[1])), md.negp, x);
+    } else {
+      // Two (three) earlier steps only shrink |r| exactly, for which rint of
+      // the rounded product suffices; the last starts from |r| < 2^50.
+      uint32_t q[2], w[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        double r = lo[2 * e + u];
+#pragma unroll
+        for (int s = 0; s < (PATH == kSteps3 ? 2 : 3); ++s) r = fma(-rint(r * md.pinv), (double)md.p, r);
+        q[u] = (uint32_t)__double2loint(fma(r, md.pinv, kRound));
+        w[u] = low32(r);
+      }
+      return pk_mad(pair16(q[0], q[1]), md.negp, pair16(w[0], w[1]));
+    }
+  }
+
+  // The residue bytes of elements 4q .. 4q + 3.
+  __device__ __forceinline__ uint32_t word(int q, const Modulus& md) const {
+    return bytes_of_pairs(pair(2 * q, md), pair(2 * q + 1, md));
+  }
+  __device__ __forceinline__ uint4 words(const Modulus& md) const {
+    static_assert(M == 16, "16 bytes");
+    return make_uint4(word(0, md), word(1, md), word(2, md), word(3, md));
+  }
+};
+
+// The N residue bytes of 16 consecutive k of one row, one 16-byte store per
+// modulus.  (8 k of two rows per thread, with 116 registers and 4 workgroups
+// per CU against 164 and 3, walks the moduli twice: 22 us against 20 us a
+// side at 2048^3, 299 against 287 us at 8192^3.)
+template <int PATH>
+__device__ __forceinline__ void store_residues(const double (&v)[16], const CrtConsts& cc,
+                                               int8_t* __restrict__ dst, size_t slice) {
+  const Scaled<PATH, 16, true> x(v);
+  for_moduli(cc, [&](int l, const Modulus& md) {
+    *reinterpret_cast<uint4*>(dst + (size_t)l * slice) = x.words(md);
+  });
 }
 
 // Workgroup barrier for the LDS tile only: it waits for this wave's LDS
@@ -229,14 +328,6 @@ __device__ __forceinline__ void tile_stage(const T (&x)[16], int rows, int k, in
   }
 }
 
-// Each thread reads 16 consecutive k of one row from the staged tile and
-// writes 16 bytes per slice (mode 0: Abar; mode 1: the N residues).
-// Residue paths of mode 1: limbs (2 or 3) or exact reduction steps (1, 3 or
-// 4; the limbs cover every N that would take two steps, and an extra step is
-// exact anyway); kAnyPath chooses at run time from the constants (grouped
-// launches, whose problems differ in N).
-enum ResiduePath { kLimbs2, kLimbs3, kSteps1, kSteps3, kSteps4, kAnyPath };
-
 int residue_path(const CrtConsts& cc) {
   if (cc.nlimbs == 2) return kLimbs2;
   if (cc.nlimbs == 3) return kLimbs3;
@@ -246,27 +337,23 @@ int residue_path(const CrtConsts& cc) {
 template <int PATH>
 __device__ __forceinline__ void store_residues_path(const double (&v)[16], const CrtConsts& cc,
                                                     int8_t* __restrict__ dst, size_t slice) {
-  switch (PATH) {
-    case kLimbs2: store_residues_limbs<2>(v, cc, dst, slice); break;
-    case kLimbs3: store_residues_limbs<3>(v, cc, dst, slice); break;
-    case kSteps1: store_residues<1>(v, cc, dst, slice); break;
-    case kSteps3: store_residues<3>(v, cc, dst, slice); break;
-    case kSteps4: store_residues<4>(v, cc, dst, slice); break;
-    default:
-      if (cc.nlimbs == 2) {          // uniform branches
-        store_residues_limbs<2>(v, cc, dst, slice);
-      } else if (cc.nlimbs == 3) {
-        store_residues_limbs<3>(v, cc, dst, slice);
-      } else if (cc.nsteps <= 1) {
-        store_residues<1>(v, cc, dst, slice);
-      } else if (cc.nsteps <= 3) {
-        store_residues<3>(v, cc, dst, slice);
-      } else {
-        store_residues<4>(v, cc, dst, slice);
-      }
+  if constexpr (PATH != kAnyPath) {
+    store_residues<PATH>(v, cc, dst, slice);
+  } else if (cc.nlimbs == 2) {          // uniform branches
+    store_residues<kLimbs2>(v, cc, dst, slice);
+  } else if (cc.nlimbs == 3) {
+    store_residues<kLimbs3>(v, cc, dst, slice);
+  } else if (cc.nsteps <= 1) {
+    store_residues<kSteps1>(v, cc, dst, slice);
+  } else if (cc.nsteps <= 3) {
+    store_residues<kSteps3>(v, cc, dst, slice);
+  } else {
+    store_residues<kSteps4>(v, cc, dst, slice);
   }
 }
 
+// Each thread reads 16 consecutive k of one row from the staged tile and
+// writes 16 bytes per slice (mode 0: Abar; mode 1: the N residues).
 template <int MODE, int PATH>
 __device__ __forceinline__ void tile_finish(const double* tile, int64_t aux, int rows, int k_pad,
                                             size_t slice, const CrtConsts& cc,
@@ -374,26 +461,15 @@ __global__ __launch_bounds__(256) void k_slices(const T* __restrict__ src, int l
 //     parts come from the residue path's arithmetic, and the third is their
 //     sum brought back into the symmetric range by one correction.
 
-// Residue of one value for modulus (p, pd, pinv) on the residue path; the
-// limb paths split the value again for each modulus, which keeps no
-// per-value state across moduli (registers stay free for the next tile's
-// loads).  c1 = mod(2^s, p) and c2 = mod(2^80, p) of the limb paths.
-template <int PATH>
-__device__ __forceinline__ int residue_one(double v, int p, double pd, double pinv, double c1,
-                                           double c2) {
-  if constexpr (PATH == kLimbs2) {
-    const double mid = round_prod(v, 0x1p-48);
-    const double lo = fma(-mid, 0x1p48, v);            // exact, |lo| <= 2^47
-    return int_of(reduce_last(fma(mid, c1, lo), pd, pinv));
-  } else if constexpr (PATH == kLimbs3) {
-    const double hi = round_prod(v, 0x1p-80);
-    const double rem = fma(-hi, 0x1p80, v);            // exact, |rem| <= 2^79
-    const double mid = round_prod(rem, 0x1p-40);
-    const double lo = fma(-mid, 0x1p40, rem);          // exact, |lo| <= 2^39
-    return int_of(reduce_last(fma(hi, c2, fma(mid, c1, lo)), pd, pinv));
-  } else {
-    return residue_i8<PATH == kSteps1 ? 1 : PATH == kSteps3 ? 3 : 4>(v, p, pinv);
-  }
+// The residues of the sums of two pairs of residues: each in [-(p-1)/2,
+// (p-1)/2] (odd p) or [-128, 128] (p = 256, bytes mod 256), so with lo =
+// -(p-1)/2 (-128) the sum less lo, u, lies in (-p, 2p), and the smallest of
+// u, u + p and u - p as unsigned 16-bit values is the one in [0, p).
+__device__ __forceinline__ uint32_t pair_sum(uint32_t a, uint32_t b, int p) {
+  const int lo = (p - 1) / 2 + 1 - p;
+  const uint32_t u = pk_add(pk_add(a, b), both16(-lo));
+  const uint32_t w = pk_min(pk_min(u, pk_add(u, both16(p))), pk_add(u, both16(-p)));
+  return pk_add(w, both16(lo));
 }
 
 // The thread's 16 staged elements of its row (the order of tile_finish).
@@ -439,39 +515,24 @@ __device__ __forceinline__ void tile_finish_cx(double (&vr)[16], double (&vi)[16
       vi[e] = trunc(ldexp(vi[e], sh));
     }
     const size_t set = (size_t)cc.N * slice;
-    for (int l = 0; l < cc.N; ++l) {
-      const int p = cc.p[l], hi = (p - 1) / 2, lo = hi + 1 - p;
-      const double pd = (double)p, pinv = cc.pinv[l];
-      double c1 = 0.0, c2 = 0.0;
-      if constexpr (PATH == kLimbs2) c1 = reduce_last(0x1p48, pd, pinv);
-      if constexpr (PATH == kLimbs3) {
-        c1 = reduce_last(0x1p40, pd, pinv);
-        c2 = reduce_last(c1 * c1, pd, pinv);
-      }
-      // residues of the parts in [-(p-1)/2, (p-1)/2] (odd p) or [-128, 128]
-      // (p = 256, stored as bytes mod 256): one correction puts their sum in
-      // the range
+    const Scaled<PATH, 16, false> xr(vr), xi(vi);
+    for_moduli(cc, [&](int l, Modulus md) {
+      md.forget(decltype(xr)::kSinv);
+      const int p = md.p;
       uint32_t wr[4], wi[4], ws[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        int br[4], bi[4], bs[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          br[u] = residue_one<PATH>(vr[4 * q + u], p, pd, pinv, c1, c2);
-          bi[u] = residue_one<PATH>(vi[4 * q + u], p, pd, pinv, c1, c2);
-          int x = br[u] + bi[u];
-          x -= x > hi ? p : 0;
-          bs[u] = x + (x < lo ? p : 0);
-        }
-        wr[q] = pack4(br[0], br[1], br[2], br[3]);
-        wi[q] = pack4(bi[0], bi[1], bi[2], bi[3]);
-        ws[q] = pack4(bs[0], bs[1], bs[2], bs[3]);
+        const uint32_t r0p = xr.pair(2 * q, md), r1p = xr.pair(2 * q + 1, md);
+        const uint32_t i0p = xi.pair(2 * q, md), i1p = xi.pair(2 * q + 1, md);
+        wr[q] = bytes_of_pairs(r0p, r1p);
+        wi[q] = bytes_of_pairs(i0p, i1p);
+        ws[q] = bytes_of_pairs(pair_sum(r0p, i0p, p), pair_sum(r1p, i1p, p));
       }
       int8_t* d = dst + (size_t)l * slice;
       *reinterpret_cast<uint4*>(d) = make_uint4(wr[0], wr[1], wr[2], wr[3]);
       *reinterpret_cast<uint4*>(d + set) = make_uint4(wi[0], wi[1], wi[2], wi[3]);
       *reinterpret_cast<uint4*>(d + 2 * set) = make_uint4(ws[0], ws[1], ws[2], ws[3]);
-    }
+    });
   }
 }
 
@@ -504,7 +565,7 @@ __device__ __forceinline__ void tile_loads_cx(const T* __restrict__ src, int ld,
 // staged and read back, then the imaginary parts, then the next tile's loads
 // go out before the arithmetic of this one.
 template <typename T, bool TRANS, int MODE, int PATH>
-__global__ __launch_bounds__(256) void k_slices_cx(const T* __restrict__ src, int ld, int rows,
+__global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_slices_cx(const T* __restrict__ src, int ld, int rows,
                                                    int k, int k_pad, int gy, int tiles,
                                                    size_t slice, const void* __restrict__ aux,
                                                    CrtConsts cc, int8_t* __restrict__ out) {
@@ -549,9 +610,7 @@ __global__ __launch_bounds__(256) void k_slices_cx(const T* __restrict__ src, in
 // (half + i, kh + h) as re; of B at row j of Bhat^T: (j, h) re, (j, kh + h) im.
 //   mode 0: the bars; rows i and half + i share mu'_i (the same maximum).
 //   mode 1: the residues; row i is scaled by shift[i], row half + i by
-//     shift[half + i] (their Cbar maxima differ).  The residue of -x is the
-//     negated residue of x (the reduction is odd-symmetric; for p = 256 the
-//     byte of -(-128) wraps to -128 as the real kernel's 128 does).
+//     shift[half + i] (their Cbar maxima differ).
 template <int MODE, int PATH, bool ASIDE>
 __device__ __forceinline__ void tile_finish_emb(const double (&vr)[16], const double (&vi)[16],
                                                 const void* __restrict__ aux, int rows, int ldo,
@@ -597,43 +656,19 @@ __device__ __forceinline__ void tile_finish_emb(const double (&vr)[16], const do
         xr[e] = trunc(ldexp(vr[e], e2));
         xi[e] = trunc(ldexp(vi[e], e2));
       }
-      int8_t* b0 = d0 + blk * dh;
-      int8_t* b1 = d1 + blk * dh;
-      for (int l = 0; l < cc.N; ++l) {
-        const int p = cc.p[l];
-        const double pd = (double)p, pinv = cc.pinv[l];
-        double c1 = 0.0, c2 = 0.0;
-        if constexpr (PATH == kLimbs2) c1 = reduce_last(0x1p48, pd, pinv);
-        if constexpr (PATH == kLimbs3) {
-          c1 = reduce_last(0x1p40, pd, pinv);
-          c2 = reduce_last(c1 * c1, pd, pinv);
-        }
-        uint32_t first[4], second[4];
+      // A side: row rg holds [re, -im], row half + rg [im, re]; B side [re, im]
+      int8_t* br = (ASIDE && blk == 1 ? d1 : d0) + blk * dh;
+      int8_t* bi = (ASIDE && blk == 1 ? d0 : d1) + blk * dh;
+      if (ASIDE && blk == 0) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          int br[4], bi[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            br[u] = residue_one<PATH>(xr[4 * q + u], p, pd, pinv, c1, c2);
-            bi[u] = residue_one<PATH>(xi[4 * q + u], p, pd, pinv, c1, c2);
-          }
-          // A side: row rg holds [re, -im], row half + rg [im, re]; B side [re, im]
-          if (!ASIDE) {
-            first[q] = pack4(br[0], br[1], br[2], br[3]);
-            second[q] = pack4(bi[0], bi[1], bi[2], bi[3]);
-          } else if (blk == 0) {
-            first[q] = pack4(br[0], br[1], br[2], br[3]);
-            second[q] = pack4(-bi[0], -bi[1], -bi[2], -bi[3]);
-          } else {
-            first[q] = pack4(bi[0], bi[1], bi[2], bi[3]);
-            second[q] = pack4(br[0], br[1], br[2], br[3]);
-          }
-        }
-        *reinterpret_cast<uint4*>(b0 + (size_t)l * slice) =
-            make_uint4(first[0], first[1], first[2], first[3]);
-        *reinterpret_cast<uint4*>(b1 + (size_t)l * slice) =
-            make_uint4(second[0], second[1], second[2], second[3]);
+        for (int e = 0; e < 16; ++e) xi[e] = -xi[e];
       }
+      const Scaled<PATH, 16, PATH != kLimbs3> sr(xr), si(xi);
+      for_moduli(cc, [&](int l, Modulus md) {
+        md.forget(decltype(sr)::kSinv);
+        *reinterpret_cast<uint4*>(br + (size_t)l * slice) = sr.words(md);
+        *reinterpret_cast<uint4*>(bi + (size_t)l * slice) = si.words(md);
+      });
     }
   }
 }
@@ -641,14 +676,14 @@ __device__ __forceinline__ void tile_finish_emb(const double (&vr)[16], const do
 // Grid-stride loop as k_slices_cx over the complex source's tiles (kh / 128
 // k tiles by gy row tiles).
 template <typename T, bool TRANS, int MODE, int PATH>
-__global__ __launch_bounds__(256) void k_slices_emb(const T* __restrict__ src, int ld, int rows,
+__global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_slices_emb(const T* __restrict__ src, int ld, int rows,
                                                     int k, int kh, int gy, int tiles, int half,
                                                     size_t slice, const void* __restrict__ aux,
                                                     CrtConsts cc, int8_t* __restrict__ out) {
-  // The A side's residues (two row blocks, four stores per modulus) hold
-  // the most registers: there the next tile's loads are not issued early,
-  // which lets two workgroups share a CU instead of one.
-  constexpr bool kPrefetch = !(TRANS && MODE == 1);
+  // The A side's residues (two row blocks, four stores per modulus) and the
+  // three-limb ones hold the most registers: there the next tile's loads are
+  // not issued early, which lets two workgroups share a CU instead of one.
+  constexpr bool kPrefetch = !(MODE == 1 && (TRANS || PATH == kLimbs3));
   __shared__ double tile[kTR * kRS];
   int i = blockIdx.x;
   if (i >= tiles) return;
@@ -831,6 +866,7 @@ __global__ __launch_bounds__(256) void k_plan_slices(const T* __restrict__ src, 
 constexpr int kMaxDevices = 64;
 constexpr int kGrouped = 2 + kAnyPath;
 constexpr int kVariants = 2 * kGrouped;
+constexpr int kPartSlots = 512;   // workgroups that shared tiles may fill (two per CU)
 std::atomic<int> g_cus[kMaxDevices];
 std::atomic<int> g_occ[2][2][kVariants];
 std::atomic<int> g_occ_cx[2][2][kGrouped];   // k_slices_cx: variant 0 = mode 2, 1 + path
@@ -878,6 +914,16 @@ void fill_occ() {
   b[1 + kSteps4] = resident_per_cu(k_slices_emb<T, TR, 1, kSteps4>);
 }
 
+// Launch grid of `tiles` tiles on `grid` workgroups that form `N` residues each
+// (1: bars): while one workgroup per tile and modulus pair fits the slots that
+// the tiles leave free, the moduli are dealt to several workgroups per tile
+// (for_moduli), at least two each.  The tile is then read again by each of
+// them, from L2.  At 256^3 (16 tiles, N = 14) a side went from 9.8 to 6.7 us.
+dim3 shared_grid(int grid, int tiles, int N) {
+  const int parts = grid == tiles ? std::min(N / 2, kPartSlots / std::max(tiles, 1)) : 1;
+  return dim3((unsigned)grid, (unsigned)std::max(parts, 1));
+}
+
 // Workgroups for `tiles` tiles: all resident slots of the device, or one per
 // tile if the device's figures are unknown.  A positive g_slice_cap (a test
 // knob set through ozaki2_debug_tuning) caps the count, so that each
@@ -912,7 +958,8 @@ struct SliceLaunch {
 template <typename T, bool TR, int MODE, int PATH>
 void launch_one(hipStream_t s, const SliceLaunch<T>& L, const CrtConsts& cc) {
   const int variant = MODE != 1 ? 0 : 1 + PATH;   // mode 2 has mode 0's resources
-  const dim3 grid((unsigned)slice_grid(std::is_same<T, float>::value, TR, variant, L.tiles));
+  const dim3 grid = shared_grid(slice_grid(std::is_same<T, float>::value, TR, variant, L.tiles),
+                                L.tiles, MODE == 1 ? cc.N : 1);
   hipLaunchKernelGGL((k_slices<T, TR, MODE, PATH>), grid, dim3(256), 0, s, L.src, L.ld, L.rows,
                      L.k, L.k_pad, L.gy, L.tiles, L.slice, L.aux, cc, L.out);
 }
@@ -939,7 +986,8 @@ void launch_side(hipStream_t s, int mode, const SliceLaunch<T>& L, const CrtCons
 template <typename T, bool TR, int MODE, int PATH>
 void launch_one_cx(hipStream_t s, const SliceLaunch<T>& L, const CrtConsts& cc) {
   const int variant = MODE != 1 ? 0 : 1 + PATH;
-  const dim3 grid((unsigned)slice_grid(std::is_same<T, float>::value, TR, variant, L.tiles, 1));
+  const dim3 grid = shared_grid(slice_grid(std::is_same<T, float>::value, TR, variant, L.tiles, 1),
+                                L.tiles, MODE == 1 ? cc.N : 1);
   hipLaunchKernelGGL((k_slices_cx<T, TR, MODE, PATH>), grid, dim3(256), 0, s, L.src, L.ld, L.rows,
                      L.k, L.k_pad, L.gy, L.tiles, L.slice, L.aux, cc, L.out);
 }
@@ -1100,7 +1148,8 @@ template <typename T, bool TR, int MODE, int PATH>
 void emb_one(hipStream_t s, const T* src, int ld, int rows, int k, int kh, int gy, int tiles,
              int half, size_t slice, const void* aux, const CrtConsts& cc, int8_t* out) {
   const int variant = MODE == 0 ? 0 : 1 + PATH;
-  const dim3 grid((unsigned)slice_grid(std::is_same<T, float>::value, TR, variant, tiles, 2));
+  const dim3 grid = shared_grid(slice_grid(std::is_same<T, float>::value, TR, variant, tiles, 2),
+                                tiles, MODE == 1 ? cc.N : 1);
   hipLaunchKernelGGL((k_slices_emb<T, TR, MODE, PATH>), grid, dim3(256), 0, s, src, ld, rows, k,
                      kh, gy, tiles, half, slice, aux, cc, out);
 }

@@ -31,7 +31,7 @@ struct SmallMod {
   int p, hi;
   float pinv;
   __device__ explicit SmallMod(const CrtConsts& cc, int l)
-      : p(cc.p[l]), hi((cc.p[l] - 1) / 2), pinv((float)cc.pinv[l]) {}
+      : p(cc.mod[l].p), hi((cc.mod[l].p - 1) / 2), pinv((float)cc.mod[l].pinv) {}
   __device__ uint32_t byte(int x, int i) const {
     return (uint32_t)(mod_small(x, p, pinv, hi) & 0xFF) << (8 * i);
   }

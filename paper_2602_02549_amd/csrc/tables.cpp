@@ -333,8 +333,8 @@ bool build_consts(int N, int b, int table, CrtConsts* out) {
   }
 
   for (int l = 0; l < N; ++l) {
-    cc.p[l] = kModuli[l];
-    cc.pinv[l] = 1.0 / (double)kModuli[l];
+    cc.mod[l].p = kModuli[l];
+    cc.mod[l].pinv = 1.0 / (double)kModuli[l];
     if (b == 64) {
       // s_l1: upper beta_l bits of x_l, i.e. truncation to the grid
       // 2^(floor(log2 r) + 1 + ceil(log2 rho) - 53); s_l2 = double(x_l - s_l1).
@@ -387,6 +387,23 @@ bool build_consts(int N, int b, int table, CrtConsts* out) {
   // B <= 50 one reduction step is cheaper.
   const int B = 6 + (int)std::floor((double)cc.Pprime);
   cc.nlimbs = B <= 50 ? 0 : (B <= 90 ? 2 : (B <= 122 ? 3 : 0));
+  for (int l = 0; l < N && cc.nlimbs; ++l) {
+    const int pl = kModuli[l], s = cc.nlimbs == 2 ? 48 : 40;
+    auto pow2 = [&](int e) {   // mod(2^e, p_l), symmetric (0 for p = 256: e >= 8)
+      int r = 1;
+      for (int q = 0; q < e; ++q) r = 2 * r % pl;
+      return r > pl / 2 ? r - pl : r;
+    };
+    cc.mod[l].c1 = pow2(s);
+    cc.mod[l].c2 = cc.nlimbs == 3 ? pow2(80) : 0;
+  }
+  for (int l = 0; l < N; ++l) {
+    auto both16 = [](int v) { return ((uint32_t)v & 0xFFFF) * 0x10001u; };
+    ModConst& md = cc.mod[l];
+    md.c1p = both16((int)md.c1);
+    md.c2p = both16((int)md.c2);
+    md.negp = both16(-md.p);
+  }
   *out = cc;
   return true;
 }
