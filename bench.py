@@ -455,8 +455,10 @@ def memory_phases(torch, dev, phase_ms: dict, m: int, n: int, k: int, N: int, s:
     ref = hbm_reference(torch, dev)
     algo = {
         "absmax_A": s * m * k, "absmax_B": s * k * n,
-        "bar_A": s * m * k + m * k, "bar_B": s * k * n + k * n,
-        "residue_A": s * m * k + N * m * k, "residue_B": s * k * n + N * k * n,
+        # above the one-read limit of B the bars of both operands are one launch
+        "bars": s * m * k + m * k + (s * k * n + k * n if "bar_B" not in phase_ms else 0),
+        "bar_B": s * k * n + k * n,
+        "residues": s * (m * k + k * n) + N * (m * k + k * n),
         "crt": N * m * n + s * m * n,
     }
     out = {"hbm_reference": ref}

@@ -362,7 +362,7 @@ const char *ozaki2_profile_name(int phase);
  * none of them).  Sets knob to value and stores the old value in *previous
  * (HOST pointer, may be NULL).  Affects calls made after it; a batch already
  * captured keeps the choices it was captured with unless its knobs differ.
- *   OZAKI2_KNOB_SLICE_WORKGROUPS : cap on the workgroups of each residue /
+ *   OZAKI2_KNOB_SLICE_WORKGROUPS : cap on the workgroups per operand of a residue /
  *                                  slice launch (0 = none, the default)
  *   OZAKI2_KNOB_GEMM_TILE        : product tile of single-problem calls
  *                                  (0 = automatic, 1 = 256x256, 2 = 128x128)

@@ -52,12 +52,12 @@ bool g_plan_ok[2][2] = {};
 // profiling (HIP events around each phase on the library stream)
 // ---------------------------------------------------------------------------
 enum Phase {
-  PH_INIT, PH_ABSMAX_A, PH_ABSMAX_B, PH_BAR_A, PH_BAR_B, PH_GEMM_SCALE, PH_SHIFTS, PH_RES_A,
-  PH_RES_B, PH_GEMM_RES, PH_CRT, PH_PLAN, PH_BATCH, PH_COUNT
+  PH_INIT, PH_ABSMAX_A, PH_ABSMAX_B, PH_BARS, PH_BAR_B, PH_GEMM_SCALE, PH_RES, PH_GEMM_RES, PH_CRT,
+  PH_PLAN, PH_BATCH, PH_COUNT
 };
-const char* kPhaseNames[PH_COUNT] = {"init", "absmax_A", "absmax_B", "bar_A", "bar_B",
-                                     "gemm_scale", "shifts", "residue_A", "residue_B",
-                                     "gemm_residue", "crt", "plan", "batched"};
+const char* kPhaseNames[PH_COUNT] = {"init", "absmax_A", "absmax_B", "bars", "bar_B",
+                                     "gemm_scale", "residues", "gemm_residue", "crt", "plan",
+                                     "batched"};
 struct ProfRec {
   int phase;
   hipEvent_t a, b;
@@ -309,7 +309,10 @@ int run_pipeline(Prec pr, int m, int n, int k, const void* A, int lda, const voi
     rmax = const_cast<int*>(pre->rmax);
     cmax = const_cast<int*>(pre->cmax);
     flag = pre->flag;
-  } else {
+  }
+  const SliceOperand oa{A, lda, m, L.mp, rowbits, rmax, mu, As};
+  const SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nu, Bs};
+  if (!pre) {
     {
       Scope sc(PH_INIT, s);
       launch_init(s, rowbits, L.mp, colbits, L.np, rmax, cmax, flag);
@@ -326,15 +329,12 @@ int run_pipeline(Prec pr, int m, int n, int k, const void* A, int lda, const voi
       launch_absmax_cols(s, pr, B, ldb, k, n, colbits, flag);
     }
     {
-      Scope sc(PH_BAR_A, s);
-      launch_slices(s, pr, 0, true, A, lda, m, k, L.mp, L.kp, rowbits, nullptr, cc, As);
+      Scope sc(PH_BARS, s);
+      launch_slices(s, pr, SliceSet::Real, true, &oa, fuse_b ? nullptr : &ob, k, L.kp, cc);
     }
-    {
+    if (fuse_b) {
       Scope sc(PH_BAR_B, s);
-      if (fuse_b)
-        launch_absbar_cols(s, pr, B, ldb, k, n, L.np, L.kp, colbits, flag, Bs);
-      else
-        launch_slices(s, pr, 0, false, B, ldb, n, k, L.np, L.kp, colbits, nullptr, cc, Bs);
+      launch_absbar_cols(s, pr, B, ldb, k, n, L.np, L.kp, colbits, flag, Bs);
     }
     // Cbar = Abar Bbar; keep row maxima (over j) and column maxima (over i).
     {
@@ -343,18 +343,12 @@ int run_pipeline(Prec pr, int m, int n, int k, const void* A, int lda, const voi
                      at<int8_t>(ws, L.part), L.part_bytes);
     }
   }
+  if (want_ef)
+    launch_debug_shifts(s, rowbits, rmax, m, colbits, cmax, n, at<int>(ws, L.mu_p),
+                        at<int>(ws, L.nu_p), at<float>(ws, L.ef));
   {
-    Scope sc(PH_SHIFTS, s);
-    launch_shifts(s, rowbits, rmax, m, colbits, cmax, n, cc.Pprime, cc.c, at<int>(ws, L.mu_p),
-                  at<int>(ws, L.nu_p), mu, nu, want_ef ? at<float>(ws, L.ef) : nullptr);
-  }
-  {
-    Scope sc(PH_RES_A, s);
-    launch_slices(s, pr, 1, true, A, lda, m, k, L.mp, L.kp, nullptr, mu, cc, As);
-  }
-  {
-    Scope sc(PH_RES_B, s);
-    launch_slices(s, pr, 1, false, B, ldb, n, k, L.np, L.kp, nullptr, nu, cc, Bs);
+    Scope sc(PH_RES, s);
+    launch_slices(s, pr, SliceSet::Real, false, &oa, &ob, k, L.kp, cc);
   }
   {
     Scope sc(PH_GEMM_RES, s);
@@ -364,9 +358,8 @@ int run_pipeline(Prec pr, int m, int n, int k, const void* A, int lda, const voi
   }
   {
     Scope sc(PH_CRT, s);
-    launch_crt(s, pr, W, (size_t)L.np * L.mp, L.mp, mu, nu, m, n, cc, flag, C, ldc);
+    launch_crt(s, pr, W, (size_t)L.np * L.mp, L.mp, mu, nu, m, n, cc, flag, status, C, ldc);
   }
-  launch_or_status(s, flag, status);
   return hipGetLastError() == hipSuccess ? OZAKI2_OK : OZAKI2_ERR_HIP;
 }
 
@@ -529,22 +522,19 @@ int zgemm_impl(Prec pr, int m, int n, int k, const void* A, int lda, const void*
   launch_init(s, rowbits, L.mp, colbits, L.np, rmax, cmax, flag);
   launch_absmax_rows(s, pr, A, lda, m, k, rowbits, flag, true, H);
   launch_absmax_cols(s, pr, B, ldb, k, n, colbits, flag, true);
-  launch_slices_embed(s, pr, 0, true, A, lda, m, k, Z.kh, L.mp, H, rowbits, nullptr, cc, As);
-  launch_slices_embed(s, pr, 0, false, B, ldb, n, k, Z.kh, L.np, 0, colbits, nullptr, cc, Bs);
+  const SliceOperand oa{A, lda, m, L.mp, rowbits, rmax, mu, As};
+  const SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nu, Bs};
+  launch_slices(s, pr, SliceSet::Embedding, true, &oa, &ob, k, Z.kh, cc);
   launch_gemm_i8(s, 1, As, 0, Bs, 0, L.mp, L.np, L.kp, 1, cc, nullptr, 0, 0, rmax, cmax,
                  at<int8_t>(ws, L.part), L.part_bytes);
-  launch_shifts(s, rowbits, rmax, L.mp, colbits, cmax, n, cc.Pprime, cc.c, at<int>(ws, L.mu_p),
-                at<int>(ws, L.nu_p), mu, nu, nullptr);
   // Algorithm 3 on the embedding, its residues formed from the complex
   // source; the CRT writes rows i (real) and H + i (imaginary) as pairs.
-  launch_slices_embed(s, pr, 1, true, A, lda, m, k, Z.kh, L.mp, H, nullptr, mu, cc, As);
-  launch_slices_embed(s, pr, 1, false, B, ldb, n, k, Z.kh, L.np, 0, nullptr, nu, cc, Bs);
+  launch_slices(s, pr, SliceSet::Embedding, false, &oa, &ob, k, Z.kh, cc);
   launch_gemm_i8(s, 0, As, (size_t)L.mp * L.kp, Bs, (size_t)L.np * L.kp, L.mp, L.np, L.kp, N, cc,
                  W, (size_t)L.np * L.mp, L.mp, nullptr, nullptr, at<int8_t>(ws, L.part),
                  L.part_bytes);
-  launch_crt_complex(s, pr, W, W + H, (size_t)L.np * L.mp, L.mp, mu, mu + H, nu, m, n, cc, flag, C,
-                     ldc);
-  launch_or_status(s, flag, status);
+  launch_crt_complex(s, pr, W, W + H, (size_t)L.np * L.mp, L.mp, mu, mu + H, nu, m, n, cc, flag,
+                     status, C, ldc);
   return hipGetLastError() == hipSuccess ? OZAKI2_OK : OZAKI2_ERR_HIP;
 }
 
@@ -604,22 +594,21 @@ int zgemm3m_impl(Prec pr, int m, int n, int k, const void* A, int lda, const voi
   launch_init(s, rowbits, L.mp, colbits, L.np, rmax, cmax, flag);
   launch_absmax_rows(s, pr, A, lda, m, k, rowbits, flag, true);
   launch_absmax_cols(s, pr, B, ldb, k, n, colbits, flag, true);
-  launch_slices_complex(s, pr, 2, true, A, lda, m, k, L.mp, L.kp, rowbits, nullptr, cc, X[2]);
-  launch_slices_complex(s, pr, 2, false, B, ldb, n, k, L.np, L.kp, colbits, nullptr, cc, Y[2]);
+  SliceOperand oa{A, lda, m, L.mp, rowbits, rmax, mu, X[2]};
+  SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nu, Y[2]};
+  launch_slices(s, pr, SliceSet::Complex3, true, &oa, &ob, k, L.kp, cc);
   launch_gemm_i8(s, 1, X[2], 0, Y[2], 0, L.mp, L.np, L.kp, 1, cc, nullptr, 0, 0, rmax, cmax,
                  at<int8_t>(w, L.part), L.part_bytes);
-  launch_shifts(s, rowbits, rmax, m, colbits, cmax, n, cc.Pprime, cc.c, at<int>(w, L.mu_p),
-                at<int>(w, L.nu_p), mu, nu, nullptr, -1);
   // Algorithm 3: residues of A'r, A'i and A'r + A'i (and of B) in one pass
-  // per operand, three residue products per modulus, and the CRT of the real
+  // over both operands, three residue products per modulus, and the CRT of the real
   // and imaginary residues formed from the three W.
-  launch_slices_complex(s, pr, 1, true, A, lda, m, k, L.mp, L.kp, nullptr, mu, cc, X[0]);
-  launch_slices_complex(s, pr, 1, false, B, ldb, n, k, L.np, L.kp, nullptr, nu, cc, Y[0]);
+  oa.out = X[0];
+  ob.out = Y[0];
+  launch_slices(s, pr, SliceSet::Complex3, false, &oa, &ob, k, L.kp, cc, -1);
   for (int q = 0; q < 3; ++q)
     launch_gemm_i8(s, 0, X[q], sa, Y[q], sb, L.mp, L.np, L.kp, N, cc, W[q], sw, L.mp, nullptr,
                    nullptr, at<int8_t>(w, L.part), L.part_bytes);
-  launch_crt_3m(s, pr, W[0], W[1], W[2], sw, L.mp, mu, nu, m, n, cc, flag, C, ldc);
-  launch_or_status(s, flag, status);
+  launch_crt_3m(s, pr, W[0], W[1], W[2], sw, L.mp, mu, nu, m, n, cc, flag, status, C, ldc);
   return hipGetLastError() == hipSuccess ? OZAKI2_OK : OZAKI2_ERR_HIP;
 }
 
@@ -667,7 +656,7 @@ namespace {
 // residues of B for every problem.
 enum BatchSlot {
   BS_INIT, BS_ABS_A, BS_ABS_B, BS_ABB, BS_SL_A, BS_BAR_B, BS_SL_B, BS_GS_BIG, BS_GS_SMALL,
-  BS_SHIFTS, BS_GR_BIG, BS_GR_SMALL, BS_CRT, BS_COUNT
+  BS_GR_BIG, BS_GR_SMALL, BS_CRT, BS_COUNT
 };
 constexpr int kMaxBatchEntries = 8;
 
@@ -776,7 +765,6 @@ void build_table(const std::vector<ProbDesc>& D, int split, std::vector<char>* o
     cp[BS_SL_B] = (d.kp / 128) * (d.np / 32);
     cp[BS_GS_BIG] = big ? group_gemm_blocks(d.mp, d.np, 256, 1) : 0;
     cp[BS_GS_SMALL] = big ? 0 : group_gemm_blocks(d.mp, d.np, 128, 1);
-    cp[BS_SHIFTS] = cdiv_i(d.m + d.n, 256);
     cp[BS_GR_BIG] = big ? group_gemm_blocks(d.mp, d.np, 256, d.N) : 0;
     cp[BS_GR_SMALL] = big ? 0 : group_gemm_blocks(d.mp, d.np, 128, d.N);
     cp[BS_CRT] = (int)crt_blocks(d.m, d.n);
@@ -848,12 +836,11 @@ void enqueue_batch(Prec pr, const BatchEntry& e, const CrtConsts* ctab, int* sta
   auto B = [&](int sl) { return e.blocks[sl]; };
   for (int p : e.zero_fill) launch_fill_zero(s, pr, C[p], ldc[p], mnkN[4 * p], mnkN[4 * p + 1]);
   if (e.active == 0) return;
-  launch_group_scale(s, pr, GP_INIT, D, M(BS_INIT), B(BS_INIT), ctab);
-  launch_group_scale(s, pr, GP_ABSMAX_A, D, M(BS_ABS_A), B(BS_ABS_A), ctab);
-  launch_group_scale(s, pr, GP_ABSMAX_B, D, M(BS_ABS_B), B(BS_ABS_B), ctab);
-  launch_group_scale(s, pr, GP_ABSBAR_B, D, M(BS_ABB), B(BS_ABB), ctab);
-  launch_group_slices(s, pr, 0, true, -1, D, M(BS_SL_A), B(BS_SL_A), ctab);
-  launch_group_slices(s, pr, 0, false, -1, D, M(BS_BAR_B), B(BS_BAR_B), ctab);
+  launch_group_scale(s, pr, GP_INIT, D, M(BS_INIT), B(BS_INIT));
+  launch_group_scale(s, pr, GP_ABSMAX_A, D, M(BS_ABS_A), B(BS_ABS_A));
+  launch_group_scale(s, pr, GP_ABSMAX_B, D, M(BS_ABS_B), B(BS_ABS_B));
+  launch_group_scale(s, pr, GP_ABSBAR_B, D, M(BS_ABB), B(BS_ABB));
+  launch_group_slices(s, pr, true, -1, D, M(BS_SL_A), B(BS_SL_A), M(BS_BAR_B), B(BS_BAR_B), ctab);
   if (e.per_problem) {
     for (size_t q = 0; q < e.hd.size(); ++q) {
       const ProbDesc& d = e.hd[q];
@@ -864,11 +851,10 @@ void enqueue_batch(Prec pr, const BatchEntry& e, const CrtConsts* ctab, int* sta
     launch_group_gemm(s, 1, 256, D, M(BS_GS_BIG), B(BS_GS_BIG), ctab);
     launch_group_gemm(s, 1, 128, D, M(BS_GS_SMALL), B(BS_GS_SMALL), ctab);
   }
-  launch_group_scale(s, pr, GP_SHIFTS, D, M(BS_SHIFTS), B(BS_SHIFTS), ctab);
-  launch_group_slices(s, pr, 1, true, e.res_path, D, M(BS_SL_A), B(BS_SL_A), ctab);
-  launch_group_slices(s, pr, 1, false, e.res_path, D, M(BS_SL_B), B(BS_SL_B), ctab);
+  launch_group_slices(s, pr, false, e.res_path, D, M(BS_SL_A), B(BS_SL_A), M(BS_SL_B), B(BS_SL_B),
+                      ctab);
   enqueue_residue_products(e, ctab, s);
-  launch_group_crt(s, pr, D, M(BS_CRT), B(BS_CRT), e.active, ctab, status);
+  launch_group_crt(s, pr, D, M(BS_CRT), B(BS_CRT), ctab, status);
 }
 
 // Copies a host table to the entry's device table, growing it if needed.
@@ -1303,15 +1289,14 @@ void plan_terms(Prec pr, int m, int n, int k, const void* A, int lda, const void
   launch_init(s, rowbits, L.mp, colbits, L.np, rmax, cmax, flag);
   launch_absmax_rows(s, pr, A, lda, m, k, rowbits, flag);
   // Cbar maxima exactly as the emulation computes them (Algorithm 2)
-  launch_slices(s, pr, 0, true, A, lda, m, k, L.mp, L.kp, rowbits, nullptr, cc,
-                at<int8_t>(ws, L.Abar));
-  if (L.kp <= kAbsBarMaxK) {
+  const bool fuse_b = L.kp <= kAbsBarMaxK;
+  if (fuse_b)
     launch_absbar_cols(s, pr, B, ldb, k, n, L.np, L.kp, colbits, flag, at<int8_t>(ws, L.Bbar));
-  } else {
+  else
     launch_absmax_cols(s, pr, B, ldb, k, n, colbits, flag);
-    launch_slices(s, pr, 0, false, B, ldb, n, k, L.np, L.kp, colbits, nullptr, cc,
-                  at<int8_t>(ws, L.Bbar));
-  }
+  const SliceOperand oa{A, lda, m, L.mp, rowbits, nullptr, nullptr, at<int8_t>(ws, L.Abar)};
+  const SliceOperand ob{B, ldb, n, L.np, colbits, nullptr, nullptr, at<int8_t>(ws, L.Bbar)};
+  launch_slices(s, pr, SliceSet::Real, true, &oa, fuse_b ? nullptr : &ob, k, L.kp, cc);
   // and one byte per entry, Cbar_ij != 0, which holds exactly when
   // (|A||B|)_ij > 0 (Abar, Bbar are >= 1 wherever A, B are nonzero): an
   // entry whose lower bound of S below underflows to 0 is then known to be

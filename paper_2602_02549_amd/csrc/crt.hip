@@ -72,6 +72,12 @@ __device__ __forceinline__ void crt_sums(const int8_t* __restrict__ wp, size_t s
   }
 }
 
+// One thread of a launch folds the call's non-finite flag into the sticky word.
+__device__ __forceinline__ void fold_status(const int* __restrict__ flag,
+                                            int* __restrict__ status) {
+  if (threadIdx.x == 0 && *flag) atomicOr(status, 1);
+}
+
 // Q, C'' and the output 2^ex C'' (NaN when the non-finite flag is set) of
 // one entry from its C'(1), C'(2).
 template <typename T>
@@ -312,8 +318,9 @@ __global__ __launch_bounds__(256) void k_crt_3m(const int8_t* __restrict__ W1,
                                                 const int8_t* __restrict__ W3, size_t sw, int ldw,
                                                 const int* __restrict__ mu,
                                                 const int* __restrict__ nu, int m, int n,
-                                                CrtConsts cc, const int* __restrict__ flag,
+                                                CrtConsts cc, const int* __restrict__ flag, int* __restrict__ status,
                                                 T* __restrict__ C, int ldc) {
+  if (blockIdx.x == 0) fold_status(flag, status);
   crt_3m_body<T, R>(W1, W2, W3, sw, ldw, mu, nu, m, n, cc, flag, C, ldc,
                     (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
@@ -322,7 +329,8 @@ template <typename T, int R>
 __global__ __launch_bounds__(256) void k_crt_complex(
     const int8_t* __restrict__ Wr, const int8_t* __restrict__ Wi, size_t sw, int ldw,
     const int* __restrict__ mur, const int* __restrict__ mui, const int* __restrict__ nu, int m,
-    int n, CrtConsts cc, const int* __restrict__ flag, T* __restrict__ C, int ldc) {
+    int n, CrtConsts cc, const int* __restrict__ flag, int* __restrict__ status, T* __restrict__ C, int ldc) {
+  if (blockIdx.x == 0) fold_status(flag, status);
   crt_complex_body<T, R>(Wr, Wi, sw, ldw, mur, mui, nu, m, n, cc, flag, C, ldc,
                          (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
@@ -331,7 +339,8 @@ template <typename T, int R>
 __global__ __launch_bounds__(256) void k_crt(const int8_t* __restrict__ W, size_t sw, int ldw,
                                              const int* __restrict__ mu, const int* __restrict__ nu,
                                              int m, int n, CrtConsts cc,
-                                             const int* __restrict__ flag, T* __restrict__ C, int ldc) {
+                                             const int* __restrict__ flag, int* __restrict__ status, T* __restrict__ C, int ldc) {
+  if (blockIdx.x == 0) fold_status(flag, status);
   crt_body<T, R>(W, sw, ldw, mu, nu, m, n, cc, flag, C, ldc,
                  (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
@@ -350,18 +359,13 @@ __global__ __launch_bounds__(256) void k_crt_debug(const int8_t* __restrict__ W,
 template <typename T>
 __global__ __launch_bounds__(256) void kg_crt(const ProbDesc* __restrict__ P,
                                               const BlockRef* __restrict__ map,
-                                              const CrtConsts* __restrict__ ctab) {
+                                              const CrtConsts* __restrict__ ctab,
+                                              int* __restrict__ status) {
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
+  if (e.y == 0) fold_status(d.flag, status);
   crt_body<T, kCrtRows>(d.W, (size_t)d.np * d.mp, d.mp, d.mu, d.nu, d.m, d.n, ctab[d.N], d.flag,
                         (T*)d.C, d.ldc, (int64_t)e.y * 256 + threadIdx.x);
-}
-
-// Any problem's non-finite flag sets the sticky status word.
-__global__ __launch_bounds__(256) void kg_or_status(const ProbDesc* __restrict__ P, int count,
-                                                    int* __restrict__ status) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p < count && *P[p].flag) atomicOr(status, 1);
 }
 
 template <typename T>
@@ -372,70 +376,61 @@ __global__ __launch_bounds__(256) void k_fill_zero(T* __restrict__ C, int ldc, i
   if (i < m) C[i + (size_t)j * ldc] = (T)0;
 }
 
-__global__ void k_or_status(const int* __restrict__ flag, int* __restrict__ status) {
-  if (threadIdx.x == 0 && *flag) atomicOr(status, 1);
-}
-
 }  // namespace
 
-void launch_or_status(hipStream_t s, const int* flag, int* status) {
-  hipLaunchKernelGGL(k_or_status, dim3(1), dim3(64), 0, s, flag, status);
-}
-
 void launch_group_crt(hipStream_t s, Prec pr, const ProbDesc* P, const BlockRef* map, int blocks,
-                      int count, const CrtConsts* ctab, int* status) {
-  if (blocks > 0) {
-    if (pr == Prec::F64)
-      hipLaunchKernelGGL(kg_crt<double>, dim3((unsigned)blocks), dim3(256), 0, s, P, map, ctab);
-    else
-      hipLaunchKernelGGL(kg_crt<float>, dim3((unsigned)blocks), dim3(256), 0, s, P, map, ctab);
-  }
-  hipLaunchKernelGGL(kg_or_status, dim3((unsigned)cdiv_i(count, 256)), dim3(256), 0, s, P, count,
-                     status);
+                      const CrtConsts* ctab, int* status) {
+  if (blocks <= 0) return;
+  const dim3 g((unsigned)blocks), b(256);
+  if (pr == Prec::F64)
+    hipLaunchKernelGGL(kg_crt<double>, g, b, 0, s, P, map, ctab, status);
+  else
+    hipLaunchKernelGGL(kg_crt<float>, g, b, 0, s, P, map, ctab, status);
 }
 
 namespace {
 
 template <typename T>
 void launch_crt_t(hipStream_t s, const int8_t* W, size_t sw, int ldw, const int* mu, const int* nu,
-                  int m, int n, const CrtConsts& cc, const int* flag, void* C, int ldc) {
+                  int m, int n, const CrtConsts& cc, const int* flag, int* status,
+                  void* C, int ldc) {
   hipLaunchKernelGGL((k_crt<T, kCrtRows>), dim3((unsigned)crt_blocks(m, n)), dim3(256), 0, s, W, sw,
-                     ldw, mu, nu, m, n, cc, flag, (T*)C, ldc);
+                     ldw, mu, nu, m, n, cc, flag, status, (T*)C, ldc);
 }
 
 }  // namespace
 
 void launch_crt(hipStream_t s, Prec pr, const int8_t* W, size_t sw, int ldw, const int* mu,
-                const int* nu, int m, int n, const CrtConsts& cc, const int* flag, void* C,
-                int ldc) {
+                const int* nu, int m, int n, const CrtConsts& cc, const int* flag, int* status,
+                void* C, int ldc) {
   if (pr == Prec::F64)
-    launch_crt_t<double>(s, W, sw, ldw, mu, nu, m, n, cc, flag, C, ldc);
+    launch_crt_t<double>(s, W, sw, ldw, mu, nu, m, n, cc, flag, status, C, ldc);
   else
-    launch_crt_t<float>(s, W, sw, ldw, mu, nu, m, n, cc, flag, C, ldc);
+    launch_crt_t<float>(s, W, sw, ldw, mu, nu, m, n, cc, flag, status, C, ldc);
 }
 
 void launch_crt_3m(hipStream_t s, Prec pr, const int8_t* W1, const int8_t* W2, const int8_t* W3,
                    size_t sw, int ldw, const int* mu, const int* nu, int m, int n,
-                   const CrtConsts& cc, const int* flag, void* C, int ldc) {
+                   const CrtConsts& cc, const int* flag, int* status, void* C, int ldc) {
   const dim3 grid((unsigned)crt_blocks(m, n)), block(256);
   if (pr == Prec::F64)
     hipLaunchKernelGGL((k_crt_3m<double, kCrtRows>), grid, block, 0, s, W1, W2, W3, sw, ldw, mu, nu,
-                       m, n, cc, flag, (double*)C, ldc);
+                       m, n, cc, flag, status, (double*)C, ldc);
   else
     hipLaunchKernelGGL((k_crt_3m<float, kCrtRows>), grid, block, 0, s, W1, W2, W3, sw, ldw, mu, nu,
-                       m, n, cc, flag, (float*)C, ldc);
+                       m, n, cc, flag, status, (float*)C, ldc);
 }
 
 void launch_crt_complex(hipStream_t s, Prec pr, const int8_t* Wr, const int8_t* Wi, size_t sw,
                         int ldw, const int* mur, const int* mui, const int* nu, int m, int n,
-                        const CrtConsts& cc, const int* flag, void* C, int ldc) {
+                        const CrtConsts& cc, const int* flag, int* status, void* C, int ldc) {
   const dim3 grid((unsigned)crt_blocks(m, n)), block(256);
   if (pr == Prec::F64)
     hipLaunchKernelGGL((k_crt_complex<double, kCrtRows>), grid, block, 0, s, Wr, Wi, sw, ldw, mur,
-                       mui, nu, m, n, cc, flag, (double*)C, ldc);
+                       mui, nu, m, n, cc, flag, status, (double*)C, ldc);
   else
     hipLaunchKernelGGL((k_crt_complex<float, kCrtRows>), grid, block, 0, s, Wr, Wi, sw, ldw, mur,
-                       mui, nu, m, n, cc, flag, (float*)C, ldc);
+                       mui, nu, m, n, cc, flag, status, (float*)C, ldc);
 }
 
 void launch_crt_debug(hipStream_t s, Prec pr, const int8_t* W, size_t sw, int ldw, const int* mu,

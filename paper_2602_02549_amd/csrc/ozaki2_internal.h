@@ -15,6 +15,7 @@ constexpr int kMaxK = (1 << 19) - 1;
 constexpr int kRowPad = 256;     // m and n are padded to this multiple in the workspace
 constexpr int kMaxDim = 0x7FFFFF00; // largest m, n whose padding to kRowPad fits in int
 constexpr int kKPad = 128;       // k is padded to this multiple (bytes of INT8 per row)
+constexpr int kShiftSteps = 17;  // c log2f(M) + P' spans less than 16 for M < 2^31
 constexpr int kCrtRows = 4;      // CRT: consecutive rows per thread (256 threads per block)
 
 // Per-(N, b) constants of Section 3.1 and Algorithms 2-3, passed to kernels
@@ -37,6 +38,10 @@ struct CrtConsts {
   int nlimbs;       // 2 or 3: residues from limbs of A' (0: use nsteps)
   float Pprime;     // P' = single_down(log2(P-1)/2 - 0.5)
   float c;          // single_down(-0.5 / (1 - 4 u_32))
+  // Algorithm 2's shift as a step function of the maximum M of Cbar:
+  // floor(c log2f(single_up(max(M, 1))) + P') = shift0 - #{j : M >= step[j]}.
+  int shift0;
+  int step[kShiftSteps];
   double P1, P2;    // double-double P (P2 = 0 for b = 32)
   double Pinv;      // double(1/P)
   ModConst mod[kMaxModuli]; // p_l
@@ -102,6 +107,18 @@ __device__ inline int shift_prime_bits(uint64_t bits) {
   return 5 - fl;
 }
 
+// mu (nu) of Algorithm 2 from a row's abs-max bit pattern and its maximum M of
+// Cbar; bias is added to mu' of nonzero rows.  A zero maximum counts as 1 (R7).
+// The table of steps stands for the log2f and the floor (24 integer
+// instructions a row against about 1500 for the double-double log2f), so that
+// the residue kernels form the shifts they need themselves.
+__device__ __forceinline__ int shift_of(uint64_t bits, int M, const CrtConsts& cc, int bias) {
+  int s = shift_prime_bits(bits) + (bits ? bias : 0) + cc.shift0;
+#pragma unroll
+  for (int j = 0; j < kShiftSteps; ++j) s -= M >= cc.step[j] ? 1 : 0;
+  return s;
+}
+
 // ---------------------------------------------------------------------------
 // Grouped (batched) execution: one launch per phase covers every problem of a
 // batch.  Each problem has a descriptor; per phase, a block map gives every
@@ -130,7 +147,7 @@ struct ProbDesc {
 typedef int2 BlockRef;
 
 enum GroupPhase {
-  GP_INIT, GP_ABSMAX_A, GP_ABSMAX_B, GP_ABSBAR_B, GP_SLICE_A, GP_SLICE_B, GP_GEMM_SCALE, GP_SHIFTS,
+  GP_INIT, GP_ABSMAX_A, GP_ABSMAX_B, GP_ABSBAR_B, GP_SLICE_A, GP_SLICE_B, GP_GEMM_SCALE,
   GP_GEMM_RES, GP_CRT, GP_COUNT
 };
 
@@ -175,11 +192,10 @@ constexpr int kAbsBarWaveK = 2048;   // up to here one wave per column, else a w
 int absbar_group_blocks(int n_pad, int k_pad);
 void launch_absbar_cols(hipStream_t s, Prec pr, const void* B, int ldb, int k, int n, int n_pad,
                         int k_pad, uint64_t* colbits, int* flag, int8_t* out);
-// bias: added to mu' and nu' of nonzero rows and columns (0 for Algorithm 2;
-// -1 for the complex 3-product form, whose bars sum two parts).
-void launch_shifts(hipStream_t s, const uint64_t* rowbits, const int* rmax, int m,
-                   const uint64_t* colbits, const int* cmax, int n, float Pprime, float c,
-                   int* mu_p, int* nu_p, int* mu, int* nu, float* ef, int bias = 0);
+// mu', nu' and the log2f values e (rows) then f (columns) for the stage dumps.
+void launch_debug_shifts(hipStream_t s, const uint64_t* rowbits, const int* rmax, int m,
+                         const uint64_t* colbits, const int* cmax, int n, int* mu_p, int* nu_p,
+                         float* ef);
 void launch_log2f(hipStream_t s, const float* d, float* out, int count);
 
 // Tuning and test knobs (ozaki2_debug_tuning): a cap on the workgroups of a
@@ -194,35 +210,38 @@ extern std::atomic<int> g_split_k;
 // called once per device before its first launch, outside stream capture.
 void init_slice_launch(int dev);
 
-// residue.hip: INT8 slices in K-major layout [S][rows_pad][k_pad].
-//   src element (r, h) is at  trans ? src[r + h*ld] : src[h + r*ld].
-//   mode 0 (bar):     S = 1, byte = ceil(2^shift |x|) (>= 1 if x != 0),
-//                     shift = mu' computed from `bits` (row abs-max bit patterns)
-//   mode 2 (bar):     mode 0 with shift = mu' - 1 (the complex 3-product form)
-//   mode 1 (residue): S = N, byte_l = mod(trunc(2^shift x), p_l), shift from `shift`
-void launch_slices(hipStream_t s, Prec pr, int mode, bool trans, const void* src, int ld, int rows,
-                   int k, int rows_pad, int k_pad, const uint64_t* bits, const int* shift,
-                   const CrtConsts& cc, int8_t* out);
-// The same passes over an interleaved complex source (the 3-product form),
-// each reading the complex matrix once:
-//   mode 2: one slice at out, byte = ceil(2^(mu'-1) |re|) + ceil(2^(mu'-1) |im|);
-//   mode 1: 3 N slices from out: the residues of the real parts, of the
-//           imaginary parts, and of their sums (mod p_l of the two bytes).
-void launch_slices_complex(hipStream_t s, Prec pr, int mode, bool trans, const void* src, int ld,
-                           int rows, int k, int rows_pad, int k_pad, const uint64_t* bits,
-                           const int* shift, const CrtConsts& cc, int8_t* out);
-// The slices of the real embedding Ahat = [[Ar, -Ai], [Ai, Ar]],
-// Bhat = [[Br], [Bi]] of a complex product, read from the interleaved
-// complex source in place (modes 0 and 1 as launch_slices).  The embedding
-// is laid out with its halves at aligned offsets, zeros between: k-half kh
-// (a multiple of 128; slice rows are 2 kh long) and, on the A side, row half
-// `half` (rows i and half + i of the embedding come from complex row i;
-// rows_pad = 2 half).  Zero rows and columns change none of the embedding's
-// products, maxima or shifts.  Mode 1 on the A side takes the shifts of row
-// i from shift[i] and of row half + i from shift[half + i].
-void launch_slices_embed(hipStream_t s, Prec pr, int mode, bool aside, const void* src, int ld,
-                         int rows, int k, int kh, int rows_pad, int half, const uint64_t* bits,
-                         const int* shift, const CrtConsts& cc, int8_t* out);
+// residue.hip: INT8 slices in K-major layout [S][rows_pad][k_pad] of A
+// (column-major m x k: element (r, h) at src[r + h ld]) and of B (k x n: element
+// (h, r) at src[h + r ld]), either or both in one launch (null: not this one).
+//   bars:     S = 1, byte = ceil(2^shift |x|) (>= 1 if x != 0), shift = mu'
+//             from `bits`; zero in the padding rows.
+//   residues: S = N, byte_l = mod(trunc(2^shift x), p_l), shift = mu / nu of
+//             Algorithm 2 from `bits` (with bias added to mu' and nu' of nonzero
+//             rows) and the maxima of Cbar `mx`, also written to `shift`.
+//   Real:      as above.
+//   Complex3:  the 3-product form, from interleaved (re, im) pairs (ld in
+//              complex elements): bars ceil(2^(mu'-1) |re|) + ceil(2^(mu'-1) |im|);
+//              residues 3 N slices: of the real parts, of the imaginary parts
+//              and of their sums (mod p_l of the two bytes).
+//   Embedding: the slices of the real embedding Ahat = [[Ar, -Ai], [Ai, Ar]],
+//              Bhat = [[Br], [Bi]] of a complex product, from the pairs in place,
+//              laid out with the halves at aligned offsets, zeros between: k
+//              half k_pad (slice rows are 2 k_pad long) and, on the A side, row
+//              half rows_pad / 2 (rows i and rows_pad / 2 + i of the embedding
+//              come from complex row i).  Zero rows and columns change none of
+//              the embedding's products, maxima or shifts.  bits, mx and shift
+//              are indexed by the embedding's rows.
+enum class SliceSet { Real, Complex3, Embedding };
+struct SliceOperand {
+  const void* src;
+  int ld, rows, rows_pad;
+  const uint64_t* bits;
+  const int* mx;
+  int* shift;
+  int8_t* out;
+};
+void launch_slices(hipStream_t s, Prec pr, SliceSet set, bool bars, const SliceOperand* A,
+                   const SliceOperand* B, int k, int k_pad, const CrtConsts& cc, int bias = 0);
 
 // Planner operands (BF16, K-major [rows_pad][k_pad]) and per-64-k-tile row
 // sums partial[k_pad/64][rows_pad] of |x| 2^-alpha.
@@ -278,12 +297,12 @@ void launch_certify(hipStream_t s, Prec pr, const void* C, int ldc, const int* m
 // Grouped launches (one per phase for a whole batch of `count` problems);
 // `map` holds `blocks` entries, one per workgroup.
 void launch_group_scale(hipStream_t s, Prec pr, int phase, const ProbDesc* P, const BlockRef* map,
-                        int blocks, const CrtConsts* ctab);
+                        int blocks);
 // The residue path every problem of a batch shares (a code for
 // launch_group_slices), or the per-tile choice when they differ.
 int group_residue_path(const CrtConsts* const* cc, int count);
-void launch_group_slices(hipStream_t s, Prec pr, int mode, bool aside, int path,
-                         const ProbDesc* P, const BlockRef* map, int blocks,
+void launch_group_slices(hipStream_t s, Prec pr, bool bars, int path, const ProbDesc* P,
+                         const BlockRef* amap, int atiles, const BlockRef* bmap, int btiles,
                          const CrtConsts* ctab);
 void launch_group_gemm(hipStream_t s, int epi, int tile, const ProbDesc* P, const BlockRef* map,
                        int blocks, const CrtConsts* ctab);
@@ -295,32 +314,31 @@ int persist_grid(int tile);
 void launch_group_gemm_persist(hipStream_t s, int tile, bool fold, int grid, const ProbDesc* P,
                                const BlockRef* map, int items, const CrtConsts* ctab);
 void launch_group_crt(hipStream_t s, Prec pr, const ProbDesc* P, const BlockRef* map, int blocks,
-                      int count, const CrtConsts* ctab, int* status);
+                      const CrtConsts* ctab, int* status);
 
-// crt.hip: C(i, j) from W_l[j][i] (slices of row length ldw), mu, nu.
+// crt.hip: C(i, j) from W_l[j][i] (slices of row length ldw), mu, nu.  A set
+// non-finite flag makes every entry NaN and also sets *status, the sticky word.
 void launch_crt(hipStream_t s, Prec pr, const int8_t* W, size_t sw, int ldw, const int* mu,
-                const int* nu, int m, int n, const CrtConsts& cc, const int* flag, void* C,
-                int ldc);
+                const int* nu, int m, int n, const CrtConsts& cc, const int* flag, int* status,
+                void* C, int ldc);
 // The CRT of a complex result: real parts from (Wr, mur), imaginary parts
 // from (Wi, mui), column shifts nu, written as interleaved (re, im) pairs into
 // the column-major complex C (ldc in complex elements).
 void launch_crt_complex(hipStream_t s, Prec pr, const int8_t* Wr, const int8_t* Wi, size_t sw,
                         int ldw, const int* mur, const int* mui, const int* nu, int m, int n,
-                        const CrtConsts& cc, const int* flag, void* C, int ldc);
+                        const CrtConsts& cc, const int* flag, int* status, void* C, int ldc);
 // The CRT of the 3-product form: the real and imaginary residues of modulus l
 // are mod(W1 - W2, p_l) and mod(W3 - W1 - W2, p_l), formed per byte from the
 // three products' W; shifts mu (rows) and nu (columns) for both parts;
 // interleaved complex output as launch_crt_complex.
 void launch_crt_3m(hipStream_t s, Prec pr, const int8_t* W1, const int8_t* W2, const int8_t* W3,
                    size_t sw, int ldw, const int* mu, const int* nu, int m, int n,
-                   const CrtConsts& cc, const int* flag, void* C, int ldc);
+                   const CrtConsts& cc, const int* flag, int* status, void* C, int ldc);
 // launch_crt plus C'(1), C'(2), Q, C'' as FP64 [4][n][m] into dbg (stage dumps).
 void launch_crt_debug(hipStream_t s, Prec pr, const int8_t* W, size_t sw, int ldw, const int* mu,
                       const int* nu, int m, int n, const CrtConsts& cc, const int* flag, void* C,
                       int ldc, double* dbg);
 void launch_fill_zero(hipStream_t s, Prec pr, void* C, int ldc, int m, int n);
-// Folds the per-call non-finite flag into the sticky status word.
-void launch_or_status(hipStream_t s, const int* flag, int* status);
 
 // complex.hip: the real embedding of a complex product (interleaved (re, im)
 // column-major inputs; leading dimensions in complex elements) into

@@ -277,14 +277,43 @@ __device__ __forceinline__ void tile_loads(const T* __restrict__ src, int ld, in
   }
 }
 
-// Per-row input of the thread's output row r0 + t/8 (clamped): the abs-max
-// bit pattern (mode 0) or the shift mu / nu (mode 1).
+// One operand of a slice launch.
+struct SliceSide {
+  const void* src;
+  const uint64_t* bits;   // abs-max bit patterns of the rows
+  const int* mx;          // mode 1: maxima of Cbar over the rows
+  int* shift;             // mode 1: where the rows' shifts (mu, nu) go
+  int8_t* out;
+  size_t slice;           // bytes from one slice to the next
+  int ld, rows, gy;       // gy: row tiles
+  int tiles, blocks;      // tiles, and the workgroups that walk them
+};
+struct SliceArgs {
+  SliceSide a, b;         // A (column-major) and B (k contiguous)
+  int k, k_pad;           // k_pad: padded k (the embedding: of one k half)
+  int half;               // the embedding: rows of one row half on the A side
+  int bias;               // added to mu' and nu' of nonzero rows (mode 1)
+};
+
+// Shift of the thread's output row rg (clamped): mu' from the abs-max bit
+// pattern (mode 0; mode 2: mu' - 1), or mu / nu from the pattern and the
+// maximum of Cbar (mode 1: Algorithm 2's shift, from the table of its steps).
+// The inputs are loaded early (load) and used later (get).
 template <int MODE>
-__device__ __forceinline__ int64_t row_aux(const void* __restrict__ aux, int rows, int r0) {
-  const int rg = min(r0 + (int)(threadIdx.x >> 3), rows - 1);
-  if (MODE != 1) return (int64_t)static_cast<const uint64_t*>(aux)[rg];
-  return static_cast<const int*>(aux)[rg];
-}
+struct RowShift {
+  uint64_t bits;
+  int mx;
+  __device__ __forceinline__ void load(const uint64_t* __restrict__ b, const int* __restrict__ m,
+                                       int rows, int rg) {
+    rg = min(rg, rows - 1);
+    bits = b[rg];
+    mx = MODE == 1 ? m[rg] : 0;
+  }
+  __device__ __forceinline__ int get(const CrtConsts& cc, int bias) const {
+    if (MODE == 1) return shift_of(bits, mx, cc, bias);
+    return shift_prime_bits(bits) - (MODE == 2 ? 1 : 0);
+  }
+};
 
 // LDS position of element (r, h) of a tile:
 //   r * kRS + (h ^ (((h / 32) ^ (r / 8)) & 3)),
@@ -355,8 +384,8 @@ __device__ __forceinline__ void store_residues_path(const double (&v)[16], const
 // Each thread reads 16 consecutive k of one row from the staged tile and
 // writes 16 bytes per slice (mode 0: Abar; mode 1: the N residues).
 template <int MODE, int PATH>
-__device__ __forceinline__ void tile_finish(const double* tile, int64_t aux, int rows, int k_pad,
-                                            size_t slice, const CrtConsts& cc,
+__device__ __forceinline__ void tile_finish(const double* tile, int sh, int* __restrict__ shift_out,
+                                            int rows, int k_pad, size_t slice, const CrtConsts& cc,
                                             int8_t* __restrict__ out, int r0, int h0) {
   const int t = threadIdx.x;
   const int r = t >> 3, c = t & 7, rg = r0 + r;
@@ -372,7 +401,6 @@ __device__ __forceinline__ void tile_finish(const double* tile, int64_t aux, int
   int8_t* dst = out + (size_t)rg * k_pad + h0 + 16 * c;
 
   if (MODE != 1) {
-    const int sh = rg < rows ? shift_prime_bits((uint64_t)aux) - (MODE == 2 ? 1 : 0) : 0;
     int b[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -387,7 +415,7 @@ __device__ __forceinline__ void tile_finish(const double* tile, int64_t aux, int
     w.w = pack4(b[12], b[13], b[14], b[15]);
     *reinterpret_cast<uint4*>(dst) = w;
   } else if (rg < rows) {
-    const int sh = (int)aux;
+    if (h0 == 0 && c == 0 && blockIdx.y == 0) shift_out[rg] = sh;
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = trunc(ldexp(v[e], sh));
     store_residues_path<PATH>(v, cc, dst, slice);
@@ -410,40 +438,40 @@ __device__ inline void slice_tile(int b, int k_pad, int gy, int* kx, int* ry) {
   }
 }
 
-// Grid-stride loop over `tiles` tiles (row tiles: gy; mode 1 leaves out the
-// tiles of padding rows, whose residues no product of real rows reads; Abar
-// and Bbar padding must stay zero, since the scaling product's maxima cover
-// whole rows and columns).  Each workgroup stages tile i in LDS, issues the
-// loads of its next tile, and only then computes and stores tile i, so that
-// HBM reads overlap the residue arithmetic.
+// Workgroup `w` of the s.blocks that walk one operand's tiles in a stride
+// (mode 1 leaves out the tiles of padding rows, whose residues no product of
+// real rows reads; Abar and Bbar padding must stay zero, since the scaling
+// product's maxima cover whole rows and columns).  Each workgroup stages tile
+// i in LDS, issues the loads of its next tile, and only then computes and
+// stores tile i, so that HBM reads overlap the residue arithmetic.
 template <typename T, bool TRANS, int MODE, int PATH>
-__global__ __launch_bounds__(256) void k_slices(const T* __restrict__ src, int ld, int rows, int k,
-                                                int k_pad, int gy, int tiles, size_t slice,
-                                                const void* __restrict__ aux, CrtConsts cc,
-                                                int8_t* __restrict__ out) {
-  __shared__ double tile[kTR * kRS];
-  int i = blockIdx.x;
-  if (i >= tiles) return;
+__device__ __forceinline__ void walk_real(const SliceArgs& a, const SliceSide& s, int w,
+                                          const CrtConsts& cc, double* tile) {
+  int i = w;
+  if (i >= s.tiles) return;
+  const T* src = static_cast<const T*>(s.src);
+  const int row = (int)(threadIdx.x >> 3);
   int kx, ry;
-  slice_tile<TRANS>(i, k_pad, gy, &kx, &ry);
+  slice_tile<TRANS>(i, a.k_pad, s.gy, &kx, &ry);
   T x[16];
-  tile_loads<T, TRANS>(src, ld, rows, k, ry * kTR, kx * kTK, x);
-  int64_t xa = row_aux<MODE>(aux, rows, ry * kTR);
+  tile_loads<T, TRANS>(src, s.ld, s.rows, a.k, ry * kTR, kx * kTK, x);
+  RowShift<MODE> rs;
+  rs.load(s.bits, s.mx, s.rows, ry * kTR + row);
   for (;;) {
     const int r0 = ry * kTR, h0 = kx * kTK;
     lds_barrier();                 // every wave is done with the previous tile
-    tile_stage<T, TRANS>(x, rows, k, r0, h0, tile);
+    tile_stage<T, TRANS>(x, s.rows, a.k, r0, h0, tile);
     __asm__ volatile("" ::: "memory");  // x is free: the next loads reuse its registers
-    const int64_t a = xa;
-    const int ni = i + (int)gridDim.x;
-    if (ni < tiles) {
-      slice_tile<TRANS>(ni, k_pad, gy, &kx, &ry);
-      tile_loads<T, TRANS>(src, ld, rows, k, ry * kTR, kx * kTK, x);
-      xa = row_aux<MODE>(aux, rows, ry * kTR);
+    const int sh = rs.get(cc, a.bias);
+    const int ni = i + s.blocks;
+    if (ni < s.tiles) {
+      slice_tile<TRANS>(ni, a.k_pad, s.gy, &kx, &ry);
+      tile_loads<T, TRANS>(src, s.ld, s.rows, a.k, ry * kTR, kx * kTK, x);
+      rs.load(s.bits, s.mx, s.rows, ry * kTR + row);
     }
     lds_barrier();                 // the tile is staged
-    tile_finish<MODE, PATH>(tile, a, rows, k_pad, slice, cc, out, r0, h0);
-    if (ni >= tiles) break;
+    tile_finish<MODE, PATH>(tile, sh, s.shift, s.rows, a.k_pad, s.slice, cc, s.out, r0, h0);
+    if (ni >= s.tiles) break;
     i = ni;
   }
 }
@@ -486,15 +514,15 @@ __device__ __forceinline__ void tile_row16(const double* tile, double (&v)[16]) 
 }
 
 template <int MODE, int PATH>
-__device__ __forceinline__ void tile_finish_cx(double (&vr)[16], double (&vi)[16], int64_t aux,
-                                               int rows, int k_pad, size_t slice,
+__device__ __forceinline__ void tile_finish_cx(double (&vr)[16], double (&vi)[16], int sh,
+                                               int* __restrict__ shift_out, int rows, int k_pad,
+                                               size_t slice,
                                                const CrtConsts& cc, int8_t* __restrict__ out,
                                                int r0, int h0) {
   const int t = threadIdx.x;
   const int rg = r0 + (t >> 3);
   int8_t* dst = out + (size_t)rg * k_pad + h0 + 16 * (t & 7);
   if constexpr (MODE == 2) {
-    const int sh = rg < rows ? shift_prime_bits((uint64_t)aux) - 1 : 0;
     auto bar = [&](double v) {
       const double x = fabs(v);
       const double cl = ceil(ldexp(x, sh));
@@ -508,7 +536,7 @@ __device__ __forceinline__ void tile_finish_cx(double (&vr)[16], double (&vi)[16
     *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
   } else {
     if (rg >= rows) return;
-    const int sh = (int)aux;
+    if (h0 == 0 && (t & 7) == 0 && blockIdx.y == 0) shift_out[rg] = sh;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       vr[e] = trunc(ldexp(vr[e], sh));
@@ -561,43 +589,48 @@ __device__ __forceinline__ void tile_loads_cx(const T* __restrict__ src, int ld,
   }
 }
 
-// The grid-stride loop of k_slices over complex tiles: the real parts are
-// staged and read back, then the imaginary parts, then the next tile's loads
-// go out before the arithmetic of this one.
+// The walk over complex tiles: the real parts are staged and read back, then
+// the imaginary parts, then the next tile's loads go out before the
+// arithmetic of this one.
 template <typename T, bool TRANS, int MODE, int PATH>
-__global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_slices_cx(const T* __restrict__ src, int ld, int rows,
-                                                   int k, int k_pad, int gy, int tiles,
-                                                   size_t slice, const void* __restrict__ aux,
-                                                   CrtConsts cc, int8_t* __restrict__ out) {
-  __shared__ double tile[kTR * kRS];
-  int i = blockIdx.x;
-  if (i >= tiles) return;
+__device__ __forceinline__ void walk_cx(const SliceArgs& a, const SliceSide& s, int w,
+                                        const CrtConsts& cc, double* tile) {
+  int i = w;
+  if (i >= s.tiles) return;
+  const T* src = static_cast<const T*>(s.src);
+  const int row = (int)(threadIdx.x >> 3);
   int kx, ry;
-  slice_tile<TRANS>(i, k_pad, gy, &kx, &ry);
+  slice_tile<TRANS>(i, a.k_pad, s.gy, &kx, &ry);
+  // The next tile's loads go out early only for the residues, and not for the
+  // three-limb ones, which hold too many registers for it (two workgroups a CU
+  // instead of one); the bars run four workgroups a CU without.
+  constexpr bool kPrefetch = MODE == 1 && PATH != kLimbs3;
   T x[16], y[16];
-  tile_loads_cx<T, TRANS>(src, ld, rows, k, ry * kTR, kx * kTK, x, y);
-  int64_t xa = row_aux<MODE>(aux, rows, ry * kTR);
+  if (kPrefetch) tile_loads_cx<T, TRANS>(src, s.ld, s.rows, a.k, ry * kTR, kx * kTK, x, y);
+  RowShift<MODE> rs;
+  rs.load(s.bits, s.mx, s.rows, ry * kTR + row);
   for (;;) {
     const int r0 = ry * kTR, h0 = kx * kTK;
     double vr[16], vi[16];
+    if (!kPrefetch) tile_loads_cx<T, TRANS>(src, s.ld, s.rows, a.k, r0, h0, x, y);
     lds_barrier();                 // every wave is done with the previous tile
-    tile_stage<T, TRANS>(x, rows, k, r0, h0, tile);
+    tile_stage<T, TRANS>(x, s.rows, a.k, r0, h0, tile);
     lds_barrier();
     tile_row16(tile, vr);
     lds_barrier();
-    tile_stage<T, TRANS>(y, rows, k, r0, h0, tile);
+    tile_stage<T, TRANS>(y, s.rows, a.k, r0, h0, tile);
     __asm__ volatile("" ::: "memory");  // x, y are free: the next loads reuse their registers
-    const int64_t a = xa;
-    const int ni = i + (int)gridDim.x;
-    if (ni < tiles) {
-      slice_tile<TRANS>(ni, k_pad, gy, &kx, &ry);
-      tile_loads_cx<T, TRANS>(src, ld, rows, k, ry * kTR, kx * kTK, x, y);
-      xa = row_aux<MODE>(aux, rows, ry * kTR);
+    const int sh = rs.get(cc, a.bias);
+    const int ni = i + s.blocks;
+    if (ni < s.tiles) {
+      slice_tile<TRANS>(ni, a.k_pad, s.gy, &kx, &ry);
+      if (kPrefetch) tile_loads_cx<T, TRANS>(src, s.ld, s.rows, a.k, ry * kTR, kx * kTK, x, y);
+      rs.load(s.bits, s.mx, s.rows, ry * kTR + row);
     }
     lds_barrier();
     tile_row16(tile, vi);
-    tile_finish_cx<MODE, PATH>(vr, vi, a, rows, k_pad, slice, cc, out, r0, h0);
-    if (ni >= tiles) break;
+    tile_finish_cx<MODE, PATH>(vr, vi, sh, s.shift, s.rows, a.k_pad, s.slice, cc, s.out, r0, h0);
+    if (ni >= s.tiles) break;
     i = ni;
   }
 }
@@ -613,19 +646,18 @@ __global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_slices_cx(const T* _
 //     shift[half + i] (their Cbar maxima differ).
 template <int MODE, int PATH, bool ASIDE>
 __device__ __forceinline__ void tile_finish_emb(const double (&vr)[16], const double (&vi)[16],
-                                                const void* __restrict__ aux, int rows, int ldo,
-                                                int kh, int half, size_t slice,
-                                                const CrtConsts& cc, int8_t* __restrict__ out,
-                                                int r0, int h0) {
+                                                const SliceArgs& a, const SliceSide& s,
+                                                const CrtConsts& cc, int r0, int h0) {
   const int t = threadIdx.x;
   const int rg = r0 + (t >> 3);
+  const int rows = s.rows, kh = a.k_pad, ldo = 2 * kh, half = a.half;
+  const size_t slice = s.slice;
+  int8_t* __restrict__ out = s.out;
   int8_t* d0 = out + (size_t)rg * ldo + h0 + 16 * (t & 7);    // (rg, h)
   int8_t* d1 = d0 + kh;                                         // (rg, kh + h)
   const size_t dh = (size_t)half * ldo;                         // to row half + rg
   if constexpr (MODE == 0) {
-    const int sh = rg < rows
-                       ? shift_prime_bits(static_cast<const uint64_t*>(aux)[min(rg, rows - 1)])
-                       : 0;
+    const int sh = shift_prime_bits(s.bits[min(rg, rows - 1)]);
     auto bar = [&](double v) {
       const double x = fabs(v);
       const double cl = ceil(ldexp(x, sh));
@@ -646,10 +678,11 @@ __device__ __forceinline__ void tile_finish_emb(const double (&vr)[16], const do
     }
   } else {
     if (rg >= rows) return;
-    const int* sh = static_cast<const int*>(aux);
     // block 0: rows rg (A side) or the only row (B side); block 1: row half + rg
     for (int blk = 0; blk < (ASIDE ? 2 : 1); ++blk) {
-      const int e2 = sh[rg + blk * half];
+      const int ro = rg + blk * half;
+      const int e2 = shift_of(s.bits[ro], s.mx[ro], cc, a.bias);
+      if (h0 == 0 && (t & 7) == 0 && blockIdx.y == 0) s.shift[ro] = e2;
       double xr[16], xi[16];
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
@@ -673,53 +706,65 @@ __device__ __forceinline__ void tile_finish_emb(const double (&vr)[16], const do
   }
 }
 
-// Grid-stride loop as k_slices_cx over the complex source's tiles (kh / 128
-// k tiles by gy row tiles).
+// The walk of walk_cx over the complex source's tiles (kh / 128 k tiles by gy
+// row tiles), without early loads: the residues hold both parts' limbs (on the
+// A side for two row blocks), and only without them do two workgroups share a
+// CU.
 template <typename T, bool TRANS, int MODE, int PATH>
-__global__ __launch_bounds__(256, MODE == 1 ? 2 : 1) void k_slices_emb(const T* __restrict__ src, int ld, int rows,
-                                                    int k, int kh, int gy, int tiles, int half,
-                                                    size_t slice, const void* __restrict__ aux,
-                                                    CrtConsts cc, int8_t* __restrict__ out) {
-  // The A side's residues (two row blocks, four stores per modulus) and the
-  // three-limb ones hold the most registers: there the next tile's loads are
-  // not issued early, which lets two workgroups share a CU instead of one.
-  constexpr bool kPrefetch = !(MODE == 1 && (TRANS || PATH == kLimbs3));
-  __shared__ double tile[kTR * kRS];
-  int i = blockIdx.x;
-  if (i >= tiles) return;
+__device__ __forceinline__ void walk_emb(const SliceArgs& a, const SliceSide& s, int w,
+                                         const CrtConsts& cc, double* tile) {
+  int i = w;
+  if (i >= s.tiles) return;
+  const T* src = static_cast<const T*>(s.src);
   int kx, ry;
-  slice_tile<TRANS>(i, kh, gy, &kx, &ry);
+  slice_tile<TRANS>(i, a.k_pad, s.gy, &kx, &ry);
   T x[16], y[16];
-  if (kPrefetch) tile_loads_cx<T, TRANS>(src, ld, rows, k, ry * kTR, kx * kTK, x, y);
   for (;;) {
     const int r0 = ry * kTR, h0 = kx * kTK;
     double vr[16], vi[16];
-    if (!kPrefetch) tile_loads_cx<T, TRANS>(src, ld, rows, k, r0, h0, x, y);
+    tile_loads_cx<T, TRANS>(src, s.ld, s.rows, a.k, r0, h0, x, y);
     lds_barrier();                 // every wave is done with the previous tile
-    tile_stage<T, TRANS>(x, rows, k, r0, h0, tile);
+    tile_stage<T, TRANS>(x, s.rows, a.k, r0, h0, tile);
     lds_barrier();
     tile_row16(tile, vr);
     lds_barrier();
-    tile_stage<T, TRANS>(y, rows, k, r0, h0, tile);
-    __asm__ volatile("" ::: "memory");  // x, y are free: the next loads reuse their registers
-    const int ni = i + (int)gridDim.x;
-    if (ni < tiles) {
-      slice_tile<TRANS>(ni, kh, gy, &kx, &ry);
-      if (kPrefetch) tile_loads_cx<T, TRANS>(src, ld, rows, k, ry * kTR, kx * kTK, x, y);
-    }
+    tile_stage<T, TRANS>(y, s.rows, a.k, r0, h0, tile);
+    const int ni = i + s.blocks;
+    if (ni < s.tiles) slice_tile<TRANS>(ni, a.k_pad, s.gy, &kx, &ry);
     lds_barrier();
     tile_row16(tile, vi);
-    tile_finish_emb<MODE, PATH, TRANS>(vr, vi, aux, rows, 2 * kh, kh, half, slice, cc, out, r0,
-                                       h0);
-    if (ni >= tiles) break;
+    tile_finish_emb<MODE, PATH, TRANS>(vr, vi, a, s, cc, r0, h0);
+    if (ni >= s.tiles) break;
     i = ni;
+  }
+}
+
+// The slices of A and of B in one launch: the first a.a.blocks workgroups walk
+// A's tiles, the others B's.  One launch of both sides saves a launch (about
+// 5 us) and a partly empty last round of workgroups per pass.
+enum SliceForm { kReal, kCx, kEmb };
+template <typename T, int FORM, int MODE, int PATH>
+__global__ __launch_bounds__(256, FORM == kReal ? 1 : MODE == 1 ? 2 : 3) void k_slices(
+    SliceArgs a, CrtConsts cc) {
+  __shared__ double tile[kTR * kRS];
+  const int w = (int)blockIdx.x;
+  if (w < a.a.blocks) {
+    if constexpr (FORM == kReal) walk_real<T, true, MODE, PATH>(a, a.a, w, cc, tile);
+    if constexpr (FORM == kCx) walk_cx<T, true, MODE, PATH>(a, a.a, w, cc, tile);
+    if constexpr (FORM == kEmb) walk_emb<T, true, MODE, PATH>(a, a.a, w, cc, tile);
+  } else {
+    if constexpr (FORM == kReal) walk_real<T, false, MODE, PATH>(a, a.b, w - a.a.blocks, cc, tile);
+    if constexpr (FORM == kCx) walk_cx<T, false, MODE, PATH>(a, a.b, w - a.a.blocks, cc, tile);
+    if constexpr (FORM == kEmb) walk_emb<T, false, MODE, PATH>(a, a.b, w - a.a.blocks, cc, tile);
   }
 }
 
 // One tile of the grouped launch: which problem side and where.
 struct TileJob {
   const void* src;
-  const void* aux;
+  const uint64_t* bits;
+  const int* mx;
+  int* shift;
   int8_t* out;
   size_t slice;
   int ld, rows, k, k_pad, r0, h0, N;
@@ -738,8 +783,9 @@ __device__ __forceinline__ bool tile_job(const ProbDesc* __restrict__ P,
   j->h0 = kx * kTK;
   if (MODE == 1 && j->r0 >= rows) return false;
   j->src = ASIDE ? d.A : d.B;
-  j->aux = MODE == 0 ? (const void*)(ASIDE ? d.rowbits : d.colbits)
-                     : (const void*)(ASIDE ? d.mu : d.nu);
+  j->bits = ASIDE ? d.rowbits : d.colbits;
+  j->mx = ASIDE ? d.rmax : d.cmax;
+  j->shift = ASIDE ? d.mu : d.nu;
   j->out = ASIDE ? d.As : d.Bs;
   j->slice = (size_t)rows_pad * d.kp;
   j->ld = ASIDE ? d.lda : d.ldb;
@@ -750,41 +796,57 @@ __device__ __forceinline__ bool tile_job(const ProbDesc* __restrict__ P,
   return true;
 }
 
-// Grouped: A side (TRANS, rows = m) or B side (rows = n) of every problem;
-// the same grid-stride loop over the `tiles` entries of the block map.
+// Workgroup w of G that walk the `tiles` entries of one side's block map (A
+// rows = m, B rows = n) of every problem, as walk_real.
 template <typename T, bool ASIDE, int MODE, int PATH>
-__global__ __launch_bounds__(256) void kg_slices(const ProbDesc* __restrict__ P,
-                                                 const BlockRef* __restrict__ map, int tiles,
-                                                 const CrtConsts* __restrict__ ctab) {
-  __shared__ double tile[kTR * kRS];
-  const int G = (int)gridDim.x;
-  int i = blockIdx.x;
+__device__ __forceinline__ void walk_group(const ProbDesc* __restrict__ P,
+                                           const BlockRef* __restrict__ map, int tiles, int w, int G,
+                                           const CrtConsts* __restrict__ ctab, double* tile) {
+  const int row = (int)(threadIdx.x >> 3);
+  int i = w;
   TileJob cur;
   while (i < tiles && !tile_job<ASIDE, MODE>(P, map, i, &cur)) i += G;
   if (i >= tiles) return;
   T x[16];
   tile_loads<T, ASIDE>(static_cast<const T*>(cur.src), cur.ld, cur.rows, cur.k, cur.r0, cur.h0, x);
-  int64_t xa = row_aux<MODE>(cur.aux, cur.rows, cur.r0);
+  RowShift<MODE> rs;
+  rs.load(cur.bits, cur.mx, cur.rows, cur.r0 + row);
   for (;;) {
     lds_barrier();
     tile_stage<T, ASIDE>(x, cur.rows, cur.k, cur.r0, cur.h0, tile);
     __asm__ volatile("" ::: "memory");
-    const int64_t a = xa;
+    const int sh = rs.get(ctab[cur.N], 0);
     TileJob nxt;
     int ni = i + G;
     while (ni < tiles && !tile_job<ASIDE, MODE>(P, map, ni, &nxt)) ni += G;
     if (ni < tiles) {
       tile_loads<T, ASIDE>(static_cast<const T*>(nxt.src), nxt.ld, nxt.rows, nxt.k, nxt.r0,
                            nxt.h0, x);
-      xa = row_aux<MODE>(nxt.aux, nxt.rows, nxt.r0);
+      rs.load(nxt.bits, nxt.mx, nxt.rows, nxt.r0 + row);
     }
     lds_barrier();
-    tile_finish<MODE, PATH>(tile, a, cur.rows, cur.k_pad, cur.slice, ctab[cur.N], cur.out, cur.r0,
-                            cur.h0);
+    tile_finish<MODE, PATH>(tile, sh, cur.shift, cur.rows, cur.k_pad, cur.slice, ctab[cur.N],
+                            cur.out, cur.r0, cur.h0);
     if (ni >= tiles) break;
     i = ni;
     cur = nxt;
   }
+}
+
+// Grouped: both sides of every problem in one launch (the first `ablocks`
+// workgroups walk the A side's map).
+template <typename T, int MODE, int PATH>
+__global__ __launch_bounds__(256) void kg_slices(const ProbDesc* __restrict__ P,
+                                                 const BlockRef* __restrict__ amap, int atiles,
+                                                 int ablocks, const BlockRef* __restrict__ bmap,
+                                                 int btiles, const CrtConsts* __restrict__ ctab) {
+  __shared__ double tile[kTR * kRS];
+  const int w = (int)blockIdx.x;
+  if (w < ablocks)
+    walk_group<T, true, MODE, PATH>(P, amap, atiles, w, ablocks, ctab, tile);
+  else
+    walk_group<T, false, MODE, PATH>(P, bmap, btiles, w - ablocks, (int)gridDim.x - ablocks, ctab,
+                                     tile);
 }
 
 // Planner operands: x = |a| 2^-alpha (alpha = floor(log2 max_h |a_ih|), so
@@ -859,18 +921,15 @@ __global__ __launch_bounds__(256) void k_plan_slices(const T* __restrict__ src, 
 
 // Resident workgroups per compute unit of each slice kernel and compute
 // units per device, filled once per device by init_slice_launch (outside
-// any stream capture); a grid-stride launch uses at most that many
-// workgroups.  Index: [float][trans / A side][variant], variant 0 = mode 0,
-// 1 + path = mode 1 on that residue path (kAnyPath: chosen per tile), and
-// the same plus kGrouped for the grouped kernels.
+// any stream capture); a launch uses at most that many workgroups.  Index:
+// [float][kReal, kCx, kEmb, grouped][variant], variant 0 = the bars, 1 + path =
+// the residues on that path (kAnyPath, chosen per tile: grouped only).
 constexpr int kMaxDevices = 64;
-constexpr int kGrouped = 2 + kAnyPath;
-constexpr int kVariants = 2 * kGrouped;
+constexpr int kVariants = 2 + kAnyPath;
+constexpr int kGroupForm = 3;
 constexpr int kPartSlots = 512;   // workgroups that shared tiles may fill (two per CU)
 std::atomic<int> g_cus[kMaxDevices];
-std::atomic<int> g_occ[2][2][kVariants];
-std::atomic<int> g_occ_cx[2][2][kGrouped];   // k_slices_cx: variant 0 = mode 2, 1 + path
-std::atomic<int> g_occ_emb[2][2][kGrouped];  // k_slices_emb: variant 0 = mode 0, 1 + path
+std::atomic<int> g_occ[2][4][kVariants];
 
 template <typename K>
 int resident_per_cu(K* kern) {
@@ -882,181 +941,124 @@ int resident_per_cu(K* kern) {
   return n;
 }
 
-template <typename T, bool TR>
+template <typename T, int FORM>
+void fill_occ_form() {
+  constexpr int kBar = FORM == kCx ? 2 : 0;
+  std::atomic<int>* o = g_occ[std::is_same<T, float>::value ? 1 : 0][FORM];
+  o[0] = resident_per_cu(k_slices<T, FORM, kBar, kAnyPath>);
+  o[1 + kLimbs2] = resident_per_cu(k_slices<T, FORM, 1, kLimbs2>);
+  o[1 + kLimbs3] = resident_per_cu(k_slices<T, FORM, 1, kLimbs3>);
+  o[1 + kSteps1] = resident_per_cu(k_slices<T, FORM, 1, kSteps1>);
+  o[1 + kSteps3] = resident_per_cu(k_slices<T, FORM, 1, kSteps3>);
+  o[1 + kSteps4] = resident_per_cu(k_slices<T, FORM, 1, kSteps4>);
+}
+
+template <typename T>
 void fill_occ() {
-  std::atomic<int>* o = g_occ[std::is_same<T, float>::value ? 1 : 0][TR ? 1 : 0];
-  o[0] = resident_per_cu(k_slices<T, TR, 0, kAnyPath>);
-  o[1 + kLimbs2] = resident_per_cu(k_slices<T, TR, 1, kLimbs2>);
-  o[1 + kLimbs3] = resident_per_cu(k_slices<T, TR, 1, kLimbs3>);
-  o[1 + kSteps1] = resident_per_cu(k_slices<T, TR, 1, kSteps1>);
-  o[1 + kSteps3] = resident_per_cu(k_slices<T, TR, 1, kSteps3>);
-  o[1 + kSteps4] = resident_per_cu(k_slices<T, TR, 1, kSteps4>);
-  o[kGrouped] = resident_per_cu(kg_slices<T, TR, 0, kAnyPath>);
-  o[kGrouped + 1 + kLimbs2] = resident_per_cu(kg_slices<T, TR, 1, kLimbs2>);
-  o[kGrouped + 1 + kLimbs3] = resident_per_cu(kg_slices<T, TR, 1, kLimbs3>);
-  o[kGrouped + 1 + kSteps1] = resident_per_cu(kg_slices<T, TR, 1, kSteps1>);
-  o[kGrouped + 1 + kSteps3] = resident_per_cu(kg_slices<T, TR, 1, kSteps3>);
-  o[kGrouped + 1 + kSteps4] = resident_per_cu(kg_slices<T, TR, 1, kSteps4>);
-  o[kGrouped + 1 + kAnyPath] = resident_per_cu(kg_slices<T, TR, 1, kAnyPath>);
-  std::atomic<int>* c = g_occ_cx[std::is_same<T, float>::value ? 1 : 0][TR ? 1 : 0];
-  c[0] = resident_per_cu(k_slices_cx<T, TR, 2, kAnyPath>);
-  c[1 + kLimbs2] = resident_per_cu(k_slices_cx<T, TR, 1, kLimbs2>);
-  c[1 + kLimbs3] = resident_per_cu(k_slices_cx<T, TR, 1, kLimbs3>);
-  c[1 + kSteps1] = resident_per_cu(k_slices_cx<T, TR, 1, kSteps1>);
-  c[1 + kSteps3] = resident_per_cu(k_slices_cx<T, TR, 1, kSteps3>);
-  c[1 + kSteps4] = resident_per_cu(k_slices_cx<T, TR, 1, kSteps4>);
-  std::atomic<int>* b = g_occ_emb[std::is_same<T, float>::value ? 1 : 0][TR ? 1 : 0];
-  b[0] = resident_per_cu(k_slices_emb<T, TR, 0, kAnyPath>);
-  b[1 + kLimbs2] = resident_per_cu(k_slices_emb<T, TR, 1, kLimbs2>);
-  b[1 + kLimbs3] = resident_per_cu(k_slices_emb<T, TR, 1, kLimbs3>);
-  b[1 + kSteps1] = resident_per_cu(k_slices_emb<T, TR, 1, kSteps1>);
-  b[1 + kSteps3] = resident_per_cu(k_slices_emb<T, TR, 1, kSteps3>);
-  b[1 + kSteps4] = resident_per_cu(k_slices_emb<T, TR, 1, kSteps4>);
+  fill_occ_form<T, kReal>();
+  fill_occ_form<T, kCx>();
+  fill_occ_form<T, kEmb>();
+  std::atomic<int>* o = g_occ[std::is_same<T, float>::value ? 1 : 0][kGroupForm];
+  o[0] = resident_per_cu(kg_slices<T, 0, kAnyPath>);
+  o[1 + kLimbs2] = resident_per_cu(kg_slices<T, 1, kLimbs2>);
+  o[1 + kLimbs3] = resident_per_cu(kg_slices<T, 1, kLimbs3>);
+  o[1 + kSteps1] = resident_per_cu(kg_slices<T, 1, kSteps1>);
+  o[1 + kSteps3] = resident_per_cu(kg_slices<T, 1, kSteps3>);
+  o[1 + kSteps4] = resident_per_cu(kg_slices<T, 1, kSteps4>);
+  o[1 + kAnyPath] = resident_per_cu(kg_slices<T, 1, kAnyPath>);
 }
 
-// Launch grid of `tiles` tiles on `grid` workgroups that form `N` residues each
-// (1: bars): while one workgroup per tile and modulus pair fits the slots that
-// the tiles leave free, the moduli are dealt to several workgroups per tile
-// (for_moduli), at least two each.  The tile is then read again by each of
-// them, from L2.  At 256^3 (16 tiles, N = 14) a side went from 9.8 to 6.7 us.
-dim3 shared_grid(int grid, int tiles, int N) {
-  const int parts = grid == tiles ? std::min(N / 2, kPartSlots / std::max(tiles, 1)) : 1;
-  return dim3((unsigned)grid, (unsigned)std::max(parts, 1));
-}
-
-// Workgroups for `tiles` tiles: all resident slots of the device, or one per
-// tile if the device's figures are unknown.  A positive g_slice_cap (a test
-// knob set through ozaki2_debug_tuning) caps the count, so that each
-// workgroup walks many tiles.
-// kind: 0 = k_slices, 1 = k_slices_cx, 2 = k_slices_emb.
-int slice_grid(bool f32, bool trans, int variant, int tiles, int kind = 0) {
-  int grid = tiles;
+// Workgroups *ba and *bb for ta and tb tiles of the two sides, a tile of A
+// costing `wa` of B's: one per tile while they all fit the resident slots of
+// the device (or the device's figures are unknown), else the slots in
+// proportion to the work.  A positive g_slice_cap (a test knob set through
+// ozaki2_debug_tuning) caps each side's count, so that each workgroup walks
+// many tiles.
+void slice_blocks(bool f32, int form, int variant, int ta, int tb, int wa, int* ba, int* bb) {
+  *ba = ta;
+  *bb = tb;
   int dev = 0;
   if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices) {
-    const int cus = g_cus[dev].load(std::memory_order_relaxed);
-    const int a = f32 ? 1 : 0, b = trans ? 1 : 0;
-    const int occ = (kind == 1   ? g_occ_cx[a][b][variant]
-                     : kind == 2 ? g_occ_emb[a][b][variant]
-                                 : g_occ[a][b][variant])
-                        .load(std::memory_order_relaxed);
-    if (cus > 0 && occ > 0) grid = (int)std::min<int64_t>(tiles, (int64_t)cus * occ);
+    const int64_t slots = (int64_t)g_cus[dev].load(std::memory_order_relaxed) *
+                          g_occ[f32 ? 1 : 0][form][variant].load(std::memory_order_relaxed);
+    if (slots > 1 && (int64_t)ta + tb > slots) {
+      const double share = (double)wa * ta / ((double)wa * ta + tb);
+      int64_t a = (int64_t)(share * (double)slots + 0.5);
+      if (ta > 0) a = std::max<int64_t>(a, 1);
+      if (tb > 0) a = std::min<int64_t>(a, slots - 1);
+      *ba = (int)std::min<int64_t>(ta, a);
+      *bb = (int)std::min<int64_t>(tb, slots - a);
+    }
   }
   const int cap = g_slice_cap.load(std::memory_order_relaxed);
-  if (cap > 0) grid = std::min(grid, cap);
-  return grid;
-}
-
-template <typename T>
-struct SliceLaunch {
-  const T* src;
-  int ld, rows, k, k_pad, gy, tiles;
-  size_t slice;
-  const void* aux;
-  int8_t* out;
-};
-
-template <typename T, bool TR, int MODE, int PATH>
-void launch_one(hipStream_t s, const SliceLaunch<T>& L, const CrtConsts& cc) {
-  const int variant = MODE != 1 ? 0 : 1 + PATH;   // mode 2 has mode 0's resources
-  const dim3 grid = shared_grid(slice_grid(std::is_same<T, float>::value, TR, variant, L.tiles),
-                                L.tiles, MODE == 1 ? cc.N : 1);
-  hipLaunchKernelGGL((k_slices<T, TR, MODE, PATH>), grid, dim3(256), 0, s, L.src, L.ld, L.rows,
-                     L.k, L.k_pad, L.gy, L.tiles, L.slice, L.aux, cc, L.out);
-}
-
-template <typename T, bool TR>
-void launch_side(hipStream_t s, int mode, const SliceLaunch<T>& L, const CrtConsts& cc) {
-  if (mode == 0) {
-    launch_one<T, TR, 0, kAnyPath>(s, L, cc);
-    return;
-  }
-  if (mode == 2) {
-    launch_one<T, TR, 2, kAnyPath>(s, L, cc);
-    return;
-  }
-  switch (residue_path(cc)) {
-    case kLimbs2: launch_one<T, TR, 1, kLimbs2>(s, L, cc); break;
-    case kLimbs3: launch_one<T, TR, 1, kLimbs3>(s, L, cc); break;
-    case kSteps1: launch_one<T, TR, 1, kSteps1>(s, L, cc); break;
-    case kSteps3: launch_one<T, TR, 1, kSteps3>(s, L, cc); break;
-    default: launch_one<T, TR, 1, kSteps4>(s, L, cc); break;
+  if (cap > 0) {
+    *ba = std::min(*ba, cap);
+    *bb = std::min(*bb, cap);
   }
 }
 
-template <typename T, bool TR, int MODE, int PATH>
-void launch_one_cx(hipStream_t s, const SliceLaunch<T>& L, const CrtConsts& cc) {
+template <typename T, int FORM, int MODE, int PATH>
+void launch_one(hipStream_t s, SliceArgs& a, const CrtConsts& cc) {
   const int variant = MODE != 1 ? 0 : 1 + PATH;
-  const dim3 grid = shared_grid(slice_grid(std::is_same<T, float>::value, TR, variant, L.tiles, 1),
-                                L.tiles, MODE == 1 ? cc.N : 1);
-  hipLaunchKernelGGL((k_slices_cx<T, TR, MODE, PATH>), grid, dim3(256), 0, s, L.src, L.ld, L.rows,
-                     L.k, L.k_pad, L.gy, L.tiles, L.slice, L.aux, cc, L.out);
+  const int tiles = a.a.tiles + a.b.tiles;
+  if (tiles <= 0) return;
+  slice_blocks(std::is_same<T, float>::value, FORM, variant, a.a.tiles, a.b.tiles,
+               FORM == kEmb && MODE == 1 ? 2 : 1, &a.a.blocks, &a.b.blocks);
+  // While the tiles leave slots free, the moduli of a tile are dealt to several
+  // workgroups (for_moduli), at least two each; the tile is then read again by
+  // each of them, from L2.  At 256^3 (16 tiles a side, N = 14) this took the
+  // residues of a side from 9.8 to 6.7 us.
+  const bool one_each = a.a.blocks == a.a.tiles && a.b.blocks == a.b.tiles;
+  const int parts = MODE == 1 && one_each ? std::min(cc.N / 2, kPartSlots / tiles) : 1;
+  const dim3 grid((unsigned)(a.a.blocks + a.b.blocks), (unsigned)std::max(parts, 1));
+  hipLaunchKernelGGL((k_slices<T, FORM, MODE, PATH>), grid, dim3(256), 0, s, a, cc);
 }
 
-template <typename T, bool TR>
-void launch_side_cx(hipStream_t s, int mode, const SliceLaunch<T>& L, const CrtConsts& cc) {
-  if (mode == 2) {
-    launch_one_cx<T, TR, 2, kAnyPath>(s, L, cc);
-    return;
-  }
+template <typename T, int FORM>
+void launch_residues_t(hipStream_t s, SliceArgs& a, const CrtConsts& cc) {
   switch (residue_path(cc)) {
-    case kLimbs2: launch_one_cx<T, TR, 1, kLimbs2>(s, L, cc); break;
-    case kLimbs3: launch_one_cx<T, TR, 1, kLimbs3>(s, L, cc); break;
-    case kSteps1: launch_one_cx<T, TR, 1, kSteps1>(s, L, cc); break;
-    case kSteps3: launch_one_cx<T, TR, 1, kSteps3>(s, L, cc); break;
-    default: launch_one_cx<T, TR, 1, kSteps4>(s, L, cc); break;
+    case kLimbs2: launch_one<T, FORM, 1, kLimbs2>(s, a, cc); break;
+    case kLimbs3: launch_one<T, FORM, 1, kLimbs3>(s, a, cc); break;
+    case kSteps1: launch_one<T, FORM, 1, kSteps1>(s, a, cc); break;
+    case kSteps3: launch_one<T, FORM, 1, kSteps3>(s, a, cc); break;
+    default: launch_one<T, FORM, 1, kSteps4>(s, a, cc); break;
   }
 }
 
 template <typename T>
-void launch_t(hipStream_t s, int mode, bool trans, const T* src, int ld, int rows, int k,
-              int rows_pad, int k_pad, const uint64_t* bits, const int* shift, const CrtConsts& cc,
-              int8_t* out, bool cx = false) {
-  SliceLaunch<T> L;
-  L.src = src;
-  L.ld = ld;
-  L.rows = rows;
-  L.k = k;
-  L.k_pad = k_pad;
-  L.gy = mode != 1 ? rows_pad / kTR : cdiv_i(rows, kTR);
-  L.tiles = (k_pad / kTK) * L.gy;
-  L.slice = (size_t)rows_pad * k_pad;
-  L.aux = mode != 1 ? (const void*)bits : (const void*)shift;
-  L.out = out;
-  if (L.tiles <= 0) return;
-  if (cx) {
-    if (trans)
-      launch_side_cx<T, true>(s, mode, L, cc);
-    else
-      launch_side_cx<T, false>(s, mode, L, cc);
-  } else if (trans) {
-    launch_side<T, true>(s, mode, L, cc);
-  } else {
-    launch_side<T, false>(s, mode, L, cc);
-  }
+void launch_form(hipStream_t s, SliceSet set, bool bars, SliceArgs& a, const CrtConsts& cc) {
+  if (set == SliceSet::Real)
+    bars ? launch_one<T, kReal, 0, kAnyPath>(s, a, cc) : launch_residues_t<T, kReal>(s, a, cc);
+  else if (set == SliceSet::Complex3)
+    bars ? launch_one<T, kCx, 2, kAnyPath>(s, a, cc) : launch_residues_t<T, kCx>(s, a, cc);
+  else
+    bars ? launch_one<T, kEmb, 0, kAnyPath>(s, a, cc) : launch_residues_t<T, kEmb>(s, a, cc);
 }
 
-template <typename T, bool TR, int MODE, int PATH>
-void launch_group_one(hipStream_t s, const ProbDesc* P, const BlockRef* map, int blocks,
-                      const CrtConsts* ctab) {
-  const int variant = kGrouped + (MODE == 0 ? 0 : 1 + PATH);
-  const dim3 g((unsigned)slice_grid(std::is_same<T, float>::value, TR, variant, blocks)), b(256);
-  hipLaunchKernelGGL((kg_slices<T, TR, MODE, PATH>), g, b, 0, s, P, map, blocks, ctab);
+template <typename T, int MODE, int PATH>
+void launch_group_one(hipStream_t s, const ProbDesc* P, const BlockRef* amap, int atiles,
+                      const BlockRef* bmap, int btiles, const CrtConsts* ctab) {
+  int ba, bb;
+  slice_blocks(std::is_same<T, float>::value, kGroupForm, MODE == 0 ? 0 : 1 + PATH, atiles, btiles,
+               1, &ba, &bb);
+  hipLaunchKernelGGL((kg_slices<T, MODE, PATH>), dim3((unsigned)(ba + bb)), dim3(256), 0, s, P,
+                     amap, atiles, ba, bmap, btiles, ctab);
 }
 
-template <typename T, bool TR>
-void group_slices_t(hipStream_t s, int mode, int path, const ProbDesc* P, const BlockRef* map,
-                    int blocks, const CrtConsts* ctab) {
-  if (mode == 0) {
-    launch_group_one<T, TR, 0, kAnyPath>(s, P, map, blocks, ctab);
+template <typename T>
+void group_slices_t(hipStream_t s, bool bars, int path, const ProbDesc* P, const BlockRef* amap,
+                    int atiles, const BlockRef* bmap, int btiles, const CrtConsts* ctab) {
+  if (bars) {
+    launch_group_one<T, 0, kAnyPath>(s, P, amap, atiles, bmap, btiles, ctab);
     return;
   }
   switch (path) {
-    case kLimbs2: launch_group_one<T, TR, 1, kLimbs2>(s, P, map, blocks, ctab); break;
-    case kLimbs3: launch_group_one<T, TR, 1, kLimbs3>(s, P, map, blocks, ctab); break;
-    case kSteps1: launch_group_one<T, TR, 1, kSteps1>(s, P, map, blocks, ctab); break;
-    case kSteps3: launch_group_one<T, TR, 1, kSteps3>(s, P, map, blocks, ctab); break;
-    case kSteps4: launch_group_one<T, TR, 1, kSteps4>(s, P, map, blocks, ctab); break;
-    default: launch_group_one<T, TR, 1, kAnyPath>(s, P, map, blocks, ctab); break;
+    case kLimbs2: launch_group_one<T, 1, kLimbs2>(s, P, amap, atiles, bmap, btiles, ctab); break;
+    case kLimbs3: launch_group_one<T, 1, kLimbs3>(s, P, amap, atiles, bmap, btiles, ctab); break;
+    case kSteps1: launch_group_one<T, 1, kSteps1>(s, P, amap, atiles, bmap, btiles, ctab); break;
+    case kSteps3: launch_group_one<T, 1, kSteps3>(s, P, amap, atiles, bmap, btiles, ctab); break;
+    case kSteps4: launch_group_one<T, 1, kSteps4>(s, P, amap, atiles, bmap, btiles, ctab); break;
+    default: launch_group_one<T, 1, kAnyPath>(s, P, amap, atiles, bmap, btiles, ctab); break;
   }
 }
 
@@ -1068,10 +1070,8 @@ void init_slice_launch(int dev) {
   if (dev < 0 || dev >= kMaxDevices) return;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 0;
-  fill_occ<double, true>();
-  fill_occ<double, false>();
-  fill_occ<float, true>();
-  fill_occ<float, false>();
+  fill_occ<double>();
+  fill_occ<float>();
   g_cus[dev].store(cus, std::memory_order_relaxed);
 }
 
@@ -1085,22 +1085,15 @@ int group_residue_path(const CrtConsts* const* cc, int count) {
   return path < 0 ? kAnyPath : path;
 }
 
-void launch_group_slices(hipStream_t s, Prec pr, int mode, bool aside, int path,
-                         const ProbDesc* P, const BlockRef* map, int blocks,
+void launch_group_slices(hipStream_t s, Prec pr, bool bars, int path, const ProbDesc* P,
+                         const BlockRef* amap, int atiles, const BlockRef* bmap, int btiles,
                          const CrtConsts* ctab) {
-  if (blocks <= 0) return;
+  if (atiles + btiles <= 0) return;
   if (path < 0 || path > kAnyPath) path = kAnyPath;
-  if (pr == Prec::F64) {
-    if (aside)
-      group_slices_t<double, true>(s, mode, path, P, map, blocks, ctab);
-    else
-      group_slices_t<double, false>(s, mode, path, P, map, blocks, ctab);
-  } else {
-    if (aside)
-      group_slices_t<float, true>(s, mode, path, P, map, blocks, ctab);
-    else
-      group_slices_t<float, false>(s, mode, path, P, map, blocks, ctab);
-  }
+  if (pr == Prec::F64)
+    group_slices_t<double>(s, bars, path, P, amap, atiles, bmap, btiles, ctab);
+  else
+    group_slices_t<float>(s, bars, path, P, amap, atiles, bmap, btiles, ctab);
 }
 
 void launch_plan_slices(hipStream_t s, Prec pr, bool trans, const void* src, int ld, int rows,
@@ -1131,85 +1124,35 @@ void launch_plan_slices(hipStream_t s, Prec pr, bool trans, const void* src, int
   }
 }
 
-void launch_slices(hipStream_t s, Prec pr, int mode, bool trans, const void* src, int ld, int rows,
-                   int k, int rows_pad, int k_pad, const uint64_t* bits, const int* shift,
-                   const CrtConsts& cc, int8_t* out) {
+void launch_slices(hipStream_t s, Prec pr, SliceSet set, bool bars, const SliceOperand* A,
+                   const SliceOperand* B, int k, int k_pad, const CrtConsts& cc, int bias) {
+  SliceArgs a{};
+  a.k = k;
+  a.k_pad = k_pad;
+  a.bias = bias;
+  const bool emb = set == SliceSet::Embedding;
+  auto fill = [&](SliceSide* d, const SliceOperand* o, bool aside) {
+    if (!o) return;
+    // the embedding's A side: tiles cover its first row half
+    const int span = emb && aside ? o->rows_pad / 2 : o->rows_pad;
+    d->src = o->src;
+    d->bits = o->bits;
+    d->mx = o->mx;
+    d->shift = o->shift;
+    d->out = o->out;
+    d->slice = (size_t)o->rows_pad * k_pad * (emb ? 2 : 1);
+    d->ld = o->ld;
+    d->rows = o->rows;
+    d->gy = bars ? span / kTR : cdiv_i(o->rows, kTR);   // bars cover the padding rows
+    d->tiles = (k_pad / kTK) * d->gy;
+    if (emb && aside) a.half = span;
+  };
+  fill(&a.a, A, true);
+  fill(&a.b, B, false);
   if (pr == Prec::F64)
-    launch_t<double>(s, mode, trans, (const double*)src, ld, rows, k, rows_pad, k_pad, bits, shift,
-                     cc, out);
+    launch_form<double>(s, set, bars, a, cc);
   else
-    launch_t<float>(s, mode, trans, (const float*)src, ld, rows, k, rows_pad, k_pad, bits, shift,
-                    cc, out);
-}
-
-namespace {
-
-template <typename T, bool TR, int MODE, int PATH>
-void emb_one(hipStream_t s, const T* src, int ld, int rows, int k, int kh, int gy, int tiles,
-             int half, size_t slice, const void* aux, const CrtConsts& cc, int8_t* out) {
-  const int variant = MODE == 0 ? 0 : 1 + PATH;
-  const dim3 grid = shared_grid(slice_grid(std::is_same<T, float>::value, TR, variant, tiles, 2),
-                                tiles, MODE == 1 ? cc.N : 1);
-  hipLaunchKernelGGL((k_slices_emb<T, TR, MODE, PATH>), grid, dim3(256), 0, s, src, ld, rows, k,
-                     kh, gy, tiles, half, slice, aux, cc, out);
-}
-
-template <typename T, bool TR>
-void emb_side(hipStream_t s, int mode, const T* src, int ld, int rows, int k, int kh, int rows_pad,
-              int half, const uint64_t* bits, const int* shift, const CrtConsts& cc, int8_t* out) {
-  // mode 0 covers the padding rows (their bars must be zero); mode 1 only
-  // the tiles of real rows.  On the A side the tiles cover the first half.
-  const int span = TR ? half : rows_pad;
-  const int gy = mode == 0 ? span / kTR : cdiv_i(rows, kTR);
-  const int tiles = (kh / kTK) * gy;
-  const size_t slice = (size_t)rows_pad * 2 * kh;
-  if (tiles <= 0) return;
-  if (mode == 0) {
-    emb_one<T, TR, 0, kAnyPath>(s, src, ld, rows, k, kh, gy, tiles, half, slice, bits, cc, out);
-    return;
-  }
-  switch (residue_path(cc)) {
-    case kLimbs2: emb_one<T, TR, 1, kLimbs2>(s, src, ld, rows, k, kh, gy, tiles, half, slice, shift, cc, out); break;
-    case kLimbs3: emb_one<T, TR, 1, kLimbs3>(s, src, ld, rows, k, kh, gy, tiles, half, slice, shift, cc, out); break;
-    case kSteps1: emb_one<T, TR, 1, kSteps1>(s, src, ld, rows, k, kh, gy, tiles, half, slice, shift, cc, out); break;
-    case kSteps3: emb_one<T, TR, 1, kSteps3>(s, src, ld, rows, k, kh, gy, tiles, half, slice, shift, cc, out); break;
-    default: emb_one<T, TR, 1, kSteps4>(s, src, ld, rows, k, kh, gy, tiles, half, slice, shift, cc, out); break;
-  }
-}
-
-}  // namespace
-
-void launch_slices_embed(hipStream_t s, Prec pr, int mode, bool aside, const void* src, int ld,
-                         int rows, int k, int kh, int rows_pad, int half, const uint64_t* bits,
-                         const int* shift, const CrtConsts& cc, int8_t* out) {
-  if (mode != 0 && mode != 1) return;
-  if (pr == Prec::F64) {
-    if (aside)
-      emb_side<double, true>(s, mode, (const double*)src, ld, rows, k, kh, rows_pad, half, bits,
-                             shift, cc, out);
-    else
-      emb_side<double, false>(s, mode, (const double*)src, ld, rows, k, kh, rows_pad, 0, bits,
-                              shift, cc, out);
-  } else {
-    if (aside)
-      emb_side<float, true>(s, mode, (const float*)src, ld, rows, k, kh, rows_pad, half, bits,
-                            shift, cc, out);
-    else
-      emb_side<float, false>(s, mode, (const float*)src, ld, rows, k, kh, rows_pad, 0, bits, shift,
-                             cc, out);
-  }
-}
-
-void launch_slices_complex(hipStream_t s, Prec pr, int mode, bool trans, const void* src, int ld,
-                           int rows, int k, int rows_pad, int k_pad, const uint64_t* bits,
-                           const int* shift, const CrtConsts& cc, int8_t* out) {
-  if (mode != 1 && mode != 2) return;
-  if (pr == Prec::F64)
-    launch_t<double>(s, mode, trans, (const double*)src, ld, rows, k, rows_pad, k_pad, bits, shift,
-                     cc, out, true);
-  else
-    launch_t<float>(s, mode, trans, (const float*)src, ld, rows, k, rows_pad, k_pad, bits, shift,
-                    cc, out, true);
+    launch_form<float>(s, set, bars, a, cc);
 }
 
 }  // namespace oz2

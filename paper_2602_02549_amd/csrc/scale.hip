@@ -2,9 +2,10 @@
 //   - per-row / per-column maximum of |a| (kept as the IEEE bit pattern of
 //     the FP64 value, whose unsigned order equals the numeric order), from
 //     which mu' = 5 - floor(log2 max|a|) follows exactly;
-//   - the final shifts mu = mu' + floor(fma_down(c, e, P')) with
-//     e = log2f(single_up(max_j Cbar_ij));
-//   - log2f, correctly rounded to FP32 (double-double series evaluation).
+//   - log2f, correctly rounded to FP32 (double-double series evaluation), for
+//     the stage dumps and the exhaustive check; the final shifts mu = mu' +
+//     floor(fma_down(c, e, P')), e = log2f(single_up(max_j Cbar_ij)), come from
+//     their table of steps where they are used (shift_of).
 #include <cstdint>
 
 #include "ozaki2_internal.h"
@@ -310,52 +311,21 @@ __device__ inline float single_up_int(int M) {
   return (float)u;
 }
 
-// floor(c e + P') of the exact value: the product of two FP32 numbers is
-// exact in FP64, and TwoSum gives the sum exactly as s + err; only an integer
-// s with err < 0 needs a correction.
-__device__ inline int floor_fma(float c, float e, float Pp) {
-  double ce = (double)c * (double)e;
-  dd s = two_sum(ce, (double)Pp);
-  double f = floor(s.h);
-  if (f == s.h && s.l < 0) f -= 1.0;
-  return (int)f;
-}
-
-__device__ __forceinline__ void shifts_body(const uint64_t* __restrict__ rowbits, const int* __restrict__ rmax,
-                                   int m, const uint64_t* __restrict__ colbits,
-                                   const int* __restrict__ cmax, int n, float Pprime, float c,
-                                   int* __restrict__ mu_p, int* __restrict__ nu_p,
-                                   int* __restrict__ mu, int* __restrict__ nu,
-                                   float* __restrict__ ef, int t, int bias = 0) {
+// Stage dumps only: mu', nu' and the log2f values (the residue kernels form
+// the shifts from the table of steps, shift_of).
+__global__ __launch_bounds__(256) void k_debug_shifts(const uint64_t* __restrict__ rowbits,
+                                                      const int* __restrict__ rmax, int m,
+                                                      const uint64_t* __restrict__ colbits,
+                                                      const int* __restrict__ cmax, int n,
+                                                      int* __restrict__ mu_p, int* __restrict__ nu_p,
+                                                      float* __restrict__ ef) {
+  const int t = blockIdx.x * 256 + threadIdx.x;
   if (t >= m + n) return;
   const bool row = t < m;
   const int idx = row ? t : t - m;
-  const uint64_t bits = row ? rowbits[idx] : colbits[idx];
   const int M = row ? rmax[idx] : cmax[idx];
-  const int sp = shift_prime_bits(bits) + (bits ? bias : 0);
-  const float d = single_up_int(M > 1 ? M : 1);       // R7: a zero maximum is treated as 1
-  const float e = log2f_rn(d);
-  const int s = sp + floor_fma(c, e, Pprime);
-  if (row) {
-    if (mu_p) mu_p[idx] = sp;
-    mu[idx] = s;
-  } else {
-    if (nu_p) nu_p[idx] = sp;
-    nu[idx] = s;
-  }
-  if (ef) ef[t] = e;
-}
-
-__global__ __launch_bounds__(256) void k_shifts(const uint64_t* __restrict__ rowbits,
-                                                const int* __restrict__ rmax, int m,
-                                                const uint64_t* __restrict__ colbits,
-                                                const int* __restrict__ cmax, int n, float Pprime,
-                                                float c, int* __restrict__ mu_p,
-                                                int* __restrict__ nu_p, int* __restrict__ mu,
-                                                int* __restrict__ nu, float* __restrict__ ef,
-                                                int bias) {
-  shifts_body(rowbits, rmax, m, colbits, cmax, n, Pprime, c, mu_p, nu_p, mu, nu, ef,
-              blockIdx.x * 256 + threadIdx.x, bias);
+  (row ? mu_p : nu_p)[idx] = shift_prime_bits(row ? rowbits[idx] : colbits[idx]);
+  ef[t] = log2f_rn(single_up_int(M > 1 ? M : 1));       // R7: a zero maximum is treated as 1
 }
 
 // ---- grouped versions ------------------------------------------------------
@@ -391,16 +361,6 @@ __global__ __launch_bounds__(256) void kg_absbar_cols(const ProbDesc* __restrict
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
   absbar_cols_body<T>((const T*)d.B, d.ldb, d.k, d.n, d.np, d.kp, d.colbits, d.flag, d.Bs, e.y);
-}
-
-__global__ __launch_bounds__(256) void kg_shifts(const ProbDesc* __restrict__ P,
-                                                 const BlockRef* __restrict__ map,
-                                                 const CrtConsts* __restrict__ ctab) {
-  const BlockRef e = map[blockIdx.x];
-  const ProbDesc& d = P[e.x];
-  const CrtConsts& cc = ctab[d.N];
-  shifts_body(d.rowbits, d.rmax, d.m, d.colbits, d.cmax, d.n, cc.Pprime, cc.c, nullptr, nullptr,
-              d.mu, d.nu, nullptr, e.y * 256 + threadIdx.x);
 }
 
 __global__ __launch_bounds__(256) void k_log2f(const float* __restrict__ d, float* __restrict__ out,
@@ -473,11 +433,11 @@ void launch_absbar_cols(hipStream_t s, Prec pr, const void* B, int ldb, int k, i
                        n_pad, k_pad, colbits, flag, out);
 }
 
-void launch_shifts(hipStream_t s, const uint64_t* rowbits, const int* rmax, int m,
-                   const uint64_t* colbits, const int* cmax, int n, float Pprime, float c,
-                   int* mu_p, int* nu_p, int* mu, int* nu, float* ef, int bias) {
-  hipLaunchKernelGGL(k_shifts, dim3(cdiv(m + n, 256)), dim3(256), 0, s, rowbits, rmax, m, colbits,
-                     cmax, n, Pprime, c, mu_p, nu_p, mu, nu, ef, bias);
+void launch_debug_shifts(hipStream_t s, const uint64_t* rowbits, const int* rmax, int m,
+                         const uint64_t* colbits, const int* cmax, int n, int* mu_p, int* nu_p,
+                         float* ef) {
+  hipLaunchKernelGGL(k_debug_shifts, dim3(cdiv(m + n, 256)), dim3(256), 0, s, rowbits, rmax, m,
+                     colbits, cmax, n, mu_p, nu_p, ef);
 }
 
 void launch_log2f(hipStream_t s, const float* d, float* out, int count) {
@@ -485,7 +445,7 @@ void launch_log2f(hipStream_t s, const float* d, float* out, int count) {
 }
 
 void launch_group_scale(hipStream_t s, Prec pr, int phase, const ProbDesc* P, const BlockRef* map,
-                        int blocks, const CrtConsts* ctab) {
+                        int blocks) {
   if (blocks <= 0) return;
   const dim3 g((unsigned)blocks), b(256);
   switch (phase) {
@@ -509,9 +469,6 @@ void launch_group_scale(hipStream_t s, Prec pr, int phase, const ProbDesc* P, co
         hipLaunchKernelGGL(kg_absbar_cols<double>, g, b, 0, s, P, map);
       else
         hipLaunchKernelGGL(kg_absbar_cols<float>, g, b, 0, s, P, map);
-      break;
-    case GP_SHIFTS:
-      hipLaunchKernelGGL(kg_shifts, g, b, 0, s, P, map, ctab);
       break;
     default:
       break;

@@ -297,6 +297,71 @@ bool moduli_of(int table, int N, int* p) {
   return true;
 }
 
+namespace {
+
+// log2f of Algorithm 2 (correctly rounded FP32 log2) of an integer 1 <= d <
+// 2^32 with at most 24 significant bits.  The long double log2 is within
+// 2^-61 of the value (relative); false if it lies within 2^-55 of an FP32
+// rounding midpoint, so that it could round the other way (powers of two are
+// exact).
+bool log2f_host(uint32_t d, float* out) {
+  const long double v = std::log2((long double)d);
+  const float y = (float)v;
+  *out = y;
+  if ((d & (d - 1)) == 0) return true;
+  for (float z : {std::nextafter(y, -INFINITY), std::nextafter(y, INFINITY)}) {
+    const long double mid = ((long double)y + (long double)z) / 2;
+    if (std::fabs(v - mid) <= std::ldexp(v, -55)) return false;
+  }
+  return true;
+}
+
+// floor(c log2f(single_up(M)) + P') of Algorithm 2 for an integer M >= 1: the
+// product of two FP32 numbers is exact in FP64, and the long double sum (64
+// bits) of two numbers below 2^8 on the FP32 x FP32 grid is checked by TwoSum.
+bool shift_of_max(uint32_t M, float c, float Pprime, int* out) {
+  int bl = 0;
+  while (bl < 32 && (M >> bl) != 0) ++bl;
+  uint64_t u = M;
+  if (bl > 24) {
+    const int s = bl - 24;
+    u = ((u + (1ull << s) - 1) >> s) << s;      // FP32 round-up
+  }
+  if (u > 0xFFFFFFFFull) return false;
+  float e;
+  if (!log2f_host((uint32_t)u, &e)) return false;
+  const double ce = (double)c * (double)e, p = (double)Pprime;
+  const double s = ce + p, bb = s - ce, err = (ce - (s - bb)) + (p - bb);
+  double f = std::floor(s);
+  if (f == s && err < 0) f -= 1.0;
+  *out = (int)f;
+  return true;
+}
+
+// The steps of shift_of_max over M = 1 .. 2^31 - 1 (it never rises with M).
+bool build_shift_steps(float c, float Pprime, int* shift0, int (&step)[kShiftSteps]) {
+  const uint32_t top = 0x7FFFFFFFu;
+  int last;
+  if (!shift_of_max(1, c, Pprime, shift0) || !shift_of_max(top, c, Pprime, &last)) return false;
+  if (*shift0 - last > kShiftSteps) return false;
+  for (int j = 0; j < kShiftSteps; ++j) {
+    const int want = *shift0 - j - 1;          // step[j]: the first M with a shift <= want
+    step[j] = 0x7FFFFFFF;
+    if (last > want) continue;
+    uint32_t lo = 1, hi = top;                 // shift(lo) > want >= shift(hi)
+    while (hi - lo > 1) {
+      const uint32_t mid = lo + (hi - lo) / 2;
+      int v;
+      if (!shift_of_max(mid, c, Pprime, &v)) return false;
+      (v > want ? lo : hi) = mid;
+    }
+    step[j] = (int)hi;
+  }
+  return true;
+}
+
+}  // namespace
+
 bool build_consts(int N, int b, int table, CrtConsts* out) {
   if (N < 2 || N > kMaxModuli || (b != 64 && b != 32)) return false;
   int kModuli[kMaxModuli];
@@ -371,6 +436,7 @@ bool build_consts(int N, int b, int table, CrtConsts* out) {
   // c = single_down(-0.5 / (1 - 4 u_32)).
   long double cv = -0.5L / (1.0L - 4.0L * std::ldexp((long double)1, -24));
   cc.c = single_down(cv, nullptr);
+  if (!build_shift_steps(cc.c, cc.Pprime, &cc.shift0, cc.step)) return false;
 
   // Residue reduction steps: |A'| < 2^(6 + floor(P')); a step maps |r| <= R
   // to |r| <= 128 + R 2^-51.9 and the last one needs R < 2^50 to be exact.
