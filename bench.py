@@ -454,11 +454,9 @@ def memory_phases(torch, dev, phase_ms: dict, m: int, n: int, k: int, N: int, s:
     phase times, against the 8 TB/s peak and a live device copy."""
     ref = hbm_reference(torch, dev)
     algo = {
-        "absmax_A": s * m * k, "absmax_B": s * k * n,
-        # above the one-read limit of B the bars of both operands are one launch
-        "bars": s * m * k + m * k + (s * k * n + k * n if "bar_B" not in phase_ms else 0),
-        "bar_B": s * k * n + k * n,
-        "residues": s * (m * k + k * n) + N * (m * k + k * n),
+        # each operand read once and its bars written; long operands are read twice
+        "scan": (s + 1) * (m * k + k * n),
+        "residues": (s + N) * (m * k + k * n),
         "crt": N * m * n + s * m * n,
     }
     out = {"hbm_reference": ref}

@@ -52,12 +52,10 @@ bool g_plan_ok[2][2] = {};
 // profiling (HIP events around each phase on the library stream)
 // ---------------------------------------------------------------------------
 enum Phase {
-  PH_INIT, PH_ABSMAX_A, PH_ABSMAX_B, PH_BARS, PH_BAR_B, PH_GEMM_SCALE, PH_RES, PH_GEMM_RES, PH_CRT,
-  PH_PLAN, PH_BATCH, PH_COUNT
+  PH_SCAN, PH_GEMM_SCALE, PH_RES, PH_GEMM_RES, PH_CRT, PH_PLAN, PH_BATCH, PH_COUNT
 };
-const char* kPhaseNames[PH_COUNT] = {"init", "absmax_A", "absmax_B", "bars", "bar_B",
-                                     "gemm_scale", "residues", "gemm_residue", "crt", "plan",
-                                     "batched"};
+const char* kPhaseNames[PH_COUNT] = {"scan", "gemm_scale", "residues", "gemm_residue", "crt",
+                                     "plan", "batched"};
 struct ProfRec {
   int phase;
   hipEvent_t a, b;
@@ -313,28 +311,11 @@ int run_pipeline(Prec pr, int m, int n, int k, const void* A, int lda, const voi
   const SliceOperand oa{A, lda, m, L.mp, rowbits, rmax, mu, As};
   const SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nu, Bs};
   if (!pre) {
+    // abs-max of the rows of A and the columns of B, and Abar = ceil(2^mu' |A|),
+    // Bbar = ceil(|B| 2^nu') into slice 0 of the operand buffers
     {
-      Scope sc(PH_INIT, s);
-      launch_init(s, rowbits, L.mp, colbits, L.np, rmax, cmax, flag);
-    }
-    {
-      Scope sc(PH_ABSMAX_A, s);
-      launch_absmax_rows(s, pr, A, lda, m, k, rowbits, flag);
-    }
-    // Abar = ceil(2^mu' |A|), Bbar = ceil(|B| 2^nu') into slice 0 of the operand buffers.
-    // Up to kAbsBarMaxK the abs-max of B and Bbar come from one read of B.
-    const bool fuse_b = L.kp <= kAbsBarMaxK;
-    if (!fuse_b) {
-      Scope sc(PH_ABSMAX_B, s);
-      launch_absmax_cols(s, pr, B, ldb, k, n, colbits, flag);
-    }
-    {
-      Scope sc(PH_BARS, s);
-      launch_slices(s, pr, SliceSet::Real, true, &oa, fuse_b ? nullptr : &ob, k, L.kp, cc);
-    }
-    if (fuse_b) {
-      Scope sc(PH_BAR_B, s);
-      launch_absbar_cols(s, pr, B, ldb, k, n, L.np, L.kp, colbits, flag, Bs);
+      Scope sc(PH_SCAN, s);
+      launch_scan(s, pr, SliceSet::Real, oa, ob, k, L.kp, flag);
     }
     // Cbar = Abar Bbar; keep row maxima (over j) and column maxima (over i).
     {
@@ -348,7 +329,7 @@ int run_pipeline(Prec pr, int m, int n, int k, const void* A, int lda, const voi
                         at<int>(ws, L.nu_p), at<float>(ws, L.ef));
   {
     Scope sc(PH_RES, s);
-    launch_slices(s, pr, SliceSet::Real, false, &oa, &ob, k, L.kp, cc);
+    launch_slices(s, pr, SliceSet::Real, false, &oa, &ob, k, L.kp, cc, flag);
   }
   {
     Scope sc(PH_GEMM_RES, s);
@@ -519,17 +500,14 @@ int zgemm_impl(Prec pr, int m, int n, int k, const void* A, int lda, const void*
   // Algorithm 2 on the embedding: the row maxima of Ahat's rows i and H + i
   // are both the complex row's maximum over its two parts; a column of Bhat
   // holds both parts of a column of B.
-  launch_init(s, rowbits, L.mp, colbits, L.np, rmax, cmax, flag);
-  launch_absmax_rows(s, pr, A, lda, m, k, rowbits, flag, true, H);
-  launch_absmax_cols(s, pr, B, ldb, k, n, colbits, flag, true);
   const SliceOperand oa{A, lda, m, L.mp, rowbits, rmax, mu, As};
   const SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nu, Bs};
-  launch_slices(s, pr, SliceSet::Embedding, true, &oa, &ob, k, Z.kh, cc);
+  launch_scan(s, pr, SliceSet::Embedding, oa, ob, k, Z.kh, flag);
   launch_gemm_i8(s, 1, As, 0, Bs, 0, L.mp, L.np, L.kp, 1, cc, nullptr, 0, 0, rmax, cmax,
                  at<int8_t>(ws, L.part), L.part_bytes);
   // Algorithm 3 on the embedding, its residues formed from the complex
   // source; the CRT writes rows i (real) and H + i (imaginary) as pairs.
-  launch_slices(s, pr, SliceSet::Embedding, false, &oa, &ob, k, Z.kh, cc);
+  launch_slices(s, pr, SliceSet::Embedding, false, &oa, &ob, k, Z.kh, cc, flag);
   launch_gemm_i8(s, 0, As, (size_t)L.mp * L.kp, Bs, (size_t)L.np * L.kp, L.mp, L.np, L.kp, N, cc,
                  W, (size_t)L.np * L.mp, L.mp, nullptr, nullptr, at<int8_t>(ws, L.part),
                  L.part_bytes);
@@ -591,12 +569,9 @@ int zgemm3m_impl(Prec pr, int m, int n, int k, const void* A, int lda, const voi
   int8_t* W[3] = {at<int8_t>(w, L.W), at<int8_t>(w, L.W) + N * sw, at<int8_t>(w, L.W) + 2 * N * sw};
   // Algorithm 2 on the complex matrices, read in place: abs-max over both
   // parts, and Abar = bar(Ar) + bar(Ai) (Bbar alike) into the third set.
-  launch_init(s, rowbits, L.mp, colbits, L.np, rmax, cmax, flag);
-  launch_absmax_rows(s, pr, A, lda, m, k, rowbits, flag, true);
-  launch_absmax_cols(s, pr, B, ldb, k, n, colbits, flag, true);
   SliceOperand oa{A, lda, m, L.mp, rowbits, rmax, mu, X[2]};
   SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nu, Y[2]};
-  launch_slices(s, pr, SliceSet::Complex3, true, &oa, &ob, k, L.kp, cc);
+  launch_scan(s, pr, SliceSet::Complex3, oa, ob, k, L.kp, flag);
   launch_gemm_i8(s, 1, X[2], 0, Y[2], 0, L.mp, L.np, L.kp, 1, cc, nullptr, 0, 0, rmax, cmax,
                  at<int8_t>(w, L.part), L.part_bytes);
   // Algorithm 3: residues of A'r, A'i and A'r + A'i (and of B) in one pass
@@ -604,7 +579,7 @@ int zgemm3m_impl(Prec pr, int m, int n, int k, const void* A, int lda, const voi
   // and imaginary residues formed from the three W.
   oa.out = X[0];
   ob.out = Y[0];
-  launch_slices(s, pr, SliceSet::Complex3, false, &oa, &ob, k, L.kp, cc, -1);
+  launch_slices(s, pr, SliceSet::Complex3, false, &oa, &ob, k, L.kp, cc, flag, -1);
   for (int q = 0; q < 3; ++q)
     launch_gemm_i8(s, 0, X[q], sa, Y[q], sb, L.mp, L.np, L.kp, N, cc, W[q], sw, L.mp, nullptr,
                    nullptr, at<int8_t>(w, L.part), L.part_bytes);
@@ -651,12 +626,10 @@ namespace {
 // phase, a prefix array of workgroup counts).  The launch sequence is captured
 // once per batch signature into a hipGraph and replayed on later calls.
 // ---------------------------------------------------------------------------
-// BS_ABB: abs-max of B with Bbar in one read (k_pad <= kAbsBarMaxK);
-// BS_ABS_B and BS_BAR_B: the two passes for the other problems; BS_SL_B: the
-// residues of B for every problem.
+// BS_CLEAR, BS_ABS_A, BS_BAR_A: the problems whose scan is chunked.
 enum BatchSlot {
-  BS_INIT, BS_ABS_A, BS_ABS_B, BS_ABB, BS_SL_A, BS_BAR_B, BS_SL_B, BS_GS_BIG, BS_GS_SMALL,
-  BS_GR_BIG, BS_GR_SMALL, BS_CRT, BS_COUNT
+  BS_CLEAR, BS_ABS_A, BS_SCAN, BS_BAR_A, BS_SL_A, BS_SL_B, BS_GS_BIG, BS_GS_SMALL, BS_GR_BIG,
+  BS_GR_SMALL, BS_CRT, BS_COUNT
 };
 constexpr int kMaxBatchEntries = 8;
 
@@ -743,25 +716,32 @@ int get_ctab(int b, CrtConsts** out) {
   return OZAKI2_OK;
 }
 
+// Whether the scan of a batch splits finely (few workgroups in all).
+bool batch_scan_fine(Prec pr, const std::vector<ProbDesc>& D) {
+  int64_t units = 0;
+  for (const ProbDesc& d : D) units += scan_group_blocks(pr, d.mp, d.np, d.k, d.kp, true);
+  return scan_group_fine(units);
+}
+
 // Problem descriptors and per-slot block maps for the active problems, with
 // the tile split `split` (problems with at least `split` 256x256 tiles per
 // product use the 256x256 kernel, the rest 128x128; 0 = all 256x256).
-void build_table(const std::vector<ProbDesc>& D, int split, std::vector<char>* out,
+void build_table(Prec pr, const std::vector<ProbDesc>& D, int split, std::vector<char>* out,
                  int blocks[BS_COUNT], size_t map_off[BS_COUNT]) {
   const int cnt = (int)D.size();
   std::vector<int> c((size_t)BS_COUNT * cnt);
+  const bool fine = batch_scan_fine(pr, D);
   for (int p = 0; p < cnt; ++p) {
     const ProbDesc& d = D[p];
     const bool big = d.mp % 256 == 0 && d.np % 256 == 0 &&
                      (int64_t)(d.mp / 256) * (d.np / 256) >= split;
     int* cp = &c[(size_t)p * BS_COUNT];
-    cp[BS_INIT] = group_init_blocks(d.mp, d.np);
-    cp[BS_ABS_A] = cdiv_i(d.m, 256) * cdiv_i(d.k, 64);
-    const bool fuse_b = d.kp <= kAbsBarMaxK;
-    cp[BS_ABS_B] = fuse_b ? 0 : absmax_cols_blocks(d.n);
-    cp[BS_ABB] = fuse_b ? absbar_group_blocks(d.np, d.kp) : 0;
+    const bool chunked = scan_group_chunked(pr, d.mp, d.k, d.kp, fine);
+    cp[BS_CLEAR] = chunked ? group_clear_blocks(d.mp, d.np) : 0;
+    cp[BS_ABS_A] = chunked ? cdiv_i(d.m, 256) * cdiv_i(d.k, 64) : 0;
+    cp[BS_SCAN] = scan_group_blocks(pr, d.mp, d.np, d.k, d.kp, fine);
     cp[BS_SL_A] = (d.kp / 128) * (d.mp / 32);
-    cp[BS_BAR_B] = fuse_b ? 0 : (d.kp / 128) * (d.np / 32);
+    cp[BS_BAR_A] = chunked ? cp[BS_SL_A] : 0;
     cp[BS_SL_B] = (d.kp / 128) * (d.np / 32);
     cp[BS_GS_BIG] = big ? group_gemm_blocks(d.mp, d.np, 256, 1) : 0;
     cp[BS_GS_SMALL] = big ? 0 : group_gemm_blocks(d.mp, d.np, 128, 1);
@@ -836,11 +816,9 @@ void enqueue_batch(Prec pr, const BatchEntry& e, const CrtConsts* ctab, int* sta
   auto B = [&](int sl) { return e.blocks[sl]; };
   for (int p : e.zero_fill) launch_fill_zero(s, pr, C[p], ldc[p], mnkN[4 * p], mnkN[4 * p + 1]);
   if (e.active == 0) return;
-  launch_group_scale(s, pr, GP_INIT, D, M(BS_INIT), B(BS_INIT));
-  launch_group_scale(s, pr, GP_ABSMAX_A, D, M(BS_ABS_A), B(BS_ABS_A));
-  launch_group_scale(s, pr, GP_ABSMAX_B, D, M(BS_ABS_B), B(BS_ABS_B));
-  launch_group_scale(s, pr, GP_ABSBAR_B, D, M(BS_ABB), B(BS_ABB));
-  launch_group_slices(s, pr, true, -1, D, M(BS_SL_A), B(BS_SL_A), M(BS_BAR_B), B(BS_BAR_B), ctab);
+  launch_group_scan(s, pr, D, M(BS_CLEAR), B(BS_CLEAR), M(BS_ABS_A), B(BS_ABS_A), M(BS_SCAN),
+                    B(BS_SCAN), batch_scan_fine(pr, e.hd));
+  launch_group_slices(s, pr, true, -1, D, M(BS_BAR_A), B(BS_BAR_A), nullptr, 0, ctab);
   if (e.per_problem) {
     for (size_t q = 0; q < e.hd.size(); ++q) {
       const ProbDesc& d = e.hd[q];
@@ -880,7 +858,7 @@ int upload_table(BatchEntry* e, const std::vector<char>& host, hipStream_t s) {
 // operand slices in the workspace are this batch's own residues; the split
 // does not move them (the padding of every problem is fixed).  A forced
 // split or form (forced_split >= 0, forced_persist >= 0) is not tuned.
-int tune_batch(const std::vector<ProbDesc>& D, BatchEntry* e, const CrtConsts* ctab,
+int tune_batch(Prec pr, const std::vector<ProbDesc>& D, BatchEntry* e, const CrtConsts* ctab,
                hipStream_t s, int forced_split, int forced_persist) {
   std::vector<int> splits = forced_split >= 0 ? std::vector<int>{forced_split}
                                               : std::vector<int>{1 << 30, 16, 4, 0};
@@ -902,7 +880,7 @@ int tune_batch(const std::vector<ProbDesc>& D, BatchEntry* e, const CrtConsts* c
   int rc = OZAKI2_OK;
   std::vector<char> host;
   for (size_t c = 0; c < splits.size() && rc == OZAKI2_OK; ++c) {
-    build_table(D, splits[c], &host, e->blocks, e->map_off);
+    build_table(pr, D, splits[c], &host, e->blocks, e->map_off);
     if (!table_fits(e->blocks)) continue;
     if ((rc = upload_table(e, host, s))) break;
     for (int form : forms) {
@@ -1075,13 +1053,13 @@ int batched_impl(Prec pr, int count, const int* mnkN, const void* const* A, cons
     if ((forced < 0 || forced_persist < 0) && e->active > 0) {
       // One eager pass of the whole batch first, so that the tuner times the
       // residue products on this batch's own residues.
-      build_table(D, e->split, &host, e->blocks, e->map_off);
+      build_table(pr, D, e->split, &host, e->blocks, e->map_off);
       if (!table_fits(e->blocks)) return OZAKI2_ERR_INVALID_ARG;
       if ((rc = upload_table(e.get(), host, s))) return rc;
       enqueue_batch(pr, *e, ctab, status, s, C, ldc, mnkN);
-      if ((rc = tune_batch(D, e.get(), ctab, s, forced, forced_persist))) return rc;
+      if ((rc = tune_batch(pr, D, e.get(), ctab, s, forced, forced_persist))) return rc;
     }
-    build_table(D, e->split, &host, e->blocks, e->map_off);
+    build_table(pr, D, e->split, &host, e->blocks, e->map_off);
     if (!table_fits(e->blocks)) return OZAKI2_ERR_INVALID_ARG;
     if ((rc = upload_table(e.get(), host, s))) return rc;
     if (use_graph) {
@@ -1165,7 +1143,6 @@ size_t ozaki2_complex_workspace_bytes(int prec, int m, int n, int k, int N) {
   if ((prec != 64 && prec != 32) || m < 0 || n < 0 || k < 0) return 0;
   if (m > kMaxDim / 2 || n > kMaxDim || k > kMaxK || check_N(N, prec) != OZAKI2_OK) return 0;
   if (m == 0 || n == 0 || k == 0) return 0;
-  const size_t s = prec == 64 ? 8 : 4;
   const size_t t3 = z3layout(m, n, k, N).total;
   if (k > kMaxK / 2) return t3;   // only the 3-product form takes such k
   const size_t t4 = zlayout(m, n, k, N).L.total;
@@ -1286,17 +1263,10 @@ void plan_terms(Prec pr, int m, int n, int k, const void* A, int lda, const void
   CrtConsts cc;
   std::memset(&cc, 0, sizeof(cc));
   Scope sc(PH_PLAN, s);
-  launch_init(s, rowbits, L.mp, colbits, L.np, rmax, cmax, flag);
-  launch_absmax_rows(s, pr, A, lda, m, k, rowbits, flag);
   // Cbar maxima exactly as the emulation computes them (Algorithm 2)
-  const bool fuse_b = L.kp <= kAbsBarMaxK;
-  if (fuse_b)
-    launch_absbar_cols(s, pr, B, ldb, k, n, L.np, L.kp, colbits, flag, at<int8_t>(ws, L.Bbar));
-  else
-    launch_absmax_cols(s, pr, B, ldb, k, n, colbits, flag);
-  const SliceOperand oa{A, lda, m, L.mp, rowbits, nullptr, nullptr, at<int8_t>(ws, L.Abar)};
-  const SliceOperand ob{B, ldb, n, L.np, colbits, nullptr, nullptr, at<int8_t>(ws, L.Bbar)};
-  launch_slices(s, pr, SliceSet::Real, true, &oa, fuse_b ? nullptr : &ob, k, L.kp, cc);
+  const SliceOperand oa{A, lda, m, L.mp, rowbits, rmax, nullptr, at<int8_t>(ws, L.Abar)};
+  const SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nullptr, at<int8_t>(ws, L.Bbar)};
+  launch_scan(s, pr, SliceSet::Real, oa, ob, k, L.kp, flag);
   // and one byte per entry, Cbar_ij != 0, which holds exactly when
   // (|A||B|)_ij > 0 (Abar, Bbar are >= 1 wherever A, B are nonzero): an
   // entry whose lower bound of S below underflows to 0 is then known to be
@@ -1305,9 +1275,9 @@ void plan_terms(Prec pr, int m, int n, int k, const void* A, int lda, const void
                  cc, at<int8_t>(ws, L.mask), 0, L.mp, rmax, cmax);
   // scaled |A|, |B| as BF16 lower bounds, with upward row / column sums
   launch_plan_slices(s, pr, true, A, lda, m, k, L.mp, L.kp, rowbits, at<uint16_t>(ws, L.Abf),
-                     at<double>(ws, L.pr));
+                     at<double>(ws, L.pr), flag);
   launch_plan_slices(s, pr, false, B, ldb, n, k, L.np, L.kp, colbits, at<uint16_t>(ws, L.Bbf),
-                     at<double>(ws, L.pc));
+                     at<double>(ws, L.pc), flag);
   launch_plan_vectors(s, at<double>(ws, L.pr), L.mp, at<double>(ws, L.pc), L.np, L.kp / 64, rmax,
                       cmax, m, n, at<double>(ws, L.rs), at<double>(ws, L.cs), at<double>(ws, L.sr),
                       at<double>(ws, L.sc));

@@ -10,7 +10,7 @@
 // sticky status word (zero when the code object is loaded, cleared by
 // ozaki2_sync_status after it reports); the workspace follows.  Every
 // per-call field of the workspace (abs-max bit patterns, maxima of Cbar,
-// the non-finite flag) is set by the call's own init kernel, so nothing
+// the non-finite flag) is set by the call's own kernels, so nothing
 // else needs clearing between calls.
 #include <hip/hip_runtime.h>
 

@@ -107,6 +107,11 @@ __device__ inline int shift_prime_bits(uint64_t bits) {
   return 5 - fl;
 }
 
+// The bit pattern of an infinity or a NaN.
+__device__ __forceinline__ bool nonfinite_bits(uint64_t bits) {
+  return (bits >> 52 & 0x7FF) == 0x7FF;
+}
+
 // mu (nu) of Algorithm 2 from a row's abs-max bit pattern and its maximum M of
 // Cbar; bias is added to mu' of nonzero rows.  A zero maximum counts as 1 (R7).
 // The table of steps stands for the log2f and the floor (24 integer
@@ -146,29 +151,22 @@ struct ProbDesc {
 // Block map entry: x = problem index, y = local workgroup index.
 typedef int2 BlockRef;
 
-enum GroupPhase {
-  GP_INIT, GP_ABSMAX_A, GP_ABSMAX_B, GP_ABSBAR_B, GP_SLICE_A, GP_SLICE_B, GP_GEMM_SCALE,
-  GP_GEMM_RES, GP_CRT, GP_COUNT
-};
-
 __host__ __device__ inline int cdiv_i(int a, int b) { return (a + b - 1) / b; }
 
-// Workgroups of one problem in the grouped init phase (a grid-stride loop over
+// Workgroups of one problem in the grouped clearing (a grid-stride loop over
 // max(mp, np) entries) and in a grouped product with `tile` x `tile` output
 // tiles and nz slices (padded to a multiple of 8 so that every problem starts
 // on XCD 0).
-__host__ __device__ inline int group_init_blocks(int mp, int np) {
+__host__ __device__ inline int group_clear_blocks(int mp, int np) {
   return cdiv_i(mp > np ? mp : np, 256);
 }
 __host__ __device__ inline int group_gemm_blocks(int mp, int np, int tile, int nz) {
   return ((mp / tile) * (np / tile) * nz + 7) / 8 * 8;
 }
-// Workgroups of the CRT (one thread per kCrtRows rows of one column) and of
-// the column abs-max (one wave per column, four per workgroup).
+// Workgroups of the CRT (one thread per kCrtRows rows of one column).
 __host__ __device__ inline int64_t crt_blocks(int m, int n) {
   return ((int64_t)cdiv_i(m, kCrtRows) * n + 255) / 256;
 }
-__host__ __device__ inline int absmax_cols_blocks(int n) { return cdiv_i(n, 4); }
 
 // ---------------------------------------------------------------------------
 // Kernel launchers (each defined next to its kernel)
@@ -176,22 +174,6 @@ __host__ __device__ inline int absmax_cols_blocks(int n) { return cdiv_i(n, 4); 
 enum class Prec { F64, F32 };
 
 // scale.hip
-void launch_init(hipStream_t s, uint64_t* rowbits, int m_pad, uint64_t* colbits, int n_pad,
-                 int* rmax, int* cmax, int* flag);
-// cx: the matrix holds interleaved (re, im) pairs (leading dimension in
-// complex elements) and each maximum runs over both parts.  dup > 0: row i's
-// maximum also goes to row i + dup.
-void launch_absmax_rows(hipStream_t s, Prec pr, const void* A, int lda, int m, int k,
-                        uint64_t* rowbits, int* flag, bool cx = false, int dup = 0);
-void launch_absmax_cols(hipStream_t s, Prec pr, const void* B, int ldb, int k, int n,
-                        uint64_t* colbits, int* flag, bool cx = false);
-// Abs-max of the columns of B and Bbar (slice 0, K-major [n_pad][k_pad]) in
-// one read of B; for k_pad <= kAbsBarMaxK.
-constexpr int kAbsBarMaxK = 8192;
-constexpr int kAbsBarWaveK = 2048;   // up to here one wave per column, else a workgroup
-int absbar_group_blocks(int n_pad, int k_pad);
-void launch_absbar_cols(hipStream_t s, Prec pr, const void* B, int ldb, int k, int n, int n_pad,
-                        int k_pad, uint64_t* colbits, int* flag, int8_t* out);
 // mu', nu' and the log2f values e (rows) then f (columns) for the stage dumps.
 void launch_debug_shifts(hipStream_t s, const uint64_t* rowbits, const int* rmax, int m,
                          const uint64_t* colbits, const int* cmax, int n, int* mu_p, int* nu_p,
@@ -235,19 +217,37 @@ enum class SliceSet { Real, Complex3, Embedding };
 struct SliceOperand {
   const void* src;
   int ld, rows, rows_pad;
-  const uint64_t* bits;
-  const int* mx;
+  uint64_t* bits;
+  int* mx;
   int* shift;
   int8_t* out;
 };
+// A non-finite entry (its row's bit pattern) sets *flag in the residue launch.
 void launch_slices(hipStream_t s, Prec pr, SliceSet set, bool bars, const SliceOperand* A,
-                   const SliceOperand* B, int k, int k_pad, const CrtConsts& cc, int bias = 0);
+                   const SliceOperand* B, int k, int k_pad, const CrtConsts& cc, int* flag,
+                   int bias = 0);
+
+// scale.hip: the abs-max bit patterns `bits` of the rows of A and the columns of
+// B (over both parts of pairs) and their bars (`out`, as above), with the
+// maxima of Cbar (both `mx`) and *flag cleared.
+void launch_scan(hipStream_t s, Prec pr, SliceSet set, const SliceOperand& A, const SliceOperand& B,
+                 int k, int k_pad, int* flag);
+// A batch's scan: cleared rows and abs-max of A (kg_clear, kg_absmax_rows) for
+// the problems whose scan is chunked (their bars of A are then a slice launch),
+// and the scan itself.
+// fine: the whole batch's finest split has few workgroups (scan_group_fine).
+bool scan_group_fine(int64_t units);
+bool scan_group_chunked(Prec pr, int m_pad, int k, int k_pad, bool fine);
+int scan_group_blocks(Prec pr, int m_pad, int n_pad, int k, int k_pad, bool fine);
+void launch_group_scan(hipStream_t s, Prec pr, const ProbDesc* P, const BlockRef* clear_map,
+                       int clear_blocks, const BlockRef* abs_map, int abs_blocks,
+                       const BlockRef* scan_map, int scan_blocks, bool fine);
 
 // Planner operands (BF16, K-major [rows_pad][k_pad]) and per-64-k-tile row
-// sums partial[k_pad/64][rows_pad] of |x| 2^-alpha.
+// sums partial[k_pad/64][rows_pad] of |x| 2^-alpha; a non-finite row sets *flag.
 void launch_plan_slices(hipStream_t s, Prec pr, bool trans, const void* src, int ld, int rows,
                         int k, int rows_pad, int k_pad, const uint64_t* bits, uint16_t* out,
-                        double* partial);
+                        double* partial, int* flag);
 
 // gemm_i8.hip
 //   D[x][y] = sum_h X[x][h] * Y[y][h] over k_pad, for slices z = 0..nz-1 with
@@ -296,8 +296,6 @@ void launch_certify(hipStream_t s, Prec pr, const void* C, int ldc, const int* m
 
 // Grouped launches (one per phase for a whole batch of `count` problems);
 // `map` holds `blocks` entries, one per workgroup.
-void launch_group_scale(hipStream_t s, Prec pr, int phase, const ProbDesc* P, const BlockRef* map,
-                        int blocks);
 // The residue path every problem of a batch shares (a code for
 // launch_group_slices), or the per-tile choice when they differ.
 int group_residue_path(const CrtConsts* const* cc, int count);

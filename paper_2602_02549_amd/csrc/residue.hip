@@ -293,6 +293,18 @@ struct SliceArgs {
   int k, k_pad;           // k_pad: padded k (the embedding: of one k half)
   int half;               // the embedding: rows of one row half on the A side
   int bias;               // added to mu' and nu' of nonzero rows (mode 1)
+  int* flag;              // set by a non-finite row (mode 1)
+};
+
+// The shift of a row, stored once for the CRT, and the non-finite flag.
+struct RowResult {
+  int sh;
+  bool bad;
+  __device__ __forceinline__ void store(int* __restrict__ shift, int rg,
+                                        int* __restrict__ flag) const {
+    shift[rg] = sh;
+    if (bad) *flag = 1;
+  }
 };
 
 // Shift of the thread's output row rg (clamped): mu' from the abs-max bit
@@ -309,9 +321,9 @@ struct RowShift {
     bits = b[rg];
     mx = MODE == 1 ? m[rg] : 0;
   }
-  __device__ __forceinline__ int get(const CrtConsts& cc, int bias) const {
-    if (MODE == 1) return shift_of(bits, mx, cc, bias);
-    return shift_prime_bits(bits) - (MODE == 2 ? 1 : 0);
+  __device__ __forceinline__ RowResult get(const CrtConsts& cc, int bias) const {
+    if (MODE == 1) return {shift_of(bits, mx, cc, bias), nonfinite_bits(bits)};
+    return {shift_prime_bits(bits) - (MODE == 2 ? 1 : 0), false};
   }
 };
 
@@ -384,9 +396,11 @@ __device__ __forceinline__ void store_residues_path(const double (&v)[16], const
 // Each thread reads 16 consecutive k of one row from the staged tile and
 // writes 16 bytes per slice (mode 0: Abar; mode 1: the N residues).
 template <int MODE, int PATH>
-__device__ __forceinline__ void tile_finish(const double* tile, int sh, int* __restrict__ shift_out,
+__device__ __forceinline__ void tile_finish(const double* tile, RowResult row,
+                                            int* __restrict__ shift_out, int* __restrict__ flag,
                                             int rows, int k_pad, size_t slice, const CrtConsts& cc,
                                             int8_t* __restrict__ out, int r0, int h0) {
+  const int sh = row.sh;
   const int t = threadIdx.x;
   const int r = t >> 3, c = t & 7, rg = r0 + r;
   // element (r, 16c + e): position r*kRS + 16c + 4(e/4) + ((e%4) ^ g)
@@ -415,7 +429,7 @@ __device__ __forceinline__ void tile_finish(const double* tile, int sh, int* __r
     w.w = pack4(b[12], b[13], b[14], b[15]);
     *reinterpret_cast<uint4*>(dst) = w;
   } else if (rg < rows) {
-    if (h0 == 0 && c == 0 && blockIdx.y == 0) shift_out[rg] = sh;
+    if (h0 == 0 && c == 0 && blockIdx.y == 0) row.store(shift_out, rg, flag);
 #pragma unroll
     for (int e = 0; e < 16; ++e) v[e] = trunc(ldexp(v[e], sh));
     store_residues_path<PATH>(v, cc, dst, slice);
@@ -462,7 +476,7 @@ __device__ __forceinline__ void walk_real(const SliceArgs& a, const SliceSide& s
     lds_barrier();                 // every wave is done with the previous tile
     tile_stage<T, TRANS>(x, s.rows, a.k, r0, h0, tile);
     __asm__ volatile("" ::: "memory");  // x is free: the next loads reuse its registers
-    const int sh = rs.get(cc, a.bias);
+    const RowResult rr = rs.get(cc, a.bias);
     const int ni = i + s.blocks;
     if (ni < s.tiles) {
       slice_tile<TRANS>(ni, a.k_pad, s.gy, &kx, &ry);
@@ -470,7 +484,7 @@ __device__ __forceinline__ void walk_real(const SliceArgs& a, const SliceSide& s
       rs.load(s.bits, s.mx, s.rows, ry * kTR + row);
     }
     lds_barrier();                 // the tile is staged
-    tile_finish<MODE, PATH>(tile, sh, s.shift, s.rows, a.k_pad, s.slice, cc, s.out, r0, h0);
+    tile_finish<MODE, PATH>(tile, rr, s.shift, a.flag, s.rows, a.k_pad, s.slice, cc, s.out, r0, h0);
     if (ni >= s.tiles) break;
     i = ni;
   }
@@ -514,11 +528,12 @@ __device__ __forceinline__ void tile_row16(const double* tile, double (&v)[16]) 
 }
 
 template <int MODE, int PATH>
-__device__ __forceinline__ void tile_finish_cx(double (&vr)[16], double (&vi)[16], int sh,
-                                               int* __restrict__ shift_out, int rows, int k_pad,
-                                               size_t slice,
+__device__ __forceinline__ void tile_finish_cx(double (&vr)[16], double (&vi)[16], RowResult row,
+                                               int* __restrict__ shift_out, int* __restrict__ flag,
+                                               int rows, int k_pad, size_t slice,
                                                const CrtConsts& cc, int8_t* __restrict__ out,
                                                int r0, int h0) {
+  const int sh = row.sh;
   const int t = threadIdx.x;
   const int rg = r0 + (t >> 3);
   int8_t* dst = out + (size_t)rg * k_pad + h0 + 16 * (t & 7);
@@ -536,7 +551,7 @@ __device__ __forceinline__ void tile_finish_cx(double (&vr)[16], double (&vi)[16
     *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
   } else {
     if (rg >= rows) return;
-    if (h0 == 0 && (t & 7) == 0 && blockIdx.y == 0) shift_out[rg] = sh;
+    if (h0 == 0 && (t & 7) == 0 && blockIdx.y == 0) row.store(shift_out, rg, flag);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       vr[e] = trunc(ldexp(vr[e], sh));
@@ -620,7 +635,7 @@ __device__ __forceinline__ void walk_cx(const SliceArgs& a, const SliceSide& s, 
     lds_barrier();
     tile_stage<T, TRANS>(y, s.rows, a.k, r0, h0, tile);
     __asm__ volatile("" ::: "memory");  // x, y are free: the next loads reuse their registers
-    const int sh = rs.get(cc, a.bias);
+    const RowResult rr = rs.get(cc, a.bias);
     const int ni = i + s.blocks;
     if (ni < s.tiles) {
       slice_tile<TRANS>(ni, a.k_pad, s.gy, &kx, &ry);
@@ -629,7 +644,8 @@ __device__ __forceinline__ void walk_cx(const SliceArgs& a, const SliceSide& s, 
     }
     lds_barrier();
     tile_row16(tile, vi);
-    tile_finish_cx<MODE, PATH>(vr, vi, sh, s.shift, s.rows, a.k_pad, s.slice, cc, s.out, r0, h0);
+    tile_finish_cx<MODE, PATH>(vr, vi, rr, s.shift, a.flag, s.rows, a.k_pad, s.slice, cc, s.out, r0,
+                               h0);
     if (ni >= s.tiles) break;
     i = ni;
   }
@@ -682,7 +698,8 @@ __device__ __forceinline__ void tile_finish_emb(const double (&vr)[16], const do
     for (int blk = 0; blk < (ASIDE ? 2 : 1); ++blk) {
       const int ro = rg + blk * half;
       const int e2 = shift_of(s.bits[ro], s.mx[ro], cc, a.bias);
-      if (h0 == 0 && (t & 7) == 0 && blockIdx.y == 0) s.shift[ro] = e2;
+      if (h0 == 0 && (t & 7) == 0 && blockIdx.y == 0)
+        RowResult{e2, nonfinite_bits(s.bits[ro])}.store(s.shift, ro, a.flag);
       double xr[16], xi[16];
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
@@ -765,6 +782,7 @@ struct TileJob {
   const uint64_t* bits;
   const int* mx;
   int* shift;
+  int* flag;
   int8_t* out;
   size_t slice;
   int ld, rows, k, k_pad, r0, h0, N;
@@ -786,6 +804,7 @@ __device__ __forceinline__ bool tile_job(const ProbDesc* __restrict__ P,
   j->bits = ASIDE ? d.rowbits : d.colbits;
   j->mx = ASIDE ? d.rmax : d.cmax;
   j->shift = ASIDE ? d.mu : d.nu;
+  j->flag = d.flag;
   j->out = ASIDE ? d.As : d.Bs;
   j->slice = (size_t)rows_pad * d.kp;
   j->ld = ASIDE ? d.lda : d.ldb;
@@ -815,7 +834,7 @@ __device__ __forceinline__ void walk_group(const ProbDesc* __restrict__ P,
     lds_barrier();
     tile_stage<T, ASIDE>(x, cur.rows, cur.k, cur.r0, cur.h0, tile);
     __asm__ volatile("" ::: "memory");
-    const int sh = rs.get(ctab[cur.N], 0);
+    const RowResult rr = rs.get(ctab[cur.N], 0);
     TileJob nxt;
     int ni = i + G;
     while (ni < tiles && !tile_job<ASIDE, MODE>(P, map, ni, &nxt)) ni += G;
@@ -825,8 +844,8 @@ __device__ __forceinline__ void walk_group(const ProbDesc* __restrict__ P,
       rs.load(nxt.bits, nxt.mx, nxt.rows, nxt.r0 + row);
     }
     lds_barrier();
-    tile_finish<MODE, PATH>(tile, sh, cur.shift, cur.rows, cur.k_pad, cur.slice, ctab[cur.N],
-                            cur.out, cur.r0, cur.h0);
+    tile_finish<MODE, PATH>(tile, rr, cur.shift, cur.flag, cur.rows, cur.k_pad, cur.slice,
+                            ctab[cur.N], cur.out, cur.r0, cur.h0);
     if (ni >= tiles) break;
     i = ni;
     cur = nxt;
@@ -860,7 +879,8 @@ __global__ __launch_bounds__(256) void k_plan_slices(const T* __restrict__ src, 
                                                      int k, int k_pad, int rows_pad,
                                                      const uint64_t* __restrict__ bits,
                                                      uint16_t* __restrict__ out,
-                                                     double* __restrict__ partial) {
+                                                     double* __restrict__ partial,
+                                                     int* __restrict__ flag) {
   __shared__ double tile[kPlanTile][kPlanTile + 1];
   const int t = threadIdx.x;
   const int tk = k_pad / kPlanTile;
@@ -914,7 +934,10 @@ __global__ __launch_bounds__(256) void k_plan_slices(const T* __restrict__ src, 
     dst[1] = make_uint4(packed[4], packed[5], packed[6], packed[7]);
     sum += __shfl_xor(sum, 1);
     sum += __shfl_xor(sum, 2);
-    if ((t & 3) == 0) partial[(size_t)(cur % tk) * rows_pad + rg] = sum;
+    if ((t & 3) == 0) {
+      partial[(size_t)(cur % tk) * rows_pad + rg] = sum;
+      if (h0 == 0 && rg < rows && nonfinite_bits(bits[rg])) *flag = 1;
+    }
     if (id >= ntiles) break;
   }
 }
@@ -1098,7 +1121,7 @@ void launch_group_slices(hipStream_t s, Prec pr, bool bars, int path, const Prob
 
 void launch_plan_slices(hipStream_t s, Prec pr, bool trans, const void* src, int ld, int rows,
                         int k, int rows_pad, int k_pad, const uint64_t* bits, uint16_t* out,
-                        double* partial) {
+                        double* partial, int* flag) {
   // Four workgroups per CU (33 KB of LDS each) walk the tiles.
   const int64_t tiles = (int64_t)(k_pad / kPlanTile) * (rows_pad / kPlanTile);
   int dev = 0, cus = 0;
@@ -1110,23 +1133,25 @@ void launch_plan_slices(hipStream_t s, Prec pr, bool trans, const void* src, int
   if (pr == Prec::F64) {
     if (trans)
       hipLaunchKernelGGL((k_plan_slices<double, true>), grid, dim3(256), 0, s, (const double*)src,
-                         ld, rows, k, k_pad, rows_pad, bits, out, partial);
+                         ld, rows, k, k_pad, rows_pad, bits, out, partial, flag);
     else
       hipLaunchKernelGGL((k_plan_slices<double, false>), grid, dim3(256), 0, s, (const double*)src,
-                         ld, rows, k, k_pad, rows_pad, bits, out, partial);
+                         ld, rows, k, k_pad, rows_pad, bits, out, partial, flag);
   } else {
     if (trans)
       hipLaunchKernelGGL((k_plan_slices<float, true>), grid, dim3(256), 0, s, (const float*)src, ld,
-                         rows, k, k_pad, rows_pad, bits, out, partial);
+                         rows, k, k_pad, rows_pad, bits, out, partial, flag);
     else
       hipLaunchKernelGGL((k_plan_slices<float, false>), grid, dim3(256), 0, s, (const float*)src, ld,
-                         rows, k, k_pad, rows_pad, bits, out, partial);
+                         rows, k, k_pad, rows_pad, bits, out, partial, flag);
   }
 }
 
 void launch_slices(hipStream_t s, Prec pr, SliceSet set, bool bars, const SliceOperand* A,
-                   const SliceOperand* B, int k, int k_pad, const CrtConsts& cc, int bias) {
+                   const SliceOperand* B, int k, int k_pad, const CrtConsts& cc, int* flag,
+                   int bias) {
   SliceArgs a{};
+  a.flag = flag;
   a.k = k;
   a.k_pad = k_pad;
   a.bias = bias;

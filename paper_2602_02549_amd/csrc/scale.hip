@@ -1,7 +1,8 @@
 // Scaling-vector kernels of Algorithm 2 (Section 3.2):
 //   - per-row / per-column maximum of |a| (kept as the IEEE bit pattern of
 //     the FP64 value, whose unsigned order equals the numeric order), from
-//     which mu' = 5 - floor(log2 max|a|) follows exactly;
+//     which mu' = 5 - floor(log2 max|a|) follows exactly, and the bars that mu'
+//     scales;
 //   - log2f, correctly rounded to FP32 (double-double series evaluation), for
 //     the stage dumps and the exhaustive check; the final shifts mu = mu' +
 //     floor(fma_down(c, e, P')), e = log2f(single_up(max_j Cbar_ij)), come from
@@ -13,47 +14,329 @@
 namespace oz2 {
 namespace {
 
-constexpr uint64_t kExpMask = 0x7FF0000000000000ull;
+// ---------------------------------------------------------------------------
+// The scan: abs-max bit patterns and bars of both operands of Algorithm 2,
+//   bits_i = max_h |a_ih|,  Abar = ceil(2^mu' |A|)  (and of B's columns),
+// with the maxima of Cbar and the non-finite flag cleared for the kernels that
+// follow, in one launch.  HBM bound; what it saves is the second read of A
+// (from HBM to the workgroup's registers, to L2 or to the MALL) and launches.
+//   A (column-major): a workgroup takes a strip of rows over all of k, 16
+//     consecutive k of one row per thread: 128 bytes of each column for k >= 512,
+//     more rows for a shorter k, so that every thread has work.  It reduces the
+//     rows' maxima, keeps its first chunks of k in registers and reads the
+//     others again, latest first, for the bars, whose 16 bytes per thread go
+//     through LDS so that rows are written in whole lines.
+//   B (k contiguous): 4 to 64 lanes (up to kColWaveK) or a workgroup take a
+//     column, 4 consecutive k per thread, up to 32 elements per thread kept in
+//     registers and the others read again.
+// The launch rate of waves, about one a nanosecond, bounds batches of small
+// problems: a wave per column and 16-row strips took 406 us on 2048 problems
+// of 128^3.
+// A strip reads all of k by itself, so few strips over a long k would leave the
+// GPU idle: see strips_fit.  There A's maxima run over chunks of 64 columns with
+// atomics (k_absmax_rows) and its bars in the slice kernel.
+constexpr int kScanThreads = 512;
+constexpr int kColWaveK = 2048;
 
-__device__ __forceinline__ void init_body(uint64_t* rowbits, int m_pad, uint64_t* colbits, int n_pad,
-                                 int* rmax, int* cmax, int* flag, int t, int stride) {
-  for (int i = t; i < m_pad; i += stride) {
-    rowbits[i] = 0;
-    rmax[i] = 0;
-  }
-  for (int j = t; j < n_pad; j += stride) {
-    colbits[j] = 0;
-    cmax[j] = 0;
-  }
-  if (t == 0) *flag = 0;
+// Rows of a strip for k_pad as a power of two: 16 k per thread over 512 threads,
+// at least 128 bytes of a column, at most a wave of rows.  `fine` (a launch of
+// few workgroups, which waits for latency and not for the launch rate): the
+// fewest rows, and a wave per column below.
+template <typename T>
+constexpr int kMinStripLog2 = sizeof(T) == 8 ? 4 : 5;
+template <typename T>
+__host__ __device__ inline int strip_rows_log2(int k_pad, bool fine) {
+  int lr = fine ? kMinStripLog2<T> : 6;
+  while (lr > kMinStripLog2<T> && (kScanThreads >> lr) * 16 < k_pad) --lr;
+  return lr;
 }
-
-__global__ void k_init(uint64_t* rowbits, int m_pad, uint64_t* colbits, int n_pad, int* rmax,
-                       int* cmax, int* flag) {
-  init_body(rowbits, m_pad, colbits, n_pad, rmax, cmax, flag, blockIdx.x * blockDim.x + threadIdx.x,
-            gridDim.x * blockDim.x);
+// Threads per column for k_pad: the fewest that keep it in registers (keep
+// elements a thread), a wave up to kColWaveK, else a workgroup.
+__host__ __device__ inline int col_threads(int k_pad, int keep, bool fine) {
+  if (k_pad > kColWaveK) return kScanThreads;
+  int tpc = fine ? 64 : 4;
+  while (tpc < 64 && tpc * keep < k_pad) tpc *= 2;
+  return tpc;
 }
+// Whether `units` workgroups of the finest split are few.
+__host__ __device__ inline bool scan_fine(int64_t units) { return units <= 512; }
+template <SliceSet F>
+constexpr int kColKeep = F == SliceSet::Real ? 32 : 16;   // elements (pairs) a thread
 
-// Bit pattern of |x| as FP64 (unsigned order = numeric order).
+// One operand of the scan (real, or interleaved pairs for the complex forms).
+struct ScanSide {
+  const void* src;
+  uint64_t* bits;
+  int* mx;
+  int8_t* out;
+  int ld, rows, rows_pad;
+  int units;       // workgroups
+};
+struct ScanArgs {
+  ScanSide a, b;
+  int* flag;
+  int k, k_pad;    // k_pad: padded k (the embedding: of one k half)
+  int half;        // the embedding: rows of one row half of A
+  int lr;          // log2 of the rows of a strip
+  int tpc;         // threads per column
+  int chunked;     // A's units are (256 rows x 64 columns) pairs of abs-max only
+  int clear;       // clear the maxima and the flag
+};
+
 template <typename T>
 __device__ __forceinline__ uint64_t abs_bits(T x) {
   return (uint64_t)__double_as_longlong(fabs((double)x));
 }
+__device__ __forceinline__ uint64_t max64(uint64_t a, uint64_t b) { return a > b ? a : b; }
 
-// A column-major (m x k): one thread per row, a workgroup covers 256 rows and
-// a chunk of 64 columns (workgroup bx + gx * by); consecutive threads read
-// consecutive rows.  Loads go out 16 at a time from clamped (always valid)
-// addresses; a repeated element does not change a maximum.  CX: A holds
-// interleaved (re, im) pairs (lda in complex elements) and the maximum runs
-// over both parts (the complex 3-product form's shared row shift).
-template <typename T, bool CX = false>
+// Bar byte of Algorithm 2: ceil(2^sh |x|), 1 for a tiny nonzero x, 0 for 0.
+__device__ __forceinline__ int bar_of(double x, int sh) {
+  const double a = fabs(x), cl = ceil(ldexp(a, sh));
+  return a == 0.0 ? 0 : (cl < 1.0 ? 1 : (int)cl);
+}
+
+// The bars of one element in the form's slices: real b0; the 3-product form
+// b0 = bar(re) + bar(im); the embedding b0 = bar(re), b1 = bar(im).
+template <typename T, SliceSet F>
+__device__ __forceinline__ void bars_of(T re, T im, int sh, int* b0, int* b1) {
+  *b0 = bar_of((double)re, sh);
+  if constexpr (F != SliceSet::Real) {
+    const int i = bar_of((double)im, sh);
+    if constexpr (F == SliceSet::Complex3) *b0 += i;
+    *b1 = i;
+  }
+}
+
+__device__ __forceinline__ void scan_clear(int* mx_a, int na, int* mx_b, int nb, int* flag, int t,
+                                           int stride) {
+  for (int i = t; i < na; i += stride) mx_a[i] = 0;
+  for (int j = t; j < nb; j += stride) mx_b[j] = 0;
+  if (t == 0) *flag = 0;
+}
+
+// LDS of a strip: maxima per wave and row, and the bars of one chunk (two for
+// the embedding), 16 bytes of padding per row.
+template <SliceSet F>
+struct StripLds {
+  unsigned long long red[kScanThreads / 64][64];
+  int8_t bars[F == SliceSet::Embedding ? 2 : 1][16 * kScanThreads + 16 * 64];
+};
+
+// Strip `u` of A, 2^lr rows.
+template <typename T, SliceSet F>
+__device__ __forceinline__ void scan_strip(const T* __restrict__ src, int ld, int rows, int k,
+                                           int k_pad, int half, uint64_t* __restrict__ bits,
+                                           int8_t* __restrict__ out, int u, int lr,
+                                           StripLds<F>& lds) {
+  constexpr int E = F == SliceSet::Real ? 1 : 2;
+  constexpr bool kEmb = F == SliceSet::Embedding;
+  constexpr int KEEP = E == 1 ? 2 : 1;                   // chunks kept in registers
+  const int R = 1 << lr, lg = 9 - lr, KG = 1 << lg;      // rows, threads per row
+  const int CH = 16 << lg, row_bytes = CH + 16;          // k per pass
+  static_assert(kScanThreads == 1 << 9, "threads");
+  const int t = threadIdx.x, row = t & (R - 1), kg = t >> lr;
+  const int r0 = u * R, rg = r0 + row;
+  const bool in = rg < rows;
+  const int ldo = kEmb ? 2 * k_pad : k_pad;
+  const T* a = src + (size_t)E * min(rg, rows - 1);
+  const int nch = (k_pad + CH - 1) / CH;
+  // 16 loads before any use; clamped to the matrix (a repeated element of the
+  // row does not change its maximum)
+  auto load = [&](int c, T (&x)[16], T (&y)[16]) {
+    const int h = c * CH + 16 * kg;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const T* p = a + (size_t)E * ((size_t)min(h + e, k - 1) * ld);
+      x[e] = p[0];
+      y[e] = E == 2 ? p[E - 1] : (T)0;
+    }
+  };
+  uint64_t mx = 0;
+  auto take = [&](const T (&x)[16], const T (&y)[16]) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      mx = max64(mx, abs_bits(x[e]));
+      if (E == 2) mx = max64(mx, abs_bits(y[e]));
+    }
+  };
+  T kx[KEEP][16], ky[KEEP][16];
+  const bool some = r0 < rows;                           // uniform: any real row
+  if (some) {
+#pragma unroll
+    for (int c = 0; c < KEEP; ++c)
+      if (c < nch) load(c, kx[c], ky[c]);
+#pragma unroll
+    for (int c = 0; c < KEEP; ++c)
+      if (c < nch) take(kx[c], ky[c]);
+    for (int c = KEEP; c < nch; ++c) {
+      T x[16], y[16];
+      load(c, x, y);
+      take(x, y);
+    }
+  }
+  for (int off = R; off < 64; off <<= 1) mx = max64(mx, __shfl_xor((unsigned long long)mx, off));
+  if ((t & 63) < R) lds.red[t >> 6][row] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kScanThreads / 64; ++w) mx = max64(mx, lds.red[w][row]);
+  if (in && kg == 0) {
+    bits[rg] = mx;
+    if (kEmb) bits[half + rg] = mx;                      // both row blocks of the embedding
+  }
+  const int sh = shift_prime_bits(mx) - (F == SliceSet::Complex3 ? 1 : 0);
+  auto put = [&](int c, const T (&x)[16], const T (&y)[16]) {
+    const int h = c * CH + 16 * kg;
+    uint32_t w0[4] = {0, 0, 0, 0}, w1[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      int b0 = 0, b1 = 0;
+      bars_of<T, F>(x[e], y[e], sh, &b0, &b1);
+      const bool ok = in && h + e < k;
+      w0[e >> 2] |= (ok ? (uint32_t)b0 & 0xFF : 0u) << (8 * (e & 3));
+      if (kEmb) w1[e >> 2] |= (ok ? (uint32_t)b1 & 0xFF : 0u) << (8 * (e & 3));
+    }
+    int8_t* const q = &lds.bars[0][row * row_bytes + 16 * kg];
+    *reinterpret_cast<uint4*>(q) = make_uint4(w0[0], w0[1], w0[2], w0[3]);
+    if (kEmb)
+      *reinterpret_cast<uint4*>(q + sizeof(lds.bars[0])) = make_uint4(w1[0], w1[1], w1[2], w1[3]);
+    __syncthreads();
+    // 16 bytes of row r, rows in whole lines
+    const int r = t >> lg, ho = c * CH + 16 * (t & (KG - 1));
+    if (ho < k_pad) {
+      const int8_t* p = &lds.bars[0][r * row_bytes + 16 * (t & (KG - 1))];
+      const uint4 v = *reinterpret_cast<const uint4*>(p);
+      int8_t* d = out + (size_t)(r0 + r) * ldo + ho;
+      *reinterpret_cast<uint4*>(d) = v;
+      if (kEmb) {
+        const uint4 v1 = *reinterpret_cast<const uint4*>(p + sizeof(lds.bars[0]));
+        int8_t* d2 = d + (size_t)half * ldo;             // the row of the lower block
+        *reinterpret_cast<uint4*>(d + k_pad) = v1;
+        *reinterpret_cast<uint4*>(d2) = v1;
+        *reinterpret_cast<uint4*>(d2 + k_pad) = v;
+      }
+    }
+    __syncthreads();
+  };
+  for (int c = nch - 1; c >= KEEP; --c) {
+    T x[16], y[16];
+    if (some) load(c, x, y);
+    put(c, x, y);
+  }
+#pragma unroll
+  for (int c = KEEP - 1; c >= 0; --c)
+    if (c < nch) put(c, kx[c], ky[c]);
+}
+
+// Workgroup `u` of B's columns.
+template <typename T, SliceSet F>
+__device__ __forceinline__ void scan_cols(const T* __restrict__ src, int ld, int n, int n_pad,
+                                          int k, int k_pad, uint64_t* __restrict__ bits,
+                                          int8_t* __restrict__ out, int u, int tpc,
+                                          unsigned long long* __restrict__ red) {
+  constexpr int E = F == SliceSet::Real ? 1 : 2;
+  constexpr bool kEmb = F == SliceSet::Embedding;
+  constexpr int KEEP = kColKeep<F> / 4;                  // quads kept in registers
+  const int t = (int)threadIdx.x & (tpc - 1);
+  const int j = u * (kScanThreads / tpc) + (int)threadIdx.x / tpc;
+  const bool in = j < n;                                 // j < n_pad: whole units
+  const T* col = src + (size_t)E * ((size_t)min(j, n - 1) * ld);
+  const int ldo = kEmb ? 2 * k_pad : k_pad;
+  const int span = 4 * tpc, nq = (k_pad + span - 1) / span;
+  auto load = [&](int q, T (&x)[4], T (&y)[4]) {
+    const int h = 4 * t + span * q;
+    const T* p = col + (size_t)E * h;
+    if (span * (q + 1) <= k) {                           // uniform: the whole pass is inside
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[e] = p[E * e];
+        y[e] = E == 2 ? p[E * e + E - 1] : (T)0;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const T* c = col + (size_t)E * min(h + e, k - 1);
+        x[e] = c[0];
+        y[e] = E == 2 ? c[E - 1] : (T)0;
+      }
+    }
+  };
+  uint64_t mx = 0;
+  auto take = [&](const T (&x)[4], const T (&y)[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      mx = max64(mx, abs_bits(x[e]));
+      if (E == 2) mx = max64(mx, abs_bits(y[e]));
+    }
+  };
+  T kx[KEEP][4], ky[KEEP][4];
+  if (in) {
+#pragma unroll
+    for (int q = 0; q < KEEP; ++q)
+      if (q < nq) load(q, kx[q], ky[q]);
+#pragma unroll
+    for (int q = 0; q < KEEP; ++q)
+      if (q < nq) take(kx[q], ky[q]);
+    for (int q = KEEP; q < nq; q += 4) {
+      T x[4][4], y[4][4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) load(min(q + v, nq - 1), x[v], y[v]);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) take(x[v], y[v]);
+    }
+  }
+  for (int off = 1; off < min(tpc, 64); off <<= 1)
+    mx = max64(mx, __shfl_xor((unsigned long long)mx, off));
+  if (tpc > 64) {                                        // uniform
+    if ((t & 63) == 0) red[t >> 6] = mx;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kScanThreads / 64; ++w) mx = max64(mx, red[w]);
+  }
+  if (in && t == 0) bits[j] = mx;
+  const int sh = shift_prime_bits(mx) - (F == SliceSet::Complex3 ? 1 : 0);
+  int8_t* dst = out + (size_t)j * ldo;
+  auto put = [&](int q, const T (&x)[4], const T (&y)[4]) {
+    const int h = 4 * t + span * q;
+    if (h >= k_pad) return;
+    uint32_t w0 = 0, w1 = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      int b0 = 0, b1 = 0;
+      bars_of<T, F>(x[e], y[e], sh, &b0, &b1);
+      const bool ok = in && h + e < k;
+      w0 |= (ok ? (uint32_t)b0 & 0xFF : 0u) << (8 * e);
+      if (kEmb) w1 |= (ok ? (uint32_t)b1 & 0xFF : 0u) << (8 * e);
+    }
+    *reinterpret_cast<uint32_t*>(dst + h) = w0;
+    if (kEmb) *reinterpret_cast<uint32_t*>(dst + k_pad + h) = w1;
+  };
+  for (int q = nq - 1; q >= KEEP; q -= 4) {
+    T x[4][4], y[4][4];
+    if (in) {
+#pragma unroll
+      for (int v = 0; v < 4; ++v) load(max(q - v, KEEP), x[v], y[v]);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (q - v >= KEEP) put(q - v, x[v], y[v]);
+  }
+#pragma unroll
+  for (int q = KEEP - 1; q >= 0; --q)
+    if (q < nq) put(q, kx[q], ky[q]);
+}
+
+// Abs-max of 256 rows over 64 columns of the column-major A (atomicMax on bits
+// that a launch before has cleared): pair p of (row block, column block),
+// thread t of 256.  16 loads go out at a time from clamped addresses.
+template <typename T, SliceSet F>
 __device__ __forceinline__ void absmax_rows_body(const T* __restrict__ A, int lda, int m, int k,
-                                        uint64_t* __restrict__ rowbits, int* __restrict__ flag,
-                                        int bx, int by, int dup = 0) {
-  const int i = bx * 256 + threadIdx.x;
-  constexpr int E = CX ? 2 : 1;   // T values per element
+                                                 int half, uint64_t* __restrict__ bits, int p,
+                                                 int t) {
+  constexpr int E = F == SliceSet::Real ? 1 : 2;
+  const int gx = cdiv_i(m, 256);
+  const int i = p % gx * 256 + t, h0 = p / gx * 64;
+  if (h0 >= k) return;
   const T* a = A + (size_t)E * min(i, m - 1);
-  const int h0 = by * 64;
   uint64_t mx = 0;
 #pragma unroll
   for (int q0 = 0; q0 < 64; q0 += 16) {
@@ -62,174 +345,53 @@ __device__ __forceinline__ void absmax_rows_body(const T* __restrict__ A, int ld
     for (int u = 0; u < 16; ++u) {
       const T* e = a + (size_t)E * ((size_t)min(h0 + q0 + u, k - 1) * lda);
       x[u] = e[0];
-      if (CX) y[u] = e[1];
+      y[u] = E == 2 ? e[E - 1] : (T)0;
     }
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
-      uint64_t b = abs_bits(x[u]);
-      if (CX) {
-        const uint64_t c = abs_bits(y[u]);
-        b = c > b ? c : b;
-      }
-      mx = b > mx ? b : mx;
+      mx = max64(mx, abs_bits(x[u]));
+      if (E == 2) mx = max64(mx, abs_bits(y[u]));
     }
   }
-  if (i >= m) return;
-  if ((mx & kExpMask) == kExpMask) atomicOr(flag, 1);
-  if (mx) {
-    atomicMax((unsigned long long*)&rowbits[i], (unsigned long long)mx);
-    // dup > 0: the same maximum for row i + dup (the two row blocks of the
-    // real embedding of a complex matrix)
-    if (dup) atomicMax((unsigned long long*)&rowbits[i + dup], (unsigned long long)mx);
-  }
+  if (i >= m || !mx) return;
+  atomicMax((unsigned long long*)&bits[i], (unsigned long long)mx);
+  if (F == SliceSet::Embedding)
+    atomicMax((unsigned long long*)&bits[i + half], (unsigned long long)mx);
 }
 
-template <typename T, bool CX>
-__global__ __launch_bounds__(256) void k_absmax_rows(const T* __restrict__ A, int lda, int m, int k,
-                                                     uint64_t* __restrict__ rowbits,
-                                                     int* __restrict__ flag, int dup) {
-  const int gx = cdiv_i(m, 256);
-  absmax_rows_body<T, CX>(A, lda, m, k, rowbits, flag, blockIdx.x % gx, blockIdx.x / gx, dup);
+template <typename T, SliceSet F>
+__global__ __launch_bounds__(kScanThreads, F == SliceSet::Real ? 4 : 2) void k_scan(ScanArgs s) {
+  __shared__ StripLds<F> lds;
+  if (s.clear)
+    scan_clear(s.a.mx, s.a.rows_pad, s.b.mx, s.b.rows_pad, s.flag,
+               (int)(blockIdx.x * kScanThreads + threadIdx.x), (int)gridDim.x * kScanThreads);
+  const int u = (int)blockIdx.x;
+  if (u >= s.a.units)
+    scan_cols<T, F>(static_cast<const T*>(s.b.src), s.b.ld, s.b.rows, s.b.rows_pad, s.k, s.k_pad,
+                    s.b.bits, s.b.out, u - s.a.units, s.tpc, &lds.red[0][0]);
+  else if (s.chunked)
+    absmax_rows_body<T, F>(static_cast<const T*>(s.a.src), s.a.ld, s.a.rows, s.k, s.half, s.a.bits,
+                           2 * u + (int)(threadIdx.x >> 8), (int)(threadIdx.x & 255));
+  else
+    scan_strip<T, F>(static_cast<const T*>(s.a.src), s.a.ld, s.a.rows, s.k, s.k_pad, s.half,
+                     s.a.bits, s.a.out, u, s.lr, lds);
 }
 
-// B column-major (k x n): one wave per column j (four columns per
-// workgroup), 16 loads in flight per lane; the wave owns the column and
-// stores its maximum.  CX: interleaved (re, im) pairs, maximum over both
-// parts, as for the rows.
-template <typename T, bool CX = false>
-__device__ __forceinline__ void absmax_cols_body(const T* __restrict__ B, int ldb, int k, int n,
-                                        uint64_t* __restrict__ colbits, int* __restrict__ flag,
-                                        int wg) {
-  const int lane = threadIdx.x & 63;
-  const int j = wg * 4 + (threadIdx.x >> 6);
-  if (j >= n) return;   // whole wave
-  constexpr int E = CX ? 2 : 1;
-  const T* col = B + (size_t)E * ((size_t)j * ldb);
-  uint64_t mx = 0;
-  for (int h0 = 0; h0 < k; h0 += 1024) {
-    T x[16], y[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const T* e = col + (size_t)E * min(h0 + lane + 64 * q, k - 1);
-      x[q] = e[0];
-      if (CX) y[q] = e[1];
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      uint64_t b = abs_bits(x[q]);
-      if (CX) {
-        const uint64_t c = abs_bits(y[q]);
-        b = c > b ? c : b;
-      }
-      mx = b > mx ? b : mx;
-    }
-  }
-  for (int off = 32; off >= 1; off >>= 1) {
-    const unsigned long long o = __shfl_xor((unsigned long long)mx, off);
-    mx = o > mx ? o : mx;
-  }
-  if (lane == 0) {
-    if ((mx & kExpMask) == kExpMask) atomicOr(flag, 1);
-    colbits[j] = mx;
-  }
+// What the atomics of a chunked scan need cleared, with the maxima and the flag.
+__global__ __launch_bounds__(256) void k_clear(uint64_t* bits, int* mx_a, int na, int* mx_b, int nb,
+                                               int* flag) {
+  const int t = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
+  for (int i = t; i < na; i += stride) bits[i] = 0;
+  scan_clear(mx_a, na, mx_b, nb, flag, t, stride);
 }
 
-template <typename T, bool CX>
-__global__ __launch_bounds__(256) void k_absmax_cols(const T* __restrict__ B, int ldb, int k, int n,
-                                                     uint64_t* __restrict__ colbits,
-                                                     int* __restrict__ flag) {
-  absmax_cols_body<T, CX>(B, ldb, k, n, colbits, flag, blockIdx.x);
-}
-
-// B column-major (k x n) with k_pad <= kAbsBarMaxK: the abs-max pass and the
-// Bbar pass of Algorithm 2 in one read of B.  Each row j of the padded
-// K-major Bbar (n_pad of them) is one column of B, held in registers (two
-// consecutive k per lane, 32 per lane): a whole workgroup per column for
-// k_pad > kAbsBarWaveK, one wave per column (four per workgroup) below.  The
-// column's abs-max bit pattern is reduced over its threads, and
-// Bbar = ceil(2^nu'_j |b|) (1 for a tiny nonzero b, 0 for b = 0) is written
-// from the same registers, zero beyond k and for the padding rows j >= n.
-constexpr int kAbsBarPasses = kAbsBarMaxK / 512;
-static_assert(kAbsBarWaveK == kAbsBarPasses * 128, "a wave covers kAbsBarWaveK in the same passes");
-
-__device__ __forceinline__ bool absbar_per_wave(int k_pad) { return k_pad <= kAbsBarWaveK; }
-
-// Workgroups of absbar_cols_body for n_pad columns.
-__host__ __device__ inline int absbar_blocks(int n_pad, int k_pad) {
-  return k_pad <= kAbsBarWaveK ? (n_pad + 3) / 4 : n_pad;
-}
-
-template <typename T>
-__device__ __forceinline__ void absbar_cols_body(const T* __restrict__ B, int ldb, int k, int n,
-                                                 int n_pad, int k_pad,
-                                                 uint64_t* __restrict__ colbits,
-                                                 int* __restrict__ flag, int8_t* __restrict__ out,
-                                                 int blk) {
-  const bool per_wave = absbar_per_wave(k_pad);   // uniform over the launch
-  const int tpc = per_wave ? 64 : 256;              // threads per column
-  const int t = per_wave ? (int)(threadIdx.x & 63) : (int)threadIdx.x;
-  const int j = per_wave ? blk * 4 + (int)(threadIdx.x >> 6) : blk;
-  if (per_wave && j >= n_pad) return;               // whole wave; no barrier below for waves
-  double x[2 * kAbsBarPasses];
-  uint64_t mx = 0;
-  if (j < n) {
-    const T* col = B + (size_t)j * ldb;
-#pragma unroll
-    for (int q = 0; q < kAbsBarPasses; ++q) {
-      const int h = 2 * t + 2 * tpc * q;
-      x[2 * q] = h < k ? (double)col[h] : 0.0;
-      x[2 * q + 1] = h + 1 < k ? (double)col[h + 1] : 0.0;
-    }
-#pragma unroll
-    for (int e = 0; e < 2 * kAbsBarPasses; ++e) {
-      const uint64_t b = (uint64_t)__double_as_longlong(fabs(x[e]));
-      mx = b > mx ? b : mx;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 2 * kAbsBarPasses; ++e) x[e] = 0.0;
-  }
-  for (int off = 32; off >= 1; off >>= 1) {
-    const unsigned long long o = __shfl_xor((unsigned long long)mx, off);
-    mx = o > mx ? o : mx;
-  }
-  if (!per_wave) {
-    __shared__ unsigned long long red[4];
-    if ((t & 63) == 0) red[t >> 6] = mx;
-    __syncthreads();
-    mx = red[0];
-#pragma unroll
-    for (int w = 1; w < 4; ++w) mx = red[w] > mx ? red[w] : mx;
-  }
-  if (j < n && t == 0) {
-    if ((mx & kExpMask) == kExpMask) atomicOr(flag, 1);
-    colbits[j] = mx;
-  }
-  const int sh = j < n ? shift_prime_bits(mx) : 0;
-  int8_t* dst = out + (size_t)j * k_pad;
-#pragma unroll
-  for (int q = 0; q < kAbsBarPasses; ++q) {
-    const int h = 2 * t + 2 * tpc * q;
-    if (h < k_pad) {
-      int b[2];
-#pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const double a = fabs(x[2 * q + u]);
-        const double cl = ceil(ldexp(a, sh));
-        b[u] = a == 0.0 ? 0 : (cl < 1.0 ? 1 : (int)cl);
-      }
-      *reinterpret_cast<uint16_t*>(dst + h) = (uint16_t)((b[0] & 0xFF) | ((b[1] & 0xFF) << 8));
-    }
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_absbar_cols(const T* __restrict__ B, int ldb, int k, int n,
-                                                     int n_pad, int k_pad,
-                                                     uint64_t* __restrict__ colbits,
-                                                     int* __restrict__ flag,
-                                                     int8_t* __restrict__ out) {
-  absbar_cols_body<T>(B, ldb, k, n, n_pad, k_pad, colbits, flag, out, blockIdx.x);
+// Strips over all of k: each strip streams its 128 k bytes (256 k for pairs of
+// FP64) by itself, at about 55 GB/s, so they are taken when that is short (k <=
+// 4096) or when there are enough strips to fill the memory system.  At 128 x
+// 128 x 8192 (8 strips) they took 46 us, the chunked scan 23 us; at 4096^3 (256
+// strips) 82 us against 91 us for chunks.
+__host__ __device__ inline bool strips_fit(int rows_pad, int lr, int k) {
+  return k <= 4096 || rows_pad >> lr >= 96;
 }
 
 // ---------------------------------------------------------------------------
@@ -329,12 +491,13 @@ __global__ __launch_bounds__(256) void k_debug_shifts(const uint64_t* __restrict
 }
 
 // ---- grouped versions ------------------------------------------------------
-__global__ __launch_bounds__(256) void kg_init(const ProbDesc* __restrict__ P,
-                                               const BlockRef* __restrict__ map) {
+__global__ __launch_bounds__(256) void kg_clear(const ProbDesc* __restrict__ P,
+                                                const BlockRef* __restrict__ map) {
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
-  init_body(d.rowbits, d.mp, d.colbits, d.np, d.rmax, d.cmax, d.flag, e.y * 256 + threadIdx.x,
-            group_init_blocks(d.mp, d.np) * 256);
+  const int t = e.y * 256 + threadIdx.x, stride = group_clear_blocks(d.mp, d.np) * 256;
+  for (int i = t; i < d.mp; i += stride) d.rowbits[i] = 0;
+  scan_clear(d.rmax, d.mp, d.cmax, d.np, d.flag, t, stride);
 }
 
 template <typename T>
@@ -342,25 +505,30 @@ __global__ __launch_bounds__(256) void kg_absmax_rows(const ProbDesc* __restrict
                                                       const BlockRef* __restrict__ map) {
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
-  const int gx = cdiv_i(d.m, 256);
-  absmax_rows_body<T>((const T*)d.A, d.lda, d.m, d.k, d.rowbits, d.flag, e.y % gx, e.y / gx);
+  absmax_rows_body<T, SliceSet::Real>((const T*)d.A, d.lda, d.m, d.k, 0, d.rowbits, e.y,
+                                      threadIdx.x);
 }
 
+// A problem's strips (none where its scan is chunked), then its columns.
 template <typename T>
-__global__ __launch_bounds__(256) void kg_absmax_cols(const ProbDesc* __restrict__ P,
-                                                      const BlockRef* __restrict__ map) {
+__global__ __launch_bounds__(kScanThreads, 4) void kg_scan(const ProbDesc* __restrict__ P,
+                                                        const BlockRef* __restrict__ map,
+                                                        int fine) {
+  __shared__ StripLds<SliceSet::Real> lds;
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
-  absmax_cols_body<T>((const T*)d.B, d.ldb, d.k, d.n, d.colbits, d.flag, e.y);
-}
-
-// absbar_blocks(np, kp) workgroups per problem with k_pad <= kAbsBarMaxK.
-template <typename T>
-__global__ __launch_bounds__(256) void kg_absbar_cols(const ProbDesc* __restrict__ P,
-                                                      const BlockRef* __restrict__ map) {
-  const BlockRef e = map[blockIdx.x];
-  const ProbDesc& d = P[e.x];
-  absbar_cols_body<T>((const T*)d.B, d.ldb, d.k, d.n, d.np, d.kp, d.colbits, d.flag, d.Bs, e.y);
+  const int lr = strip_rows_log2<T>(d.kp, fine);
+  const bool chunked = !strips_fit(d.mp, lr, d.k);
+  const int strips = chunked ? 0 : d.mp >> lr;
+  if (!chunked && e.y == 0)
+    scan_clear(d.rmax, d.mp, d.cmax, d.np, d.flag, threadIdx.x, kScanThreads);
+  if (e.y < strips)
+    scan_strip<T, SliceSet::Real>((const T*)d.A, d.lda, d.m, d.k, d.kp, 0, d.rowbits, d.As, e.y, lr,
+                                  lds);
+  else
+    scan_cols<T, SliceSet::Real>((const T*)d.B, d.ldb, d.n, d.np, d.k, d.kp, d.colbits, d.Bs,
+                                 e.y - strips, col_threads(d.kp, kColKeep<SliceSet::Real>, fine),
+                                 &lds.red[0][0]);
 }
 
 __global__ __launch_bounds__(256) void k_log2f(const float* __restrict__ d, float* __restrict__ out,
@@ -373,64 +541,82 @@ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace
 
-void launch_init(hipStream_t s, uint64_t* rowbits, int m_pad, uint64_t* colbits, int n_pad,
-                 int* rmax, int* cmax, int* flag) {
-  int mx = m_pad > n_pad ? m_pad : n_pad;
-  int blocks = cdiv(mx, 256);
-  if (blocks > 1024) blocks = 1024;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(k_init, dim3(blocks), dim3(256), 0, s, rowbits, m_pad, colbits, n_pad, rmax,
-                     cmax, flag);
+namespace {
+
+int col_units(int n_pad, int tpc) { return n_pad / (kScanThreads / tpc); }   // 128 divides n_pad
+int clear_blocks(int na, int nb) {
+  const int blocks = cdiv(na > nb ? na : nb, 256);
+  return blocks > 1024 ? 1024 : blocks;
 }
 
-template <typename T, bool CX>
-void absmax_rows_t(hipStream_t s, const void* A, int lda, int m, int k, uint64_t* rowbits,
-                   int* flag, int dup) {
-  const dim3 grid((unsigned)(cdiv(m, 256) * cdiv(k, 64)));
-  hipLaunchKernelGGL((k_absmax_rows<T, CX>), grid, dim3(256), 0, s, (const T*)A, lda, m, k,
-                     rowbits, flag, dup);
+template <typename T, SliceSet F>
+void scan_t(hipStream_t s, ScanArgs& a) {
+  constexpr bool kEmb = F == SliceSet::Embedding;
+  const int span = kEmb ? a.half : a.a.rows_pad;        // rows that strips cover
+  const bool fine = scan_fine((int64_t)(span >> kMinStripLog2<T>) + a.b.rows_pad / 8);
+  a.lr = strip_rows_log2<T>(a.k_pad, fine);
+  a.tpc = col_threads(a.k_pad, kColKeep<F>, fine);
+  a.chunked = !strips_fit(span, a.lr, a.k);
+  a.clear = !a.chunked;
+  if (a.chunked)
+    hipLaunchKernelGGL(k_clear, dim3(clear_blocks(a.a.rows_pad, a.b.rows_pad)), dim3(256), 0, s,
+                       a.a.bits, a.a.mx, a.a.rows_pad, a.b.mx, a.b.rows_pad, a.flag);
+  a.a.units = a.chunked ? cdiv(cdiv(a.a.rows, 256) * cdiv(a.k, 64), 2) : span >> a.lr;
+  a.b.units = col_units(a.b.rows_pad, a.tpc);
+  hipLaunchKernelGGL((k_scan<T, F>), dim3((unsigned)(a.a.units + a.b.units)), dim3(kScanThreads), 0,
+                     s, a);
 }
 
-template <typename T, bool CX>
-void absmax_cols_t(hipStream_t s, const void* B, int ldb, int k, int n, uint64_t* colbits,
-                   int* flag) {
-  const dim3 grid((unsigned)absmax_cols_blocks(n));
-  hipLaunchKernelGGL((k_absmax_cols<T, CX>), grid, dim3(256), 0, s, (const T*)B, ldb, k, n,
-                     colbits, flag);
-}
-
-void launch_absmax_rows(hipStream_t s, Prec pr, const void* A, int lda, int m, int k,
-                        uint64_t* rowbits, int* flag, bool cx, int dup) {
-  if (pr == Prec::F64)
-    cx ? absmax_rows_t<double, true>(s, A, lda, m, k, rowbits, flag, dup)
-       : absmax_rows_t<double, false>(s, A, lda, m, k, rowbits, flag, dup);
+template <typename T>
+void scan_set(hipStream_t s, SliceSet set, ScanArgs& a) {
+  if (set == SliceSet::Real)
+    scan_t<T, SliceSet::Real>(s, a);
+  else if (set == SliceSet::Complex3)
+    scan_t<T, SliceSet::Complex3>(s, a);
   else
-    cx ? absmax_rows_t<float, true>(s, A, lda, m, k, rowbits, flag, dup)
-       : absmax_rows_t<float, false>(s, A, lda, m, k, rowbits, flag, dup);
+    scan_t<T, SliceSet::Embedding>(s, a);
 }
 
-void launch_absmax_cols(hipStream_t s, Prec pr, const void* B, int ldb, int k, int n,
-                        uint64_t* colbits, int* flag, bool cx) {
+}  // namespace
+
+void launch_scan(hipStream_t s, Prec pr, SliceSet set, const SliceOperand& A, const SliceOperand& B,
+                 int k, int k_pad, int* flag) {
+  ScanArgs a{};
+  auto side = [](const SliceOperand& o) {
+    return ScanSide{o.src, o.bits, o.mx, o.out, o.ld, o.rows, o.rows_pad, 0};
+  };
+  a.a = side(A);
+  a.b = side(B);
+  a.flag = flag;
+  a.k = k;
+  a.k_pad = k_pad;
+  a.half = A.rows_pad / 2;
   if (pr == Prec::F64)
-    cx ? absmax_cols_t<double, true>(s, B, ldb, k, n, colbits, flag)
-       : absmax_cols_t<double, false>(s, B, ldb, k, n, colbits, flag);
+    scan_set<double>(s, set, a);
   else
-    cx ? absmax_cols_t<float, true>(s, B, ldb, k, n, colbits, flag)
-       : absmax_cols_t<float, false>(s, B, ldb, k, n, colbits, flag);
+    scan_set<float>(s, set, a);
+  if (a.chunked) {   // A's bars: the constants are not used
+    CrtConsts cc{};
+    launch_slices(s, pr, set, true, &A, nullptr, k, k_pad, cc, nullptr);
+  }
 }
 
-int absbar_group_blocks(int n_pad, int k_pad) { return absbar_blocks(n_pad, k_pad); }
+namespace {
+int group_strip_log2(Prec pr, int k_pad, bool fine) {
+  return pr == Prec::F64 ? strip_rows_log2<double>(k_pad, fine)
+                         : strip_rows_log2<float>(k_pad, fine);
+}
+}  // namespace
 
-void launch_absbar_cols(hipStream_t s, Prec pr, const void* B, int ldb, int k, int n, int n_pad,
-                        int k_pad, uint64_t* colbits, int* flag, int8_t* out) {
-  if (n_pad <= 0) return;
-  const dim3 grid((unsigned)absbar_blocks(n_pad, k_pad));
-  if (pr == Prec::F64)
-    hipLaunchKernelGGL(k_absbar_cols<double>, grid, dim3(256), 0, s, (const double*)B, ldb, k, n,
-                       n_pad, k_pad, colbits, flag, out);
-  else
-    hipLaunchKernelGGL(k_absbar_cols<float>, grid, dim3(256), 0, s, (const float*)B, ldb, k, n,
-                       n_pad, k_pad, colbits, flag, out);
+bool scan_group_fine(int64_t units) { return scan_fine(units); }
+bool scan_group_chunked(Prec pr, int m_pad, int k, int k_pad, bool fine) {
+  return !strips_fit(m_pad, group_strip_log2(pr, k_pad, fine), k);
+}
+int scan_group_blocks(Prec pr, int m_pad, int n_pad, int k, int k_pad, bool fine) {
+  const int strips = scan_group_chunked(pr, m_pad, k, k_pad, fine)
+                         ? 0
+                         : m_pad >> group_strip_log2(pr, k_pad, fine);
+  return strips + col_units(n_pad, col_threads(k_pad, kColKeep<SliceSet::Real>, fine));
 }
 
 void launch_debug_shifts(hipStream_t s, const uint64_t* rowbits, const int* rmax, int m,
@@ -444,34 +630,26 @@ void launch_log2f(hipStream_t s, const float* d, float* out, int count) {
   hipLaunchKernelGGL(k_log2f, dim3(cdiv(count, 256)), dim3(256), 0, s, d, out, count);
 }
 
-void launch_group_scale(hipStream_t s, Prec pr, int phase, const ProbDesc* P, const BlockRef* map,
-                        int blocks) {
-  if (blocks <= 0) return;
-  const dim3 g((unsigned)blocks), b(256);
-  switch (phase) {
-    case GP_INIT:
-      hipLaunchKernelGGL(kg_init, g, b, 0, s, P, map);
-      break;
-    case GP_ABSMAX_A:
-      if (pr == Prec::F64)
-        hipLaunchKernelGGL(kg_absmax_rows<double>, g, b, 0, s, P, map);
-      else
-        hipLaunchKernelGGL(kg_absmax_rows<float>, g, b, 0, s, P, map);
-      break;
-    case GP_ABSMAX_B:
-      if (pr == Prec::F64)
-        hipLaunchKernelGGL(kg_absmax_cols<double>, g, b, 0, s, P, map);
-      else
-        hipLaunchKernelGGL(kg_absmax_cols<float>, g, b, 0, s, P, map);
-      break;
-    case GP_ABSBAR_B:
-      if (pr == Prec::F64)
-        hipLaunchKernelGGL(kg_absbar_cols<double>, g, b, 0, s, P, map);
-      else
-        hipLaunchKernelGGL(kg_absbar_cols<float>, g, b, 0, s, P, map);
-      break;
-    default:
-      break;
+void launch_group_scan(hipStream_t s, Prec pr, const ProbDesc* P, const BlockRef* clear_map,
+                       int clear_blocks, const BlockRef* abs_map, int abs_blocks,
+                       const BlockRef* scan_map, int scan_blocks, bool fine) {
+  if (clear_blocks > 0)
+    hipLaunchKernelGGL(kg_clear, dim3((unsigned)clear_blocks), dim3(256), 0, s, P, clear_map);
+  if (abs_blocks > 0) {
+    if (pr == Prec::F64)
+      hipLaunchKernelGGL(kg_absmax_rows<double>, dim3((unsigned)abs_blocks), dim3(256), 0, s, P,
+                         abs_map);
+    else
+      hipLaunchKernelGGL(kg_absmax_rows<float>, dim3((unsigned)abs_blocks), dim3(256), 0, s, P,
+                         abs_map);
+  }
+  if (scan_blocks > 0) {
+    if (pr == Prec::F64)
+      hipLaunchKernelGGL(kg_scan<double>, dim3((unsigned)scan_blocks), dim3(kScanThreads), 0, s, P,
+                         scan_map, fine ? 1 : 0);
+    else
+      hipLaunchKernelGGL(kg_scan<float>, dim3((unsigned)scan_blocks), dim3(kScanThreads), 0, s, P,
+                         scan_map, fine ? 1 : 0);
   }
 }
 
