@@ -321,7 +321,7 @@ int run_pipeline(Prec pr, int m, int n, int k, const void* A, int lda, const voi
     {
       Scope sc(PH_GEMM_SCALE, s);
       launch_gemm_i8(s, 1, As, 0, Bs, 0, L.mp, L.np, L.kp, 1, cc, nullptr, 0, 0, rmax, cmax,
-                     at<int8_t>(ws, L.part), L.part_bytes);
+                     at<int8_t>(ws, L.part), L.part_bytes, m, n);
     }
   }
   if (want_ef)
@@ -335,7 +335,7 @@ int run_pipeline(Prec pr, int m, int n, int k, const void* A, int lda, const voi
     Scope sc(PH_GEMM_RES, s);
     launch_gemm_i8(s, 0, As, (size_t)L.mp * L.kp, Bs, (size_t)L.np * L.kp, L.mp, L.np, L.kp,
                    cc.N, cc, W, (size_t)L.np * L.mp, L.mp, nullptr, nullptr, at<int8_t>(ws, L.part),
-                   L.part_bytes);
+                   L.part_bytes, m, n);
   }
   {
     Scope sc(PH_CRT, s);
@@ -504,13 +504,13 @@ int zgemm_impl(Prec pr, int m, int n, int k, const void* A, int lda, const void*
   const SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nu, Bs};
   launch_scan(s, pr, SliceSet::Embedding, oa, ob, k, Z.kh, flag);
   launch_gemm_i8(s, 1, As, 0, Bs, 0, L.mp, L.np, L.kp, 1, cc, nullptr, 0, 0, rmax, cmax,
-                 at<int8_t>(ws, L.part), L.part_bytes);
+                 at<int8_t>(ws, L.part), L.part_bytes, H + m, n);
   // Algorithm 3 on the embedding, its residues formed from the complex
   // source; the CRT writes rows i (real) and H + i (imaginary) as pairs.
   launch_slices(s, pr, SliceSet::Embedding, false, &oa, &ob, k, Z.kh, cc, flag);
   launch_gemm_i8(s, 0, As, (size_t)L.mp * L.kp, Bs, (size_t)L.np * L.kp, L.mp, L.np, L.kp, N, cc,
                  W, (size_t)L.np * L.mp, L.mp, nullptr, nullptr, at<int8_t>(ws, L.part),
-                 L.part_bytes);
+                 L.part_bytes, H + m, n);
   launch_crt_complex(s, pr, W, W + H, (size_t)L.np * L.mp, L.mp, mu, mu + H, nu, m, n, cc, flag,
                      status, C, ldc);
   return hipGetLastError() == hipSuccess ? OZAKI2_OK : OZAKI2_ERR_HIP;
@@ -573,7 +573,7 @@ int zgemm3m_impl(Prec pr, int m, int n, int k, const void* A, int lda, const voi
   SliceOperand ob{B, ldb, n, L.np, colbits, cmax, nu, Y[2]};
   launch_scan(s, pr, SliceSet::Complex3, oa, ob, k, L.kp, flag);
   launch_gemm_i8(s, 1, X[2], 0, Y[2], 0, L.mp, L.np, L.kp, 1, cc, nullptr, 0, 0, rmax, cmax,
-                 at<int8_t>(w, L.part), L.part_bytes);
+                 at<int8_t>(w, L.part), L.part_bytes, m, n);
   // Algorithm 3: residues of A'r, A'i and A'r + A'i (and of B) in one pass
   // over both operands, three residue products per modulus, and the CRT of the real
   // and imaginary residues formed from the three W.
@@ -582,7 +582,7 @@ int zgemm3m_impl(Prec pr, int m, int n, int k, const void* A, int lda, const voi
   launch_slices(s, pr, SliceSet::Complex3, false, &oa, &ob, k, L.kp, cc, flag, -1);
   for (int q = 0; q < 3; ++q)
     launch_gemm_i8(s, 0, X[q], sa, Y[q], sb, L.mp, L.np, L.kp, N, cc, W[q], sw, L.mp, nullptr,
-                   nullptr, at<int8_t>(w, L.part), L.part_bytes);
+                   nullptr, at<int8_t>(w, L.part), L.part_bytes, m, n);
   launch_crt_3m(s, pr, W[0], W[1], W[2], sw, L.mp, mu, nu, m, n, cc, flag, status, C, ldc);
   return hipGetLastError() == hipSuccess ? OZAKI2_OK : OZAKI2_ERR_HIP;
 }
@@ -791,7 +791,7 @@ void enqueue_residue_products(const BatchEntry& e, const CrtConsts* ctab, hipStr
       const ProbDesc& d = e.hd[q];
       launch_gemm_i8(s, 0, d.As, (size_t)d.mp * d.kp, d.Bs, (size_t)d.np * d.kp, d.mp, d.np, d.kp,
                      d.N, e.hc[q], d.W, (size_t)d.np * d.mp, d.mp, nullptr, nullptr, e.part[q],
-                     e.part_bytes[q]);
+                     e.part_bytes[q], d.m, d.n);
     }
     return;
   }
@@ -823,7 +823,7 @@ void enqueue_batch(Prec pr, const BatchEntry& e, const CrtConsts* ctab, int* sta
     for (size_t q = 0; q < e.hd.size(); ++q) {
       const ProbDesc& d = e.hd[q];
       launch_gemm_i8(s, 1, d.As, 0, d.Bs, 0, d.mp, d.np, d.kp, 1, e.hc[q], nullptr, 0, 0, d.rmax,
-                     d.cmax, e.part[q], e.part_bytes[q]);
+                     d.cmax, e.part[q], e.part_bytes[q], d.m, d.n);
     }
   } else {
     launch_group_gemm(s, 1, 256, D, M(BS_GS_BIG), B(BS_GS_BIG), ctab);

@@ -19,10 +19,11 @@
 // waves (4 x 2, each 64 x 128: two waves per SIMD, so one wave's MFMAs
 // overlap the other's LDS reads and barrier waits), a 128 x 128 tile 4 waves
 // (2 x 2) with two workgroups per CU.  K advances in groups of 128
-// bytes through two LDS group buffers: direct global->LDS copies fill one
+// bytes through a ring of two LDS group buffers (four where a CU holds one
+// workgroup of 128 x 128): direct global->LDS copies fill the buffers ahead
 // (every 128-byte line of an operand row requested as one unit) while the
-// MFMAs consume the other.  BF16 operands (the planner's lower bound of
-// |A||B|) run through the same loop, counting k in bytes.
+// MFMAs consume one.  BF16 operands (the planner's lower bound of |A||B|) run
+// through the same loop, counting k in bytes.
 //
 // Workgroup order: the hardware deals workgroups round-robin to the 8 XCDs;
 // the linear id is remapped so each XCD works on a contiguous range of
@@ -48,6 +49,7 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf16 __attribute__((ext_vector_type(8)));
 
 constexpr int kXcds = 8;
+constexpr int kCus = 256;   // compute units that the launch rules count with
 constexpr int kFoldGroups = (1 << 17) / 128;   // 128-k groups per 2^17 of k
 
 // mod(x, p) of an INT32 product as an INT8 value (Section 1.2), odd p: the
@@ -58,6 +60,23 @@ constexpr int kFoldGroups = (1 << 17) / 128;   // 128-k groups per 2^17 of k
 __device__ inline int mod_odd(int x, double p, double pinv) {
   const double xd = (double)x;
   return (int)fma(-rint(xd * pinv), p, xd);
+}
+
+// The bytes mod(x, p) of four products (odd p, or p = 256: the low bytes): q =
+// round(x/p) is in the low bits of one fma with kRound, as exact as rint in
+// mod_odd, and x - q p is formed mod 2^16, two values per packed instruction:
+// per value a conversion, an fma and 1.75 integer instructions instead of five
+// FP64 ones and 1.5 to pack.  The epilogue is a tenth of the products at k =
+// 4096: 18 of 4096^3 took 1084 us with FP64 remainders, 1057 with these.
+__device__ __forceinline__ uint32_t mod_word(int a, int b, int c, int d, double pinv,
+                                             uint32_t negp) {
+  const uint32_t qa = (uint32_t)__double2loint(fma((double)a, pinv, kRound));
+  const uint32_t qb = (uint32_t)__double2loint(fma((double)b, pinv, kRound));
+  const uint32_t qc = (uint32_t)__double2loint(fma((double)c, pinv, kRound));
+  const uint32_t qd = (uint32_t)__double2loint(fma((double)d, pinv, kRound));
+  const uint32_t x = pk_mad(pair16(qa, qb), negp, pair16((uint32_t)a, (uint32_t)b));
+  const uint32_t y = pk_mad(pair16(qc, qd), negp, pair16((uint32_t)c, (uint32_t)d));
+  return bytes_of_pairs(x, y);
 }
 
 __device__ inline uint32_t pack_bytes(int a, int b, int c, int d) {
@@ -99,26 +118,53 @@ __device__ inline void wait_vmcnt() {
 // of rows r..r+15 land in distinct bank groups (64 banks).
 __device__ inline int swz(int r) { return (r >> 1) & 7; }
 
-// Main loop structure: k advances in groups of 128 bytes; two groups (128 KB
-// for a 256x256 tile) are resident in LDS.  The copies of group g+1 (direct
-// global->LDS, every 128-byte line requested as one unit) run while the
-// MFMAs consume group g.  A group buffer holds the X tile then the Y tile as
-// rows of 128 bytes.  `bid` is the workgroup's index among the `launched`
-// workgroups of this product (launched >= tiles_x * tiles_y * nz * nsplit;
-// the surplus exits at once).  Split-k: with nsplit > 1, workgroup index
-// sidx = bid / (tiles * nz) takes the k-groups [sidx G / nsplit,
+// Workgroup -> place in the walk over tiles: the hardware deals workgroups
+// round-robin to the XCDs; each XCD gets a contiguous range of the walk.
+__device__ __forceinline__ int xcd_place(int bid, int launched) {
+  const int xcd = bid % kXcds, loc = bid / kXcds;
+  const int per = launched / kXcds, extra = launched % kXcds;
+  return xcd * per + min(xcd, extra) + loc;
+}
+
+// Place -> (slice z, tile tx, ty): slice by slice, and in a slice groups of 8
+// tile rows (the 32 workgroups of an XCD share their panels in its L2).
+struct TilePos {
+  int z, tx, ty;
+};
+__device__ __forceinline__ TilePos tile_at(int place, int tiles_x, int tiles_y) {
+  constexpr int GROUP = 8;
+  const int per_slice = tiles_x * tiles_y;
+  const int z = place / per_slice;
+  int t = place % per_slice;
+  const int g = t / (GROUP * tiles_y);
+  const int gx0 = g * GROUP;
+  const int gsz = min(GROUP, tiles_x - gx0);
+  t -= g * GROUP * tiles_y;
+  return {z, gx0 + t % gsz, t / gsz};
+}
+
+// One BX x BY tile at (x0, y0) of slice z.  k advances in groups of 128 bytes;
+// a group buffer in LDS holds the X tile then the Y tile as rows of 128 bytes,
+// and NS of them are a ring.  The copies of group g + NS - 1 (direct
+// global->LDS, every 128-byte line requested as one unit) run while the MFMAs
+// consume group g.  NS = 2 where the workgroups of a CU fill its LDS (128 KB
+// for a 256x256 tile); NS = 4 for launches of 128x128 tiles with at most one
+// workgroup per CU, whose groups otherwise wait for a copy each (0.65 us a
+// group, 0.3 us with three copies under way).  Scaling product with NS = 2 and
+// 4: 256^3 10.4 and 6.4 us, 1000x700x1300 16.0 and 10.7, 2048^3 21.3 and 14.5.
+// Split-k: with nsplit > 1, split sidx takes the k-groups [sidx G / nsplit,
 // (sidx + 1) G / nsplit) of the G = k_pad / 128 (nsplit <= G), and its
 // epilogue writes slice sidx * nz + z of W (EPI 0: mod p_z of its partial
 // sum; EPI 4: the INT32 partial sum); the caller reduces the partials.
 // SPLIT selects that build; without it nsplit is 1 and the k loop is the
 // plain one from group 0 (a dynamic start cost 2% at 8192^3).
-template <int BX, int BY, int NWX, int NWY, int EPI, bool BF16, bool FOLD, bool SPLIT = false>
-__device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t sx,
-                                          const int8_t* __restrict__ Y, size_t sy, int tiles_x,
-                                          int tiles_y, int nz, int k_pad, const CrtConsts& cc,
+template <int BX, int BY, int NWX, int NWY, int EPI, bool BF16, bool FOLD, bool SPLIT, int NS>
+__device__ __forceinline__ void gemm_body(int8_t* __restrict__ lds, const int8_t* __restrict__ X,
+                                          size_t sx, const int8_t* __restrict__ Y, size_t sy, int x0,
+                                          int y0, int z, int nz, int k_pad, const CrtConsts& cc,
                                           int8_t* __restrict__ W, size_t sw, int ldw,
-                                          int* __restrict__ xmax, int* __restrict__ ymax, int bid,
-                                          int launched, int nsplit = 1) {
+                                          int* __restrict__ xmax, int* __restrict__ ymax, int sidx,
+                                          int nsplit, int vx, int vy) {
   constexpr int BK = 128;                        // bytes of k per LDS row (one group)
   constexpr int NW = NWX * NWY;                  // waves
   constexpr int WX = BX / NWX, WY = BY / NWY;
@@ -131,33 +177,10 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
   // that every wave's share starts at a multiple of 16 rows.
   static_assert(IX % 2 == 0 && IY % 2 == 0 && WX % 32 == 0 && WY % 32 == 0, "tile / wave shape");
   constexpr int GROUP_BYTES = (BX + BY) * BK;    // one 128-k group
-  constexpr int GROUP = 8;
-  __shared__ __attribute__((aligned(1024))) int8_t lds[2 * GROUP_BYTES];
-
-  // ---- workgroup -> (slice z, tile) ------------------------------------
-  if constexpr (!SPLIT) nsplit = 1;
-  const int total = tiles_x * tiles_y * nz * nsplit;
-  {
-    const int xcd = bid % kXcds, loc = bid / kXcds;
-    const int per = launched / kXcds, extra = launched % kXcds;
-    bid = xcd * per + min(xcd, extra) + loc;
-  }
-  if (bid >= total) return;   // whole workgroup, before any barrier
-  const int per_slice = tiles_x * tiles_y;
-  const int sidx = SPLIT ? bid / (per_slice * nz) : 0;
-  bid -= sidx * per_slice * nz;
-  const int z = bid / per_slice;
-  int t = bid % per_slice;
-  const int group_span = GROUP * tiles_y;
-  const int g = t / group_span;
-  const int gx0 = g * GROUP;
-  const int gsz = min(GROUP, tiles_x - gx0);
-  t -= g * group_span;
-  const int tx_ = gx0 + t % gsz, ty_ = t / gsz;
+  static_assert((NS & (NS - 1)) == 0 && (NS - 2) * (IX + IY) < 64, "ring");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wx = wave / NWY, wy = wave % NWY;
-  const int x0 = tx_ * BX, y0 = ty_ * BY;
 
   // Copy instruction q of this wave covers rows RPI*q .. RPI*q + RPI - 1 of
   // its share; lane l takes row RPI*q + l/CPR and stores LDS chunk l%CPR,
@@ -170,19 +193,33 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
 
   // The copies of one group: the X rows (issue_x) and the Y rows (issue_y).
+  // SPLIT (a small output over a long k, bound by reading the operands): rows
+  // past the vx (vy) real ones copy the last real row again, from L2.  Nothing
+  // reads their products, and a repeated row changes no maximum of Cbar.
+  // Residue products, all rows read and this: 200x200x100000 191 and 159 us,
+  // 64x64x262144 245 and 142 us.
+  auto row_of = [&](const int8_t* src, int q, int first, int valid) {
+    if constexpr (SPLIT) {
+      const int over = first + q * RPI + lr - (valid - 1);
+      return src + q * rowstep - (over > 0 ? (size_t)over * k_pad : 0);
+    } else {
+      return src + q * rowstep;
+    }
+  };
   auto issue_x = [&](int8_t* buf, int z, int k0) {
     const uint32_t b = lds_addr(buf);
     const int8_t* xs = xsrc + (size_t)z * sx + k0;
 #pragma unroll
     for (int q = 0; q < IX; ++q)
-      dma16(xs + q * rowstep + ((q & 1) ? ch_o : ch_e), b + (uint32_t)((wave_u * IX + q) * 1024));
+      dma16(row_of(xs, q, x0 + wave * IX * RPI, vx) + ((q & 1) ? ch_o : ch_e),
+            b + (uint32_t)((wave_u * IX + q) * 1024));
   };
   auto issue_y = [&](int8_t* buf, int z, int k0) {
     const uint32_t b = lds_addr(buf);
     const int8_t* ys = ysrc + (size_t)z * sy + k0;
 #pragma unroll
     for (int q = 0; q < IY; ++q)
-      dma16(ys + q * rowstep + ((q & 1) ? ch_o : ch_e),
+      dma16(row_of(ys, q, y0 + wave * IY * RPI, vy) + ((q & 1) ? ch_o : ch_e),
             b + (uint32_t)(BX * BK + (wave_u * IY + q) * 1024));
   };
 
@@ -276,37 +313,20 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
                             (float)acc[tx][ty][4 * r4 + 2], (float)acc[tx][ty][4 * r4 + 3]);
           }
     } else if constexpr (EPI == 0) {
-      const int p = cc.mod[z].p;
+      const double pinv = cc.mod[z].pinv;
+      const uint32_t negp = cc.mod[z].negp;
       int8_t* Wz = W + (size_t)(sidx * nz + z) * sw;
-      // The modulus is uniform: one branch for the whole tile.
-      if (p == 256) {
 #pragma unroll
-        for (int tx = 0; tx < TX; ++tx)
+      for (int tx = 0; tx < TX; ++tx)
 #pragma unroll
-          for (int ty = 0; ty < TY; ++ty) {
-            uint32_t R[4];
+        for (int ty = 0; ty < TY; ++ty) {
+          uint32_t R[4];
 #pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-              R[r4] = pack_bytes(acc[tx][ty][4 * r4 + 0], acc[tx][ty][4 * r4 + 1],
-                                 acc[tx][ty][4 * r4 + 2], acc[tx][ty][4 * r4 + 3]);
-            store_block(Wz, tx, ty, R[0], R[1], R[2], R[3]);
-          }
-      } else {
-        const double pd = (double)p, pinv = cc.mod[z].pinv;
-#pragma unroll
-        for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-          for (int ty = 0; ty < TY; ++ty) {
-            uint32_t R[4];
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-              R[r4] = pack_bytes(mod_odd(acc[tx][ty][4 * r4 + 0], pd, pinv),
-                                 mod_odd(acc[tx][ty][4 * r4 + 1], pd, pinv),
-                                 mod_odd(acc[tx][ty][4 * r4 + 2], pd, pinv),
-                                 mod_odd(acc[tx][ty][4 * r4 + 3], pd, pinv));
-            store_block(Wz, tx, ty, R[0], R[1], R[2], R[3]);
-          }
-      }
+          for (int r4 = 0; r4 < 4; ++r4)
+            R[r4] = mod_word(acc[tx][ty][4 * r4 + 0], acc[tx][ty][4 * r4 + 1],
+                             acc[tx][ty][4 * r4 + 2], acc[tx][ty][4 * r4 + 3], pinv, negp);
+          store_block(Wz, tx, ty, R[0], R[1], R[2], R[3]);
+        }
     } else if constexpr (EPI == 1 || EPI == 3) {
       if constexpr (EPI == 3) {
 #pragma unroll
@@ -332,26 +352,42 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
         mv = max(mv, __shfl_xor(mv, 32));
         if (lane < 32) atomicMax(&ymax[yb + ty * 32 + lane], mv);
       }
-      // max over y for each x
+      // max over y for each x: the 16 registers of a lane (rows) against the 32
+      // lanes of its half (columns).  In each step a lane passes on half of its
+      // rows and keeps the other, 15 exchanges and one more for the last pair
+      // of lanes, instead of five for every row; lane bits 4..1 then name the
+      // row that a lane holds.
 #pragma unroll
-      for (int tx = 0; tx < TX; ++tx)
+      for (int tx = 0; tx < TX; ++tx) {
+        int v[16];
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          int mv = 0;
+          v[r] = 0;
 #pragma unroll
-          for (int ty = 0; ty < TY; ++ty) mv = max(mv, acc[tx][ty][r]);
-#pragma unroll
-          for (int off = 16; off >= 1; off >>= 1) mv = max(mv, __shfl_xor(mv, off));
-          if ((lane & 31) == 0)
-            atomicMax(&xmax[xb + tx * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)], mv);
+          for (int ty = 0; ty < TY; ++ty) v[r] = max(v[r], acc[tx][ty][r]);
         }
-    }  };
+#pragma unroll
+        for (int half = 8; half >= 1; half >>= 1) {
+          const bool up = (lane & (2 * half)) != 0;
+#pragma unroll
+          for (int r = 0; r < half; ++r) {
+            const int send = up ? v[r] : v[r + half], keep = up ? v[r + half] : v[r];
+            v[r] = max(keep, __shfl_xor(send, 2 * half));
+          }
+        }
+        const int mv = max(v[0], __shfl_xor(v[0], 1));
+        const int r = (lane >> 1) & 15;
+        if ((lane & 1) == 0)
+          atomicMax(&xmax[xb + tx * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)], mv);
+      }
+    }
+  };
 
-  // k_pad is a multiple of 128.  Group gi lives in half gi % 2 of the LDS; it
-  // is issued while group gi-1 is consumed and waited for (all copies done +
-  // barrier) before use, which also certifies that every wave has finished
-  // reading group gi-1.  No branch encloses an MFMA, so the accumulators stay
-  // in place across iterations.
+  // k_pad is a multiple of 128.  Group gi lives in buffer gi % NS of the ring;
+  // it is issued while group gi - NS + 1 is consumed and waited for (its copies
+  // done + barrier) before use, which also certifies that every wave has
+  // finished reading group gi - 1.  No branch encloses an MFMA, so the
+  // accumulators stay in place across iterations.
   const int NGall = k_pad / 128;
   const int g_lo = SPLIT ? (int)((int64_t)sidx * NGall / nsplit) : 0;
   const int NG = SPLIT ? (int)((int64_t)(sidx + 1) * NGall / nsplit) : NGall;   // end of this workgroup's groups
@@ -387,14 +423,30 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[tx][ty][r] = mod_odd(acc[tx][ty][r], pd, pinv);
   };
-  issue_x(lds + (SPLIT ? (g_lo & 1) * GROUP_BYTES : 0), z, g_lo * 128);
-  issue_y(lds + (SPLIT ? (g_lo & 1) * GROUP_BYTES : 0), z, g_lo * 128);
+  auto ring = [&](int gi) { return lds + (gi & (NS - 1)) * GROUP_BYTES; };
+#pragma unroll
+  for (int g = 0; g < NS - 1; ++g)
+    if (g == 0 || g_lo + g < NG) {
+      issue_x(SPLIT || NS > 2 ? ring(g_lo + g) : lds, z, (g_lo + g) * 128);
+      issue_y(SPLIT || NS > 2 ? ring(g_lo + g) : lds, z, (g_lo + g) * 128);
+    }
   for (int g0 = g_lo; g0 < NG; g0 += chunk) {
   const int g1 = min(NG, g0 + chunk);
   for (int gi = g0; gi < g1; ++gi) {
-    int8_t* const buf = lds + (gi & 1) * GROUP_BYTES;
-    int8_t* const next = lds + ((gi + 1) & 1) * GROUP_BYTES;
-    wait_vmcnt<0>();
+    int8_t* const buf = ring(gi);
+    int8_t* const next = ring(gi + NS - 1);
+    // the copies of the groups after gi may still be under way
+    if constexpr (NS == 4) {
+      if (gi + 2 < NG)
+        wait_vmcnt<2 * (IX + IY)>();
+      else if (gi + 1 < NG)
+        wait_vmcnt<IX + IY>();
+      else
+        wait_vmcnt<0>();
+    } else {
+      static_assert(NS == 2, "ring");
+      wait_vmcnt<0>();
+    }
     __builtin_amdgcn_s_barrier();
     v4i a0[TX], b0[TY], a1[TX], b1[TY];
     // The first fragment reads go out before the next group's copies, so
@@ -402,13 +454,13 @@ __device__ __forceinline__ void gemm_body(const int8_t* __restrict__ X, size_t s
     // them and the Y-row copies come one sub-step later, spreading the
     // copies over the first half of the group.
     load_frags(buf, 0, a0, b0);
-    if (gi + 1 < NG) issue_x(next, z, (gi + 1) * 128);
+    if (gi + NS - 1 < NG) issue_x(next, z, (gi + NS - 1) * 128);
     __builtin_amdgcn_sched_barrier(0);
     load_frags(buf, 1, a1, b1);
     mfmas(a0, b0);
     interleave();
     __builtin_amdgcn_sched_barrier(0);
-    if (gi + 1 < NG) issue_y(next, z, (gi + 1) * 128);
+    if (gi + NS - 1 < NG) issue_y(next, z, (gi + NS - 1) * 128);
     __builtin_amdgcn_sched_barrier(0);
     load_frags(buf, 2, a0, b0);
     mfmas(a1, b1);
@@ -452,7 +504,6 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
   static_assert(IX % 2 == 0 && IY % 2 == 0 && WX % 32 == 0 && WY % 32 == 0, "tile / wave shape");
   static_assert(BX == BY, "square tiles");
   constexpr int GROUP_BYTES = (BX + BY) * BK;
-  constexpr int GROUP = 8;
   __shared__ __attribute__((aligned(1024))) int8_t lds[2 * GROUP_BYTES];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -471,6 +522,7 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
     const int8_t* ys;
     int8_t* Wz;
     int k_pad, ldw, x0, y0, z, p;
+    uint32_t negp;
     double pinv;
   };
   // Entry i of the map as a job; false for the padding entries.
@@ -480,23 +532,12 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
     const int tiles_x = d.mp / BX, tiles_y = d.np / BY, nz = d.N;
     const int launched = group_gemm_blocks(d.mp, d.np, BX, nz);
     const int total = tiles_x * tiles_y * nz;
-    int bid = e.y;
-    {
-      const int xcd = bid % kXcds, loc = bid / kXcds;
-      const int per = launched / kXcds, extra = launched % kXcds;
-      bid = xcd * per + min(xcd, extra) + loc;
-    }
-    if (bid >= total) return false;
-    const int per_slice = tiles_x * tiles_y;
-    const int z = bid / per_slice;
-    int t = bid % per_slice;
-    const int group_span = GROUP * tiles_y;
-    const int g = t / group_span;
-    const int gx0 = g * GROUP;
-    const int gsz = min(GROUP, tiles_x - gx0);
-    t -= g * group_span;
-    j.x0 = (gx0 + t % gsz) * BX;
-    j.y0 = (t / gsz) * BY;
+    const int place = xcd_place(e.y, launched);
+    if (place >= total) return false;
+    const TilePos pos = tile_at(place, tiles_x, tiles_y);
+    const int z = pos.z;
+    j.x0 = pos.tx * BX;
+    j.y0 = pos.ty * BY;
     j.z = z;
     j.k_pad = d.kp;
     j.ldw = d.mp;
@@ -505,6 +546,7 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
     j.Wz = d.W + (size_t)z * d.np * d.mp;
     j.p = ctab[d.N].mod[z].p;
     j.pinv = ctab[d.N].mod[z].pinv;
+    j.negp = ctab[d.N].mod[z].negp;
     return true;
   };
   auto issue_x = [&](int8_t* buf, const Job& j, int k0) {
@@ -628,34 +670,17 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
       v.w = s13[1];
       *reinterpret_cast<uint4*>(cur.Wz + (size_t)y * cur.ldw + x) = v;
     };
-    if (cur.p == 256) {
 #pragma unroll
-      for (int tx = 0; tx < TX; ++tx)
+    for (int tx = 0; tx < TX; ++tx)
 #pragma unroll
-        for (int ty = 0; ty < TY; ++ty) {
-          uint32_t R[4];
+      for (int ty = 0; ty < TY; ++ty) {
+        uint32_t R[4];
 #pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4)
-            R[r4] = pack_bytes(acc[tx][ty][4 * r4 + 0], acc[tx][ty][4 * r4 + 1],
-                               acc[tx][ty][4 * r4 + 2], acc[tx][ty][4 * r4 + 3]);
-          store_block(tx, ty, R[0], R[1], R[2], R[3]);
-        }
-    } else {
-      const double pd = (double)cur.p, pinv = cur.pinv;
-#pragma unroll
-      for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-        for (int ty = 0; ty < TY; ++ty) {
-          uint32_t R[4];
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4)
-            R[r4] = pack_bytes(mod_odd(acc[tx][ty][4 * r4 + 0], pd, pinv),
-                               mod_odd(acc[tx][ty][4 * r4 + 1], pd, pinv),
-                               mod_odd(acc[tx][ty][4 * r4 + 2], pd, pinv),
-                               mod_odd(acc[tx][ty][4 * r4 + 3], pd, pinv));
-          store_block(tx, ty, R[0], R[1], R[2], R[3]);
-        }
-    }
+        for (int r4 = 0; r4 < 4; ++r4)
+          R[r4] = mod_word(acc[tx][ty][4 * r4 + 0], acc[tx][ty][4 * r4 + 1],
+                           acc[tx][ty][4 * r4 + 2], acc[tx][ty][4 * r4 + 3], cur.pinv, cur.negp);
+        store_block(tx, ty, R[0], R[1], R[2], R[3]);
+      }
     if (!more) break;
     cur = nxt;
     i = inext;
@@ -678,14 +703,40 @@ constexpr int tile_threads() {
   return 64 * TileShape<B>::NWX * TileShape<B>::NWY;
 }
 
-template <int B, int EPI, bool BF16 = false, bool FOLD = false, bool SPLIT = false>
+// One product (nz slices): `full` workgroups of whole tiles, and with TAIL = 2
+// (4) the tiles from place `full` on as that many 256x128 (128x128) parts each,
+// one workgroup per part.  A last round of few tiles leaves most CUs idle for
+// the time of a whole tile; cut up, it occupies them for half or a quarter.
+template <int B, int EPI, bool BF16 = false, bool FOLD = false, bool SPLIT = false, int NS = 2,
+          int TAIL = 0>
 __global__ __launch_bounds__(tile_threads<B>(), TileShape<B>::OCC) void k_gemm_i8(
     const int8_t* __restrict__ X, size_t sx, const int8_t* __restrict__ Y, size_t sy, int tiles_x,
     int tiles_y, int nz, int k_pad, CrtConsts cc, int8_t* __restrict__ W, size_t sw, int ldw,
-    int* __restrict__ xmax, int* __restrict__ ymax, int nsplit) {
-  gemm_body<B, B, TileShape<B>::NWX, TileShape<B>::NWY, EPI, BF16, FOLD, SPLIT>(
-      X, sx, Y, sy, tiles_x, tiles_y, nz, k_pad, cc, W, sw, ldw, xmax, ymax, blockIdx.x, gridDim.x,
-      nsplit);
+    int* __restrict__ xmax, int* __restrict__ ymax, int nsplit, int full, int vx, int vy) {
+  __shared__ __attribute__((aligned(1024))) int8_t lds[NS * 2 * B * 128];
+  constexpr int NWX = TileShape<B>::NWX, NWY = TileShape<B>::NWY;
+  const int bid = (int)blockIdx.x;
+  if constexpr (TAIL > 0) {
+    if (bid >= full) {
+      const int place = xcd_place(bid - full, (int)gridDim.x - full);
+      const TilePos t = tile_at(full + place / TAIL, tiles_x, tiles_y);
+      const int part = place % TAIL;
+      constexpr int SX = TAIL == 4 ? B / 2 : B, SY = B / 2;
+      gemm_body<SX, SY, NWX, NWY, EPI, BF16, FOLD, false, NS>(
+          lds, X, sx, Y, sy, t.tx * B + (TAIL == 4 ? (part & 1) * SX : 0),
+          t.ty * B + (TAIL == 4 ? part >> 1 : part) * SY, t.z, nz, k_pad, cc, W, sw, ldw, xmax, ymax,
+          0, 1, 0, 0);
+      return;
+    }
+  }
+  int place = xcd_place(bid, TAIL > 0 ? full : (int)gridDim.x);
+  const int per_split = tiles_x * tiles_y * nz;
+  const int sidx = SPLIT ? place / per_split : 0;
+  place -= sidx * per_split;
+  const TilePos t = tile_at(place, tiles_x, tiles_y);
+  gemm_body<B, B, NWX, NWY, EPI, BF16, FOLD, SPLIT, NS>(lds, X, sx, Y, sy, t.tx * B, t.ty * B, t.z,
+                                                        nz, k_pad, cc, W, sw, ldw, xmax, ymax, sidx,
+                                                        SPLIT ? nsplit : 1, vx, vy);
 }
 
 // ---- split-k reductions ------------------------------------------------------
@@ -704,11 +755,19 @@ __global__ __launch_bounds__(256) void k_reduce_w(const int8_t* __restrict__ par
     int acc[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0;
-    for (int sidx = 0; sidx < nsplit; ++sidx) {
-      const uint4 v = src[((int64_t)sidx * nz + z) * sw16 + t];
-      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    // eight loads before any use; past the last split the last one again, not added
+    for (int s0 = 0; s0 < nsplit; s0 += 8) {
+      uint4 v[8];
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] += sbyte(w[e >> 2], e & 3);
+      for (int u = 0; u < 8; ++u)
+        v[u] = src[((int64_t)min(s0 + u, nsplit - 1) * nz + z) * sw16 + t];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        if (s0 + u >= nsplit) break;
+        const uint32_t w[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] += sbyte(w[e >> 2], e & 3);
+      }
     }
     uint32_t o[4] = {0, 0, 0, 0};
 #pragma unroll
@@ -732,7 +791,13 @@ __global__ __launch_bounds__(256) void k_reduce_cbar(const int* __restrict__ par
   int v = 0;
   if (y < ny) {
     const int* src = part + (size_t)y * nx + x;
-    for (int sidx = 0; sidx < nsplit; ++sidx) v += src[sidx * per];
+    for (int s0 = 0; s0 < nsplit; s0 += 8) {   // eight loads before any use
+      int w[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) w[u] = src[min(s0 + u, nsplit - 1) * per];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v += s0 + u < nsplit ? w[u] : 0;
+    }
     int cm = v;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) cm = max(cm, __shfl_xor(cm, off));
@@ -753,10 +818,15 @@ __global__ __launch_bounds__(tile_threads<B>(), TileShape<B>::OCC) void kg_gemm(
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
   const int nz = EPI == 0 ? d.N : 1;
-  gemm_body<B, B, TileShape<B>::NWX, TileShape<B>::NWY, EPI, false, FOLD>(
-      d.As, EPI == 0 ? (size_t)d.mp * d.kp : 0, d.Bs, EPI == 0 ? (size_t)d.np * d.kp : 0, d.mp / B,
-      d.np / B, nz, d.kp, ctab[d.N], d.W, (size_t)d.np * d.mp, d.mp, d.rmax, d.cmax, e.y,
-      group_gemm_blocks(d.mp, d.np, B, nz));
+  __shared__ __attribute__((aligned(1024))) int8_t lds[2 * 2 * B * 128];
+  const int tiles_x = d.mp / B, tiles_y = d.np / B;
+  const int place = xcd_place(e.y, group_gemm_blocks(d.mp, d.np, B, nz));
+  if (place >= tiles_x * tiles_y * nz) return;   // whole workgroup, before any barrier
+  const TilePos t = tile_at(place, tiles_x, tiles_y);
+  gemm_body<B, B, TileShape<B>::NWX, TileShape<B>::NWY, EPI, false, FOLD, false, 2>(
+      lds, d.As, EPI == 0 ? (size_t)d.mp * d.kp : 0, d.Bs, EPI == 0 ? (size_t)d.np * d.kp : 0,
+      t.tx * B, t.ty * B, t.z, nz, d.kp, ctab[d.N], d.W, (size_t)d.np * d.mp, d.mp, d.rmax, d.cmax, 0,
+      1, 0, 0);
 }
 
 // Persistent grouped residue products (see gemm_persist).
@@ -767,15 +837,42 @@ __global__ __launch_bounds__(tile_threads<B>(), TileShape<B>::OCC) void kp_gemm(
   gemm_persist<B, B, TileShape<B>::NWX, TileShape<B>::NWY, FOLD>(P, map, items, ctab);
 }
 
+// Parts of each tile of the last round (0: none) for `tiles` 256x256 tiles: the
+// last round's tiles are cut when there are at most half a round of them (in
+// two) or a quarter (in four); with more, the parts make a second round of
+// their own.  14 products of 2048^3 (896 tiles, 128 in the last round): 120.5
+// us whole, 113 in parts.
+int tail_parts(long tiles) {
+  const long rem = tiles % kCus;
+  if (tiles < kCus || rem == 0 || 2 * rem > kCus) return 0;
+  return 4 * rem <= kCus ? 4 : 2;
+}
+
 template <int B>
 void launch_cfg(hipStream_t s, int epi, const int8_t* X, size_t sx, const int8_t* Y, size_t sy,
                 int nx_pad, int ny_pad, int k_pad, int nz, const CrtConsts& cc, int8_t* W,
-                size_t sw, int ldw, int* xmax, int* ymax, int nsplit, bool fold) {
+                size_t sw, int ldw, int* xmax, int* ymax, int nsplit, bool fold, int vx, int vy) {
   const int tiles_x = nx_pad / B, tiles_y = ny_pad / B;
-  const dim3 grid((unsigned)(tiles_x * tiles_y * nz * nsplit)), block(tile_threads<B>());
+  const int wgs = tiles_x * tiles_y * nz * nsplit;
+  int full = wgs;
+  dim3 grid((unsigned)wgs);
+  const dim3 block(tile_threads<B>());
+  const bool deep = B == 128 && wgs <= kCus;   // one workgroup per CU: the deep ring
+#define OZ2_GEMM_NS(E, F, S, NS, T)                                                             \
+  hipLaunchKernelGGL((k_gemm_i8<B, E, false, F, S, NS, T>), grid, block, 0, s, X, sx, Y, sy,     \
+                     tiles_x, tiles_y, nz, k_pad, cc, W, sw, ldw, xmax, ymax, nsplit, full, \
+                     vx, vy)
 #define OZ2_GEMM(E, F, S)                                                                       \
-  hipLaunchKernelGGL((k_gemm_i8<B, E, false, F, S>), grid, block, 0, s, X, sx, Y, sy, tiles_x,   \
-                     tiles_y, nz, k_pad, cc, W, sw, ldw, xmax, ymax, nsplit)
+  do {                                                                                          \
+    if constexpr (B == 128) {                                                                   \
+      if (deep)                                                                                 \
+        OZ2_GEMM_NS(E, F, S, 4, 0);                                                             \
+      else                                                                                      \
+        OZ2_GEMM_NS(E, F, S, 2, 0);                                                             \
+    } else {                                                                                    \
+      OZ2_GEMM_NS(E, F, S, 2, 0);                                                               \
+    }                                                                                           \
+  } while (0)
   const bool split = nsplit > 1;
   switch (epi) {
     case 0:
@@ -785,6 +882,18 @@ void launch_cfg(hipStream_t s, int epi, const int8_t* X, size_t sx, const int8_t
         else
           OZ2_GEMM(0, false, true);
       } else {
+        if constexpr (B == 256) {
+          const int parts = fold ? 0 : tail_parts(wgs);
+          if (parts) {
+            full = wgs / kCus * kCus;
+            grid = dim3((unsigned)(full + (wgs - full) * parts));
+            if (parts == 2)
+              OZ2_GEMM_NS(0, false, false, 2, 2);
+            else
+              OZ2_GEMM_NS(0, false, false, 2, 4);
+            break;
+          }
+        }
         if (fold)
           OZ2_GEMM(0, true, false);
         else
@@ -807,6 +916,7 @@ void launch_cfg(hipStream_t s, int epi, const int8_t* X, size_t sx, const int8_t
       break;
   }
 #undef OZ2_GEMM
+#undef OZ2_GEMM_NS
 }
 
 // Tile configuration: 0 = automatic; 1 = 256x256, 2 = 128x128 (g_gemm_tile,
@@ -827,33 +937,52 @@ bool use_256(int nx_pad, int ny_pad, int nz) {
   return fits256 && t256 > 128;
 }
 
-// Split-k of a product with few output workgroups (EPI 0 and 1): with W0 =
-// tiles * nz workgroups and G = k_pad / 128 groups of k, nsplit = the number
-// of copies of W0 that fill the workgroup slots once (CUs x occupancy: 256
-// for 256x256 tiles, 512 for 128x128), at most G / gmin and smax; 1 when W0
-// already fills a quarter of the slots.  The residue products take gmin = 4
-// (512 k or more per split), smax = 64; the scaling product, whose partials
-// are INT32 and which is one product against N, gmin = 32 and smax = 16.
-// Measured (FP64, N = 14): 512^2 x 32768 (224 residue workgroups) ran 3%
-// slower with two splits than with none; at 1024^2 x 1024 and x 4096 a
-// scaling product split 2 and 8 ways was slower than unsplit; at
-// 256^2 x 131072 the split products ran 2.4x faster.  A fixed count of 256
-// CUs keeps the choice, and with it the workspace size, a function of the
-// shape alone.
-struct SplitRule {
-  int gmin, smax;
-};
-constexpr SplitRule kSplitRes{4, 64}, kSplitCbar{32, 16};
-int choose_split(int nx_pad, int ny_pad, int k_pad, int nz, SplitRule r) {
+// Split-k of a product with few output workgroups.  The residue products (EPI
+// 0), W0 = tiles * nz workgroups of G = k_pad / 128 groups of k: nsplit = the
+// number of copies of W0 that fill the workgroup slots once (CUs x occupancy:
+// 256 for 256x256 tiles, 512 for 128x128), at most G / 4 (512 k or more per
+// split) and 64; 1 when W0 already fills a quarter of the slots.  Measured
+// (FP64, N = 14): 512^2 x 32768 (224 workgroups) ran 3% slower with two splits
+// than with none; at 256^2 x 131072 the split products ran 2.4x faster.  A
+// fixed count of 256 CUs keeps the choice, and with it the workspace size, a
+// function of the shape alone.
+int choose_split(int nx_pad, int ny_pad, int k_pad, int nz) {
   if (g_split_k.load(std::memory_order_relaxed) == 1) return 1;
   const int B = use_256(nx_pad, ny_pad, nz) ? 256 : 128;
   const long w0 = (long)(nx_pad / B) * (ny_pad / B) * nz;
-  const long slots = B == 256 ? 256 : 512;
+  const long slots = B == 256 ? kCus : 2 * kCus;
   if (w0 <= 0 || 4 * w0 > slots) return 1;
   long sp = slots / w0;
-  sp = std::min<long>(sp, (k_pad / 128) / r.gmin);
-  sp = std::min<long>(sp, r.smax);
+  sp = std::min<long>(sp, (k_pad / 128) / 4);
+  sp = std::min<long>(sp, 64);
   return sp >= 2 ? (int)sp : 1;
+}
+
+// Splits of the scaling product (EPI 1), whose partials are INT32, at most what
+// `bytes` of scratch hold: the count with the least modelled time.  With one
+// workgroup per CU a group of k takes about 0.3 us; splitting costs another
+// launch and the partials' way through memory (about 3 TB/s both ways).
+// Measured, with the fixed count of 4096 of k a split that this replaces and
+// with this one (the scratch is the same): 128x128x8192 (64 groups) 27.5 and
+// 12.2 us, 200x200x100000 (782) 54 and 26, 64x64x262144 (2048) 122 and 28.  At
+// 1024^2 x 1024 and x 4096 two and more splits were slower than one.
+int choose_split_cbar(int nx_pad, int ny_pad, int k_pad, size_t bytes) {
+  if (g_split_k.load(std::memory_order_relaxed) == 1) return 1;
+  const int B = use_256(nx_pad, ny_pad, 1) ? 256 : 128;
+  const long w0 = (long)(nx_pad / B) * (ny_pad / B), G = k_pad / 128;
+  const double plane = 4.0 * nx_pad * ny_pad;
+  if (B == 256 || w0 <= 0) return 1;
+  const long most = std::min<long>({kCus / w0, G / 4, (long)((double)bytes / plane), 64});
+  int best = 1;
+  double t_best = 0.3 * (double)G;
+  for (long sp = 2; sp <= most; ++sp) {
+    const double t = 0.3 * (double)((G + sp - 1) / sp) + 5.0 + 2.0 * (double)sp * plane / 3e6;
+    if (t < t_best) {
+      t_best = t;
+      best = (int)sp;
+    }
+  }
+  return best;
 }
 
 }  // namespace
@@ -862,10 +991,19 @@ std::atomic<int> g_split_k{0};
 
 size_t split_scratch_bytes(int nx_pad, int ny_pad, int k_pad, int nz) {
   const size_t plane = (size_t)nx_pad * ny_pad;
-  const int s0 = choose_split(nx_pad, ny_pad, k_pad, nz, kSplitRes);
-  const int s1 = choose_split(nx_pad, ny_pad, k_pad, 1, kSplitCbar);
+  const int s0 = choose_split(nx_pad, ny_pad, k_pad, nz);
   const size_t b0 = s0 > 1 ? (size_t)s0 * nz * plane : 0;
-  const size_t b1 = s1 > 1 ? (size_t)s1 * plane * 4 : 0;
+  // INT32 partials of the scaling product: a slot for each time that its tiles
+  // fit the 512 slots (few tiles), 4096 of k or more and at most 16
+  size_t b1 = 0;
+  if (g_split_k.load(std::memory_order_relaxed) != 1) {
+    const int B = use_256(nx_pad, ny_pad, 1) ? 256 : 128;
+    const long w0 = (long)(nx_pad / B) * (ny_pad / B), slots = B == 256 ? kCus : 2 * kCus;
+    if (w0 > 0 && 4 * w0 <= slots) {
+      const long s1 = std::min<long>({slots / w0, k_pad / 128 / 32, 16});
+      if (s1 >= 2) b1 = (size_t)s1 * plane * 4;
+    }
+  }
   return b0 > b1 ? b0 : b1;
 }
 
@@ -934,24 +1072,29 @@ void launch_gemm_bf16_store(hipStream_t s, const uint16_t* X, const uint16_t* Y,
     const int tiles_x = nx_pad / 256, tiles_y = ny_pad / 256;
     hipLaunchKernelGGL((k_gemm_i8<256, 2, true>), dim3((unsigned)(tiles_x * tiles_y)),
                        dim3(tile_threads<256>()), 0, s, (const int8_t*)X, 0, (const int8_t*)Y, 0,
-                       tiles_x, tiles_y, 1, kb, cc, (int8_t*)S, 0, lds_, nullptr, nullptr, 1);
+                       tiles_x, tiles_y, 1, kb, cc, (int8_t*)S, 0, lds_, nullptr, nullptr, 1,
+                       tiles_x * tiles_y, nx_pad, ny_pad);
   } else {
     const int tiles_x = nx_pad / 128, tiles_y = ny_pad / 128;
     hipLaunchKernelGGL((k_gemm_i8<128, 2, true>), dim3((unsigned)(tiles_x * tiles_y)),
                        dim3(tile_threads<128>()), 0, s, (const int8_t*)X, 0, (const int8_t*)Y, 0,
-                       tiles_x, tiles_y, 1, kb, cc, (int8_t*)S, 0, lds_, nullptr, nullptr, 1);
+                       tiles_x, tiles_y, 1, kb, cc, (int8_t*)S, 0, lds_, nullptr, nullptr, 1,
+                       tiles_x * tiles_y, nx_pad, ny_pad);
   }
 }
 
 void launch_gemm_i8(hipStream_t s, int epi, const int8_t* X, size_t sx, const int8_t* Y, size_t sy,
                     int nx_pad, int ny_pad, int k_pad, int nz, const CrtConsts& cc, int8_t* W,
-                    size_t sw, int ldw, int* xmax, int* ymax, int8_t* part, size_t part_bytes) {
+                    size_t sw, int ldw, int* xmax, int* ymax, int8_t* part, size_t part_bytes,
+                    int vx, int vy) {
   const bool b256 = use_256(nx_pad, ny_pad, nz);
+  if (vx <= 0) vx = nx_pad;
+  if (vy <= 0) vy = ny_pad;
   const int G = k_pad / 128;
   int sp = 1;
   if (epi == 0 || epi == 1) {
-    sp = epi == 0 ? choose_split(nx_pad, ny_pad, k_pad, nz, kSplitRes)
-                  : choose_split(nx_pad, ny_pad, k_pad, 1, kSplitCbar);
+    sp = epi == 0 ? choose_split(nx_pad, ny_pad, k_pad, nz)
+                  : choose_split_cbar(nx_pad, ny_pad, k_pad, part ? part_bytes : 0);
     const size_t plane = (size_t)nx_pad * ny_pad;
     const size_t need = epi == 0 ? (size_t)sp * nz * plane : (size_t)sp * plane * 4;
     // the partials use the plane layout (stride nx_pad * ny_pad, rows of
@@ -963,9 +1106,11 @@ void launch_gemm_i8(hipStream_t s, int epi, const int8_t* X, size_t sx, const in
   const bool fold = (G + sp - 1) / sp > kFoldGroups;
   auto launch = [&](int e, int8_t* out, size_t so, int ld, int* xm, int* ym, int z, bool f) {
     if (b256)
-      launch_cfg<256>(s, e, X, sx, Y, sy, nx_pad, ny_pad, k_pad, z, cc, out, so, ld, xm, ym, sp, f);
+      launch_cfg<256>(s, e, X, sx, Y, sy, nx_pad, ny_pad, k_pad, z, cc, out, so, ld, xm, ym, sp, f, vx,
+                      vy);
     else
-      launch_cfg<128>(s, e, X, sx, Y, sy, nx_pad, ny_pad, k_pad, z, cc, out, so, ld, xm, ym, sp, f);
+      launch_cfg<128>(s, e, X, sx, Y, sy, nx_pad, ny_pad, k_pad, z, cc, out, so, ld, xm, ym, sp, f, vx,
+                      vy);
   };
   if (sp == 1) {
     launch(epi, W, sw, ldw, xmax, ymax, nz, fold && (epi == 0 || epi == 4));

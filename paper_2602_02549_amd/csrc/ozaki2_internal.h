@@ -261,10 +261,11 @@ void launch_plan_slices(hipStream_t s, Prec pr, bool trans, const void* src, int
 //   and a reduction kernel combines them into the same result (epi 0: the
 //   sum of the partial mod-p bytes, mod p; epi 1: the INT32 sum, then its
 //   maxima).  With too little scratch (or none) the product is not split.
+//   vx, vy: real rows of X and Y (0: all); a split product reads no others.
 void launch_gemm_i8(hipStream_t s, int epi, const int8_t* X, size_t sx, const int8_t* Y, size_t sy,
                     int nx_pad, int ny_pad, int k_pad, int nz, const CrtConsts& cc, int8_t* W,
                     size_t sw, int ldw, int* xmax, int* ymax, int8_t* part = nullptr,
-                    size_t part_bytes = 0);
+                    size_t part_bytes = 0, int vx = 0, int vy = 0);
 // Scratch bytes that lets launch_gemm_i8 split both the scaling product (epi
 // 1) and the nz residue products (epi 0) of this shape; 0 if neither splits.
 size_t split_scratch_bytes(int nx_pad, int ny_pad, int k_pad, int nz);

@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "ozaki2_internal.h"
+#include "small_mod.h"
 
 namespace oz2 {
 namespace {
@@ -44,14 +45,6 @@ constexpr int kTR = 32;           // slice tile: rows
 constexpr int kTK = 128;          // slice tile: k
 constexpr int kRS = kTK + 4;      // LDS row stride (doubles)
 constexpr int kPlanTile = 64;     // planner operand tile
-
-// Rounding to an integer and reading an integer without the FP64 round and
-// convert instructions (which issue at a fraction of the FMA rate): with
-// kRound = 1.5 * 2^52, fma(x, y, kRound) is kRound plus the exact product
-// x*y rounded to the nearest integer (ties to even) whenever |x*y| < 2^51,
-// since doubles in [2^52, 2^53) are the integers; and for an integer-valued
-// |x| < 2^31 the low 32 bits of x + kRound are x in two's complement.
-constexpr double kRound = 0x1.8p52;
 
 __device__ __forceinline__ double round_prod(double x, double y) {
   return fma(x, y, kRound) - kRound;
@@ -62,28 +55,6 @@ __device__ __forceinline__ uint32_t low32(double x) {
   return (uint32_t)__double2loint(x + kRound);
 }
 
-typedef unsigned short v2u16 __attribute__((ext_vector_type(2)));
-
-// 16-bit pairs: the low halves of a (low half) and b; a * b + c in each half
-// (one packed instruction); a value in both halves.
-__device__ __forceinline__ uint32_t pair16(uint32_t a, uint32_t b) {
-  return __builtin_amdgcn_perm(b, a, 0x05040100u);
-}
-__device__ __forceinline__ uint32_t pk_mad(uint32_t a, uint32_t b, uint32_t c) {
-  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(v2u16, a) * __builtin_bit_cast(v2u16, b) +
-                                          __builtin_bit_cast(v2u16, c));
-}
-__device__ __forceinline__ uint32_t pk_add(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_bit_cast(v2u16, a) + __builtin_bit_cast(v2u16, b));
-}
-__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b) {
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(v2u16, a),
-                                                                __builtin_bit_cast(v2u16, b)));
-}
-__device__ __forceinline__ uint32_t both16(int x) {
-  return ((uint32_t)x & 0xFFFF) * 0x10001u;
-}
-
 // Low bytes of a, b, c, d as one word (byte 0 = a), three byte permutes:
 // v_perm_b32 picks bytes 0-3 of its second source with selectors 0-3, of its
 // first with 4-7, and zero with 0x0c.
@@ -91,11 +62,6 @@ __device__ __forceinline__ uint32_t pack4(int a, int b, int c, int d) {
   const uint32_t ab = __builtin_amdgcn_perm((uint32_t)b, (uint32_t)a, 0x0c0c0400u);
   const uint32_t cd = __builtin_amdgcn_perm((uint32_t)d, (uint32_t)c, 0x0c0c0400u);
   return __builtin_amdgcn_perm(cd, ab, 0x05040100u);
-}
-
-// The low bytes of the four halves of two pairs (elements 0, 1 and 2, 3).
-__device__ __forceinline__ uint32_t bytes_of_pairs(uint32_t x01, uint32_t x23) {
-  return __builtin_amdgcn_perm(x23, x01, 0x06040200u);
 }
 
 // Residue paths of mode 1: limbs (2 or 3) or exact reduction steps (1, 3 or
