@@ -9,17 +9,112 @@
 //   C     = C'' * 2^(-mu_i - nu_j), one rounding.
 // Every operation is an explicit fma / single rounding (built with
 // -ffp-contract=off), so the result is deterministic.
+//
+// Bound by memory: N bytes read and one entry written per entry of C.  So the
+// loads of the next moduli go out before a group is used, C leaves in whole
+// lines (through LDS where a lane's entries are more than one store), and both
+// are marked as streaming, since nothing here reads a line twice.  FP64, N = 14,
+// 8192^2 (1.48 GB): 307 us before, 275 with the first two, 250 with all three
+// (5.9 TB/s); FP32, N = 7: 167 and 127 us; 4093 x 4095 with unaligned columns
+// 98 and 72 us.
 #include <cstdint>
 #include <type_traits>
 
 #include "ozaki2_internal.h"
+#include "small_mod.h"
 
 namespace oz2 {
 namespace {
 
+template <typename V>
+__device__ __forceinline__ V load_stream(const V* p) {
+  return __builtin_nontemporal_load(p);
+}
+
+template <typename T, int E>
+__device__ __forceinline__ void store_entry(T* __restrict__ p, const T* v) {
+  typedef T V __attribute__((ext_vector_type(E)));
+  if (E == 1 || ((uintptr_t)p & (E * sizeof(T) - 1)) == 0) {
+    __builtin_nontemporal_store(*reinterpret_cast<const V*>(v), reinterpret_cast<V*>(p));
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) p[e] = v[e];
+  }
+}
+
+// Place of a thread: row chunk `i0 / R` of column j, and whether it has one (a
+// thread past the last takes the last column again and stores nothing).  The
+// block's first place is divided once, the threads' with 32 bits.
+struct CrtPlace {
+  int j, i0;
+  bool in;
+};
+__device__ __forceinline__ CrtPlace crt_place(int64_t block, int m, int n, int R) {
+  const unsigned chunks = (unsigned)cdiv_i(m, R);
+  const uint64_t g0 = (uint64_t)block * 256;
+  unsigned j0, r0;
+  if (g0 >> 32) {
+    j0 = (unsigned)(g0 / chunks);
+    r0 = (unsigned)(g0 - (uint64_t)j0 * chunks);
+  } else {
+    j0 = (unsigned)g0 / chunks;
+    r0 = (unsigned)g0 - j0 * chunks;
+  }
+  const unsigned t = r0 + threadIdx.x, dj = t / chunks;
+  const int j = (int)(j0 + dj);
+  return {j < n ? j : n - 1, (int)(t - dj * chunks) * R, j < n};
+}
+
+// The R entries of E values that each lane of a wave holds (rows i0.. of column
+// j), through LDS so that consecutive lanes store consecutive entries: whole
+// lines per store at any alignment of C.
+template <typename T, int R, int E>
+struct CrtStage {
+  T v[4][64 * R * E];
+};
+template <typename T, int R, int E>
+__device__ __forceinline__ void store_rows(CrtStage<T, R, E>& lds, T* __restrict__ C, int ldc, int m,
+                                           const CrtPlace& pl, const T (&out)[R * E]) {
+  const int lane = threadIdx.x & 63;
+  const int64_t off = (int64_t)pl.j * ldc + pl.i0;
+  const int have = pl.in ? min(m - pl.i0, R) : 0;
+  if constexpr (sizeof(T) * R * E == 16) {               // a lane's entries are one store
+    typedef T V __attribute__((ext_vector_type(R * E)));
+    if (__all(have == R && ((uintptr_t)(C + off * E) & 15) == 0)) {
+      V v;
+#pragma unroll
+      for (int e = 0; e < R * E; ++e) v[e] = out[e];
+      __builtin_nontemporal_store(v, reinterpret_cast<V*>(C + off * E));
+      return;
+    }
+  }
+  T* st = lds.v[threadIdx.x >> 6];
+#pragma unroll
+  for (int e = 0; e < R * E; ++e) st[lane * R * E + e] = out[e];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int64_t off0 = ((int64_t)__builtin_amdgcn_readfirstlane((int)(off >> 32)) << 32) |
+                       (uint32_t)__builtin_amdgcn_readfirstlane((int)off);
+  // a wave inside one column, all rows real: consecutive entries of C
+  const bool whole = __all(have == R && off == off0 + lane * R);
+#pragma unroll
+  for (int s = 0; s < R; ++s) {
+    const int q = 64 * s + lane;                         // entry of the wave
+    int64_t o = off0 + q;
+    bool in = true;
+    if (!whole) {
+      const int src = q / R, e = q % R;
+      const int64_t lo = (uint32_t)__shfl((int)off, src), hi = __shfl((int)(off >> 32), src);
+      o = (hi << 32 | lo) + e;
+      in = e < __shfl(have, src);
+    }
+    if (in) store_entry<T, E>(C + o * E, st + q * E);
+  }
+}
+
 // One thread handles R = kCrtRows consecutive rows i of one column j: one
-// R-byte load per modulus (64 R contiguous bytes per wave) and, when C is
-// aligned for it, 2-element vector stores.
+// R-byte load per modulus (64 R contiguous bytes per wave).
 // Thread g (g = 0 .. ceil(m/R) n - 1) takes row chunk g % ceil(m/R) of column
 // g / ceil(m/R): consecutive threads walk down a column and continue in the
 // next, so small-m problems keep every lane busy.
@@ -36,38 +131,50 @@ __device__ __forceinline__ void crt_sums(const int8_t* __restrict__ wp, size_t s
       WordT;
 #pragma unroll
   for (int e = 0; e < R; ++e) c1[e] = c2[e] = 0.0;
-  // Moduli in groups of 4, loads first (clamped to the last slice); a modulus
-  // past N gets weight 0, and fma(0, w, c) = c, so the l-ordered fma chains
-  // are unchanged.
+  // Moduli in groups of 4; the next group's loads (clamped to the last slice) go
+  // out before a group is used, so that four to eight are under way.
   // An INT8 value w with stored byte b becomes a double without the convert
   // instruction: the bit pattern 0x43300000:(b ^ 0x80) is 2^52 + w + 128, and
   // subtracting 2^52 + 128 is exact.
-  for (int l0 = 0; l0 < cc.N; l0 += 4) {
-    uint64_t wv[4];
+  auto load = [&](int l0, WordT (&v)[4]) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int8_t* src = wp + (size_t)min(l0 + u, cc.N - 1) * sw;
       if constexpr (ALIGNED) {
-        wv[u] = *reinterpret_cast<const WordT*>(src);
+        v[u] = load_stream(reinterpret_cast<const WordT*>(src));
       } else {
-        wv[u] = 0;
+        v[u] = 0;
 #pragma unroll
-        for (int e = 0; e < R; ++e) wv[u] |= (uint64_t)(uint8_t)src[e] << (8 * e);
+        for (int e = 0; e < R; ++e) v[u] |= (WordT)((WordT)(uint8_t)src[e] << (8 * e));
       }
     }
+  };
+  auto use = [&](WordT v, double s1, double s2) {
+    const uint64_t biased = (uint64_t)v ^ 0x8080808080808080ull;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int e = 0; e < R; ++e) {
+      const int byte = (int)((biased >> (8 * e)) & 0xFF);
+      const double w = __hiloint2double(0x43300000, byte) - 4503599627370624.0;  // 2^52 + 128
+      c1[e] = fma(s1, w, c1[e]);
+      if (sizeof(T) == 8) c2[e] = fma(s2, w, c2[e]);
+    }
+  };
+  WordT cur[4], next[4];
+  load(0, cur);
+  int l0 = 0;
+  for (; l0 + 4 <= cc.N; l0 += 4) {
+    if (l0 + 4 < cc.N) load(l0 + 4, next);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) use(cur[u], cc.s1[l0 + u], cc.s2[l0 + u]);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) cur[u] = next[u];
+  }
+  // up to three more; a modulus past N gets weight 0, and fma(0, w, c) = c
+  if (l0 < cc.N) {
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
       const int l = min(l0 + u, cc.N - 1);
-      const bool in = l0 + u < cc.N;
-      const double s1 = in ? cc.s1[l] : 0.0, s2 = in ? cc.s2[l] : 0.0;
-      const uint64_t biased = wv[u] ^ 0x8080808080808080ull;
-#pragma unroll
-      for (int e = 0; e < R; ++e) {
-        const int byte = (int)((biased >> (8 * e)) & 0xFF);
-        const double w = __hiloint2double(0x43300000, byte) - 4503599627370624.0;  // 2^52 + 128
-        c1[e] = fma(s1, w, c1[e]);
-        if (sizeof(T) == 8) c2[e] = fma(s2, w, c2[e]);
-      }
+      use(cur[u], l0 + u < cc.N ? cc.s1[l] : 0.0, l0 + u < cc.N ? cc.s2[l] : 0.0);
     }
   }
 }
@@ -103,28 +210,27 @@ __device__ __forceinline__ T crt_value(double c1, double c2, const CrtConsts& cc
 
 template <typename T, int R, bool DBG = false>
 __device__ __forceinline__ void crt_body(const int8_t* __restrict__ W, size_t sw, int ldw,
-                                const int* __restrict__ mu, const int* __restrict__ nu, int m,
-                                int n, const CrtConsts& cc, const int* __restrict__ flag,
-                                T* __restrict__ C, int ldc, int64_t g,
-                                double* __restrict__ dbg = nullptr) {
-  static_assert(R == 2 || R == 4 || R == 8, "rows per thread");
-  const int chunks = cdiv_i(m, R);
-  const int j = (int)(g / chunks);
-  if (j >= n) return;
-  const int i0 = (int)(g - (int64_t)j * chunks) * R;
-  double c1[R], c2[R];
-  crt_sums<T, R>(W + (size_t)j * ldw + i0, sw, cc, c1, c2);
+                                         const int* __restrict__ mu, const int* __restrict__ nu,
+                                         int m, int n, const CrtConsts& cc,
+                                         const int* __restrict__ flag, T* __restrict__ C, int ldc,
+                                         int64_t block, double* __restrict__ dbg = nullptr) {
+  __shared__ __attribute__((aligned(16))) CrtStage<T, R, 1> lds;
+  const CrtPlace pl = crt_place(block, m, n, R);
   const bool bad = *flag != 0;
-  const int nuj = nu[j];
+  const int nuj = nu[pl.j];
+  int ex[R];
+#pragma unroll
+  for (int e = 0; e < R; ++e) ex[e] = -mu[min(pl.i0 + e, m - 1)] - nuj;
+  double c1[R], c2[R];
+  crt_sums<T, R>(W + (size_t)pl.j * ldw + pl.i0, sw, cc, c1, c2);
   T out[R];
 #pragma unroll
   for (int e = 0; e < R; ++e) {
-    const int i = min(i0 + e, m - 1);
     double q, cppd;
-    out[e] = crt_value<T>(c1[e], c2[e], cc, -mu[i] - nuj, bad, &q, &cppd);
+    out[e] = crt_value<T>(c1[e], c2[e], cc, ex[e], bad, &q, &cppd);
     if constexpr (DBG) {
-      if (i0 + e < m) {
-        const size_t mn = (size_t)m * n, o = (size_t)j * m + i0 + e;
+      if (pl.in && pl.i0 + e < m) {
+        const size_t mn = (size_t)m * n, o = (size_t)pl.j * m + pl.i0 + e;
         dbg[o] = c1[e];
         dbg[mn + o] = c2[e];
         dbg[2 * mn + o] = q;
@@ -132,27 +238,7 @@ __device__ __forceinline__ void crt_body(const int8_t* __restrict__ W, size_t sw
       }
     }
   }
-  T* cp = C + (size_t)j * ldc + i0;
-  if (i0 + R <= m && ((uintptr_t)cp & (2 * sizeof(T) - 1)) == 0) {
-#pragma unroll
-    for (int e = 0; e < R; e += 2) {
-      if (sizeof(T) == 8) {
-        double2 v;
-        v.x = (double)out[e];
-        v.y = (double)out[e + 1];
-        *reinterpret_cast<double2*>(cp + e) = v;
-      } else {
-        float2 v;
-        v.x = (float)out[e];
-        v.y = (float)out[e + 1];
-        *reinterpret_cast<float2*>(cp + e) = v;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < R; ++e)
-      if (i0 + e < m) cp[e] = out[e];
-  }
+  store_rows<T, R, 1>(lds, C, ldc, m, pl, out);
 }
 
 // Complex output: the real parts from (Wr, mur) and the imaginary parts from
@@ -161,37 +247,6 @@ __device__ __forceinline__ void crt_body(const int8_t* __restrict__ W, size_t sw
 // loads of a partial last chunk read up to row rup(m, R) - 1 past Wr and Wi,
 // inside the padded column (the embedding's column holds 2m rows padded to a
 // multiple of 128, at least m + rup(m, R)).
-// R consecutive complex entries (rows i0.., column j) as interleaved pairs,
-// with 2-element vector stores when the address allows.
-template <typename T, int R>
-__device__ __forceinline__ void store_complex(T* __restrict__ C, int ldc, int j, int i0, int m,
-                                              const T (&re)[R], const T (&im)[R]) {
-  T* cp = C + 2 * ((size_t)j * ldc + i0);
-  if (i0 + R <= m && ((uintptr_t)cp & (2 * sizeof(T) - 1)) == 0) {
-#pragma unroll
-    for (int e = 0; e < R; ++e) {
-      if (sizeof(T) == 8) {
-        double2 v;
-        v.x = (double)re[e];
-        v.y = (double)im[e];
-        *reinterpret_cast<double2*>(cp + 2 * e) = v;
-      } else {
-        float2 v;
-        v.x = (float)re[e];
-        v.y = (float)im[e];
-        *reinterpret_cast<float2*>(cp + 2 * e) = v;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < R; ++e)
-      if (i0 + e < m) {
-        cp[2 * e] = re[e];
-        cp[2 * e + 1] = im[e];
-      }
-  }
-}
-
 template <typename T, int R>
 __device__ __forceinline__ void crt_complex_body(const int8_t* __restrict__ Wr,
                                                  const int8_t* __restrict__ Wi, size_t sw, int ldw,
@@ -199,29 +254,29 @@ __device__ __forceinline__ void crt_complex_body(const int8_t* __restrict__ Wr,
                                                  const int* __restrict__ mui,
                                                  const int* __restrict__ nu, int m, int n,
                                                  const CrtConsts& cc, const int* __restrict__ flag,
-                                                 T* __restrict__ C, int ldc, int64_t g) {
-  const int chunks = cdiv_i(m, R);
-  const int j = (int)(g / chunks);
-  if (j >= n) return;
-  const int i0 = (int)(g - (int64_t)j * chunks) * R;
+                                                 T* __restrict__ C, int ldc, int64_t block) {
+  __shared__ __attribute__((aligned(16))) CrtStage<T, R, 2> lds;
+  const CrtPlace pl = crt_place(block, m, n, R);
+  const size_t o = (size_t)pl.j * ldw + pl.i0;
   const bool bad = *flag != 0;
-  const int nuj = nu[j];
+  const int nuj = nu[pl.j];
   double c1[R], c2[R], q, cppd;
-  T re[R], im[R];
-  crt_sums<T, R>(Wr + (size_t)j * ldw + i0, sw, cc, c1, c2);
+  T out[2 * R];
+  crt_sums<T, R>(Wr + o, sw, cc, c1, c2);
 #pragma unroll
   for (int e = 0; e < R; ++e)
-    re[e] = crt_value<T>(c1[e], c2[e], cc, -mur[min(i0 + e, m - 1)] - nuj, bad, &q, &cppd);
+    out[2 * e] = crt_value<T>(c1[e], c2[e], cc, -mur[min(pl.i0 + e, m - 1)] - nuj, bad, &q, &cppd);
   // the imaginary rows of the real embedding start at row m, which need not
   // be a multiple of R (uniform over the launch)
   if (((uintptr_t)Wi & (R - 1)) == 0)
-    crt_sums<T, R, true>(Wi + (size_t)j * ldw + i0, sw, cc, c1, c2);
+    crt_sums<T, R, true>(Wi + o, sw, cc, c1, c2);
   else
-    crt_sums<T, R, false>(Wi + (size_t)j * ldw + i0, sw, cc, c1, c2);
+    crt_sums<T, R, false>(Wi + o, sw, cc, c1, c2);
 #pragma unroll
   for (int e = 0; e < R; ++e)
-    im[e] = crt_value<T>(c1[e], c2[e], cc, -mui[min(i0 + e, m - 1)] - nuj, bad, &q, &cppd);
-  store_complex<T, R>(C, ldc, j, i0, m, re, im);
+    out[2 * e + 1] =
+        crt_value<T>(c1[e], c2[e], cc, -mui[min(pl.i0 + e, m - 1)] - nuj, bad, &q, &cppd);
+  store_rows<T, R, 2>(lds, C, ldc, m, pl, out);
 }
 
 // The 3-product form (reading R25 of the complex GEMM): per modulus l the
@@ -231,8 +286,9 @@ __device__ __forceinline__ void crt_complex_body(const int8_t* __restrict__ Wr,
 // lie in [lo, hi] = [(1-p)/2, (p-1)/2] (odd p) or [-128, 127] (p = 256), so
 // a difference or sum of two lies in [-(p-1), p-1] and one correction by p
 // brings it back into [lo, hi]: W1 - W2 directly, W3 - W1 - W2 as W3 minus
-// the corrected W1 + W2.  Moduli in groups of 4, loads first; a modulus past
-// N gets weight 0 (fma(0, w, c) = c).  W1, W2, W3 are whole planes
+// the corrected W1 + W2, two values per packed 16-bit instruction (12.5 integer
+// operations per modulus and entry against 26 one value at a time, which took
+// longer than the loads).  Moduli as in crt_sums.  W1, W2, W3 are whole planes
 // (tile-aligned), so each R-byte load is aligned.
 template <typename T, int R>
 __device__ __forceinline__ void crt_sums_3m(const int8_t* __restrict__ w1,
@@ -240,40 +296,45 @@ __device__ __forceinline__ void crt_sums_3m(const int8_t* __restrict__ w1,
                                             const int8_t* __restrict__ w3, size_t sw,
                                             const CrtConsts& cc, double (&c1r)[R], double (&c2r)[R],
                                             double (&c1i)[R], double (&c2i)[R]) {
-  typedef typename std::conditional<R == 2, uint16_t,
-                                    typename std::conditional<R == 4, uint32_t, uint64_t>::type>::type
-      WordT;
 #pragma unroll
   for (int e = 0; e < R; ++e) c1r[e] = c2r[e] = c1i[e] = c2i[e] = 0.0;
-  for (int l0 = 0; l0 < cc.N; l0 += 4) {
-    uint64_t a[4], b[4], c[4];
+  static_assert(R == 4, "two pairs");
+  struct Three {
+    uint32_t a[4], b[4], c[4];
+  } cur, next;
+  auto load = [&](int l0, Three& v) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const size_t off = (size_t)min(l0 + u, cc.N - 1) * sw;
-      a[u] = *reinterpret_cast<const WordT*>(w1 + off);
-      b[u] = *reinterpret_cast<const WordT*>(w2 + off);
-      c[u] = *reinterpret_cast<const WordT*>(w3 + off);
+      v.a[u] = load_stream(reinterpret_cast<const uint32_t*>(w1 + off));
+      v.b[u] = load_stream(reinterpret_cast<const uint32_t*>(w2 + off));
+      v.c[u] = load_stream(reinterpret_cast<const uint32_t*>(w3 + off));
     }
+  };
+  auto use = [&](uint32_t wa, uint32_t wb, uint32_t wc, int p, double s1, double s2) {
+    const int lo = (p - 1) / 2 + 1 - p;
+    // x - lo for the representative x of a value in [lo, lo + p): of d, d + p
+    // and d - p the smallest as an unsigned 16-bit number
+    auto fix = [&](uint32_t d, int bias) {
+      return pk_min(pk_min(pk_add(d, both16(bias - lo)), pk_add(d, both16(bias - lo + p))),
+                    pk_add(d, both16(bias - lo - p)));
+    };
+    const uint32_t a = wa ^ 0x80808080u, b = wb ^ 0x80808080u, c = wc ^ 0x80808080u;
+    // 2^52 + (x - lo) less 2^52 - lo is x exactly
+    const double base = 4503599627370496.0 - (double)lo;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int l = min(l0 + u, cc.N - 1);
-      const bool in = l0 + u < cc.N;
-      const double s1 = in ? cc.s1[l] : 0.0, s2 = in ? cc.s2[l] : 0.0;
-      const int p = cc.mod[l].p, hi = (p - 1) / 2, lo = hi + 1 - p;
-      auto fix = [&](int x) {
-        x -= x > hi ? p : 0;
-        return x + (x < lo ? p : 0);
-      };
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t sel = h ? 0x0c030c02u : 0x0c010c00u;
+      const uint32_t a2 = __builtin_amdgcn_perm(0, a, sel), b2 = __builtin_amdgcn_perm(0, b, sel),
+                     c2 = __builtin_amdgcn_perm(0, c, sel);
+      const uint32_t xr = fix(pk_sub(a2, b2), 0);
+      const uint32_t xs = fix(pk_add(a2, b2), -256);     // t1 + t2, less lo
+      const uint32_t xi = fix(pk_sub(c2, xs), -128 - lo);  // t3 - (t1 + t2)
 #pragma unroll
-      for (int e = 0; e < R; ++e) {
-        const int t1 = (int)(int8_t)(a[u] >> (8 * e)), t2 = (int)(int8_t)(b[u] >> (8 * e)),
-                  t3 = (int)(int8_t)(c[u] >> (8 * e));
-        // w in [-128, 127] becomes a double without the convert instruction,
-        // as in crt_sums: 0x43300000:(w + 128) is 2^52 + w + 128
-        const double wr =
-            __hiloint2double(0x43300000, fix(t1 - t2) + 128) - 4503599627370624.0;
-        const double wi =
-            __hiloint2double(0x43300000, fix(t3 - fix(t1 + t2)) + 128) - 4503599627370624.0;
+      for (int q = 0; q < 2; ++q) {
+        const int e = 2 * h + q;
+        const double wr = __hiloint2double(0x43300000, q ? xr >> 16 : xr & 0xFFFF) - base;
+        const double wi = __hiloint2double(0x43300000, q ? xi >> 16 : xi & 0xFFFF) - base;
         c1r[e] = fma(s1, wr, c1r[e]);
         c1i[e] = fma(s1, wi, c1i[e]);
         if (sizeof(T) == 8) {
@@ -281,6 +342,23 @@ __device__ __forceinline__ void crt_sums_3m(const int8_t* __restrict__ w1,
           c2i[e] = fma(s2, wi, c2i[e]);
         }
       }
+    }
+  };
+  load(0, cur);
+  int l0 = 0;
+  for (; l0 + 4 <= cc.N; l0 += 4) {
+    if (l0 + 4 < cc.N) load(l0 + 4, next);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      use(cur.a[u], cur.b[u], cur.c[u], cc.mod[l0 + u].p, cc.s1[l0 + u], cc.s2[l0 + u]);
+    cur = next;
+  }
+  if (l0 < cc.N) {                                       // as in crt_sums
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+      const int l = min(l0 + u, cc.N - 1);
+      use(cur.a[u], cur.b[u], cur.c[u], cc.mod[l].p, l0 + u < cc.N ? cc.s1[l] : 0.0,
+          l0 + u < cc.N ? cc.s2[l] : 0.0);
     }
   }
 }
@@ -292,57 +370,56 @@ __device__ __forceinline__ void crt_3m_body(const int8_t* __restrict__ W1,
                                             const int* __restrict__ mu, const int* __restrict__ nu,
                                             int m, int n, const CrtConsts& cc,
                                             const int* __restrict__ flag, T* __restrict__ C,
-                                            int ldc, int64_t g) {
-  const int chunks = cdiv_i(m, R);
-  const int j = (int)(g / chunks);
-  if (j >= n) return;
-  const int i0 = (int)(g - (int64_t)j * chunks) * R;
+                                            int ldc, int64_t block) {
+  __shared__ __attribute__((aligned(16))) CrtStage<T, R, 2> lds;
+  const CrtPlace pl = crt_place(block, m, n, R);
   const bool bad = *flag != 0;
-  const int nuj = nu[j];
-  const size_t o = (size_t)j * ldw + i0;
+  const int nuj = nu[pl.j];
+  const size_t o = (size_t)pl.j * ldw + pl.i0;
   double c1r[R], c2r[R], c1i[R], c2i[R], q, cppd;
   crt_sums_3m<T, R>(W1 + o, W2 + o, W3 + o, sw, cc, c1r, c2r, c1i, c2i);
-  T re[R], im[R];
+  T out[2 * R];
 #pragma unroll
   for (int e = 0; e < R; ++e) {
-    const int ex = -mu[min(i0 + e, m - 1)] - nuj;
-    re[e] = crt_value<T>(c1r[e], c2r[e], cc, ex, bad, &q, &cppd);
-    im[e] = crt_value<T>(c1i[e], c2i[e], cc, ex, bad, &q, &cppd);
+    const int ex = -mu[min(pl.i0 + e, m - 1)] - nuj;
+    out[2 * e] = crt_value<T>(c1r[e], c2r[e], cc, ex, bad, &q, &cppd);
+    out[2 * e + 1] = crt_value<T>(c1i[e], c2i[e], cc, ex, bad, &q, &cppd);
   }
-  store_complex<T, R>(C, ldc, j, i0, m, re, im);
+  store_rows<T, R, 2>(lds, C, ldc, m, pl, out);
 }
 
+// The constants come last, so that the arguments before them share a line or two.
 template <typename T, int R>
 __global__ __launch_bounds__(256) void k_crt_3m(const int8_t* __restrict__ W1,
                                                 const int8_t* __restrict__ W2,
                                                 const int8_t* __restrict__ W3, size_t sw, int ldw,
                                                 const int* __restrict__ mu,
                                                 const int* __restrict__ nu, int m, int n,
-                                                CrtConsts cc, const int* __restrict__ flag, int* __restrict__ status,
-                                                T* __restrict__ C, int ldc) {
+                                                const int* __restrict__ flag,
+                                                int* __restrict__ status, T* __restrict__ C,
+                                                int ldc, CrtConsts cc) {
+  crt_3m_body<T, R>(W1, W2, W3, sw, ldw, mu, nu, m, n, cc, flag, C, ldc, blockIdx.x);
   if (blockIdx.x == 0) fold_status(flag, status);
-  crt_3m_body<T, R>(W1, W2, W3, sw, ldw, mu, nu, m, n, cc, flag, C, ldc,
-                    (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 template <typename T, int R>
 __global__ __launch_bounds__(256) void k_crt_complex(
     const int8_t* __restrict__ Wr, const int8_t* __restrict__ Wi, size_t sw, int ldw,
     const int* __restrict__ mur, const int* __restrict__ mui, const int* __restrict__ nu, int m,
-    int n, CrtConsts cc, const int* __restrict__ flag, int* __restrict__ status, T* __restrict__ C, int ldc) {
+    int n, const int* __restrict__ flag, int* __restrict__ status, T* __restrict__ C, int ldc,
+    CrtConsts cc) {
+  crt_complex_body<T, R>(Wr, Wi, sw, ldw, mur, mui, nu, m, n, cc, flag, C, ldc, blockIdx.x);
   if (blockIdx.x == 0) fold_status(flag, status);
-  crt_complex_body<T, R>(Wr, Wi, sw, ldw, mur, mui, nu, m, n, cc, flag, C, ldc,
-                         (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 template <typename T, int R>
 __global__ __launch_bounds__(256) void k_crt(const int8_t* __restrict__ W, size_t sw, int ldw,
                                              const int* __restrict__ mu, const int* __restrict__ nu,
-                                             int m, int n, CrtConsts cc,
-                                             const int* __restrict__ flag, int* __restrict__ status, T* __restrict__ C, int ldc) {
+                                             int m, int n, const int* __restrict__ flag,
+                                             int* __restrict__ status, T* __restrict__ C, int ldc,
+                                             CrtConsts cc) {
+  crt_body<T, R>(W, sw, ldw, mu, nu, m, n, cc, flag, C, ldc, blockIdx.x);
   if (blockIdx.x == 0) fold_status(flag, status);
-  crt_body<T, R>(W, sw, ldw, mu, nu, m, n, cc, flag, C, ldc,
-                 (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 template <typename T>
@@ -352,8 +429,7 @@ __global__ __launch_bounds__(256) void k_crt_debug(const int8_t* __restrict__ W,
                                                    CrtConsts cc, const int* __restrict__ flag,
                                                    T* __restrict__ C, int ldc,
                                                    double* __restrict__ dbg) {
-  crt_body<T, kCrtRows, true>(W, sw, ldw, mu, nu, m, n, cc, flag, C, ldc,
-                              (int64_t)blockIdx.x * 256 + threadIdx.x, dbg);
+  crt_body<T, kCrtRows, true>(W, sw, ldw, mu, nu, m, n, cc, flag, C, ldc, blockIdx.x, dbg);
 }
 
 template <typename T>
@@ -363,9 +439,9 @@ __global__ __launch_bounds__(256) void kg_crt(const ProbDesc* __restrict__ P,
                                               int* __restrict__ status) {
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
-  if (e.y == 0) fold_status(d.flag, status);
   crt_body<T, kCrtRows>(d.W, (size_t)d.np * d.mp, d.mp, d.mu, d.nu, d.m, d.n, ctab[d.N], d.flag,
-                        (T*)d.C, d.ldc, (int64_t)e.y * 256 + threadIdx.x);
+                        (T*)d.C, d.ldc, e.y);
+  if (e.y == 0) fold_status(d.flag, status);
 }
 
 template <typename T>
@@ -395,7 +471,7 @@ void launch_crt_t(hipStream_t s, const int8_t* W, size_t sw, int ldw, const int*
                   int m, int n, const CrtConsts& cc, const int* flag, int* status,
                   void* C, int ldc) {
   hipLaunchKernelGGL((k_crt<T, kCrtRows>), dim3((unsigned)crt_blocks(m, n)), dim3(256), 0, s, W, sw,
-                     ldw, mu, nu, m, n, cc, flag, status, (T*)C, ldc);
+                     ldw, mu, nu, m, n, flag, status, (T*)C, ldc, cc);
 }
 
 }  // namespace
@@ -415,10 +491,10 @@ void launch_crt_3m(hipStream_t s, Prec pr, const int8_t* W1, const int8_t* W2, c
   const dim3 grid((unsigned)crt_blocks(m, n)), block(256);
   if (pr == Prec::F64)
     hipLaunchKernelGGL((k_crt_3m<double, kCrtRows>), grid, block, 0, s, W1, W2, W3, sw, ldw, mu, nu,
-                       m, n, cc, flag, status, (double*)C, ldc);
+                       m, n, flag, status, (double*)C, ldc, cc);
   else
     hipLaunchKernelGGL((k_crt_3m<float, kCrtRows>), grid, block, 0, s, W1, W2, W3, sw, ldw, mu, nu,
-                       m, n, cc, flag, status, (float*)C, ldc);
+                       m, n, flag, status, (float*)C, ldc, cc);
 }
 
 void launch_crt_complex(hipStream_t s, Prec pr, const int8_t* Wr, const int8_t* Wi, size_t sw,
@@ -427,10 +503,10 @@ void launch_crt_complex(hipStream_t s, Prec pr, const int8_t* Wr, const int8_t* 
   const dim3 grid((unsigned)crt_blocks(m, n)), block(256);
   if (pr == Prec::F64)
     hipLaunchKernelGGL((k_crt_complex<double, kCrtRows>), grid, block, 0, s, Wr, Wi, sw, ldw, mur,
-                       mui, nu, m, n, cc, flag, status, (double*)C, ldc);
+                       mui, nu, m, n, flag, status, (double*)C, ldc, cc);
   else
     hipLaunchKernelGGL((k_crt_complex<float, kCrtRows>), grid, block, 0, s, Wr, Wi, sw, ldw, mur,
-                       mui, nu, m, n, cc, flag, status, (float*)C, ldc);
+                       mui, nu, m, n, flag, status, (float*)C, ldc, cc);
 }
 
 void launch_crt_debug(hipStream_t s, Prec pr, const int8_t* W, size_t sw, int ldw, const int* mu,
