@@ -1,4 +1,4 @@
-// INT8 x INT8 -> INT32 matrix-core products (CDNA4 v_mfma_i32_32x32x32_i8):
+// INT8 x INT8 -> INT32 matrix-core products (CDNA4 v_mfma_i32_16x16x64_i8):
 //   epi 0: the N residue products C'_l = A'_l B'_l of Algorithm 3 with the
 //          reduction W_l = mod(C'_l, p_l) fused into the epilogue;
 //   epi 1: the scaling product Cbar = Abar Bbar of Algorithm 2, of which only
@@ -11,18 +11,28 @@
 // needs no bounds checks:  D[x][y] = sum_h X[x][h] Y[y][h], with X the A side
 // (x = output row i) and Y the B side (y = output column j).  In the MFMA
 // accumulator layout a lane holds 4 consecutive x for one y, so the W_l bytes
-// of 4 consecutive rows i are packed into one 32-bit store of the
-// column-major W_l[j][i].
+// of 4 consecutive rows i are packed into one word, and four such words into
+// one 16-byte store of the column-major W_l[j][i].
+//
+// Instruction: large products run at the clock that the power limit leaves, not
+// at the issue rate, so the instruction with the least energy per product is
+// the fastest.  16x16x64 adds 64 products for each accumulator it reads and
+// writes, 32x32x32 half as many.  With random bytes held in registers the first
+// ran at 3.99 PO/s (4.05 when consecutive instructions share an operand), the
+// second at 3.36; with zeros both at 4.9.  Here: 14 products of 8192^3 6410 and
+// 5800 us (2.43 and 2.65 PO/s), 18 of 4096^3 1060 and 970, 7 of 16384^3 27.2
+// and 24.3 ms.  The BF16 product (the planner's lower bound of |A||B|) stays
+// with 32x32x16, whose order of FP32 additions its results depend on.
 //
 // Tiling: a workgroup of NWX x NWY waves computes a BX x BY tile; each wave
-// owns (BX/NWX) x (BY/NWY) as blocks of 32 x 32.  A 256 x 256 tile runs 8
-// waves (4 x 2, each 64 x 128: two waves per SIMD, so one wave's MFMAs
-// overlap the other's LDS reads and barrier waits), a 128 x 128 tile 4 waves
-// (2 x 2) with two workgroups per CU.  K advances in groups of 128
-// bytes through a ring of two LDS group buffers (four where a CU holds one
-// workgroup of 128 x 128): direct global->LDS copies fill the buffers ahead
-// (every 128-byte line of an operand row requested as one unit) while the
-// MFMAs consume one.  BF16 operands (the planner's lower bound of |A||B|) run
+// owns (BX/NWX) x (BY/NWY).  A 256 x 256 tile runs 8 waves (4 x 2, each 64 x
+// 128: two waves per SIMD, so one wave's MFMAs overlap the other's LDS reads
+// and barrier waits; four waves of 128 x 128 read a third less from LDS but
+// took 37% longer), a 128 x 128 tile 4 waves (2 x 2) with two workgroups per
+// CU.  K advances in groups of 128 bytes through a ring of two LDS group
+// buffers (four where a CU holds one workgroup of 128 x 128): direct
+// global->LDS copies fill the buffers ahead (every 128-byte line of an operand
+// row requested as one unit) while the MFMAs consume one.  BF16 operands run
 // through the same loop, counting k in bytes.
 //
 // Workgroup order: the hardware deals workgroups round-robin to the 8 XCDs;
@@ -30,7 +40,9 @@
 // tiles, and tiles are walked in groups of GROUP rows of tiles so that the
 // workgroups resident on one XCD share A- and B-panels in its L2.
 //
-// Accumulator layout of the 32x32x32 MFMA (lane l, register r):
+// Accumulator layout of the 16x16x64 MFMA (lane l, register r):
+//   row (X side) = 4*(l/16) + r,   column (Y side) = l%16;
+// of the 32x32x16 one:
 //   row (X side) = 8*(r/4) + 4*(l/32) + r%4,   column (Y side) = l%32.
 #include <algorithm>
 #include <atomic>
@@ -44,7 +56,6 @@ namespace oz2 {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf16 __attribute__((ext_vector_type(8)));
 
@@ -143,6 +154,274 @@ __device__ __forceinline__ TilePos tile_at(int place, int tiles_x, int tiles_y) 
   return {z, gx0 + t % gsz, t / gsz};
 }
 
+// Interleaving of a sub-step for the scheduler: READS fragment reads (of the
+// next sub-step) alternate one for one with MFMAS matrix instructions, the rest
+// of either follow.
+template <int READS, int MFMAS>
+__device__ __forceinline__ void interleave() {
+  constexpr int BOTH = READS < MFMAS ? READS : MFMAS;
+#pragma unroll
+  for (int q = 0; q < BOTH; ++q) {
+    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+  }
+  if constexpr (READS > BOTH) __builtin_amdgcn_sched_group_barrier(0x100, READS - BOTH, 0);
+  if constexpr (MFMAS > BOTH) __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - BOTH, 0);
+}
+
+// A wave's share of a BX x BY tile of bytes, WX x WY as 16 x 16 blocks: its
+// accumulators and the products of one 128-k group in LDS (rows of 128 bytes,
+// X then Y).  Four sub-steps: 64 of k times half of the Y blocks.
+template <int BX, int BY, int NWX, int NWY>
+struct WaveTile {
+  static constexpr int WX = BX / NWX, WY = BY / NWY;
+  static constexpr int TX = WX / 16, TY = WY / 16, TH = TY / 2;
+  static_assert(TX == 4 && TY % 2 == 0, "wave shape");
+  v4i acc[TX][TY];
+  int lane, xrow, yrow;     // first rows of the share in LDS
+  int fo[2];                // lane: row lane % 16 of a block, 16-byte chunk lane / 16 of 64 k
+
+  __device__ __forceinline__ WaveTile() {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    lane = threadIdx.x & 63;
+    xrow = wave / NWY * WX;
+    yrow = wave % NWY * WY;
+    const int r = lane & 15;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) fo[h] = r * 128 + (((4 * h + (lane >> 4)) ^ swz(r)) * 16);
+  }
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int a = 0; a < TX; ++a)
+#pragma unroll
+      for (int b = 0; b < TY; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[a][b][r] = 0;
+  }
+  __device__ __forceinline__ void load_x(const int8_t* buf, int h, v4i (&a)[TX]) const {
+#pragma unroll
+    for (int t = 0; t < TX; ++t)
+      a[t] = *reinterpret_cast<const v4i*>(buf + (xrow + t * 16) * 128 + fo[h]);
+  }
+  __device__ __forceinline__ void load_y(const int8_t* buf, int h, int half, v4i (&b)[TH]) const {
+#pragma unroll
+    for (int t = 0; t < TH; ++t)
+      b[t] = *reinterpret_cast<const v4i*>(buf + (BX + yrow + (half * TH + t) * 16) * 128 + fo[h]);
+  }
+  // back and forth over X: each instruction shares an operand with the one before
+  __device__ __forceinline__ void mfmas(const v4i (&a)[TX], const v4i (&b)[TH], int half) {
+#pragma unroll
+    for (int t = 0; t < TH; ++t)
+#pragma unroll
+      for (int q = 0; q < TX; ++q) {
+        const int x = t & 1 ? TX - 1 - q : q, y = half * TH + t;
+        acc[x][y] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[x], b[t], acc[x][y], 0, 0, 0);
+      }
+  }
+  // The first fragment reads go out before the next group's copies, so their
+  // LDS latency overlaps the copy issue; the X-row copies follow them and the
+  // Y-row copies come one sub-step later, spreading the copies over the group.
+  template <class CopyX, class CopyY>
+  __device__ __forceinline__ void group(const int8_t* buf, CopyX copy_x, CopyY copy_y) {
+    v4i a0[TX], a1[TX], b0[TH], b1[TH];
+    load_x(buf, 0, a0);
+    load_y(buf, 0, 0, b0);
+    copy_x();
+    __builtin_amdgcn_sched_barrier(0);
+    load_y(buf, 0, 1, b1);
+    mfmas(a0, b0, 0);
+    interleave<TH, TX * TH>();
+    __builtin_amdgcn_sched_barrier(0);
+    copy_y();
+    __builtin_amdgcn_sched_barrier(0);
+    load_x(buf, 1, a1);
+    load_y(buf, 1, 0, b0);
+    mfmas(a0, b1, 1);
+    interleave<TX + TH, TX * TH>();
+    __builtin_amdgcn_sched_barrier(0);
+    load_y(buf, 1, 1, b1);
+    mfmas(a1, b0, 0);
+    interleave<TH, TX * TH>();
+    __builtin_amdgcn_sched_barrier(0);
+    mfmas(a1, b1, 1);
+  }
+  // The same with one wave per SIMD, where nothing else covers the latency of a
+  // fragment read: all of them go out at once, and the MFMAs follow as they come
+  // (scaling product of 2048^3, 16 groups: 15.6 us, interleaved 16.7).
+  template <class CopyX, class CopyY>
+  __device__ __forceinline__ void group_alone(const int8_t* buf, CopyX copy_x, CopyY copy_y) {
+    v4i a0[TX], a1[TX], b00[TH], b01[TH], b10[TH], b11[TH];
+    load_x(buf, 0, a0);
+    load_y(buf, 0, 0, b00);
+    load_y(buf, 0, 1, b01);
+    load_x(buf, 1, a1);
+    load_y(buf, 1, 0, b10);
+    load_y(buf, 1, 1, b11);
+    __builtin_amdgcn_sched_barrier(0);
+    copy_x();
+    copy_y();
+    __builtin_amdgcn_sched_barrier(0);
+    mfmas(a0, b00, 0);
+    mfmas(a0, b01, 1);
+    mfmas(a1, b10, 0);
+    mfmas(a1, b11, 1);
+  }
+  // acc = mod(acc, p), odd p
+  __device__ __forceinline__ void reduce(double p, double pinv) {
+#pragma unroll
+    for (int a = 0; a < TX; ++a)
+#pragma unroll
+      for (int b = 0; b < TY; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[a][b][r] = mod_odd(acc[a][b][r], p, pinv);
+  }
+  // One byte per entry, word(v4i) of each block, into the column-major byte
+  // matrix at W (the share's first entry; columns ldw apart).  A lane holds rows
+  // 4 (l/16) .. + 3 of column l%16 of the blocks 0..3; exchanging words between
+  // its rows of 16 lanes leaves it rows 0..15 of block l/16, one 16-byte store.
+  template <class Word>
+  __device__ __forceinline__ void store_bytes(int8_t* __restrict__ W, int ldw, Word word) const {
+#pragma unroll
+    for (int t = 0; t < TY; ++t) {
+      const uint32_t w0 = word(acc[0][t]), w1 = word(acc[1][t]), w2 = word(acc[2][t]),
+                     w3 = word(acc[3][t]);
+      const auto a = __builtin_amdgcn_permlane32_swap(w0, w2, false, false);
+      const auto b = __builtin_amdgcn_permlane32_swap(w1, w3, false, false);
+      const auto c = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+      const auto d = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+      *reinterpret_cast<uint4*>(W + (size_t)(t * 16 + (lane & 15)) * ldw + 16 * (lane >> 4)) =
+          make_uint4(c[0], c[1], d[0], d[1]);
+    }
+  }
+  // Row and column maxima of the accumulators (>= 0) into xmax and ymax (the
+  // share's first row and column), atomicMax, order-free.
+  __device__ __forceinline__ void maxima(int* __restrict__ xmax, int* __restrict__ ymax) const {
+#pragma unroll
+    for (int t = 0; t < TY; ++t) {
+      int mv = 0;
+#pragma unroll
+      for (int x = 0; x < TX; ++x)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) mv = max(mv, acc[x][t][r]);
+      mv = max(mv, __shfl_xor(mv, 16));
+      mv = max(mv, __shfl_xor(mv, 32));
+      if (lane < 16) atomicMax(&ymax[t * 16 + lane], mv);
+    }
+    // The 16 rows of a lane against the 16 lanes of its row of lanes (columns):
+    // in each step a lane passes on half of its rows and keeps the other, 15
+    // exchanges instead of four for every row; lane % 16 then names the row that
+    // a lane holds.
+    int v[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      v[r] = 0;
+#pragma unroll
+      for (int t = 0; t < TY; ++t) v[r] = max(v[r], acc[r >> 2][t][r & 3]);
+    }
+#pragma unroll
+    for (int half = 8; half >= 1; half >>= 1) {
+      const int up = (lane & half) != 0 ? -1 : 0;        // as a mask: v stays in registers
+#pragma unroll
+      for (int r = 0; r < half; ++r) {
+        const int send = (v[r] & up) | (v[r + half] & ~up);
+        const int keep = (v[r + half] & up) | (v[r] & ~up);
+        v[r] = max(keep, __shfl_xor(send, half));
+      }
+    }
+    const int r = lane & 15;
+    atomicMax(&xmax[16 * (r >> 2) + 4 * (lane >> 4) + (r & 3)], v[0]);
+  }
+  // The INT32 accumulators, column-major (the share's first entry, columns ld apart).
+  __device__ __forceinline__ void store_words(int* __restrict__ D, int ld) const {
+#pragma unroll
+    for (int t = 0; t < TY; ++t)
+#pragma unroll
+      for (int x = 0; x < TX; ++x)
+        *reinterpret_cast<v4i*>(D + (size_t)(t * 16 + (lane & 15)) * ld + 16 * x +
+                                4 * (lane >> 4)) = acc[x][t];
+  }
+};
+
+// The same for BF16 rows (128 bytes are 64 of k) as 32 x 32 blocks with FP32
+// accumulators, k in steps of 16.
+template <int BX, int BY, int NWX, int NWY>
+struct WaveTileBf16 {
+  static constexpr int WX = BX / NWX, WY = BY / NWY, TX = WX / 32, TY = WY / 32;
+  v16f acc[TX][TY];
+  int lane, xrow, yrow;
+  int fo[4];                // lane: row lane % 32 of a block, chunk lane / 32 of 32 bytes
+
+  __device__ __forceinline__ WaveTileBf16() {
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    lane = threadIdx.x & 63;
+    xrow = wave / NWY * WX;
+    yrow = wave % NWY * WY;
+    const int r = lane & 31;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fo[j] = r * 128 + (((2 * j + (lane >> 5)) ^ swz(r)) * 16);
+  }
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int a = 0; a < TX; ++a)
+#pragma unroll
+      for (int b = 0; b < TY; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[a][b][r] = 0;
+  }
+  __device__ __forceinline__ void load(const int8_t* buf, int j, v4i (&a)[TX], v4i (&b)[TY]) const {
+#pragma unroll
+    for (int t = 0; t < TX; ++t)
+      a[t] = *reinterpret_cast<const v4i*>(buf + (xrow + t * 32) * 128 + fo[j]);
+#pragma unroll
+    for (int t = 0; t < TY; ++t)
+      b[t] = *reinterpret_cast<const v4i*>(buf + (BX + yrow + t * 32) * 128 + fo[j]);
+  }
+  __device__ __forceinline__ void mfmas(const v4i (&a)[TX], const v4i (&b)[TY]) {
+#pragma unroll
+    for (int x = 0; x < TX; ++x)
+#pragma unroll
+      for (int y = 0; y < TY; ++y)
+        acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf16, a[x]),
+                                                            __builtin_bit_cast(v8bf16, b[y]),
+                                                            acc[x][y], 0, 0, 0);
+  }
+  template <class CopyX, class CopyY>
+  __device__ __forceinline__ void group(const int8_t* buf, CopyX copy_x, CopyY copy_y) {
+    v4i a0[TX], b0[TY], a1[TX], b1[TY];
+    load(buf, 0, a0, b0);
+    copy_x();
+    __builtin_amdgcn_sched_barrier(0);
+    load(buf, 1, a1, b1);
+    mfmas(a0, b0);
+    interleave<TX + TY, TX * TY>();
+    __builtin_amdgcn_sched_barrier(0);
+    copy_y();
+    __builtin_amdgcn_sched_barrier(0);
+    load(buf, 2, a0, b0);
+    mfmas(a1, b1);
+    interleave<TX + TY, TX * TY>();
+    __builtin_amdgcn_sched_barrier(0);
+    load(buf, 3, a1, b1);
+    mfmas(a0, b0);
+    interleave<TX + TY, TX * TY>();
+    __builtin_amdgcn_sched_barrier(0);
+    mfmas(a1, b1);
+  }
+  // FP32 accumulators, column-major: 4 consecutive rows per lane and store
+  __device__ __forceinline__ void store(float* __restrict__ S, int ld) const {
+#pragma unroll
+    for (int x = 0; x < TX; ++x)
+#pragma unroll
+      for (int y = 0; y < TY; ++y)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4)
+          *reinterpret_cast<float4*>(S + (size_t)(y * 32 + (lane & 31)) * ld + x * 32 + 8 * r4 +
+                                     4 * (lane >> 5)) =
+              make_float4(acc[x][y][4 * r4 + 0], acc[x][y][4 * r4 + 1], acc[x][y][4 * r4 + 2],
+                          acc[x][y][4 * r4 + 3]);
+  }
+};
+
 // One BX x BY tile at (x0, y0) of slice z.  k advances in groups of 128 bytes;
 // a group buffer in LDS holds the X tile then the Y tile as rows of 128 bytes,
 // and NS of them are a ring.  The copies of group g + NS - 1 (direct
@@ -167,20 +446,17 @@ __device__ __forceinline__ void gemm_body(int8_t* __restrict__ lds, const int8_t
                                           int nsplit, int vx, int vy) {
   constexpr int BK = 128;                        // bytes of k per LDS row (one group)
   constexpr int NW = NWX * NWY;                  // waves
-  constexpr int WX = BX / NWX, WY = BY / NWY;
-  constexpr int TX = WX / 32, TY = WY / 32;
   constexpr int CPR = BK / 16;                   // 16-byte chunks per LDS row
   constexpr int RPI = 1024 / BK;                 // rows per copy instruction
   constexpr int IX = BX / RPI / NW, IY = BY / RPI / NW;
   // Each wave copies IX (IY) instructions of RPI rows; the chunk swizzle
   // repeats every 16 rows and the even/odd instruction offsets below assume
   // that every wave's share starts at a multiple of 16 rows.
-  static_assert(IX % 2 == 0 && IY % 2 == 0 && WX % 32 == 0 && WY % 32 == 0, "tile / wave shape");
+  static_assert(IX % 2 == 0 && IY % 2 == 0, "tile / wave shape");
   constexpr int GROUP_BYTES = (BX + BY) * BK;    // one 128-k group
   static_assert((NS & (NS - 1)) == 0 && (NS - 2) * (IX + IY) < 64, "ring");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wx = wave / NWY, wy = wave % NWY;
 
   // Copy instruction q of this wave covers rows RPI*q .. RPI*q + RPI - 1 of
   // its share; lane l takes row RPI*q + l/CPR and stores LDS chunk l%CPR,
@@ -223,163 +499,32 @@ __device__ __forceinline__ void gemm_body(int8_t* __restrict__ lds, const int8_t
             b + (uint32_t)(BX * BK + (wave_u * IY + q) * 1024));
   };
 
-  using AccT = typename std::conditional<BF16, v16f, v16i>::type;
-  AccT acc[TX][TY];
-#pragma unroll
-  for (int a = 0; a < TX; ++a)
-#pragma unroll
-    for (int b = 0; b < TY; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][b][r] = 0;
+  using Tile = typename std::conditional<BF16, WaveTileBf16<BX, BY, NWX, NWY>,
+                                         WaveTile<BX, BY, NWX, NWY>>::type;
+  Tile tile;
+  tile.clear();
 
-  // fragment offsets of the four 32-k sub-steps j of a group: lane reads row
-  // frow of a 32-row block, k chunk 2j + lane/32 of the group
-  const int frow = lane & 31;
-  int fo[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) fo[j] = frow * BK + (((2 * j + (lane >> 5)) ^ swz(frow)) * 16);
-  auto load_frags = [&](const int8_t* buf, int j, v4i (&a)[TX], v4i (&b)[TY]) {
-#pragma unroll
-    for (int tx = 0; tx < TX; ++tx)
-      a[tx] = *reinterpret_cast<const v4i*>(buf + (wx * WX + tx * 32) * BK + fo[j]);
-#pragma unroll
-    for (int ty = 0; ty < TY; ++ty)
-      b[ty] = *reinterpret_cast<const v4i*>(buf + (BX + wy * WY + ty * 32) * BK + fo[j]);
-  };
-  auto mfmas = [&](const v4i (&a)[TX], const v4i (&b)[TY]) {
-#pragma unroll
-    for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-      for (int ty = 0; ty < TY; ++ty)
-        if constexpr (BF16)
-          acc[tx][ty] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(v8bf16, a[tx]), __builtin_bit_cast(v8bf16, b[ty]), acc[tx][ty], 0,
-              0, 0);
-        else
-          acc[tx][ty] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[tx], b[ty], acc[tx][ty], 0, 0, 0);
-  };
-
-  const int xb = x0 + wx * WX, yb = y0 + wy * WY;
-  // Per 32 x 32 block, lane l holds rows {0-3, 8-11, 16-19, 24-27} + 4 (l/32)
-  // of column l%32, packed as 4 dwords R0..R3 (one byte per row).  Swapping
-  // R0<->R2 and R1<->R3 between lanes l and l+32 (v_permlane32_swap) leaves
-  // rows 0-15 in lane l and rows 16-31 in lane l+32, each stored as one
-  // 16-byte write into the column-major byte matrix Wz (row length ldw).
-  auto store_block = [&](int8_t* Wz, int tx, int ty, uint32_t R0, uint32_t R1, uint32_t R2,
-                         uint32_t R3) {
-    const auto s02 = __builtin_amdgcn_permlane32_swap(R0, R2, false, false);
-    const auto s13 = __builtin_amdgcn_permlane32_swap(R1, R3, false, false);
-    const int x = xb + tx * 32 + 16 * (lane >> 5);
-    const int y = yb + ty * 32 + (lane & 31);
-    uint4 v;
-    v.x = s02[0];
-    v.y = s02[1];
-    v.z = s13[0];
-    v.w = s13[1];
-    *reinterpret_cast<uint4*>(Wz + (size_t)y * ldw + x) = v;
-  };
   // Epilogue (EPI 0: mod p_z into W_z; EPI 1: maxima; EPI 2: FP32 store;
   // EPI 3: maxima and nonzero bytes; EPI 4: INT32 store).
   auto finish = [&]() {
-    if constexpr (EPI == 4) {
-      // INT32 accumulators of slice z stored column-major: D_z[y][x]
-      int* Dz = reinterpret_cast<int*>(W) + (size_t)(sidx * nz + z) * sw;
-#pragma unroll
-      for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-        for (int ty = 0; ty < TY; ++ty)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4) {
-            const int x = xb + tx * 32 + 8 * r4 + 4 * (lane >> 5);
-            const int y = yb + ty * 32 + (lane & 31);
-            *reinterpret_cast<int4*>(Dz + (size_t)y * ldw + x) =
-                make_int4(acc[tx][ty][4 * r4 + 0], acc[tx][ty][4 * r4 + 1],
-                          acc[tx][ty][4 * r4 + 2], acc[tx][ty][4 * r4 + 3]);
-          }
-    }
-    if constexpr (EPI == 2) {
-      // FP32 accumulators stored column-major: S[y][x], 4 consecutive x per lane
-      float* S = reinterpret_cast<float*>(W);
-#pragma unroll
-      for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-        for (int ty = 0; ty < TY; ++ty)
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4) {
-            const int x = xb + tx * 32 + 8 * r4 + 4 * (lane >> 5);
-            const int y = yb + ty * 32 + (lane & 31);
-            *reinterpret_cast<float4*>(S + (size_t)y * ldw + x) =
-                make_float4((float)acc[tx][ty][4 * r4 + 0], (float)acc[tx][ty][4 * r4 + 1],
-                            (float)acc[tx][ty][4 * r4 + 2], (float)acc[tx][ty][4 * r4 + 3]);
-          }
-    } else if constexpr (EPI == 0) {
+    const int xb = x0 + tile.xrow, yb = y0 + tile.yrow;
+    const size_t first = (size_t)yb * ldw + xb;
+    if constexpr (EPI == 0) {
       const double pinv = cc.mod[z].pinv;
       const uint32_t negp = cc.mod[z].negp;
-      int8_t* Wz = W + (size_t)(sidx * nz + z) * sw;
-#pragma unroll
-      for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-        for (int ty = 0; ty < TY; ++ty) {
-          uint32_t R[4];
-#pragma unroll
-          for (int r4 = 0; r4 < 4; ++r4)
-            R[r4] = mod_word(acc[tx][ty][4 * r4 + 0], acc[tx][ty][4 * r4 + 1],
-                             acc[tx][ty][4 * r4 + 2], acc[tx][ty][4 * r4 + 3], pinv, negp);
-          store_block(Wz, tx, ty, R[0], R[1], R[2], R[3]);
-        }
-    } else if constexpr (EPI == 1 || EPI == 3) {
-      if constexpr (EPI == 3) {
-#pragma unroll
-        for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-          for (int ty = 0; ty < TY; ++ty) {
-            uint32_t R[4];
-#pragma unroll
-            for (int r4 = 0; r4 < 4; ++r4)
-              R[r4] = pack_bytes(acc[tx][ty][4 * r4 + 0] != 0, acc[tx][ty][4 * r4 + 1] != 0,
-                                 acc[tx][ty][4 * r4 + 2] != 0, acc[tx][ty][4 * r4 + 3] != 0);
-            store_block(W, tx, ty, R[0], R[1], R[2], R[3]);
-          }
-      }
-      // max over x for each y
-#pragma unroll
-      for (int ty = 0; ty < TY; ++ty) {
-        int mv = 0;
-#pragma unroll
-        for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) mv = max(mv, acc[tx][ty][r]);
-        mv = max(mv, __shfl_xor(mv, 32));
-        if (lane < 32) atomicMax(&ymax[yb + ty * 32 + lane], mv);
-      }
-      // max over y for each x: the 16 registers of a lane (rows) against the 32
-      // lanes of its half (columns).  In each step a lane passes on half of its
-      // rows and keeps the other, 15 exchanges and one more for the last pair
-      // of lanes, instead of five for every row; lane bits 4..1 then name the
-      // row that a lane holds.
-#pragma unroll
-      for (int tx = 0; tx < TX; ++tx) {
-        int v[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          v[r] = 0;
-#pragma unroll
-          for (int ty = 0; ty < TY; ++ty) v[r] = max(v[r], acc[tx][ty][r]);
-        }
-#pragma unroll
-        for (int half = 8; half >= 1; half >>= 1) {
-          const bool up = (lane & (2 * half)) != 0;
-#pragma unroll
-          for (int r = 0; r < half; ++r) {
-            const int send = up ? v[r] : v[r + half], keep = up ? v[r + half] : v[r];
-            v[r] = max(keep, __shfl_xor(send, 2 * half));
-          }
-        }
-        const int mv = max(v[0], __shfl_xor(v[0], 1));
-        const int r = (lane >> 1) & 15;
-        if ((lane & 1) == 0)
-          atomicMax(&xmax[xb + tx * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)], mv);
-      }
+      tile.store_bytes(W + (size_t)(sidx * nz + z) * sw + first, ldw, [&](const v4i& v) {
+        return mod_word(v[0], v[1], v[2], v[3], pinv, negp);
+      });
+    } else if constexpr (EPI == 2) {
+      tile.store(reinterpret_cast<float*>(W) + first, ldw);
+    } else if constexpr (EPI == 4) {
+      tile.store_words(reinterpret_cast<int*>(W) + (size_t)(sidx * nz + z) * sw + first, ldw);
+    } else {
+      if constexpr (EPI == 3)
+        tile.store_bytes(W + first, ldw, [](const v4i& v) {
+          return pack_bytes(v[0] != 0, v[1] != 0, v[2] != 0, v[3] != 0);
+        });
+      tile.maxima(xmax + xb, ymax + yb);
     }
   };
 
@@ -390,18 +535,8 @@ __device__ __forceinline__ void gemm_body(int8_t* __restrict__ lds, const int8_t
   // accumulators stay in place across iterations.
   const int NGall = k_pad / 128;
   const int g_lo = SPLIT ? (int)((int64_t)sidx * NGall / nsplit) : 0;
-  const int NG = SPLIT ? (int)((int64_t)(sidx + 1) * NGall / nsplit) : NGall;   // end of this workgroup's groups
-  // Within each 32-k sub-step the fragment reads of the next sub-step (into
-  // the other register set) alternate one for one with the MFMAs of the
-  // current one; the remaining MFMAs follow.
-  auto interleave = [&]() {
-#pragma unroll
-    for (int q = 0; q < TX + TY; ++q) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // one LDS read
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-    }
-    if constexpr (TX * TY > TX + TY) __builtin_amdgcn_sched_group_barrier(0x008, TX * TY - (TX + TY), 0);
-  };
+  // end of this workgroup's groups
+  const int NG = SPLIT ? (int)((int64_t)(sidx + 1) * NGall / nsplit) : NGall;
   // Beyond 2^17 of k (residue products, EPI 0 and its INT32 dump EPI 4) the
   // accumulators are reduced mod p_z (odd p) after every 2^17 of k: a chunk
   // adds at most 127^2 2^17 < 2^31 - 127 in magnitude to a reduced value, so
@@ -415,13 +550,7 @@ __device__ __forceinline__ void gemm_body(int8_t* __restrict__ lds, const int8_t
   auto fold = [&]() {
     const int p = cc.mod[z].p;
     if (p == 256) return;
-    const double pd = (double)p, pinv = cc.mod[z].pinv;
-#pragma unroll
-    for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-      for (int ty = 0; ty < TY; ++ty)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[tx][ty][r] = mod_odd(acc[tx][ty][r], pd, pinv);
+    if constexpr (!BF16) tile.reduce((double)p, cc.mod[z].pinv);
   };
   auto ring = [&](int gi) { return lds + (gi & (NS - 1)) * GROUP_BYTES; };
 #pragma unroll
@@ -448,29 +577,16 @@ __device__ __forceinline__ void gemm_body(int8_t* __restrict__ lds, const int8_t
       wait_vmcnt<0>();
     }
     __builtin_amdgcn_s_barrier();
-    v4i a0[TX], b0[TY], a1[TX], b1[TY];
-    // The first fragment reads go out before the next group's copies, so
-    // their LDS latency overlaps the copy issue; the X-row copies follow
-    // them and the Y-row copies come one sub-step later, spreading the
-    // copies over the first half of the group.
-    load_frags(buf, 0, a0, b0);
-    if (gi + NS - 1 < NG) issue_x(next, z, (gi + NS - 1) * 128);
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags(buf, 1, a1, b1);
-    mfmas(a0, b0);
-    interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    if (gi + NS - 1 < NG) issue_y(next, z, (gi + NS - 1) * 128);
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags(buf, 2, a0, b0);
-    mfmas(a1, b1);
-    interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags(buf, 3, a1, b1);
-    mfmas(a0, b0);
-    interleave();
-    __builtin_amdgcn_sched_barrier(0);
-    mfmas(a1, b1);
+    auto copy_x = [&] {
+      if (gi + NS - 1 < NG) issue_x(next, z, (gi + NS - 1) * 128);
+    };
+    auto copy_y = [&] {
+      if (gi + NS - 1 < NG) issue_y(next, z, (gi + NS - 1) * 128);
+    };
+    if constexpr (NS == 4)
+      tile.group_alone(buf, copy_x, copy_y);
+    else
+      tile.group(buf, copy_x, copy_y);
   }
   if constexpr (kFold) {
     if (g1 < NG) fold();
@@ -496,25 +612,18 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
                                              const CrtConsts* __restrict__ ctab) {
   constexpr int BK = 128;
   constexpr int NW = NWX * NWY;
-  constexpr int WX = BX / NWX, WY = BY / NWY;
-  constexpr int TX = WX / 32, TY = WY / 32;
   constexpr int CPR = BK / 16;
   constexpr int RPI = 1024 / BK;
   constexpr int IX = BX / RPI / NW, IY = BY / RPI / NW;
-  static_assert(IX % 2 == 0 && IY % 2 == 0 && WX % 32 == 0 && WY % 32 == 0, "tile / wave shape");
+  static_assert(IX % 2 == 0 && IY % 2 == 0, "tile / wave shape");
   static_assert(BX == BY, "square tiles");
   constexpr int GROUP_BYTES = (BX + BY) * BK;
   __shared__ __attribute__((aligned(1024))) int8_t lds[2 * GROUP_BYTES];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wx = wave / NWY, wy = wave % NWY;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   const int lr = lane / CPR, slot = lane % CPR;
   const int ch_e = (slot ^ swz(lr)) * 16, ch_o = (slot ^ swz(RPI + lr)) * 16;
-  const int frow = lane & 31;
-  int fo[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) fo[j] = frow * BK + (((2 * j + (lane >> 5)) ^ swz(frow)) * 16);
 
   // One tile of one residue product.
   struct Job {
@@ -571,31 +680,7 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
     return items;
   };
 
-  v16i acc[TX][TY];
-  auto load_frags = [&](const int8_t* buf, int j, v4i (&a)[TX], v4i (&b)[TY]) {
-#pragma unroll
-    for (int tx = 0; tx < TX; ++tx)
-      a[tx] = *reinterpret_cast<const v4i*>(buf + (wx * WX + tx * 32) * BK + fo[j]);
-#pragma unroll
-    for (int ty = 0; ty < TY; ++ty)
-      b[ty] = *reinterpret_cast<const v4i*>(buf + (BX + wy * WY + ty * 32) * BK + fo[j]);
-  };
-  auto mfmas = [&](const v4i (&a)[TX], const v4i (&b)[TY]) {
-#pragma unroll
-    for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-      for (int ty = 0; ty < TY; ++ty)
-        acc[tx][ty] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[tx], b[ty], acc[tx][ty], 0, 0, 0);
-  };
-  auto interleave = [&]() {
-#pragma unroll
-    for (int q = 0; q < TX + TY; ++q) {
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    }
-    if constexpr (TX * TY > TX + TY) __builtin_amdgcn_sched_group_barrier(0x008, TX * TY - (TX + TY), 0);
-  };
-
+  WaveTile<BX, BY, NWX, NWY> tile;
   Job cur, nxt;
   int i = next_job((int)blockIdx.x, cur);
   if (i >= items) return;   // whole workgroup, before any barrier
@@ -605,12 +690,7 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
   for (;;) {
     const int inext = next_job(i + (int)gridDim.x, nxt);
     const bool more = inext < items;
-#pragma unroll
-    for (int a = 0; a < TX; ++a)
-#pragma unroll
-      for (int b = 0; b < TY; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[a][b][r] = 0;
+    tile.clear();
     const int NG = cur.k_pad / 128;
     for (int g0 = 0; g0 < NG; g0 += FOLD ? kFoldGroups : NG) {
       const int g1 = FOLD ? min(NG, g0 + kFoldGroups) : NG;
@@ -619,68 +699,29 @@ __device__ __forceinline__ void gemm_persist(const ProbDesc* __restrict__ P,
         int8_t* const next = lds + ((ph + gi + 1) & 1) * GROUP_BYTES;
         wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
-        v4i a0[TX], b0[TY], a1[TX], b1[TY];
-        load_frags(buf, 0, a0, b0);
-        if (gi + 1 < NG)
-          issue_x(next, cur, (gi + 1) * 128);
-        else if (more)
-          issue_x(next, nxt, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(buf, 1, a1, b1);
-        mfmas(a0, b0);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
-        if (gi + 1 < NG)
-          issue_y(next, cur, (gi + 1) * 128);
-        else if (more)
-          issue_y(next, nxt, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(buf, 2, a0, b0);
-        mfmas(a1, b1);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
-        load_frags(buf, 3, a1, b1);
-        mfmas(a0, b0);
-        interleave();
-        __builtin_amdgcn_sched_barrier(0);
-        mfmas(a1, b1);
+        tile.group(
+            buf,
+            [&] {
+              if (gi + 1 < NG)
+                issue_x(next, cur, (gi + 1) * 128);
+              else if (more)
+                issue_x(next, nxt, 0);
+            },
+            [&] {
+              if (gi + 1 < NG)
+                issue_y(next, cur, (gi + 1) * 128);
+              else if (more)
+                issue_y(next, nxt, 0);
+            });
       }
-      if (FOLD && g1 < NG && cur.p != 256) {   // reduction every 2^17 of k (see gemm_body)
-        const double pd = (double)cur.p;
-#pragma unroll
-        for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-          for (int ty = 0; ty < TY; ++ty)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[tx][ty][r] = mod_odd(acc[tx][ty][r], pd, cur.pinv);
-      }
+      // reduction every 2^17 of k (see gemm_body)
+      if (FOLD && g1 < NG && cur.p != 256) tile.reduce((double)cur.p, cur.pinv);
     }
     ph = (ph + NG) & 1;
     // epilogue: W_z = mod(C'_z, p_z), as in gemm_body
-    const int xb = cur.x0 + wx * WX, yb = cur.y0 + wy * WY;
-    auto store_block = [&](int tx, int ty, uint32_t R0, uint32_t R1, uint32_t R2, uint32_t R3) {
-      const auto s02 = __builtin_amdgcn_permlane32_swap(R0, R2, false, false);
-      const auto s13 = __builtin_amdgcn_permlane32_swap(R1, R3, false, false);
-      const int x = xb + tx * 32 + 16 * (lane >> 5);
-      const int y = yb + ty * 32 + (lane & 31);
-      uint4 v;
-      v.x = s02[0];
-      v.y = s02[1];
-      v.z = s13[0];
-      v.w = s13[1];
-      *reinterpret_cast<uint4*>(cur.Wz + (size_t)y * cur.ldw + x) = v;
-    };
-#pragma unroll
-    for (int tx = 0; tx < TX; ++tx)
-#pragma unroll
-      for (int ty = 0; ty < TY; ++ty) {
-        uint32_t R[4];
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-          R[r4] = mod_word(acc[tx][ty][4 * r4 + 0], acc[tx][ty][4 * r4 + 1],
-                           acc[tx][ty][4 * r4 + 2], acc[tx][ty][4 * r4 + 3], cur.pinv, cur.negp);
-        store_block(tx, ty, R[0], R[1], R[2], R[3]);
-      }
+    tile.store_bytes(
+        cur.Wz + (size_t)(cur.y0 + tile.yrow) * cur.ldw + cur.x0 + tile.xrow, cur.ldw,
+        [&](const v4i& v) { return mod_word(v[0], v[1], v[2], v[3], cur.pinv, cur.negp); });
     if (!more) break;
     cur = nxt;
     i = inext;
@@ -722,7 +763,9 @@ __global__ __launch_bounds__(tile_threads<B>(), TileShape<B>::OCC) void k_gemm_i
       const TilePos t = tile_at(full + place / TAIL, tiles_x, tiles_y);
       const int part = place % TAIL;
       constexpr int SX = TAIL == 4 ? B / 2 : B, SY = B / 2;
-      gemm_body<SX, SY, NWX, NWY, EPI, BF16, FOLD, false, NS>(
+      // a wave's share is 64 rows of X in every build
+      constexpr int PX = SX / 64, PY = NWX * NWY / PX;
+      gemm_body<SX, SY, PX, PY, EPI, BF16, FOLD, false, NS>(
           lds, X, sx, Y, sy, t.tx * B + (TAIL == 4 ? (part & 1) * SX : 0),
           t.ty * B + (TAIL == 4 ? part >> 1 : part) * SY, t.z, nz, k_pad, cc, W, sw, ldw, xmax, ymax,
           0, 1, 0, 0);
