@@ -1148,6 +1148,15 @@ void launch_gemm_i8(hipStream_t s, int epi, const int8_t* X, size_t sx, const in
                   : choose_split_cbar(nx_pad, ny_pad, k_pad, part ? part_bytes : 0);
     const size_t plane = (size_t)nx_pad * ny_pad;
     const size_t need = epi == 0 ? (size_t)sp * nz * plane : (size_t)sp * plane * 4;
+    // Fewer splits, one workgroup per CU with the deep ring, where these fill 15 of
+    // 16 CUs.  Residue products with two workgroups per CU and with one: 128x128 x
+    // 16384 27.8 and 22.8 us, 100x100x50000 42.3 and 35.3, 64x64x262144 143 and
+    // 135; where 224 of 256 CUs would have one, 200x200x100000, 158 and 164.
+    if (epi == 0 && !b256 && sp > 1) {
+      const long w0 = (long)(nx_pad / 128) * (ny_pad / 128) * nz;
+      const long sp1 = kCus / w0;
+      if (sp1 >= 2 && 16 * sp1 * w0 >= 15 * kCus) sp = (int)std::min<long>(sp, sp1);
+    }
     // the partials use the plane layout (stride nx_pad * ny_pad, rows of
     // nx_pad): W must have it too
     const bool plane_w = epi == 1 || (sw == plane && ldw == nx_pad);
