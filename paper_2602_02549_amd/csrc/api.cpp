@@ -719,7 +719,7 @@ int get_ctab(int b, CrtConsts** out) {
 // Whether the scan of a batch splits finely (few workgroups in all).
 bool batch_scan_fine(Prec pr, const std::vector<ProbDesc>& D) {
   int64_t units = 0;
-  for (const ProbDesc& d : D) units += scan_group_blocks(pr, d.mp, d.np, d.k, d.kp, true);
+  for (const ProbDesc& d : D) units += scan_group_blocks(pr, d, true);
   return scan_group_fine(units);
 }
 
@@ -736,10 +736,10 @@ void build_table(Prec pr, const std::vector<ProbDesc>& D, int split, std::vector
     const bool big = d.mp % 256 == 0 && d.np % 256 == 0 &&
                      (int64_t)(d.mp / 256) * (d.np / 256) >= split;
     int* cp = &c[(size_t)p * BS_COUNT];
-    const bool chunked = scan_group_chunked(pr, d.mp, d.k, d.kp, fine);
+    const bool chunked = scan_group_chunked(pr, d, fine);
     cp[BS_CLEAR] = chunked ? group_clear_blocks(d.mp, d.np) : 0;
     cp[BS_ABS_A] = chunked ? cdiv_i(d.m, 256) * cdiv_i(d.k, 64) : 0;
-    cp[BS_SCAN] = scan_group_blocks(pr, d.mp, d.np, d.k, d.kp, fine);
+    cp[BS_SCAN] = scan_group_blocks(pr, d, fine);
     cp[BS_SL_A] = (d.kp / 128) * (d.mp / 32);
     cp[BS_BAR_A] = chunked ? cp[BS_SL_A] : 0;
     cp[BS_SL_B] = (d.kp / 128) * (d.np / 32);

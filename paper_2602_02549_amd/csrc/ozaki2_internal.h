@@ -237,8 +237,8 @@ void launch_scan(hipStream_t s, Prec pr, SliceSet set, const SliceOperand& A, co
 // and the scan itself.
 // fine: the whole batch's finest split has few workgroups (scan_group_fine).
 bool scan_group_fine(int64_t units);
-bool scan_group_chunked(Prec pr, int m_pad, int k, int k_pad, bool fine);
-int scan_group_blocks(Prec pr, int m_pad, int n_pad, int k, int k_pad, bool fine);
+bool scan_group_chunked(Prec pr, const ProbDesc& d, bool fine);
+int scan_group_blocks(Prec pr, const ProbDesc& d, bool fine);
 void launch_group_scan(hipStream_t s, Prec pr, const ProbDesc* P, const BlockRef* clear_map,
                        int clear_blocks, const BlockRef* abs_map, int abs_blocks,
                        const BlockRef* scan_map, int scan_blocks, bool fine);

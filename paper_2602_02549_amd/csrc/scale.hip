@@ -33,8 +33,10 @@ namespace {
 // problems: a wave per column and 16-row strips took 406 us on 2048 problems
 // of 128^3.
 // A strip reads all of k by itself, so few strips over a long k would leave the
-// GPU idle: see strips_fit.  There A's maxima run over chunks of 64 columns with
-// atomics (k_absmax_rows) and its bars in the slice kernel.
+// GPU idle: see strips_fit.  There A's maxima run over chunks of columns, those
+// of few columns of B over chunks of rows (cols_chunked), with one atomic per
+// chunk and row (one per wave or thread took 110 us at 64x64x262144, these 58:
+// the atomics of a row go one at a time), and the bars in the slice kernel.
 constexpr int kScanThreads = 512;
 constexpr int kColWaveK = 2048;
 
@@ -79,8 +81,9 @@ struct ScanArgs {
   int half;        // the embedding: rows of one row half of A
   int lr;          // log2 of the rows of a strip
   int tpc;         // threads per column
-  int chunked;     // A's units are (256 rows x 64 columns) pairs of abs-max only
-  int clear;       // clear the maxima and the flag
+  int chunked;     // A's units are chunks, for the abs-max only
+  int tr;          // rows of such a chunk
+  int cols_chunked;   // so are B's: kColChunk elements of a column each
 };
 
 template <typename T>
@@ -138,15 +141,19 @@ __device__ __forceinline__ void scan_strip(const T* __restrict__ src, int ld, in
   const int r0 = u * R, rg = r0 + row;
   const bool in = rg < rows;
   const int ldo = kEmb ? 2 * k_pad : k_pad;
-  const T* a = src + (size_t)E * min(rg, rows - 1);
+  const uint32_t rc = (uint32_t)(min(rg, rows - 1) - r0);
   const int nch = (k_pad + CH - 1) / CH;
   // 16 loads before any use; clamped to the matrix (a repeated element of the
   // row does not change its maximum)
   auto load = [&](int c, T (&x)[16], T (&y)[16]) {
-    const int h = c * CH + 16 * kg;
+    // uniform, with offsets below 2^32 (strips_fit)
+    const char* base =
+        reinterpret_cast<const char*>(src + (size_t)E * (r0 + (size_t)(c * CH) * ld));
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const T* p = a + (size_t)E * ((size_t)min(h + e, k - 1) * ld);
+      const uint32_t h = (uint32_t)min(16 * kg + e, k - 1 - c * CH);
+      const T* p =
+          reinterpret_cast<const T*>(base + (h * (uint32_t)ld + rc) * (uint32_t)(E * sizeof(T)));
       x[e] = p[0];
       y[e] = E == 2 ? p[E - 1] : (T)0;
     }
@@ -325,19 +332,15 @@ __device__ __forceinline__ void scan_cols(const T* __restrict__ src, int ld, int
     if (q < nq) put(q, kx[q], ky[q]);
 }
 
-// Abs-max of 256 rows over 64 columns of the column-major A (atomicMax on bits
-// that a launch before has cleared): pair p of (row block, column block),
-// thread t of 256.  16 loads go out at a time from clamped addresses.
+// Abs-max of row i over the 64 columns from h0 of the column-major A, 16 loads
+// at a time from clamped addresses (0 past the last column).
 template <typename T, SliceSet F>
-__device__ __forceinline__ void absmax_rows_body(const T* __restrict__ A, int lda, int m, int k,
-                                                 int half, uint64_t* __restrict__ bits, int p,
-                                                 int t) {
+__device__ __forceinline__ uint64_t absmax_row_part(const T* __restrict__ A, int lda, int m, int k,
+                                                    int i, int h0) {
   constexpr int E = F == SliceSet::Real ? 1 : 2;
-  const int gx = cdiv_i(m, 256);
-  const int i = p % gx * 256 + t, h0 = p / gx * 64;
-  if (h0 >= k) return;
   const T* a = A + (size_t)E * min(i, m - 1);
   uint64_t mx = 0;
+  if (h0 >= k) return mx;
 #pragma unroll
   for (int q0 = 0; q0 < 64; q0 += 16) {
     T x[16], y[16];
@@ -353,46 +356,132 @@ __device__ __forceinline__ void absmax_rows_body(const T* __restrict__ A, int ld
       if (E == 2) mx = max64(mx, abs_bits(y[u]));
     }
   }
-  if (i >= m || !mx) return;
+  return mx;
+}
+
+// Abs-max of chunk p of A by a workgroup (atomicMax on bits that a launch before
+// has cleared): tr rows by kScanThreads / tr times 64 columns, combined in LDS
+// first, since the atomics of a row go one at a time.
+__host__ __device__ inline int chunk_rows(int m) { return m > 128 ? 256 : m > 64 ? 128 : 64; }
+__host__ __device__ inline int row_chunks(int m, int k, int tr) {
+  return cdiv_i(m, tr) * cdiv_i(k, 64 * (kScanThreads / tr));
+}
+template <typename T, SliceSet F>
+__device__ __forceinline__ void absmax_row_chunk(const T* __restrict__ A, int lda, int m, int k,
+                                                 int half, uint64_t* __restrict__ bits, int p,
+                                                 int tr, unsigned long long* __restrict__ red) {
+  const int t = (int)threadIdx.x, gx = cdiv_i(m, tr), groups = kScanThreads / tr;
+  const int i = p % gx * tr + (t & (tr - 1));
+  uint64_t mx = absmax_row_part<T, F>(A, lda, m, k, i, (p / gx * groups + t / tr) * 64);
+  red[t] = mx;
+  __syncthreads();
+  if (t >= tr || i >= m) return;
+  for (int g = 1; g < groups; ++g) mx = max64(mx, red[g * tr + t]);
+  if (!mx) return;
   atomicMax((unsigned long long*)&bits[i], (unsigned long long)mx);
   if (F == SliceSet::Embedding)
     atomicMax((unsigned long long*)&bits[i + half], (unsigned long long)mx);
 }
 
+// Abs-max of chunk u of B: kColChunk elements of one column, 16 per thread in
+// quads (the first column index fastest, so that chunks of a column do not
+// meet at its maximum).
+constexpr int kColChunk = 16 * kScanThreads;
+template <typename T, SliceSet F>
+__device__ __forceinline__ void absmax_col_chunk(const T* __restrict__ B, int ldb, int n, int k,
+                                                 uint64_t* __restrict__ bits, int u,
+                                                 unsigned long long* __restrict__ red) {
+  constexpr int E = F == SliceSet::Real ? 1 : 2;
+  const int j = u % n, c0 = u / n * kColChunk, h0 = c0 + (int)threadIdx.x * 4;
+  const T* b = B + (size_t)E * ((size_t)j * ldb);
+  uint64_t mx = 0;
+  if (c0 + kColChunk <= k) {                             // uniform: the whole chunk is inside
+    const T* p = b + (size_t)E * h0;
+    T x[16 * E];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4 * E; ++e) x[4 * E * q + e] = p[E * (4 * kScanThreads * q) + e];
+#pragma unroll
+    for (int q = 0; q < 16 * E; ++q) mx = max64(mx, abs_bits(x[q]));
+  } else {
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const T* p = b + (size_t)E * min(h0 + 4 * kScanThreads * q + e, k - 1);
+        mx = max64(mx, abs_bits(p[0]));
+        if (E == 2) mx = max64(mx, abs_bits(p[E - 1]));
+      }
+  }
+  for (int off = 1; off < 64; off <<= 1) mx = max64(mx, __shfl_xor((unsigned long long)mx, off));
+  red[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x) return;
+  for (int w = 1; w < kScanThreads / 64; ++w) mx = max64(mx, red[w]);
+  if (mx) atomicMax((unsigned long long*)&bits[j], (unsigned long long)mx);
+}
+
 template <typename T, SliceSet F>
 __global__ __launch_bounds__(kScanThreads, F == SliceSet::Real ? 4 : 2) void k_scan(ScanArgs s) {
   __shared__ StripLds<F> lds;
-  if (s.clear)
-    scan_clear(s.a.mx, s.a.rows_pad, s.b.mx, s.b.rows_pad, s.flag,
-               (int)(blockIdx.x * kScanThreads + threadIdx.x), (int)gridDim.x * kScanThreads);
+  scan_clear(s.a.mx, s.a.rows_pad, s.b.mx, s.b.rows_pad, s.flag,
+             (int)(blockIdx.x * kScanThreads + threadIdx.x), (int)gridDim.x * kScanThreads);
   const int u = (int)blockIdx.x;
   if (u >= s.a.units)
     scan_cols<T, F>(static_cast<const T*>(s.b.src), s.b.ld, s.b.rows, s.b.rows_pad, s.k, s.k_pad,
                     s.b.bits, s.b.out, u - s.a.units, s.tpc, &lds.red[0][0]);
-  else if (s.chunked)
-    absmax_rows_body<T, F>(static_cast<const T*>(s.a.src), s.a.ld, s.a.rows, s.k, s.half, s.a.bits,
-                           2 * u + (int)(threadIdx.x >> 8), (int)(threadIdx.x & 255));
   else
     scan_strip<T, F>(static_cast<const T*>(s.a.src), s.a.ld, s.a.rows, s.k, s.k_pad, s.half,
                      s.a.bits, s.a.out, u, s.lr, lds);
 }
 
+// The chunked scan, in a kernel of its own for the registers of k_scan.
+template <typename T, SliceSet F>
+__global__ __launch_bounds__(kScanThreads, F == SliceSet::Real ? 4 : 2) void k_scan_chunks(
+    ScanArgs s) {
+  __shared__ unsigned long long red[kScanThreads];
+  const int u = (int)blockIdx.x;
+  if (u < s.a.units)
+    absmax_row_chunk<T, F>(static_cast<const T*>(s.a.src), s.a.ld, s.a.rows, s.k, s.half, s.a.bits,
+                           u, s.tr, red);
+  else if (s.cols_chunked)
+    absmax_col_chunk<T, F>(static_cast<const T*>(s.b.src), s.b.ld, s.b.rows, s.k, s.b.bits,
+                           u - s.a.units, red);
+  else
+    scan_cols<T, F>(static_cast<const T*>(s.b.src), s.b.ld, s.b.rows, s.b.rows_pad, s.k, s.k_pad,
+                    s.b.bits, s.b.out, u - s.a.units, s.tpc, red);
+}
+
 // What the atomics of a chunked scan need cleared, with the maxima and the flag.
-__global__ __launch_bounds__(256) void k_clear(uint64_t* bits, int* mx_a, int na, int* mx_b, int nb,
-                                               int* flag) {
+__global__ __launch_bounds__(256) void k_clear(uint64_t* bits, int* mx_a, int na, uint64_t* bits_b,
+                                               int* mx_b, int nb, int* flag) {
   const int t = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
   for (int i = t; i < na; i += stride) bits[i] = 0;
+  if (bits_b)
+    for (int j = t; j < nb; j += stride) bits_b[j] = 0;
   scan_clear(mx_a, na, mx_b, nb, flag, t, stride);
 }
 
 // Strips over all of k: each strip streams its 128 k bytes (256 k for pairs of
 // FP64) by itself, at about 55 GB/s, so they are taken when that is short (k <=
 // 4096) or when there are enough strips to fill the memory system.  At 128 x
-// 128 x 8192 (8 strips) they took 46 us, the chunked scan 23 us; at 4096^3 (256
+// 128 x 8192 (8 strips) they took 46 us, the chunked scan 20 us; at 4096^3 (256
 // strips) 82 us against 91 us for chunks.
-__host__ __device__ inline bool strips_fit(int rows_pad, int lr, int k) {
-  return k <= 4096 || rows_pad >> lr >= 96;
+// A pass of a strip addresses its columns with 32 bits (pitch: bytes from one to
+// the next), which saves the registers that 64-bit addresses spilled: 16.5 and
+// 13.5 us at 1000x700x1300.
+__host__ __device__ inline bool strips_fit(int rows_pad, int lr, int k, size_t pitch) {
+  const int pass = 16 << (9 - lr);
+  return (k <= 4096 || rows_pad >> lr >= 96) &&
+         (size_t)((pass < k ? pass : k) + 1) * pitch < (size_t)1 << 32;
 }
+
+// B's columns in chunks too, with bars in the slice kernel.  By columns, a
+// workgroup streams each twice, which is as much traffic in less work but leaves
+// most compute units idle when there are few.  Whole calls by columns and in
+// chunks: 60 columns of 100000 493 and 474 us, 64 of 262144 533 and 445; 128 of
+// 16384 69 and 71, 200 of 100000 479 and 493.
+__host__ __device__ inline bool cols_chunked(int n) { return n <= 100; }
 
 // ---------------------------------------------------------------------------
 // double-double helpers (Dekker / Knuth error-free transformations)
@@ -505,8 +594,10 @@ __global__ __launch_bounds__(256) void kg_absmax_rows(const ProbDesc* __restrict
                                                       const BlockRef* __restrict__ map) {
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
-  absmax_rows_body<T, SliceSet::Real>((const T*)d.A, d.lda, d.m, d.k, 0, d.rowbits, e.y,
-                                      threadIdx.x);
+  const int gx = cdiv_i(d.m, 256), i = e.y % gx * 256 + (int)threadIdx.x;
+  const uint64_t mx =
+      absmax_row_part<T, SliceSet::Real>((const T*)d.A, d.lda, d.m, d.k, i, e.y / gx * 64);
+  if (i < d.m && mx) atomicMax((unsigned long long*)&d.rowbits[i], (unsigned long long)mx);
 }
 
 // A problem's strips (none where its scan is chunked), then its columns.
@@ -518,7 +609,7 @@ __global__ __launch_bounds__(kScanThreads, 4) void kg_scan(const ProbDesc* __res
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
   const int lr = strip_rows_log2<T>(d.kp, fine);
-  const bool chunked = !strips_fit(d.mp, lr, d.k);
+  const bool chunked = !strips_fit(d.mp, lr, d.k, d.lda * sizeof(T));
   const int strips = chunked ? 0 : d.mp >> lr;
   if (!chunked && e.y == 0)
     scan_clear(d.rmax, d.mp, d.cmax, d.np, d.flag, threadIdx.x, kScanThreads);
@@ -556,15 +647,20 @@ void scan_t(hipStream_t s, ScanArgs& a) {
   const bool fine = scan_fine((int64_t)(span >> kMinStripLog2<T>) + a.b.rows_pad / 8);
   a.lr = strip_rows_log2<T>(a.k_pad, fine);
   a.tpc = col_threads(a.k_pad, kColKeep<F>, fine);
-  a.chunked = !strips_fit(span, a.lr, a.k);
-  a.clear = !a.chunked;
+  a.chunked = !strips_fit(span, a.lr, a.k, a.a.ld * sizeof(T) * (F == SliceSet::Real ? 1 : 2));
+  a.cols_chunked = a.chunked && cols_chunked(a.b.rows);
+  a.tr = chunk_rows(a.a.rows);
   if (a.chunked)
     hipLaunchKernelGGL(k_clear, dim3(clear_blocks(a.a.rows_pad, a.b.rows_pad)), dim3(256), 0, s,
-                       a.a.bits, a.a.mx, a.a.rows_pad, a.b.mx, a.b.rows_pad, a.flag);
-  a.a.units = a.chunked ? cdiv(cdiv(a.a.rows, 256) * cdiv(a.k, 64), 2) : span >> a.lr;
-  a.b.units = col_units(a.b.rows_pad, a.tpc);
-  hipLaunchKernelGGL((k_scan<T, F>), dim3((unsigned)(a.a.units + a.b.units)), dim3(kScanThreads), 0,
-                     s, a);
+                       a.a.bits, a.a.mx, a.a.rows_pad, a.cols_chunked ? a.b.bits : nullptr, a.b.mx,
+                       a.b.rows_pad, a.flag);
+  a.a.units = a.chunked ? row_chunks(a.a.rows, a.k, a.tr) : span >> a.lr;
+  a.b.units = a.cols_chunked ? a.b.rows * cdiv(a.k, kColChunk) : col_units(a.b.rows_pad, a.tpc);
+  const dim3 grid((unsigned)(a.a.units + a.b.units)), block(kScanThreads);
+  if (a.chunked)
+    hipLaunchKernelGGL((k_scan_chunks<T, F>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_scan<T, F>), grid, block, 0, s, a);
 }
 
 template <typename T>
@@ -595,9 +691,9 @@ void launch_scan(hipStream_t s, Prec pr, SliceSet set, const SliceOperand& A, co
     scan_set<double>(s, set, a);
   else
     scan_set<float>(s, set, a);
-  if (a.chunked) {   // A's bars: the constants are not used
+  if (a.chunked) {   // A's bars, and B's: the constants are not used
     CrtConsts cc{};
-    launch_slices(s, pr, set, true, &A, nullptr, k, k_pad, cc, nullptr);
+    launch_slices(s, pr, set, true, &A, a.cols_chunked ? &B : nullptr, k, k_pad, cc, nullptr);
   }
 }
 
@@ -609,14 +705,14 @@ int group_strip_log2(Prec pr, int k_pad, bool fine) {
 }  // namespace
 
 bool scan_group_fine(int64_t units) { return scan_fine(units); }
-bool scan_group_chunked(Prec pr, int m_pad, int k, int k_pad, bool fine) {
-  return !strips_fit(m_pad, group_strip_log2(pr, k_pad, fine), k);
+bool scan_group_chunked(Prec pr, const ProbDesc& d, bool fine) {
+  return !strips_fit(d.mp, group_strip_log2(pr, d.kp, fine), d.k,
+                     d.lda * (pr == Prec::F64 ? sizeof(double) : sizeof(float)));
 }
-int scan_group_blocks(Prec pr, int m_pad, int n_pad, int k, int k_pad, bool fine) {
-  const int strips = scan_group_chunked(pr, m_pad, k, k_pad, fine)
-                         ? 0
-                         : m_pad >> group_strip_log2(pr, k_pad, fine);
-  return strips + col_units(n_pad, col_threads(k_pad, kColKeep<SliceSet::Real>, fine));
+int scan_group_blocks(Prec pr, const ProbDesc& d, bool fine) {
+  const int strips =
+      scan_group_chunked(pr, d, fine) ? 0 : d.mp >> group_strip_log2(pr, d.kp, fine);
+  return strips + col_units(d.np, col_threads(d.kp, kColKeep<SliceSet::Real>, fine));
 }
 
 void launch_debug_shifts(hipStream_t s, const uint64_t* rowbits, const int* rmax, int m,
