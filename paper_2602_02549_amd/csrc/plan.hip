@@ -66,21 +66,73 @@ __device__ inline bool plan_ok(const PlanTable& pt, int N, double A1, double P2,
   return T <= target;
 }
 
-// The per-entry kernels below walk the m x n entries in a grid-stride loop
-// over tasks of 256 consecutive i of one column j, and combine their results
-// with one atomic per workgroup: one per 256 entries would serialise on the
-// single result word (about 11 ns each).
+// The per-entry kernels below walk the m x n entries by waves in a grid-stride
+// loop over tasks of 256 consecutive i of one column j, four rows per lane, and
+// combine their results with one atomic per workgroup: one per 256 entries would
+// serialise on the single result word (about 11 ns each).  With one row per lane
+// and a division, a reduction or both per 256 entries they were bound by
+// instructions: 64 us (plan_entries), 38 (plan_verify) and 74 (certify) at
+// 4096^2 against 52, 25 and 58 so; the bytes take 13, 13 and 40.
 constexpr int kEntryWorkgroups = 2048;
 
 template <typename F>
-__device__ __forceinline__ void for_entries(int m, int n, int iblocks, F&& f) {
-  const int64_t tasks = (int64_t)iblocks * n;
-  for (int64_t task = blockIdx.x; task < tasks; task += gridDim.x) {
-    const int j = (int)(task / iblocks);
-    const int i = (int)(task % iblocks) * 256 + (int)threadIdx.x;
-    if (i < m) f(i, j);
+__device__ __forceinline__ void for_quads(int m, int n, F&& f) {
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int blocks = cdiv_i(m, 256), stride = (int)gridDim.x * 4;
+  const int first = (int)blockIdx.x * 4 + wave;
+  const int dj = stride / blocks, db = stride - dj * blocks;
+  int64_t j = first / blocks;
+  int b = first % blocks;
+  while (j < n) {
+    f(b * 256 + 4 * lane, (int)j);
+    j += dj;
+    b += db;
+    if (b >= blocks) {
+      b -= blocks;
+      ++j;
+    }
   }
 }
+
+// v[i0 .. i0 + 3], past the last row m - 1 that one again.
+template <typename T>
+__device__ __forceinline__ void load_rows(const T* __restrict__ v, int i0, int m, T (&x)[4]) {
+  if (i0 + 4 <= m) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = v[i0 + e];
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = v[min(i0 + e, m - 1)];
+  }
+}
+
+// Four entries of a column of S (columns lds_ apart, a multiple of 128) with
+// their lower bounds: `pos` marks those with a positive one, `null` those that
+// are nonzero without.
+struct Quad {
+  double Sl[4];
+  bool pos[4], null[4];
+  __device__ __forceinline__ Quad(const float* __restrict__ S, const uint8_t* __restrict__ nz,
+                                  int lds_, int m, int i0, int j, double scale) {
+    const size_t o = (size_t)j * lds_ + i0;
+    const float4 v = *reinterpret_cast<const float4*>(S + o);
+    const float w[4] = {v.x, v.y, v.z, v.w};
+    bool some = false;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      Sl[e] = (double)w[e] * scale;
+      pos[e] = i0 + e < m && Sl[e] > 0.0;
+      null[e] = i0 + e < m && !(Sl[e] > 0.0);
+      some |= null[e];
+    }
+    if (some) {
+      const uint32_t b = *reinterpret_cast<const uint32_t*>(nz + o);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) null[e] = null[e] && (b >> (8 * e) & 0xFF) != 0;
+    }
+  }
+};
 
 // Maximum of v over the workgroup (256 threads), valid in thread 0.
 template <typename T>
@@ -104,43 +156,46 @@ __device__ __forceinline__ T block_max(T v) {
 // coefficients are wave-uniform (scalar) loads.
 __global__ __launch_bounds__(256) void k_plan_entries(const float* __restrict__ S,
                                                       const uint8_t* __restrict__ nz, int lds_,
-                                                      int m, int n, int iblocks,
-                                                      const double* __restrict__ rs,
+                                                      int m, int n, const double* __restrict__ rs,
                                                       const double* __restrict__ cs,
                                                       const double* __restrict__ sr,
                                                       const double* __restrict__ sc, PlanTable pt,
                                                       int* __restrict__ out) {
   int need = 0;   // wave-uniform running bound
-  const int64_t tasks = (int64_t)iblocks * n;
-  for (int64_t task = blockIdx.x; task < tasks; task += gridDim.x) {
-    const int j = (int)(task / iblocks);
-    const int i = (int)(task % iblocks) * 256 + (int)threadIdx.x;
-    bool live = false;
-    double A1 = 0.0, P2 = 0.0, target = 0.0;
-    if (i < m) {
-      const double Sl = (double)S[(size_t)j * lds_ + i] * pt.acc_scale;
-      if (Sl > 0.0) {
-        A1 = rs[i] * sc[j] + sr[i] * cs[j];
-        P2 = sr[i] * sc[j];
-        target = pt.eps * Sl;
-        live = true;
-      } else if (nz[(size_t)j * lds_ + i]) {
-        live = true;          // nonzero (|A||B|)_ij with no positive lower bound:
-        target = -1.0;        // T >= 0 never meets it, so no N is accepted
+  for_quads(m, n, [&](int i0, int j) {
+    bool live[4] = {false, false, false, false};
+    double A1[4], P2[4], target[4];
+    if (i0 < m) {
+      const Quad q(S, nz, lds_, m, i0, j, pt.acc_scale);
+      double r[4], g[4];
+      load_rows(rs, i0, m, r);
+      load_rows(sr, i0, m, g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        A1[e] = r[e] * sc[j] + g[e] * cs[j];
+        P2[e] = g[e] * sc[j];
+        // nonzero (|A||B|)_ij with no positive lower bound: T >= 0 never meets
+        // -1, so no N is accepted
+        target[e] = q.pos[e] ? pt.eps * q.Sl[e] : -1.0;
+        live[e] = q.pos[e] || q.null[e];
       }
     }
-    int first = 0;
+    int found = 0;
     for (int N = max(pt.nlo, need); N <= pt.nhi; ++N) {
-      if (!__any(live)) break;
-      if (live && plan_ok(pt, N, A1, P2, target)) {
-        first = N;
-        live = false;
-      }
+      if (!__any(live[0] || live[1] || live[2] || live[3])) break;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (live[e] && plan_ok(pt, N, A1[e], P2[e], target[e])) {
+          found = N;
+          live[e] = false;
+        }
     }
-    if (live) first = pt.nhi + 1;
-    for (int off = 32; off >= 1; off >>= 1) first = max(first, __shfl_xor(first, off));
-    need = __builtin_amdgcn_readfirstlane(max(need, first));
-  }
+    if (live[0] || live[1] || live[2] || live[3]) found = pt.nhi + 1;
+    if (__any(found > need)) {
+      for (int off = 32; off >= 1; off >>= 1) found = max(found, __shfl_xor(found, off));
+      need = __builtin_amdgcn_readfirstlane(max(need, found));
+    }
+  });
   need = block_max(need);
   if (threadIdx.x == 0 && need > 0) atomicMax(out, need);
 }
@@ -150,8 +205,7 @@ __global__ __launch_bounds__(256) void k_plan_entries(const float* __restrict__ 
 // checked if it exceeds nhi.
 __global__ __launch_bounds__(256) void k_plan_verify(const float* __restrict__ S,
                                                      const uint8_t* __restrict__ nz, int lds_, int m,
-                                                     int n, int iblocks,
-                                                     const double* __restrict__ rs,
+                                                     int n, const double* __restrict__ rs,
                                                      const double* __restrict__ cs,
                                                      const double* __restrict__ sr,
                                                      const double* __restrict__ sc, PlanTable pt,
@@ -160,14 +214,17 @@ __global__ __launch_bounds__(256) void k_plan_verify(const float* __restrict__ S
   if (Nsrc) N = max(__builtin_amdgcn_readfirstlane(*Nsrc), pt.nlo);
   if (N > pt.nhi) return;   // uniform: before any barrier
   int fail = 0;
-  for_entries(m, n, iblocks, [&](int i, int j) {
-    const double Sl = (double)S[(size_t)j * lds_ + i] * pt.acc_scale;
-    if (Sl > 0.0) {
-      const double A1 = rs[i] * sc[j] + sr[i] * cs[j];
-      const double P2 = sr[i] * sc[j];
-      if (!plan_ok(pt, N, A1, P2, pt.eps * Sl)) fail = 1;
-    } else if (nz[(size_t)j * lds_ + i]) {
-      fail = 1;
+  for_quads(m, n, [&](int i0, int j) {
+    if (i0 >= m) return;
+    const Quad q(S, nz, lds_, m, i0, j, pt.acc_scale);
+    double r[4], g[4];
+    load_rows(rs, i0, m, r);
+    load_rows(sr, i0, m, g);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const double A1 = r[e] * sc[j] + g[e] * cs[j];
+      const double P2 = g[e] * sc[j];
+      if (q.null[e] || (q.pos[e] && !plan_ok(pt, N, A1, P2, pt.eps * q.Sl[e]))) fail = 1;
     }
   });
   fail = block_max(fail);
@@ -191,24 +248,34 @@ __global__ __launch_bounds__(256) void k_certify(const T* __restrict__ C, int ld
                                                  const int* __restrict__ nu,
                                                  const float* __restrict__ S,
                                                  const uint8_t* __restrict__ nz, int lds_, int m,
-                                                 int n, int iblocks, const double* __restrict__ rs,
+                                                 int n, const double* __restrict__ rs,
                                                  const double* __restrict__ cs,
                                                  const double* __restrict__ sr,
                                                  const double* __restrict__ sc, CertTable ct,
                                                  unsigned long long* __restrict__ out) {
   double ratio = 0.0;
-  for_entries(m, n, iblocks, [&](int i, int j) {
-    const double Sl = (double)S[(size_t)j * lds_ + i] * ct.acc_scale;
-    if (Sl > 0.0) {
-      const double c = fabs((double)C[i + (size_t)j * ldc]) + ct.tiny;
-      const double cpp = ldexp(c, mu[i] + nu[j]);
-      const double A1 = rs[i] * sc[j] + sr[i] * cs[j];
-      const double P2 = sr[i] * sc[j];
+  for_quads(m, n, [&](int i0, int j) {
+    if (i0 >= m) return;
+    const Quad q(S, nz, lds_, m, i0, j, ct.acc_scale);
+    double r[4], g[4];
+    int u[4];
+    T c[4];
+    load_rows(rs, i0, m, r);
+    load_rows(sr, i0, m, g);
+    load_rows(mu, i0, m, u);
+    load_rows(C + (size_t)j * ldc, i0, m, c);
+    const int nuj = nu[j];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (q.null[e]) ratio = INFINITY;   // nonzero (|A||B|)_ij with no positive lower bound
+      if (!q.pos[e]) continue;
+      const double cpp = ldexp(fabs((double)c[e]) + ct.tiny, u[e] + nuj);
+      const double A1 = r[e] * sc[j] + g[e] * cs[j];
+      const double P2 = g[e] * sc[j];
       const double est =
           (ct.t * A1 + (ct.k * ct.tt + ct.extra + ct.rel * (cpp + ct.rconst) * kTUp) * P2) * kTUp;
-      ratio = fmax(ratio, est / Sl * kTUp);
-    } else if (nz[(size_t)j * lds_ + i]) {
-      ratio = INFINITY;     // nonzero (|A||B|)_ij with no positive lower bound
+      // the quotient only where it can be the maximum
+      if (!(est <= ratio * q.Sl[e] * (1.0 - 0x1p-20))) ratio = fmax(ratio, est / q.Sl[e] * kTUp);
     }
   });
   ratio = block_max(ratio);
@@ -216,9 +283,9 @@ __global__ __launch_bounds__(256) void k_certify(const T* __restrict__ C, int ld
     atomicMax(out, (unsigned long long)__double_as_longlong(ratio));
 }
 
-unsigned entry_grid(int iblocks, int n) {
-  const int64_t tasks = (int64_t)iblocks * n;
-  return (unsigned)(tasks < kEntryWorkgroups ? tasks : kEntryWorkgroups);
+unsigned entry_grid(int m, int n) {
+  const int64_t groups = ((int64_t)cdiv_i(m, 256) * n + 3) / 4;
+  return (unsigned)(groups < kEntryWorkgroups ? groups : kEntryWorkgroups);
 }
 
 }  // namespace
@@ -227,14 +294,13 @@ void launch_certify(hipStream_t s, Prec pr, const void* C, int ldc, const int* m
                     const float* S, const uint8_t* nz, int lds_, int m, int n, const double* rs,
                     const double* cs, const double* sr, const double* sc, const CertTable& ct,
                     unsigned long long* out) {
-  const int iblocks = (m + 255) / 256;
-  const dim3 grid(entry_grid(iblocks, n)), block(256);
+  const dim3 grid(entry_grid(m, n)), block(256);
   if (pr == Prec::F64)
     hipLaunchKernelGGL(k_certify<double>, grid, block, 0, s, (const double*)C, ldc, mu, nu, S, nz,
-                       lds_, m, n, iblocks, rs, cs, sr, sc, ct, out);
+                       lds_, m, n, rs, cs, sr, sc, ct, out);
   else
     hipLaunchKernelGGL(k_certify<float>, grid, block, 0, s, (const float*)C, ldc, mu, nu, S, nz,
-                       lds_, m, n, iblocks, rs, cs, sr, sc, ct, out);
+                       lds_, m, n, rs, cs, sr, sc, ct, out);
 }
 
 void launch_plan_vectors(hipStream_t s, const double* pr, int m_pad, const double* pc, int n_pad,
@@ -247,17 +313,15 @@ void launch_plan_vectors(hipStream_t s, const double* pr, int m_pad, const doubl
 void launch_plan_entries(hipStream_t s, const float* S, const uint8_t* nz, int lds_, int m, int n,
                          const double* rs, const double* cs, const double* sr, const double* sc,
                          const PlanTable& pt, int* out) {
-  const int iblocks = (m + 255) / 256;
-  hipLaunchKernelGGL(k_plan_entries, dim3(entry_grid(iblocks, n)), dim3(256), 0, s, S, nz,
-                     lds_, m, n, iblocks, rs, cs, sr, sc, pt, out);
+  hipLaunchKernelGGL(k_plan_entries, dim3(entry_grid(m, n)), dim3(256), 0, s, S, nz,
+                     lds_, m, n, rs, cs, sr, sc, pt, out);
 }
 
 void launch_plan_verify(hipStream_t s, const float* S, const uint8_t* nz, int lds_, int m, int n,
                         const double* rs, const double* cs, const double* sr, const double* sc,
                         const PlanTable& pt, int N, const int* Nsrc, int* bad) {
-  const int iblocks = (m + 255) / 256;
-  hipLaunchKernelGGL(k_plan_verify, dim3(entry_grid(iblocks, n)), dim3(256), 0, s, S, nz,
-                     lds_, m, n, iblocks, rs, cs, sr, sc, pt, N, Nsrc, bad);
+  hipLaunchKernelGGL(k_plan_verify, dim3(entry_grid(m, n)), dim3(256), 0, s, S, nz,
+                     lds_, m, n, rs, cs, sr, sc, pt, N, Nsrc, bad);
 }
 
 }  // namespace oz2
