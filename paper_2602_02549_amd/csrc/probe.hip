@@ -1,6 +1,7 @@
-// MFMA-rate probe: v_mfma_i32_32x32x32_i8, the instruction of the residue
-// products, issued back to back on INT8 operands that change every step,
-// with no memory traffic at all.  The rate it sustains is the ceiling the
+// MFMA-rate probe: v_mfma_i32_32x32x32_i8, the larger of the two INT8
+// instructions (the products use 16x16x64, which takes less energy per
+// operation), issued back to back on INT8 operands that change every step, with
+// no memory traffic at all.  The rate it sustains is the ceiling the
 // chip's power limit leaves for that instruction on changing data, against
 // which the residue products can be read (a measurement aid, not part of
 // the method).
