@@ -61,6 +61,7 @@ typedef __bf16 v8bf16 __attribute__((ext_vector_type(8)));
 
 constexpr int kXcds = 8;
 constexpr int kCus = 256;   // compute units that the launch rules count with
+constexpr size_t kRoundBytes = (size_t)96 << 20;   // operands of a slice: see walk_in_rounds
 constexpr int kFoldGroups = (1 << 17) / 128;   // 128-k groups per 2^17 of k
 
 // mod(x, p) of an INT32 product as an INT8 value (Section 1.2), odd p: the
@@ -137,20 +138,29 @@ __device__ __forceinline__ int xcd_place(int bid, int launched) {
   return xcd * per + min(xcd, extra) + loc;
 }
 
-// Place -> (slice z, tile tx, ty): slice by slice, and in a slice groups of 8
-// tile rows (the 32 workgroups of an XCD share their panels in its L2).
+// The same for launches of one workgroup per CU: every kCus of the walk in a
+// round over all XCDs, in which an XCD takes 8 x 4 of 16 x 16 places, so that a
+// round reads 32 panels of the operands from memory and not 12 for each XCD.
+__device__ __forceinline__ int round_place(int bid, int launched) {
+  const int first = bid & ~(kCus - 1);
+  if (first + kCus > launched) return first + xcd_place(bid - first, launched - first);
+  const int xcd = bid % kXcds, loc = (bid - first) / kXcds;
+  return first + 16 * (4 * (xcd >> 1) + (loc >> 3)) + 8 * (xcd & 1) + (loc & 7);
+}
+
+// Place -> (slice z, tile tx, ty): slice by slice, and in a slice groups of
+// `group` tile rows (the 32 workgroups of an XCD share their panels in its L2).
 struct TilePos {
   int z, tx, ty;
 };
-__device__ __forceinline__ TilePos tile_at(int place, int tiles_x, int tiles_y) {
-  constexpr int GROUP = 8;
+__device__ __forceinline__ TilePos tile_at(int place, int tiles_x, int tiles_y, int group = 8) {
   const int per_slice = tiles_x * tiles_y;
   const int z = place / per_slice;
   int t = place % per_slice;
-  const int g = t / (GROUP * tiles_y);
-  const int gx0 = g * GROUP;
-  const int gsz = min(GROUP, tiles_x - gx0);
-  t -= g * GROUP * tiles_y;
+  const int g = t / (group * tiles_y);
+  const int gx0 = g * group;
+  const int gsz = min(group, tiles_x - gx0);
+  t -= g * group * tiles_y;
   return {z, gx0 + t % gsz, t / gsz};
 }
 
@@ -761,14 +771,15 @@ __global__ __launch_bounds__(tile_threads<B>(), TileShape<B>::OCC) void k_gemm_i
     const int8_t* __restrict__ X, size_t sx, const int8_t* __restrict__ Y, size_t sy, int tiles_x,
     int tiles_y, int nz, int k_pad, int8_t* __restrict__ W, size_t sw, int ldw,
     int* __restrict__ xmax, int* __restrict__ ymax, int nsplit, int full, int vx, int vy,
-    CrtConsts cc) {
+    int rounds, CrtConsts cc) {
   __shared__ __attribute__((aligned(1024))) int8_t lds[NS * 2 * B * 128];
   constexpr int NWX = TileShape<B>::NWX, NWY = TileShape<B>::NWY;
   const int bid = (int)blockIdx.x;
+  const int group = B == 256 && rounds ? 16 : 8;
   if constexpr (TAIL > 0) {
     if (bid >= full) {
       const int place = xcd_place(bid - full, (int)gridDim.x - full);
-      const TilePos t = tile_at(full + place / TAIL, tiles_x, tiles_y);
+      const TilePos t = tile_at(full + place / TAIL, tiles_x, tiles_y, group);
       const int part = place % TAIL;
       constexpr int SX = TAIL == 4 ? B / 2 : B, SY = B / 2;
       // a wave's share is 64 rows of X in every build
@@ -780,11 +791,12 @@ __global__ __launch_bounds__(tile_threads<B>(), TileShape<B>::OCC) void k_gemm_i
       return;
     }
   }
-  int place = xcd_place(bid, TAIL > 0 ? full : (int)gridDim.x);
+  const int whole = TAIL > 0 ? full : (int)gridDim.x;
+  int place = B == 256 && rounds ? round_place(bid, whole) : xcd_place(bid, whole);
   const int per_split = tiles_x * tiles_y * nz;
   const int sidx = SPLIT ? place / per_split : 0;
   place -= sidx * per_split;
-  const TilePos t = tile_at(place, tiles_x, tiles_y);
+  const TilePos t = tile_at(place, tiles_x, tiles_y, group);
   gemm_body<B, B, NWX, NWY, EPI, BF16, FOLD, SPLIT, NS>(lds, X, sx, Y, sy, t.tx * B, t.ty * B, t.z,
                                                         nz, k_pad, cc, W, sw, ldw, xmax, ymax, sidx,
                                                         SPLIT ? nsplit : 1, vx, vy);
@@ -899,6 +911,17 @@ int tail_parts(long tiles) {
   return 4 * rem <= kCus ? 4 : 2;
 }
 
+// Whether a launch walks its tiles in rounds over all XCDs (round_place) or
+// gives each XCD a range of its own.  In ranges, the XCDs work on up to eight
+// slices at once, whose operands the MALL (256 MB) holds when they are small; in
+// rounds all read the same panels.  Residue products in ranges and in rounds:
+// 7 of 16384^3 (537 MB a slice) 23.8 and 21.4 ms, 14 of 8192^3 (134 MB) 5550 and
+// 5390 us, of 3000x3000x20000 (122 MB) 2160 and 2045; but of 4096x4096x8192 (67
+// MB) 1383 and 1445, 18 of 4096^3 (34 MB) 936 and 987.
+bool walk_in_rounds(int nx_pad, int ny_pad, int k_pad) {
+  return (size_t)(nx_pad + ny_pad) * k_pad > kRoundBytes;
+}
+
 template <int B>
 void launch_cfg(hipStream_t s, int epi, const int8_t* X, size_t sx, const int8_t* Y, size_t sy,
                 int nx_pad, int ny_pad, int k_pad, int nz, const CrtConsts& cc, int8_t* W,
@@ -906,13 +929,14 @@ void launch_cfg(hipStream_t s, int epi, const int8_t* X, size_t sx, const int8_t
   const int tiles_x = nx_pad / B, tiles_y = ny_pad / B;
   const int wgs = tiles_x * tiles_y * nz * nsplit;
   int full = wgs;
+  const int rounds = B == 256 && nsplit == 1 && walk_in_rounds(nx_pad, ny_pad, k_pad);
   dim3 grid((unsigned)wgs);
   const dim3 block(tile_threads<B>());
   const bool deep = B == 128 && wgs <= kCus;   // one workgroup per CU: the deep ring
 #define OZ2_GEMM_NS(E, F, S, NS, T)                                                             \
   hipLaunchKernelGGL((k_gemm_i8<B, E, false, F, S, NS, T>), grid, block, 0, s, X, sx, Y, sy,     \
                      tiles_x, tiles_y, nz, k_pad, W, sw, ldw, xmax, ymax, nsplit, full, vx, \
-                     vy, cc)
+                     vy, rounds, cc)
 #define OZ2_GEMM(E, F, S)                                                                       \
   do {                                                                                          \
     if constexpr (B == 128) {                                                                   \
@@ -1124,13 +1148,13 @@ void launch_gemm_bf16_store(hipStream_t s, const uint16_t* X, const uint16_t* Y,
     hipLaunchKernelGGL((k_gemm_i8<256, 2, true>), dim3((unsigned)(tiles_x * tiles_y)),
                        dim3(tile_threads<256>()), 0, s, (const int8_t*)X, 0, (const int8_t*)Y, 0,
                        tiles_x, tiles_y, 1, kb, (int8_t*)S, 0, lds_, nullptr, nullptr, 1,
-                       tiles_x * tiles_y, nx_pad, ny_pad, cc);
+                       tiles_x * tiles_y, nx_pad, ny_pad, 0, cc);
   } else {
     const int tiles_x = nx_pad / 128, tiles_y = ny_pad / 128;
     hipLaunchKernelGGL((k_gemm_i8<128, 2, true>), dim3((unsigned)(tiles_x * tiles_y)),
                        dim3(tile_threads<128>()), 0, s, (const int8_t*)X, 0, (const int8_t*)Y, 0,
                        tiles_x, tiles_y, 1, kb, (int8_t*)S, 0, lds_, nullptr, nullptr, 1,
-                       tiles_x * tiles_y, nx_pad, ny_pad, cc);
+                       tiles_x * tiles_y, nx_pad, ny_pad, 0, cc);
   }
 }
 
