@@ -110,11 +110,24 @@ __device__ __forceinline__ void bars_of(T re, T im, int sh, int* b0, int* b1) {
   }
 }
 
-__device__ __forceinline__ void scan_clear(int* mx_a, int na, int* mx_b, int nb, int* flag, int t,
-                                           int stride) {
-  for (int i = t; i < na; i += stride) mx_a[i] = 0;
-  for (int j = t; j < nb; j += stride) mx_b[j] = 0;
+// By thread t of `stride` (at most 2^31, so that no index wraps).
+__device__ __forceinline__ void scan_clear(int* mx_a, int na, int* mx_b, int nb, int* flag,
+                                           unsigned t, unsigned stride) {
+  for (unsigned i = t; i < (unsigned)na; i += stride) mx_a[i] = 0;
+  for (unsigned j = t; j < (unsigned)nb; j += stride) mx_b[j] = 0;
   if (t == 0) *flag = 0;
+}
+
+// Workgroups of a scan in two grid dimensions: a launch takes fewer than 2^32
+// threads along x, which 2^23 columns of more than kColWaveK rows, a workgroup
+// each (69 GB of FP32), would exceed.
+constexpr int kScanGridX = 1 << 22;
+inline dim3 scan_grid(int units) {
+  return dim3((unsigned)(units < kScanGridX ? units : kScanGridX),
+              (unsigned)((units - 1) / kScanGridX + 1));
+}
+__device__ __forceinline__ int scan_unit() {
+  return (int)(blockIdx.y * gridDim.x + blockIdx.x);
 }
 
 // LDS of a strip: maxima per wave and row, and the bars of one chunk (two for
@@ -424,9 +437,11 @@ __device__ __forceinline__ void absmax_col_chunk(const T* __restrict__ B, int ld
 template <typename T, SliceSet F>
 __global__ __launch_bounds__(kScanThreads, F == SliceSet::Real ? 4 : 2) void k_scan(ScanArgs s) {
   __shared__ StripLds<F> lds;
-  scan_clear(s.a.mx, s.a.rows_pad, s.b.mx, s.b.rows_pad, s.flag,
-             (int)(blockIdx.x * kScanThreads + threadIdx.x), (int)gridDim.x * kScanThreads);
-  const int u = (int)blockIdx.x;
+  const int u = scan_unit();
+  if (u >= s.a.units + s.b.units) return;                // whole workgroup
+  if (blockIdx.y == 0)                                   // at most 2^31 threads
+    scan_clear(s.a.mx, s.a.rows_pad, s.b.mx, s.b.rows_pad, s.flag,
+               blockIdx.x * kScanThreads + threadIdx.x, gridDim.x * kScanThreads);
   if (u >= s.a.units)
     scan_cols<T, F>(static_cast<const T*>(s.b.src), s.b.ld, s.b.rows, s.b.rows_pad, s.k, s.k_pad,
                     s.b.bits, s.b.out, u - s.a.units, s.tpc, &lds.red[0][0]);
@@ -440,7 +455,8 @@ template <typename T, SliceSet F>
 __global__ __launch_bounds__(kScanThreads, F == SliceSet::Real ? 4 : 2) void k_scan_chunks(
     ScanArgs s) {
   __shared__ unsigned long long red[kScanThreads];
-  const int u = (int)blockIdx.x;
+  const int u = scan_unit();
+  if (u >= s.a.units + s.b.units) return;                // whole workgroup
   if (u < s.a.units)
     absmax_row_chunk<T, F>(static_cast<const T*>(s.a.src), s.a.ld, s.a.rows, s.k, s.half, s.a.bits,
                            u, s.tr, red);
@@ -455,10 +471,10 @@ __global__ __launch_bounds__(kScanThreads, F == SliceSet::Real ? 4 : 2) void k_s
 // What the atomics of a chunked scan need cleared, with the maxima and the flag.
 __global__ __launch_bounds__(256) void k_clear(uint64_t* bits, int* mx_a, int na, uint64_t* bits_b,
                                                int* mx_b, int nb, int* flag) {
-  const int t = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
-  for (int i = t; i < na; i += stride) bits[i] = 0;
+  const unsigned t = blockIdx.x * 256 + threadIdx.x, stride = gridDim.x * 256;
+  for (unsigned i = t; i < (unsigned)na; i += stride) bits[i] = 0;
   if (bits_b)
-    for (int j = t; j < nb; j += stride) bits_b[j] = 0;
+    for (unsigned j = t; j < (unsigned)nb; j += stride) bits_b[j] = 0;
   scan_clear(mx_a, na, mx_b, nb, flag, t, stride);
 }
 
@@ -584,8 +600,9 @@ __global__ __launch_bounds__(256) void kg_clear(const ProbDesc* __restrict__ P,
                                                 const BlockRef* __restrict__ map) {
   const BlockRef e = map[blockIdx.x];
   const ProbDesc& d = P[e.x];
-  const int t = e.y * 256 + threadIdx.x, stride = group_clear_blocks(d.mp, d.np) * 256;
-  for (int i = t; i < d.mp; i += stride) d.rowbits[i] = 0;
+  const unsigned t = (unsigned)e.y * 256 + threadIdx.x;
+  const unsigned stride = (unsigned)group_clear_blocks(d.mp, d.np) * 256;
+  for (unsigned i = t; i < (unsigned)d.mp; i += stride) d.rowbits[i] = 0;
   scan_clear(d.rmax, d.mp, d.cmax, d.np, d.flag, t, stride);
 }
 
@@ -604,9 +621,10 @@ __global__ __launch_bounds__(256) void kg_absmax_rows(const ProbDesc* __restrict
 template <typename T>
 __global__ __launch_bounds__(kScanThreads, 4) void kg_scan(const ProbDesc* __restrict__ P,
                                                         const BlockRef* __restrict__ map,
-                                                        int fine) {
+                                                        int units, int fine) {
   __shared__ StripLds<SliceSet::Real> lds;
-  const BlockRef e = map[blockIdx.x];
+  if (scan_unit() >= units) return;                      // whole workgroup
+  const BlockRef e = map[scan_unit()];
   const ProbDesc& d = P[e.x];
   const int lr = strip_rows_log2<T>(d.kp, fine);
   const bool chunked = !strips_fit(d.mp, lr, d.k, d.lda * sizeof(T));
@@ -656,7 +674,7 @@ void scan_t(hipStream_t s, ScanArgs& a) {
                        a.b.rows_pad, a.flag);
   a.a.units = a.chunked ? row_chunks(a.a.rows, a.k, a.tr) : span >> a.lr;
   a.b.units = a.cols_chunked ? a.b.rows * cdiv(a.k, kColChunk) : col_units(a.b.rows_pad, a.tpc);
-  const dim3 grid((unsigned)(a.a.units + a.b.units)), block(kScanThreads);
+  const dim3 grid = scan_grid(a.a.units + a.b.units), block(kScanThreads);
   if (a.chunked)
     hipLaunchKernelGGL((k_scan_chunks<T, F>), grid, block, 0, s, a);
   else
@@ -741,11 +759,11 @@ void launch_group_scan(hipStream_t s, Prec pr, const ProbDesc* P, const BlockRef
   }
   if (scan_blocks > 0) {
     if (pr == Prec::F64)
-      hipLaunchKernelGGL(kg_scan<double>, dim3((unsigned)scan_blocks), dim3(kScanThreads), 0, s, P,
-                         scan_map, fine ? 1 : 0);
+      hipLaunchKernelGGL(kg_scan<double>, scan_grid(scan_blocks), dim3(kScanThreads), 0, s, P,
+                         scan_map, scan_blocks, fine ? 1 : 0);
     else
-      hipLaunchKernelGGL(kg_scan<float>, dim3((unsigned)scan_blocks), dim3(kScanThreads), 0, s, P,
-                         scan_map, fine ? 1 : 0);
+      hipLaunchKernelGGL(kg_scan<float>, scan_grid(scan_blocks), dim3(kScanThreads), 0, s, P,
+                         scan_map, scan_blocks, fine ? 1 : 0);
   }
 }
 
