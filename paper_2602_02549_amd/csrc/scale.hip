@@ -478,17 +478,25 @@ __global__ __launch_bounds__(256) void k_clear(uint64_t* bits, int* mx_a, int na
   scan_clear(mx_a, na, mx_b, nb, flag, t, stride);
 }
 
-// Strips over all of k: each strip streams its 128 k bytes (256 k for pairs of
-// FP64) by itself, at about 55 GB/s, so they are taken when that is short (k <=
-// 4096) or when there are enough strips to fill the memory system.  At 128 x
-// 128 x 8192 (8 strips) they took 46 us, the chunked scan 20 us; at 4096^3 (256
-// strips) 82 us against 91 us for chunks.
+// Strips over all of k: each strip streams its columns by itself, a pass of 512 k
+// (FP64; 256 for FP32, whose strips have twice the rows) about every 1.9 us, and
+// all but the first passes twice.  So they are taken for up to 8 passes, when there
+// are enough of them to fill the memory system, and while the n columns of B, which
+// start a workgroup every 8 ns, take as long.  Otherwise the scan goes by chunks, for
+// about 10 us of launches.  At 128 x 128 x 8192 (8 strips) strips took 46 us, the
+// chunked scan 20 us; at 4096^3 (256 strips) 82 us against 91 us for chunks.  FP32
+// calls, strips and chunks: cgemm 130 x 1000 x 4096 160 and 123 us, sgemm of
+// 16 x 16 x 3000 42 and 33, of 2000 x 3000 x 2100 163 and 169.
+// The strips of a batch of many workgroups run beside those of other problems: there
+// up to 4096 of k (`many`).
 // A pass of a strip addresses its columns with 32 bits (pitch: bytes from one to
 // the next), which saves the registers that 64-bit addresses spilled: 16.5 and
 // 13.5 us at 1000x700x1300.
-__host__ __device__ inline bool strips_fit(int rows_pad, int lr, int k, size_t pitch) {
-  const int pass = 16 << (9 - lr);
-  return (k <= 4096 || rows_pad >> lr >= 96) &&
+__host__ __device__ inline bool strips_fit(int rows_pad, int lr, int k, int n, bool many,
+                                           size_t pitch) {
+  const int pass = 16 << (9 - lr), passes = (k + pass - 1) >> (13 - lr);
+  const bool brief = passes <= 8 || (k <= 4096 && (many || 450 * passes <= n + 1250));
+  return (brief || rows_pad >> lr >= 96) &&
          (size_t)((pass < k ? pass : k) + 1) * pitch < (size_t)1 << 32;
 }
 
@@ -627,7 +635,7 @@ __global__ __launch_bounds__(kScanThreads, 4) void kg_scan(const ProbDesc* __res
   const BlockRef e = map[scan_unit()];
   const ProbDesc& d = P[e.x];
   const int lr = strip_rows_log2<T>(d.kp, fine);
-  const bool chunked = !strips_fit(d.mp, lr, d.k, d.lda * sizeof(T));
+  const bool chunked = !strips_fit(d.mp, lr, d.k, d.n, !fine, d.lda * sizeof(T));
   const int strips = chunked ? 0 : d.mp >> lr;
   if (!chunked && e.y == 0)
     scan_clear(d.rmax, d.mp, d.cmax, d.np, d.flag, threadIdx.x, kScanThreads);
@@ -665,7 +673,8 @@ void scan_t(hipStream_t s, ScanArgs& a) {
   const bool fine = scan_fine((int64_t)(span >> kMinStripLog2<T>) + a.b.rows_pad / 8);
   a.lr = strip_rows_log2<T>(a.k_pad, fine);
   a.tpc = col_threads(a.k_pad, kColKeep<F>, fine);
-  a.chunked = !strips_fit(span, a.lr, a.k, a.a.ld * sizeof(T) * (F == SliceSet::Real ? 1 : 2));
+  a.chunked = !strips_fit(span, a.lr, a.k, a.b.rows, false,
+                          a.a.ld * sizeof(T) * (F == SliceSet::Real ? 1 : 2));
   a.cols_chunked = a.chunked && cols_chunked(a.b.rows);
   a.tr = chunk_rows(a.a.rows);
   if (a.chunked)
@@ -724,7 +733,7 @@ int group_strip_log2(Prec pr, int k_pad, bool fine) {
 
 bool scan_group_fine(int64_t units) { return scan_fine(units); }
 bool scan_group_chunked(Prec pr, const ProbDesc& d, bool fine) {
-  return !strips_fit(d.mp, group_strip_log2(pr, d.kp, fine), d.k,
+  return !strips_fit(d.mp, group_strip_log2(pr, d.kp, fine), d.k, d.n, !fine,
                      d.lda * (pr == Prec::F64 ? sizeof(double) : sizeof(float)));
 }
 int scan_group_blocks(Prec pr, const ProbDesc& d, bool fine) {
