@@ -485,8 +485,8 @@ __global__ __launch_bounds__(256) void k_clear(uint64_t* bits, int* mx_a, int na
 // start a workgroup every 8 ns, take as long.  Otherwise the scan goes by chunks, for
 // about 10 us of launches.  At 128 x 128 x 8192 (8 strips) strips took 46 us, the
 // chunked scan 20 us; at 4096^3 (256 strips) 82 us against 91 us for chunks.  FP32
-// calls, strips and chunks: cgemm 130 x 1000 x 4096 160 and 123 us, sgemm of
-// 16 x 16 x 3000 42 and 33, of 2000 x 3000 x 2100 163 and 169.
+// calls, strips and chunks: cgemm 130 x 1000 x 4096 161 and 124 us, sgemm of
+// 16 x 16 x 3000 53 and 41, of 2000 x 3000 x 2100 163 and 169.
 // The strips of a batch of many workgroups run beside those of other problems: there
 // up to 4096 of k (`many`).
 // A pass of a strip addresses its columns with 32 bits (pitch: bytes from one to
@@ -504,8 +504,14 @@ __host__ __device__ inline bool strips_fit(int rows_pad, int lr, int k, int n, b
 // workgroup streams each twice, which is as much traffic in less work but leaves
 // most compute units idle when there are few.  Whole calls by columns and in
 // chunks: 60 columns of 100000 493 and 474 us, 64 of 262144 533 and 445; 128 of
-// 16384 69 and 71, 200 of 100000 479 and 493.
-__host__ __device__ inline bool cols_chunked(int n) { return n <= 100; }
+// 16384 69 and 71, 200 of 100000 479 and 493.  Pairs of FP32 always go in chunks: a
+// workgroup streams them no faster than pairs of FP64, for half the bytes (N = 2, 64
+// x 2000 x 100000, both forms: by columns 2230 and 2320 us, in chunks 1540 and 1600;
+// in FP64 2370 and 2440, in chunks 2510 and 2610).
+template <typename T, SliceSet F>
+bool cols_chunked(int n) {
+  return n <= 100 || (F != SliceSet::Real && sizeof(T) == 4);
+}
 
 // ---------------------------------------------------------------------------
 // double-double helpers (Dekker / Knuth error-free transformations)
@@ -675,7 +681,7 @@ void scan_t(hipStream_t s, ScanArgs& a) {
   a.tpc = col_threads(a.k_pad, kColKeep<F>, fine);
   a.chunked = !strips_fit(span, a.lr, a.k, a.b.rows, false,
                           a.a.ld * sizeof(T) * (F == SliceSet::Real ? 1 : 2));
-  a.cols_chunked = a.chunked && cols_chunked(a.b.rows);
+  a.cols_chunked = a.chunked && cols_chunked<T, F>(a.b.rows);
   a.tr = chunk_rows(a.a.rows);
   if (a.chunked)
     hipLaunchKernelGGL(k_clear, dim3(clear_blocks(a.a.rows_pad, a.b.rows_pad)), dim3(256), 0, s,
