@@ -1041,13 +1041,23 @@ int choose_split(int nx_pad, int ny_pad, int k_pad, int nz) {
 // with this one (the scratch is the same): 128x128x8192 (64 groups) 27.5 and
 // 12.2 us, 200x200x100000 (782) 54 and 26, 64x64x262144 (2048) 122 and 28.  At
 // 1024^2 x 1024 and x 4096 two and more splits were slower than one.
+// With more than 32 tiles over 256 groups or more the L2 bounds it, not the latency
+// of a group: one workgroup per CU reads 10 to 12 TB/s, two read 13 to 15, if they
+// fill the slots (at least 16 of 9 splits).  One and two per CU, scratch permitting:
+// 36 tiles of 1024 groups 108 and 100 us, 54 of 256 59 and 54, of 2048 332 and 265,
+// 100 of 256 97 and 78, of 2048 614 and 432; but 32 of 1024 97 and 102, and two of
+// the 15 shapes from 512 groups on lose 2 and 4% (64 and 48 tiles of 512).
 int choose_split_cbar(int nx_pad, int ny_pad, int k_pad, size_t bytes) {
   if (g_split_k.load(std::memory_order_relaxed) == 1) return 1;
   const int B = use_256(nx_pad, ny_pad, 1) ? 256 : 128;
   const long w0 = (long)(nx_pad / B) * (ny_pad / B), G = k_pad / 128;
   const double plane = 4.0 * nx_pad * ny_pad;
   if (B == 256 || w0 <= 0) return 1;
-  const long most = std::min<long>({kCus / w0, G / 4, (long)((double)bytes / plane), 64});
+  auto fit = [&](long slots) {
+    return std::min<long>({slots / w0, G / 4, (long)((double)bytes / plane), 64});
+  };
+  const long most = fit(kCus), two = fit(2 * kCus);
+  if (w0 > 32 && G >= 256 && two >= 2 && 9 * two >= 16 * most) return (int)two;
   int best = 1;
   double t_best = 0.3 * (double)G;
   for (long sp = 2; sp <= most; ++sp) {
