@@ -478,25 +478,32 @@ __global__ __launch_bounds__(256) void k_clear(uint64_t* bits, int* mx_a, int na
   scan_clear(mx_a, na, mx_b, nb, flag, t, stride);
 }
 
-// Strips over all of k: each strip streams its columns by itself, a pass of 512 k
-// (FP64; 256 for FP32, whose strips have twice the rows) about every 1.9 us, and
-// all but the first passes twice.  So they are taken for up to 8 passes, when there
-// are enough of them to fill the memory system, and while the n columns of B, which
-// start a workgroup every 8 ns, take as long.  Otherwise the scan goes by chunks, for
-// about 10 us of launches.  At 128 x 128 x 8192 (8 strips) strips took 46 us, the
-// chunked scan 20 us; at 4096^3 (256 strips) 82 us against 91 us for chunks.  FP32
-// calls, strips and chunks: cgemm 130 x 1000 x 4096 161 and 124 us, sgemm of
-// 16 x 16 x 3000 53 and 41, of 2000 x 3000 x 2100 163 and 169.
-// The strips of a batch of many workgroups run beside those of other problems: there
-// up to 4096 of k (`many`).
+// Strips over all of k: each strip streams its columns by itself in passes of 512 k
+// (FP64; 256 for FP32, whose strips have twice the rows), waiting for one after the
+// other, and all but the first twice.  A chunked scan moves the same bytes at the rate
+// of memory, for two or three launches more (about 10 us).  A round of 256 strips
+// takes 7 us a pass, as chunks of as much do, a partial one 4 to 5 however few strips
+// it has.  So strips are taken for few passes, the more the fuller their rounds, and
+// for whole rounds up to 24576 of k (longer ones fall behind).  Scans of FP64 with
+// strips and in chunks: 96 strips of 9 passes 32 and 32 us, of 16 52 and 45, of 32 131
+// and 80; 192 of 16 72 and 77, of 32 193 and 178; 384 of 16 172 and 172, of 32 376 and
+// 343; 256 of 32 222 and 236, of 137 1052 and 985; 512 of 16 203 and 234, of 137 2085
+// and 1995.  (Strips of every k from 96 on, the rule before, lost up to 40% to the
+// separate passes that the scan replaced.)  FP32 calls: cgemm 130 x 1000 x 4096 161
+// and 124 us, sgemm of 16 x 16 x 3000 53 and 41, of 2000 x 3000 x 2100 163 and 169.
+// More passes also fit while the n columns of B, which start a workgroup every 8 ns,
+// take as long as the strips, and beside the other problems of a batch of many
+// workgroups (`many`), up to 4096 of k.
 // A pass of a strip addresses its columns with 32 bits (pitch: bytes from one to
 // the next), which saves the registers that 64-bit addresses spilled: 16.5 and
 // 13.5 us at 1000x700x1300.
 __host__ __device__ inline bool strips_fit(int rows_pad, int lr, int k, int n, bool many,
                                            size_t pitch) {
   const int pass = 16 << (9 - lr), passes = (k + pass - 1) >> (13 - lr);
+  const int strips = rows_pad >> lr, rounds = (strips + 255) >> 8;
   const bool brief = passes <= 8 || (k <= 4096 && (many || 450 * passes <= n + 1250));
-  return (brief || rows_pad >> lr >= 96) &&
+  const bool full = 16 * strips >= 15 * 256 * rounds;
+  return (brief || (full ? k <= 24576 : 16 * (passes - 4) * rounds <= strips)) &&
          (size_t)((pass < k ? pass : k) + 1) * pitch < (size_t)1 << 32;
 }
 
