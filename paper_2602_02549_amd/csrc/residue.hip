@@ -957,13 +957,14 @@ void fill_occ() {
   o[1 + kAnyPath] = resident_per_cu(kg_slices<T, 1, kAnyPath>);
 }
 
-// Workgroups *ba and *bb for ta and tb tiles of the two sides, a tile of A
-// costing `wa` of B's: one per tile while they all fit the resident slots of
+// Workgroups *ba and *bb for ta and tb tiles of the two sides, whose tiles cost
+// wa and wb: one per tile while they all fit the resident slots of
 // the device (or the device's figures are unknown), else the slots in
 // proportion to the work.  A positive g_slice_cap (a test knob set through
 // ozaki2_debug_tuning) caps each side's count, so that each workgroup walks
 // many tiles.
-void slice_blocks(bool f32, int form, int variant, int ta, int tb, int wa, int* ba, int* bb) {
+void slice_blocks(bool f32, int form, int variant, int ta, int tb, int wa, int wb, int* ba,
+                  int* bb) {
   *ba = ta;
   *bb = tb;
   int dev = 0;
@@ -971,7 +972,7 @@ void slice_blocks(bool f32, int form, int variant, int ta, int tb, int wa, int* 
     const int64_t slots = (int64_t)g_cus[dev].load(std::memory_order_relaxed) *
                           g_occ[f32 ? 1 : 0][form][variant].load(std::memory_order_relaxed);
     if (slots > 1 && (int64_t)ta + tb > slots) {
-      const double share = (double)wa * ta / ((double)wa * ta + tb);
+      const double share = (double)wa * ta / ((double)wa * ta + (double)wb * tb);
       int64_t a = (int64_t)(share * (double)slots + 0.5);
       if (ta > 0) a = std::max<int64_t>(a, 1);
       if (tb > 0) a = std::min<int64_t>(a, slots - 1);
@@ -991,8 +992,13 @@ void launch_one(hipStream_t s, SliceArgs& a, const CrtConsts& cc) {
   const int variant = MODE != 1 ? 0 : 1 + PATH;
   const int tiles = a.a.tiles + a.b.tiles;
   if (tiles <= 0) return;
+  // The embedding's residues: a tile of A is read once, as one of B, and each of its
+  // moduli written twice.  Apart, a tile of A took 1.4 times one of B's time at N = 2,
+  // 1.8 times at N = 7 and 15.  8192 x 2000 x 33000 in FP64, N = 2: 1966 us at two to
+  // one, 1729 so.
+  const bool two_rows = FORM == kEmb && MODE == 1;
   slice_blocks(std::is_same<T, float>::value, FORM, variant, a.a.tiles, a.b.tiles,
-               FORM == kEmb && MODE == 1 ? 2 : 1, &a.a.blocks, &a.b.blocks);
+               two_rows ? 3 + 2 * cc.N : 1, two_rows ? 3 + cc.N : 1, &a.a.blocks, &a.b.blocks);
   // While the tiles leave slots free, the moduli of a tile are dealt to several
   // workgroups (for_moduli), at least two each; the tile is then read again by
   // each of them, from L2.  At 256^3 (16 tiles a side, N = 14) this took the
@@ -1029,7 +1035,7 @@ void launch_group_one(hipStream_t s, const ProbDesc* P, const BlockRef* amap, in
                       const BlockRef* bmap, int btiles, const CrtConsts* ctab) {
   int ba, bb;
   slice_blocks(std::is_same<T, float>::value, kGroupForm, MODE == 0 ? 0 : 1 + PATH, atiles, btiles,
-               1, &ba, &bb);
+               1, 1, &ba, &bb);
   hipLaunchKernelGGL((kg_slices<T, MODE, PATH>), dim3((unsigned)(ba + bb)), dim3(256), 0, s, P,
                      amap, atiles, ba, bmap, btiles, ctab);
 }
