@@ -1185,11 +1185,16 @@ void launch_gemm_i8(hipStream_t s, int epi, const int8_t* X, size_t sx, const in
     // Fewer splits, one workgroup per CU with the deep ring, where these fill 15 of
     // 16 CUs.  Residue products with two workgroups per CU and with one: 128x128 x
     // 16384 27.8 and 22.8 us, 100x100x50000 42.3 and 35.3, 64x64x262144 143 and
-    // 135; where 224 of 256 CUs would have one, 200x200x100000, 158 and 164.
+    // 135; where 224 of 256 CUs would have one, 200x200x100000, 158 and 164.  With
+    // more than 4 tiles a slice, whose workgroups share panels in L2, two are faster
+    // (16 tiles, N = 8: 16384 of k 41 and 47; 60 tiles, N = 2: 36 and 45, 50000 107
+    // and 125), up to 16 tiles below 2^17 of k (there 363 and 346; 25 tiles, N = 5,
+    // 309 and 327).
     if (epi == 0 && !b256 && sp > 1) {
-      const long w0 = (long)(nx_pad / 128) * (ny_pad / 128) * nz;
+      const long tiles = (long)(nx_pad / 128) * (ny_pad / 128), w0 = tiles * nz;
       const long sp1 = kCus / w0;
-      if (sp1 >= 2 && 16 * sp1 * w0 >= 15 * kCus) sp = (int)std::min<long>(sp, sp1);
+      if (sp1 >= 2 && 16 * sp1 * w0 >= 15 * kCus && (tiles <= 4 || (tiles <= 16 && G >= 1024)))
+        sp = (int)std::min<long>(sp, sp1);
     }
     // the partials use the plane layout (stride nx_pad * ny_pad, rows of
     // nx_pad): W must have it too
