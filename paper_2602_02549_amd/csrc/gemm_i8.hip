@@ -917,9 +917,19 @@ int tail_parts(long tiles) {
 // rounds all read the same panels.  Residue products in ranges and in rounds:
 // 7 of 16384^3 (537 MB a slice) 23.8 and 21.4 ms, 14 of 8192^3 (134 MB) 5550 and
 // 5390 us, of 3000x3000x20000 (122 MB) 2160 and 2045; but of 4096x4096x8192 (67
-// MB) 1383 and 1445, 18 of 4096^3 (34 MB) 936 and 987.
-bool walk_in_rounds(int nx_pad, int ny_pad, int k_pad) {
-  return (size_t)(nx_pad + ny_pad) * k_pad > kRoundBytes;
+// MB) 1383 and 1445, 18 of 4096^3 (34 MB) 936 and 987.  The bytes are not all of it:
+// below the line 5000^3 (52 MB) and 6000^3 (75 MB) would gain 3 to 4%, where their
+// neighbours at powers of two lose as much.  Outputs of fewer than 8 tiles one way
+// and no more than a round of them have no 16 x 16 places to share panels in and gain
+// only from a longer k: 7 products of 24576x256x8192 429 and 486 us, x 66000 3810 and
+// 3595; of 16384x1000x8192 663 and 743, x 66000 7019 and 6586 (but the whole call of
+// 60000x500x8192, 470 tiles, 3766 and 3634).  A launch of less than one round stays
+// in ranges (scaling product of 3000x3000x66000, 144 tiles: 909 and 1027 us).
+bool walk_in_rounds(int nx_pad, int ny_pad, int k_pad, int wgs) {
+  const int tx = nx_pad / 256, ty = ny_pad / 256;
+  const bool thin = std::min(tx, ty) < 8 && (int64_t)tx * ty <= kCus;
+  return (size_t)(nx_pad + ny_pad) * k_pad > kRoundBytes && wgs >= kCus &&
+         (!thin || k_pad >= 1 << 15);
 }
 
 template <int B>
@@ -929,7 +939,7 @@ void launch_cfg(hipStream_t s, int epi, const int8_t* X, size_t sx, const int8_t
   const int tiles_x = nx_pad / B, tiles_y = ny_pad / B;
   const int wgs = tiles_x * tiles_y * nz * nsplit;
   int full = wgs;
-  const int rounds = B == 256 && nsplit == 1 && walk_in_rounds(nx_pad, ny_pad, k_pad);
+  const int rounds = B == 256 && nsplit == 1 && walk_in_rounds(nx_pad, ny_pad, k_pad, wgs);
   dim3 grid((unsigned)wgs);
   const dim3 block(tile_threads<B>());
   const bool deep = B == 128 && wgs <= kCus;   // one workgroup per CU: the deep ring
