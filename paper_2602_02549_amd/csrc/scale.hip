@@ -491,17 +491,19 @@ __global__ __launch_bounds__(256) void k_clear(uint64_t* bits, int* mx_a, int na
 // and 1995.  (Strips of every k from 96 on, the rule before, lost up to 40% to the
 // separate passes that the scan replaced.)  FP32 calls: cgemm 130 x 1000 x 4096 161
 // and 124 us, sgemm of 16 x 16 x 3000 53 and 41, of 2000 x 3000 x 2100 163 and 169.
-// More passes also fit while the n columns of B, which start a workgroup every 8 ns,
-// take as long as the strips, and beside the other problems of a batch of many
-// workgroups (`many`), up to 4096 of k.
+// More passes also fit, up to 4096 of k, while the n columns of B, which start a
+// workgroup every 8 ns, and chunks of as many rows take as long as the strips (sgemm
+// of 2304^3 149 and 153), and beside the other problems of a batch of many
+// workgroups (`many`).
 // A pass of a strip addresses its columns with 32 bits (pitch: bytes from one to
 // the next), which saves the registers that 64-bit addresses spilled: 16.5 and
 // 13.5 us at 1000x700x1300.
 __host__ __device__ inline bool strips_fit(int rows_pad, int lr, int k, int n, bool many,
                                            size_t pitch) {
   const int pass = 16 << (9 - lr), passes = (k + pass - 1) >> (13 - lr);
-  const int strips = rows_pad >> lr, rounds = (strips + 255) >> 8;
-  const bool brief = passes <= 8 || (k <= 4096 && (many || 450 * passes <= n + 1250));
+  const int64_t strips = rows_pad >> lr, rounds = (strips + 255) >> 8;
+  const bool brief =
+      passes <= 8 || (k <= 4096 && (many || 450 * passes <= n + 16 * strips + 1250));
   const bool full = 16 * strips >= 15 * 256 * rounds;
   return (brief || (full ? k <= 24576 : 16 * (passes - 4) * rounds <= strips)) &&
          (size_t)((pass < k ? pass : k) + 1) * pitch < (size_t)1 << 32;
