@@ -53,12 +53,21 @@ __host__ __device__ inline int strip_rows_log2(int k_pad, bool fine) {
   return lr;
 }
 // Threads per column for k_pad: the fewest that keep it in registers (keep
-// elements a thread), a wave up to kColWaveK, else a workgroup.
-__host__ __device__ inline int col_threads(int k_pad, int keep, bool fine) {
-  if (k_pad > kColWaveK) return kScanThreads;
+// elements a thread), a wave up to wave_k, else a workgroup.
+__host__ __device__ inline int col_threads(int k_pad, int keep, bool fine,
+                                           int wave_k = kColWaveK) {
+  if (k_pad > wave_k) return kScanThreads;
   int tpc = fine ? 64 : 4;
   while (tpc < 64 && tpc * keep < k_pad) tpc *= 2;
   return tpc;
+}
+// In a batch of many workgroups, which the launch rate of waves bounds, a wave takes
+// columns of up to 32 KB.  Whole batches with a workgroup and with a wave a column:
+// FP32, 200 of 64 x 64 x 2500 791 and 688 us (778 before the merged scan), 40 of 500 x
+// 700 x 2100 903 and 781, 20 of 100 x 1000 x 6000 889 and 812; FP64, 200 of 64 x 64 x
+// 2500 1192 and 1107, but 20 of 300 x 300 x 8000 1276 and 1303.
+__host__ __device__ inline int group_wave_k(bool fine, size_t size) {
+  return fine ? kColWaveK : (int)(32768 / size);
 }
 // Whether `units` workgroups of the finest split are few.
 __host__ __device__ inline bool scan_fine(int64_t units) { return units <= 512; }
@@ -659,7 +668,9 @@ __global__ __launch_bounds__(kScanThreads, 4) void kg_scan(const ProbDesc* __res
                                   lds);
   else
     scan_cols<T, SliceSet::Real>((const T*)d.B, d.ldb, d.n, d.np, d.k, d.kp, d.colbits, d.Bs,
-                                 e.y - strips, col_threads(d.kp, kColKeep<SliceSet::Real>, fine),
+                                 e.y - strips,
+                                 col_threads(d.kp, kColKeep<SliceSet::Real>, fine,
+                                             group_wave_k(fine, sizeof(T))),
                                  &lds.red[0][0]);
 }
 
@@ -740,6 +751,7 @@ void launch_scan(hipStream_t s, Prec pr, SliceSet set, const SliceOperand& A, co
 }
 
 namespace {
+size_t elem_size(Prec pr) { return pr == Prec::F64 ? sizeof(double) : sizeof(float); }
 int group_strip_log2(Prec pr, int k_pad, bool fine) {
   return pr == Prec::F64 ? strip_rows_log2<double>(k_pad, fine)
                          : strip_rows_log2<float>(k_pad, fine);
@@ -749,12 +761,13 @@ int group_strip_log2(Prec pr, int k_pad, bool fine) {
 bool scan_group_fine(int64_t units) { return scan_fine(units); }
 bool scan_group_chunked(Prec pr, const ProbDesc& d, bool fine) {
   return !strips_fit(d.mp, group_strip_log2(pr, d.kp, fine), d.k, d.n, !fine,
-                     d.lda * (pr == Prec::F64 ? sizeof(double) : sizeof(float)));
+                     d.lda * elem_size(pr));
 }
 int scan_group_blocks(Prec pr, const ProbDesc& d, bool fine) {
   const int strips =
       scan_group_chunked(pr, d, fine) ? 0 : d.mp >> group_strip_log2(pr, d.kp, fine);
-  return strips + col_units(d.np, col_threads(d.kp, kColKeep<SliceSet::Real>, fine));
+  return strips + col_units(d.np, col_threads(d.kp, kColKeep<SliceSet::Real>, fine,
+                                              group_wave_k(fine, elem_size(pr))));
 }
 
 void launch_debug_shifts(hipStream_t s, const uint64_t* rowbits, const int* rmax, int m,
