@@ -351,7 +351,11 @@ int ozaki2_debug_mfma_probe(int iters, int changing, float *ms, double *ops);
  *   enable != 0 turns recording on (and clears previous records); 0 off.
  * ozaki2_profile_read copies up to `cap` records (name index, milliseconds)
  * of the calls made since the last enable; returns the number of records.
- * ozaki2_profile_name returns the kernel-phase name of an index.
+ * ozaki2_profile_name returns the kernel-phase name of an index ("" past the
+ * last).  A phase keeps its index; the abs-max, bars and clearing are now one
+ * phase "scan" and the residues of both operands one phase "residues", so that
+ * "init", "absmax_A", "absmax_B", "bar_A", "bar_B", "shifts", "residue_A" and
+ * "residue_B" have no records.
  */
 int ozaki2_profile(int enable);
 int ozaki2_profile_read(int *phase, float *ms, int cap);

@@ -51,11 +51,15 @@ bool g_plan_ok[2][2] = {};
 // ---------------------------------------------------------------------------
 // profiling (HIP events around each phase on the library stream)
 // ---------------------------------------------------------------------------
+// Indices are part of the interface: a phase keeps its own (those whose kernels have
+// gone into others record nothing), and new ones come last.
 enum Phase {
-  PH_SCAN, PH_GEMM_SCALE, PH_RES, PH_GEMM_RES, PH_CRT, PH_PLAN, PH_BATCH, PH_COUNT
+  PH_GEMM_SCALE = 5, PH_GEMM_RES = 9, PH_CRT, PH_PLAN, PH_BATCH, PH_SCAN, PH_RES, PH_COUNT
 };
-const char* kPhaseNames[PH_COUNT] = {"scan", "gemm_scale", "residues", "gemm_residue", "crt",
-                                     "plan", "batched"};
+const char* kPhaseNames[PH_COUNT] = {"init", "absmax_A", "absmax_B", "bar_A", "bar_B",
+                                     "gemm_scale", "shifts", "residue_A", "residue_B",
+                                     "gemm_residue", "crt", "plan", "batched", "scan",
+                                     "residues"};
 struct ProfRec {
   int phase;
   hipEvent_t a, b;
