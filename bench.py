@@ -140,7 +140,7 @@ def mfma_probe(oz, kernel_tops: float) -> dict:
                 best = {"ms": round(ms, 4), "ops": ops, "tops": round(tops, 1)}
         out[name] = best
     out["residue_products_frac_of_probe"] = round(kernel_tops / out["changing_operands"]["tops"], 4)
-    out["what"] = ("v_mfma_i32_32x32x32_i8 back to back, one workgroup of 8 waves per CU, no memory "
+    out["what"] = ("v_mfma_i32_16x16x64_i8 back to back, one workgroup of 8 waves per CU, no memory "
                    "traffic; operands changing every step, or fixed")
     return out
 

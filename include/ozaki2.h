@@ -334,9 +334,9 @@ int ozaki2_debug_log2f(const float *d, float *out, int count);
 
 /*
  * ozaki2_debug_mfma_probe - a measurement aid for the roofline of the residue
- * products: one workgroup of 8 waves per CU issues `iters` steps of 8
- * v_mfma_i32_32x32x32_i8 (2 x 32^3 INT8 operations each; the products use the
- * 16x16x64 form, which takes less energy per operation), with no memory traffic, on operands that change every
+ * products: one workgroup of 8 waves per CU issues `iters` steps of 16
+ * v_mfma_i32_16x16x64_i8 (the products' instruction, 2 x 16 x 16 x 64 INT8
+ * operations each), with no memory traffic, on operands that change every
  * step (changing = 1: the rate the chip sustains for that instruction on
  * changing data under its power limit) or stay fixed (changing = 0: the
  * issue rate with little data toggling).  *ms (HOST) receives its duration,

@@ -1,19 +1,18 @@
-// MFMA-rate probe: v_mfma_i32_32x32x32_i8, the larger of the two INT8
-// instructions (the products use 16x16x64, which takes less energy per
-// operation), issued back to back on INT8 operands that change every step, with
-// no memory traffic at all.  The rate it sustains is the ceiling the
-// chip's power limit leaves for that instruction on changing data, against
-// which the residue products can be read (a measurement aid, not part of
-// the method).
+// MFMA-rate probe: v_mfma_i32_16x16x64_i8, the residue products' instruction,
+// issued back to back on INT8 operands that change every step, with no memory
+// traffic at all.  The rate it sustains is the ceiling the chip's power limit
+// leaves for that instruction on changing data, against which the residue
+// products can be read (a measurement aid, not part of the method).
 //
-// Each workgroup is 8 waves, each wave 2 x 4 accumulators of 32 x 32 (the
-// shape of one wave's 64 x 128 share of a 256 x 256 residue-product tile),
-// one workgroup per CU as in the product kernel.  Per step a wave issues 8
-// MFMAs; with CHANGE it also adds an odd constant to each of its 24 operand
-// dwords (a Weyl sequence per dword, so every byte keeps changing), without
-// it the operands stay fixed (the issue rate with little data toggling).
-// Each thread stores one checksum word at the end so that no MFMA can be
-// dropped.
+// Each workgroup is 8 waves, each wave 4 x 4 accumulators of 16 x 16 (half of
+// one wave's 64 x 128 share of a 256 x 256 residue-product tile), one workgroup
+// per CU as in the product kernel, and goes back and forth over the first
+// operand as the products do, so that an instruction shares an operand with the
+// one before.  Per step a wave issues 16 MFMAs; with CHANGE it also adds an odd
+// constant to each of its 32 operand dwords (a Weyl sequence per dword, so every
+// byte keeps changing), without it the operands stay fixed (the issue rate with
+// little data toggling).  Each thread stores one checksum word at the end so
+// that no MFMA can be dropped.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -25,7 +24,6 @@ namespace oz2 {
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kProbeThreads = 512;
 constexpr int kProbeMaxBlocks = 1024;
@@ -41,27 +39,27 @@ __global__ __launch_bounds__(kProbeThreads, 1) void k_mfma_probe(int iters, int*
     h ^= h << 5;
     return (int)h;
   };
-  v4i a[2], b[4];
+  v4i a[4], b[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) a[i] = v4i{next(), next(), next(), next()};
+  for (int i = 0; i < 4; ++i) a[i] = v4i{next(), next(), next(), next()};
 #pragma unroll
   for (int i = 0; i < 4; ++i) b[i] = v4i{next(), next(), next(), next()};
-  v16i acc[2][4];
+  v4i acc[4][4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = v4i{0, 0, 0, 0};
+  for (int it = 0; it < iters; ++it) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
-  for (int it = 0; it < iters; ++it) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], b[j], acc[i][j], 0, 0, 0);
+      for (int q = 0; q < 4; ++q) {
+        const int i = j & 1 ? 3 - q : q;
+        acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[i], b[j], acc[i][j], 0, 0, 0);
+      }
     if constexpr (CHANGE) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 4; ++i)
         a[i] += v4i{(int)0x9e3779b9, (int)0x7f4a7c15, (int)0x85ebca6b, (int)0xc2b2ae35};
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -70,11 +68,11 @@ __global__ __launch_bounds__(kProbeThreads, 1) void k_mfma_probe(int iters, int*
   }
   int x = 0;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) x ^= acc[i][j][r];
+      for (int r = 0; r < 4; ++r) x ^= acc[i][j][r];
   sink[t] = x;
 }
 
@@ -106,8 +104,8 @@ int probe_mfma(hipStream_t s, int blocks, int iters, bool change, float* ms, dou
   (void)hipEventDestroy(e1);
   if (!ok) return OZAKI2_ERR_HIP;
   *ms = t;
-  // 8 MFMAs of 2 x 32 x 32 x 32 operations per wave and step
-  *ops = (double)blocks * (kProbeThreads / 64) * (double)iters * 8.0 * 65536.0;
+  // 16 MFMAs of 2 x 16 x 16 x 64 operations per wave and step
+  *ops = (double)blocks * (kProbeThreads / 64) * (double)iters * 16.0 * 32768.0;
   return OZAKI2_OK;
 }
 
