@@ -120,10 +120,10 @@ __device__ __forceinline__ void store_rows(CrtStage<T, R, E>& lds, T* __restrict
 // next, so small-m problems keep every lane busy.
 // With DBG, C'(1), C'(2), Q and C'' of every entry are also stored, as FP64
 // column-major m x n arrays at dbg + s * m * n for s = 0..3 (stage dumps).
-// C'(1) and C'(2) of R consecutive rows (wp: row i0 of column j of slice 0).
-// ALIGNED: wp is a multiple of R bytes, so each slice's R bytes are one load;
-// otherwise they are gathered byte by byte.
-template <typename T, int R, bool ALIGNED = true>
+
+// C'(1) and C'(2) of R consecutive rows (wp: row i0 of column j of slice 0, a
+// multiple of R bytes, so that each slice's R bytes are one load).
+template <typename T, int R>
 __device__ __forceinline__ void crt_sums(const int8_t* __restrict__ wp, size_t sw,
                                          const CrtConsts& cc, double (&c1)[R], double (&c2)[R]) {
   typedef typename std::conditional<R == 2, uint16_t,
@@ -140,13 +140,7 @@ __device__ __forceinline__ void crt_sums(const int8_t* __restrict__ wp, size_t s
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int8_t* src = wp + (size_t)min(l0 + u, cc.N - 1) * sw;
-      if constexpr (ALIGNED) {
-        v[u] = load_stream(reinterpret_cast<const WordT*>(src));
-      } else {
-        v[u] = 0;
-#pragma unroll
-        for (int e = 0; e < R; ++e) v[u] |= (WordT)((WordT)(uint8_t)src[e] << (8 * e));
-      }
+      v[u] = load_stream(reinterpret_cast<const WordT*>(src));
     }
   };
   auto use = [&](WordT v, double s1, double s2) {
@@ -244,9 +238,8 @@ __device__ __forceinline__ void crt_body(const int8_t* __restrict__ W, size_t sw
 // Complex output: the real parts from (Wr, mur) and the imaginary parts from
 // (Wi, mui), both with the column shifts nu, written as interleaved (re, im)
 // pairs into the column-major complex C (ldc in complex elements).  The
-// loads of a partial last chunk read up to row rup(m, R) - 1 past Wr and Wi,
-// inside the padded column (the embedding's column holds 2m rows padded to a
-// multiple of 128, at least m + rup(m, R)).
+// imaginary rows start at half of the padded rows, a multiple of 64, and the
+// loads of a partial last chunk stay inside each half.
 template <typename T, int R>
 __device__ __forceinline__ void crt_complex_body(const int8_t* __restrict__ Wr,
                                                  const int8_t* __restrict__ Wi, size_t sw, int ldw,
@@ -266,12 +259,7 @@ __device__ __forceinline__ void crt_complex_body(const int8_t* __restrict__ Wr,
 #pragma unroll
   for (int e = 0; e < R; ++e)
     out[2 * e] = crt_value<T>(c1[e], c2[e], cc, -mur[min(pl.i0 + e, m - 1)] - nuj, bad, &q, &cppd);
-  // the imaginary rows of the real embedding start at row m, which need not
-  // be a multiple of R (uniform over the launch)
-  if (((uintptr_t)Wi & (R - 1)) == 0)
-    crt_sums<T, R, true>(Wi + o, sw, cc, c1, c2);
-  else
-    crt_sums<T, R, false>(Wi + o, sw, cc, c1, c2);
+  crt_sums<T, R>(Wi + o, sw, cc, c1, c2);
 #pragma unroll
   for (int e = 0; e < R; ++e)
     out[2 * e + 1] =
