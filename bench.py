@@ -334,7 +334,8 @@ def certified_measurement(torch, oz, rng) -> list:
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_gemm_i8_residue_fp64_8192_N14_traffic.txt")
-GEMM_SOURCE = os.path.join(ROOT, "paper_2602_02549_amd", "csrc", "gemm_i8.hip")
+GEMM_SOURCES = [os.path.join(ROOT, "paper_2602_02549_amd", "csrc", f)
+                for f in ("gemm_i8.hip", "tile_walk.h")]
 
 
 def measured_traffic(N: int, m: int):
@@ -351,9 +352,11 @@ def measured_traffic(N: int, m: int):
             if ":" in line and not line.startswith("#"):
                 key, val = line.split(":", 1)
                 fields[key.strip()] = val.strip()
-    with open(GEMM_SOURCE, "rb") as f:
-        sha = hashlib.sha256(f.read()).hexdigest()
-    if fields.get("source_sha256") != sha or fields.get("N") != str(N) or fields.get("size") != str(m):
+    sha = hashlib.sha256()
+    for name in GEMM_SOURCES:
+        with open(name, "rb") as f:
+            sha.update(f.read())
+    if fields.get("source_sha256") != sha.hexdigest() or fields.get("N") != str(N) or fields.get("size") != str(m):
         return None
     try:
         return float(fields["traffic_bytes_per_launch"])

@@ -14,14 +14,15 @@
 // of 4 consecutive rows i are packed into one word, and four such words into
 // one 16-byte store of the column-major W_l[j][i].
 //
-// Instruction: large products run at the clock that the power limit leaves, not
-// at the issue rate, so the instruction with the least energy per product is
-// the fastest.  16x16x64 adds 64 products for each accumulator it reads and
-// writes, 32x32x32 half as many.  With random bytes held in registers the first
-// ran at 3.99 PO/s (4.05 when consecutive instructions share an operand), the
-// second at 3.36; with zeros both at 4.9.  Here: 14 products of 8192^3 6410 and
-// 5800 us (2.43 and 2.65 PO/s), 18 of 4096^3 1060 and 970, 7 of 16384^3 27.2
-// and 24.3 ms.  The BF16 product (the planner's lower bound of |A||B|) stays
+// Instruction: large products run at a clock that the power limit lowers, so an
+// instruction with less energy per product is faster.  16x16x64 adds 64 products
+// for each accumulator it reads and writes, 32x32x32 half as many.  Alone, from
+// registers (the probe), the first runs at 3.8 to 4.0 PO/s on fixed random bytes
+// and 3.0 to 3.3 on bytes that change every step, the second at 3.3 to 3.4 and
+// 2.95 to 3.1; on zeros both at 4.9.  Here: 14 products of 8192^3 6410 (32x32x32)
+// and 5800 us (2.43 and 2.65 PO/s), 18 of 4096^3 1060 and 970, 7 of 16384^3 27.2
+// and 24.3 ms.  On zeros, where power does not bind, the loop takes 4900 us: its
+// own waits leave 65% of the issue rate.  The BF16 product (the planner's lower bound of |A||B|) stays
 // with 32x32x16, whose order of FP32 additions its results depend on.
 //
 // Tiling: a workgroup of NWX x NWY waves computes a BX x BY tile; each wave
@@ -222,7 +223,8 @@ struct WaveTile {
   }
   // The same with one wave per SIMD, where nothing else covers the latency of a
   // fragment read: all of them go out at once, and the MFMAs follow as they come
-  // (scaling product of 2048^3, 16 groups: 15.6 us, interleaved 16.7).
+  // (scaling product of 2048^3, 16 groups, with its events: 15.6 us, interleaved
+  // 16.7).
   template <class CopyX, class CopyY>
   __device__ __forceinline__ void group_alone(const int8_t* buf, CopyX copy_x, CopyY copy_y) {
     v4i a0[TX], a1[TX], b00[TH], b01[TH], b10[TH], b11[TH];
@@ -404,8 +406,10 @@ struct WaveTileBf16 {
 // consume group g.  NS = 2 where the workgroups of a CU fill its LDS (128 KB
 // for a 256x256 tile); NS = 4 for launches of 128x128 tiles with at most one
 // workgroup per CU, whose groups otherwise wait for a copy each (0.65 us a
-// group, 0.3 us with three copies under way).  Scaling product with NS = 2 and
-// 4: 256^3 10.4 and 6.4 us, 1000x700x1300 16.0 and 10.7, 2048^3 21.3 and 14.5.
+// group, 0.3 us with three copies under way).  Scaling product in the kernel
+// trace, NS = 2 on 32x32x32 and as it is: 256^3 8.8 and 4.2 us, 1000x700x1300
+// 15.1 and 9.3, 2048^3 20.2 and 13.3 (with its events 14.5 when the deep ring ran
+// 32x32x32, 15.3 since).
 // Split-k: with nsplit > 1, split sidx takes the k-groups [sidx G / nsplit,
 // (sidx + 1) G / nsplit) of the G = k_pad / 128 (nsplit <= G), and its
 // epilogue writes slice sidx * nz + z of W (EPI 0: mod p_z of its partial

@@ -147,7 +147,7 @@ __device__ __forceinline__ T block_max(T v) {
 // Pass 1: a lower bound of the smallest N in [nlo, nhi] that satisfies
 // T(N) <= eps S on every entry with S > 0 (nhi + 1 if an entry has none); the
 // maximum over the workgroups goes to *out.  Each wave keeps a running bound
-// `need` and, for its next 64 entries, looks for the first N >= need that
+// `need` and, for its next 256 entries, looks for the first N >= need that
 // each entry satisfies.  Any N that satisfies every entry is >= every such
 // first N (by induction over the entries: it is >= each earlier bound, so it
 // is one of the candidates searched), so the maximum stays a lower bound;

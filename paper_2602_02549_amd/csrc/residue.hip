@@ -725,6 +725,16 @@ __device__ __forceinline__ void walk_emb(const SliceArgs& a, const SliceSide& s,
 // The slices of A and of B in one launch: the first a.a.blocks workgroups walk
 // A's tiles, the others B's.  One launch of both sides saves a launch (about
 // 5 us) and a partly empty last round of workgroups per pass.
+// The bounds hold two workgroups on a CU for the two complex forms' residues
+// (three for their slices of the scaling product).  Both walks in one kernel need
+// more registers than one, and some forms keep a few in scratch for it: the
+// embedding 3 with two limbs and 22 with three (92 bytes a thread), the complex
+// form's three steps in FP64 28.  A launch a side without scratch (A's and B's
+// added) and this one, kernel times at 2000^3: embedding FP64 N = 14 136 and
+// 110 us, N = 24 288 and 267, N = 31 353 and 290, FP32 N = 7 59 and 46; complex
+// N = 24 254 and 210, N = 36 376 and 328.  The real FP64 form in one step takes
+// 130 registers for 116, three workgroups a CU for four: 2500^3 N = 8 43 and 37 us,
+// 8192^3 N = 10 488 and 485.
 enum SliceForm { kReal, kCx, kEmb };
 template <typename T, int FORM, int MODE, int PATH>
 __global__ __launch_bounds__(256, FORM == kReal ? 1 : MODE == 1 ? 2 : 3) void k_slices(

@@ -638,6 +638,9 @@ __global__ __launch_bounds__(256) void kg_clear(const ProbDesc* __restrict__ P,
   scan_clear(d.rmax, d.mp, d.cmax, d.np, d.flag, t, stride);
 }
 
+// One atomic per row and 64 columns, not one per chunk as in absmax_row_chunk: in a
+// batch the atomics of one row meet only those of its own problem, and the passes of
+// other problems run beside them.
 template <typename T>
 __global__ __launch_bounds__(256) void kg_absmax_rows(const ProbDesc* __restrict__ P,
                                                       const BlockRef* __restrict__ map) {

@@ -317,8 +317,8 @@ bool log2f_host(uint32_t d, float* out) {
 }
 
 // floor(c log2f(single_up(M)) + P') of Algorithm 2 for an integer M >= 1: the
-// product of two FP32 numbers is exact in FP64, and the long double sum (64
-// bits) of two numbers below 2^8 on the FP32 x FP32 grid is checked by TwoSum.
+// product of two FP32 numbers is exact in FP64, and TwoSum gives the FP64 sum
+// exactly as s + err, so that only an integer s with err < 0 needs a correction.
 bool shift_of_max(uint32_t M, float c, float Pprime, int* out) {
   int bl = 0;
   while (bl < 32 && (M >> bl) != 0) ++bl;
