@@ -58,7 +58,7 @@ def parse():
     ap.add_argument("--mfma-probe", action="store_true",
                     help="run the library's MFMA-rate probe (the residue products' INT8 MFMA on "
                          "changing operands, no memory traffic: the rate the chip sustains for that "
-                         "instruction under its power limit); on by default")
+                         "instruction with nothing beside it); on by default")
     ap.add_argument("--no-mfma-probe", action="store_true", help="skip the MFMA-rate probe")
     ap.add_argument("--extras", action="store_true",
                     help="also measure the 4096^3 phi sweep (N from the bound at 1e-15), the "

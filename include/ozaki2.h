@@ -337,9 +337,9 @@ int ozaki2_debug_log2f(const float *d, float *out, int count);
  * products: one workgroup of 8 waves per CU issues `iters` steps of 16
  * v_mfma_i32_16x16x64_i8 (the products' instruction, 2 x 16 x 16 x 64 INT8
  * operations each), with no memory traffic, on operands that change every
- * step (changing = 1: the rate the chip sustains for that instruction on
- * changing data under its power limit) or stay fixed (changing = 0: the
- * issue rate with little data toggling).  *ms (HOST) receives its duration,
+ * step (changing = 1: additions between the products take part of the issue)
+ * or stay fixed (changing = 0: the rate that the chip's power limit leaves for
+ * that instruction on random bytes).  *ms (HOST) receives its duration,
  * *ops (HOST) its operation count.  Synchronises the stream.
  * OZAKI2_ERR_INVALID_ARG for iters outside [1, 2^20] (2^20 steps take about
  * 0.4 s), changing not 0 or 1, or NULL outputs.

@@ -21,9 +21,11 @@
 // and 3.0 to 3.3 on bytes that change every step, the second at 3.3 to 3.4 and
 // 2.95 to 3.1; on zeros both at 4.9.  Here: 14 products of 8192^3 6410 (32x32x32)
 // and 5800 us (2.43 and 2.65 PO/s), 18 of 4096^3 1060 and 970, 7 of 16384^3 27.2
-// and 24.3 ms.  On zeros, where power does not bind, the loop takes 4900 us: its
-// own waits leave 65% of the issue rate.  The BF16 product (the planner's lower bound of |A||B|) stays
-// with 32x32x16, whose order of FP32 additions its results depend on.
+// and 24.3 ms.  Power and the loop's own waits both cap it: on zeros, at 2.34 GHz,
+// the loop keeps the pipes 67% busy (3.1 to 3.3 PO/s); on random residues the clock
+// falls to 1.68 GHz and, memory being nearer by as much, they are 77% busy (2.85).
+// The BF16 product (the planner's lower bound of |A||B|) stays with 32x32x16, whose
+// order of FP32 additions its results depend on.
 //
 // Tiling: a workgroup of NWX x NWY waves computes a BX x BY tile; each wave
 // owns (BX/NWX) x (BY/NWY).  A 256 x 256 tile runs 8 waves (4 x 2, each 64 x
